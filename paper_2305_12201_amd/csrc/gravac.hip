@@ -1464,6 +1464,7 @@ __device__ __forceinline__ void stream_subtile(const Params& p, uint32_t v, int 
 #pragma unroll
         for (int q = 0; q < ROWS; ++q) row_load<M>(p, s0 + q * ROW + 4 * lane, x[q], y[q], m[q]);
         float a[ROWS][4];
+        uint32_t rk[RND ? ROWS : 1][4];  // Random-k: the priorities, each computed once (four quarter-rate multiplications)
         uint32_t nc = 0;  // candidates for the message in this sub-tile
 #pragma unroll
         for (int q = 0; q < ROWS; ++q) {
@@ -1471,14 +1472,22 @@ __device__ __forceinline__ void stream_subtile(const Params& p, uint32_t v, int 
             uint32_t key[4];
             keys_of_row<RND, NCF>(c, a[q], s0 + q * ROW + 4 * lane, key);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) nc += (uint32_t)__popcll(__ballot(key[e] >= c.lo_c));
+            for (int e = 0; e < 4; ++e) {
+                if (RND) rk[q][e] = key[e];
+                nc += (uint32_t)__popcll(__ballot(key[e] >= c.lo_c));
+            }
         }
         dense = nc >= DENSE_SUB;
 #pragma unroll
         for (int q = 0; q < ROWS; ++q) {
             const int64_t g = s0 + q * ROW + 4 * lane;
             uint32_t key[4];
-            keys_of_row<RND, NCF>(c, a[q], g, key);
+            if (RND) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) key[e] = rk[q][e];
+            } else {
+                keys_of_row<RND, NCF>(c, a[q], g, key);
+            }
             if (M == SM_EF) {
                 // acc goes back into the residual; in a sub-tile that keeps a candidate list an entry above the committed
                 // CF's bracket leaves +0 there already: it is selected unless the bracket fails (the list keeps its value,
@@ -3782,12 +3791,15 @@ static int compress_impl(const float* grad, float* residual, int64_t n, const do
     else
         hipLaunchKernelGGL((threshold_kernel<1, false>), dim3(ns, 1), dim3(1024), 0, stream, p);
     {
-        // the Top-k pass exists in forms for 1, 2, 3, 4 and MAXCF CFs (its loops over the CFs are unrolled)
+        // the pass exists in forms for 1, 2, 3, 4 and MAXCF CFs (its loops over the CFs are unrolled)
         void (*const ef_forms[5])(Params) = {stream_kernel<SM_EF, false, 1>, stream_kernel<SM_EF, false, 2>,
                                              stream_kernel<SM_EF, false, 3>, stream_kernel<SM_EF, false, 4>,
                                              stream_kernel<SM_EF, false, MAXCF>};
+        void (*const rk_forms[5])(Params) = {stream_kernel<SM_EF, true, 1>, stream_kernel<SM_EF, true, 2>,
+                                             stream_kernel<SM_EF, true, 3>, stream_kernel<SM_EF, true, 4>,
+                                             stream_kernel<SM_EF, true, MAXCF>};
         void (*kern)(Params) = single ? stream_kernel<SM_SINGLE, false, 1>   // (a second-level call has one CF)
-                                      : (random ? stream_kernel<SM_EF, true, MAXCF> : ef_forms[ncf_form]);
+                                      : (random ? rk_forms[ncf_form] : ef_forms[ncf_form]);
         if (!have_tiles) {
             if (ev) { (void)hipEventRecord((hipEvent_t)ev->pass_begin, stream); (void)hipEventRecord((hipEvent_t)ev->pass_end, stream); }
         } else if (ev)  // the kernel's own begin and end time stamps
