@@ -74,14 +74,9 @@ constexpr uint32_t LONG_WALK = 256;   // a tile with at least this many listed e
 #ifndef GV_NT
 #define GV_NT 1                     // non-temporal hints on the streaming loads and stores
 #endif
-#ifndef GV_XGRID
-#define GV_XGRID 1024
-#endif
-constexpr uint32_t XGRID = GV_XGRID;  // workgroups of the two exact-route kernels (they loop over the tiles)
 constexpr int REP = 8;              // copies of the bracket histogram and of the gather lists
 constexpr int NBIN = 2048;          // bins of the bracket / refine / coarse histograms
 constexpr uint32_t OVF = NBIN - 1;  // bins 0 .. OVF - 1 cover the bracket; bin OVF stands for everything above it
-constexpr uint32_t XBINS = 1024;    // bins in use after an exact route has binned a segment again
 constexpr int SBIN = 4096;          // bins of the sample histogram: 2^17 keys each (64 per octave, 1.1 % in magnitude)
 constexpr uint32_t SSHIFT = 17;     // from |x| = 2^-48 up to 2^16; smaller magnitudes share bin 0, larger ones the last bin
 constexpr uint32_t SKEY0 = 79u << 23;
@@ -96,15 +91,18 @@ constexpr int DENSE_BLOCKS = 128;        // ... so that there are at most this m
 constexpr int LCAP = 4096;          // keys a gather list can hold
 constexpr int MAXCF = GRAVAC_MAX_CF;
 constexpr double ZMARGIN = 5.0;     // safety margin of the sampled rank, in standard deviations
+constexpr int XQ_WORDS = 8;         // a segment's work queue in the plan step: chunks claimed, then chunks done per phase
 constexpr uint32_t NONE = 0xFFFFFFFFu;
 constexpr uint32_t KEY_END = 0x80000000u;  // one past the largest key
 
-enum : uint32_t { MODE_RESOLVED = 0, MODE_GATHER = 1, MODE_HIST = 2, MODE_FAIL = 3 };
-// SegState::fail, the heavier kind over the segment's CFs wins:
-//   FAIL_NARROW  the bin that holds the k-th largest is known but too coarse and too full to resolve: only the
-//                CFs concerned are binned again, inside that bin, from the bracket lists (no pass over the gradient);
+enum : uint32_t { MODE_RESOLVED = 0, MODE_GATHER = 1, MODE_FAIL = 3 };
+// What the plan step found for a segment, the heaviest kind over its CFs:
+//   FAIL_TIES    the bin that holds the k-th largest is at most 2^11 keys wide and too full to gather (a mass of equal
+//                values): it is counted key by key, from the bracket lists;
+//   FAIL_NARROW  the bin is known but too coarse and too full to resolve: only the CFs concerned are binned again, inside
+//                that bin, from the bracket lists (no pass over the gradient);
 //   FAIL_FULL    the k-th largest lies outside the bracket (or there was none): acc is read again.
-enum : uint32_t { FAIL_NONE = 0, FAIL_NARROW = 1, FAIL_FULL = 3 };
+enum : uint32_t { FAIL_NONE = 0, FAIL_TIES = 1, FAIL_NARROW = 2, FAIL_FULL = 3 };
 // where a call's brackets come from
 enum : uint32_t { BOUNDS_SAMPLED = 0, BOUNDS_RANDOM = 1, BOUNDS_FORCED = 2,
                   BOUNDS_FIXED = 3 };  // the threshold sparsifier: the caller gives the threshold, nothing is searched for
@@ -122,10 +120,8 @@ struct CfState {
     uint32_t tau;       // key of the k-th largest (valid once resolved)
     uint32_t need;      // how many keys equal to tau are selected (lowest indices first)
     uint32_t cnt_gt;    // number of keys greater than tau
-    uint32_t redo;      // 1 if this CF is binned again on the narrow route (set by the locate step)
-    uint32_t lo2, s2;   // ... with these bounds: the located bin, cut into XBINS parts
     uint32_t top;       // the pass over the gradient has counted keys >= top as above the bracket (KEY_END: none)
-    uint32_t pad;
+    uint32_t pad[4];
 };
 static_assert(sizeof(CfState) == 64, "CfState layout");
 
@@ -207,9 +203,9 @@ struct Params {
     uint32_t* hist1;     // [copy blocks][NBIN] bracket histograms: REP copies per CF of a large tensor, one otherwise
     uint32_t* ovfc;      // [n_seg][n_cf][64][32] counts above the bracket (the histogram's last bin), spread over
                          // 64 cache lines; word 0 of each line is used
-    uint32_t* hist2;     // [n_seg][n_cf][NBIN] refine histogram
+    uint32_t* xq;        // [n_seg][n_cf][NBIN], of which a segment's first 8 words are in use: the plan step's work queue (XQ_*)
     uint32_t* coarse;    // [n_seg][NBIN] histogram of key >> 20 (exact route)
-    uint32_t* list_key;  // [copy blocks][LCAP] gather lists: key ...
+    uint32_t* list_key;  // [copy blocks][LCAP] gather lists: key ... (before they are filled: the exact routes' histograms)
     uint32_t* list_tile; //                          ... tile ...
     float* list_val;     //                          ... and value (written for Random-k only) of the listed entries
     uint32_t* list_cnt;  // [copy blocks][32] fill counts of the gather lists, one cache line each
@@ -285,6 +281,13 @@ __device__ __forceinline__ void bracket_bins(uint32_t lo, uint32_t hi, uint32_t&
     const uint64_t t = (uint64_t)lo + ((uint64_t)OVF << s);
     top = t >= (uint64_t)KEY_END ? KEY_END : (uint32_t)t;
 }
+
+// Where bin b of a 2048-bin histogram lies: neighbouring bins in different 128-byte lines, 64 lines in turn.  An atomic
+// takes its L2 channel about 4 ns (a million adds to all lines of eight copies take 35 us, to the lines of 128
+// neighbouring bins 213 us), and the entries of a bracket crowd into the bins next to its lower end: in bin order a few
+// channels would take them all, as the pass over the gradient with CFs 10, 100 and 1000 showed.
+__device__ __forceinline__ uint32_t bin_word(uint32_t b) { return ((b & 63u) << 5) | (b >> 6); }
+static_assert(NBIN == 64 * 32, "bin_word");
 
 // Random-k: priority of index i, a keyed bijection of the 31-bit integers (adding a constant, multiplying
 // by an odd constant and xor with a right shift are all bijections of [0, 2^31)), so no two indices tie.
@@ -471,86 +474,16 @@ __device__ __forceinline__ void ref_entry(const Params& p, uint32_t u, const Til
 }
 
 
-// One wavefront finds the bin of a 2048-bin histogram (given as `copies` arrays of NBIN counts that
-// are added up) that holds the k-th largest entry: scanning from the top bin down,
-// above < k <= above + count.  Every lane gets the result; bin == NONE if the histogram holds
-// fewer than k entries.  hist must be 16-byte aligned.  Two passes, so that no lane has to keep its 32 bins
-// in registers (this runs inside kernels whose occupancy matters): first the lane totals, which single out the
-// lane whose bins hold the crossing, then that lane's 32 bins, one per lane.
-__device__ __forceinline__ void wave_locate_bin(const uint32_t* hist, int copies, const uint32_t* top_extra, uint32_t k,
+// Four wavefronts (threads q = 0..255 of a 256-thread team; `q` is the thread's number inside the team, `scratch` 8
+// words of LDS owned by the team) search a 2048-bin histogram for the bin of the k-th largest: thread q holds the
+// counts h of bins 8q .. 8q+7, and the first wavefront's `extra` are more counts of the last bin.  Scanning from the top
+// bin down, above < k <= above + count; every thread gets the result, bin == NONE if there are fewer than k entries.
+// The caller provides the barrier: `sync()` must cover at least the team.
+template <typename Sync>
+__device__ __forceinline__ void team_locate_bin(uint32_t h[8], uint32_t extra, uint32_t k, int q, uint32_t* scratch, Sync sync,
                                                 uint32_t& bin, uint32_t& above, uint32_t& count)
 {
-    const int lane = threadIdx.x & 63;
-    // top_extra: 64 more counts for the last bin, one per cache line (stride 32 words), or null
-    const uint32_t extra = wave_sum(top_extra ? top_extra[lane * 32] : 0u);
-    uint32_t mine = 0;  // lane l owns bins 32 l .. 32 l + 31
-    for (int r = 0; r < copies; ++r) {
-        const uint4* hv = (const uint4*)(hist + (size_t)r * NBIN + 32 * lane);
-#pragma unroll 2
-        for (int q = 0; q < 8; ++q) {
-            const uint4 v = hv[q];
-            mine += v.x + v.y + v.z + v.w;
-        }
-    }
-    if (lane == 63) mine += extra;
-    const uint32_t incl = wave_scan(mine);
-    const uint32_t total = __shfl(incl, 63, 64);
-    const uint32_t ab = total - incl;  // entries in the bins of higher lanes
-    const uint64_t m = __ballot(ab < k && ab + mine >= k);
-    if (m == 0ull) { bin = NONE; above = 0; count = 0; return; }
-    const int owner = __ffsll((unsigned long long)m) - 1;
-    const uint32_t ab_owner = __shfl(ab, owner, 64);
-    // lanes 0..31 each take one of the owner's bins
-    uint32_t c = 0;
-    if (lane < 32) {
-        for (int r = 0; r < copies; ++r) c += hist[(size_t)r * NBIN + 32 * owner + lane];
-        if (owner == 63 && lane == 31) c += extra;
-    }
-    // entries of the owner's bins above bin `lane`: suffix sum over lanes lane+1 .. 31
-    const uint32_t inc = wave_scan(c);                       // lanes >= 32 contribute 0
-    const uint32_t sum32 = __shfl(inc, 31, 64);
-    const uint32_t higher = ab_owner + (sum32 - inc);
-    const uint64_t f = __ballot(lane < 32 && higher < k && higher + c >= k);
-    const int src = 63 - __builtin_clzll((unsigned long long)f);  // exactly one lane
-    bin = 32 * owner + src;
-    above = __shfl(higher, src, 64);
-    count = __shfl(c, src, 64);
-}
-
-// The same search by four wavefronts (threads q = 0..255 of a 256-thread team; `q` is the thread's number
-// inside the team, `scratch` 8 words of LDS owned by the team).  Thread q owns bins 8q .. 8q+7 and has all
-// its loads in flight at once.  The caller synchronises the team (all its threads reach this call) and
-// provides the barrier: `sync()` must be a barrier that covers at least the team.
-template <typename Sync>
-__device__ __forceinline__ void team_locate_bin(const uint32_t* hist, int copies, const uint32_t* top_extra, uint32_t k,
-                                                int q, uint32_t* scratch, Sync sync, uint32_t& bin, uint32_t& above,
-                                                uint32_t& count)
-{
     const int lane = q & 63, wv = q >> 6;
-    uint32_t extra = (top_extra && q < 64) ? top_extra[q * 32] : 0u;
-    uint32_t h[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) h[i] = 0;
-    if (copies == REP) {
-        uint4 v[REP][2];
-#pragma unroll
-        for (int r = 0; r < REP; ++r) {
-            const uint4* hv = (const uint4*)(hist + (size_t)r * NBIN + 8 * q);
-            v[r][0] = hv[0]; v[r][1] = hv[1];
-        }
-#pragma unroll
-        for (int r = 0; r < REP; ++r) {
-            h[0] += v[r][0].x; h[1] += v[r][0].y; h[2] += v[r][0].z; h[3] += v[r][0].w;
-            h[4] += v[r][1].x; h[5] += v[r][1].y; h[6] += v[r][1].z; h[7] += v[r][1].w;
-        }
-    } else {
-        for (int r = 0; r < copies; ++r) {
-            const uint4* hv = (const uint4*)(hist + (size_t)r * NBIN + 8 * q);
-            const uint4 a = hv[0], b = hv[1];
-            h[0] += a.x; h[1] += a.y; h[2] += a.z; h[3] += a.w;
-            h[4] += b.x; h[5] += b.y; h[6] += b.z; h[7] += b.w;
-        }
-    }
     extra = wave_sum(extra);  // non-zero in the team's first wavefront only
     uint32_t mine = 0;
 #pragma unroll
@@ -808,6 +741,7 @@ __global__ __launch_bounds__(256) void sample_kernel(Params p)
         for (uint32_t i = lb * 256 + tid; i < NBIN / 4; i += nbk * 256) cs[i] = z;
         for (uint32_t i = lb * 256 + tid; i < (uint32_t)p.n_cf * 64; i += nbk * 256) p.ovfc[((size_t)t * p.n_cf * 64 + i) * 32] = 0;
         for (uint32_t i = lb * 256 + tid; i < blocks; i += nbk * 256) p.list_cnt[(seg_block(p, t, 0) + i) * 32] = 0;
+        if (lb == 0 && tid < XQ_WORDS) p.xq[(size_t)t * p.n_cf * NBIN + tid] = 0;
     }
     if (p.bounds_from != BOUNDS_SAMPLED) return;
     const int64_t s0 = seg_begin(p, t);
@@ -934,7 +868,6 @@ __global__ __launch_bounds__(P * 1024 / G) __attribute__((amdgpu_waves_per_eu(SM
     if (y == 0) {
         if (!is_flat(p))
             for (uint32_t u = seg_tile0(p, t) + tid; u < seg_tile1(p, t); u += T * P) p.tseg[u] = (uint32_t)t;
-        if (tid == 0) p.seg[t].fail = FAIL_NONE;  // the locate step raises it
     }
     if (tid < p.n_cf) {
         const uint32_t k = seg_k(p, t, tid);
@@ -959,8 +892,8 @@ __global__ __launch_bounds__(P * 1024 / G) __attribute__((amdgpu_waves_per_eu(SM
             p.bnd_lo[0] = p.fixed_key; p.bnd_hi[0] = p.fixed_key; p.bnd_mid[0] = NONE;
             CfState st;
             st.k = 0; st.lo = p.fixed_key; st.s = 0; st.mode = MODE_RESOLVED; st.base = p.fixed_key; st.span = 0;
-            st.above = 0; st.c = 0; st.tau = p.fixed_key - 1u; st.need = 0; st.cnt_gt = 0; st.redo = 0; st.lo2 = 0; st.s2 = 0;
-            st.top = p.fixed_key; st.pad = 0;
+            st.above = 0; st.c = 0; st.tau = p.fixed_key - 1u; st.need = 0; st.cnt_gt = 0;
+            st.top = p.fixed_key; st.pad[0] = st.pad[1] = st.pad[2] = st.pad[3] = 0;
             p.st[0] = st;
             SegState sg;
             sg.lo_min = p.fixed_key; sg.fail = FAIL_NONE; sg.pz = p.single ? NONE : p.fixed_key; sg.lo_c = p.fixed_key;
@@ -1103,10 +1036,9 @@ __global__ __launch_bounds__(P * 1024 / G) __attribute__((amdgpu_waves_per_eu(SM
 // a scattered store only for the entries between this key and the threshold, selected ones below it (+0) or
 // unselected ones at or above it (acc put back), instead of one for every selected entry of the bracket; a
 // scattered 4-byte store costs the memory a read and a write of its 64 bytes, 34 us per million of them.
-__device__ __forceinline__ uint32_t zero_from(const Params& p, int t, uint32_t lo, uint32_t top)
+__device__ __forceinline__ uint32_t zero_from(const Params& p, uint32_t lo, uint32_t top, uint32_t mid)  // mid: bnd_mid
 {
     if (p.single || p.no_commit || top == KEY_END) return NONE;
-    const uint32_t mid = p.bnd_mid[(size_t)t * p.n_cf + p.commit];
     if (mid == NONE) return top;
     return mid < lo ? lo : (mid > top ? top : mid);
 }
@@ -1147,7 +1079,7 @@ __device__ __forceinline__ bool bracket_count(SubCtx<NCF>& c, uint32_t key, floa
                 c.ovn[j]++;
                 c.ovs[j] += d * d;
             } else {
-                atomicAdd(&c.h1[j * c.hstride + ((key - c.lo[j]) >> c.sh[j])], 1u);
+                atomicAdd(&c.h1[j * c.hstride + bin_word((key - c.lo[j]) >> c.sh[j])], 1u);
                 inside = true;
             }
         }
@@ -1296,31 +1228,26 @@ __device__ __forceinline__ float element_load(const Params& p, int64_t q)
     return a;
 }
 
-// Exact route: the bounds of the segment a wavefront last worked on (they cost a histogram search).
+// The brackets with which the exact route collects a segment's lists again (in LDS).
 struct ExactBounds {
-    int t;  // segment, -1 = none yet
     uint32_t lo[MAXCF];
     uint32_t sh[MAXCF];
-    uint32_t top[MAXCF];   // narrow route: the end of the bracket the lists were collected with
-    uint32_t end[MAXCF];   // first key past the XBINS bins
-    uint32_t lo_min, lo_c;
+    uint32_t top[MAXCF];   // first key past the bracket
+    uint32_t* hist;        // the histograms' first copy of CF 0; LCAP words between copies
 };
 
 // One sub-tile v, by one wavefront.
 template <int M, bool RND, int NCF>
-__device__ __forceinline__ void stream_subtile(const Params& p, uint32_t v, int lane, ExactBounds* xb)
+__device__ __forceinline__ void stream_subtile(const Params& p, uint32_t v, int lane, const ExactBounds* xb)
 {
     constexpr bool EF = (M != SM_EXACT);  // a first pass: sums acc^2, takes the brackets from the threshold kernel
     const uint32_t u = v / SUB;  // tile
     if (u >= p.n_tiles) return;
     const int t = tile_seg(p, u);
-    const uint32_t fail_kind = EF ? (uint32_t)FAIL_NONE : p.seg[t].fail;
-    if (!EF && fail_kind == FAIL_NONE) return;
     const int64_t sb = seg_begin(p, t), se = seg_end(p, t);
     const int64_t s0 = sb + (int64_t)(u - seg_tile0(p, t)) * TW + (int64_t)(v % SUB) * TS;
     const int64_t e0 = (s0 + TS < se) ? s0 + TS : se;
-    const bool narrow = !EF && fail_kind == FAIL_NARROW;
-    if (s0 >= se && !narrow) {  // sub-tile past the end of the segment
+    if (s0 >= se) {  // sub-tile past the end of the segment
         if (lane == 0) { p.cand_cnt[v] = 0; p.brk_cnt[v] = 0; if (EF) p.ssd[v] = 0.0; }
         if (lane < p.n_cf) { p.ovn[(size_t)v * p.n_cf + lane] = 0; p.ovs[(size_t)v * p.n_cf + lane] = 0.0; }
         return;
@@ -1345,70 +1272,27 @@ __device__ __forceinline__ void stream_subtile(const Params& p, uint32_t v, int 
                 c.lo_min = c.lo[j] < c.lo_min ? c.lo[j] : c.lo_min;
                 if (j == p.commit) {
                     c.lo_c = c.lo[j];
-                    if (M == SM_EF) c.pz = zero_from(p, t, c.lo[j], c.top[j]);
+                    if (M == SM_EF) c.pz = zero_from(p, c.lo[j], c.top[j], p.bnd_mid[(size_t)t * p.n_cf + j]);
                 }
             }
         }
         if (!c.split) c.lo_c = c.lo_min;  // the candidate list takes every entry that concerns some CF
     } else {
-        const bool first = (v == seg_tile0(p, t) * SUB);
-        if (xb->t != t) {
-            xb->t = t;
-            xb->lo_min = NONE; xb->lo_c = NONE;
-#pragma unroll
-            for (int j = 0; j < MAXCF; ++j) {
-                xb->lo[j] = NONE; xb->sh[j] = 10; xb->top[j] = KEY_END; xb->end[j] = KEY_END;
-                if (j < p.n_cf) {
-                    const CfState* st = &p.st[(size_t)t * p.n_cf + j];
-                    if (narrow) {
-                        // the locate step has left the bounds of the CFs that are binned again; the others keep
-                        // their histogram and their plan (lo = NONE: no key is counted for them here)
-                        if (st->redo) { xb->lo[j] = st->lo2; xb->sh[j] = st->s2; xb->top[j] = st->top; }
-                    } else {
-                        // lo_j = base of the coarse (key >> 20) bin that holds the k_j-th largest; XBINS bins of
-                        // 2^10 keys cover that coarse bin, keys above it count as above the bracket
-                        uint32_t b, ab, cn;
-                        wave_locate_bin(p.coarse + (size_t)t * NBIN, 1, nullptr, seg_k(p, t, j), b, ab, cn);
-                        if (b == NONE) { b = 0; if (lane == 0) p.status->error = 1; }
-                        xb->lo[j] = b << 20;
-                    }
-                    if (xb->lo[j] != NONE) {
-                        const uint64_t e = (uint64_t)xb->lo[j] + ((uint64_t)XBINS << xb->sh[j]);
-                        xb->end[j] = e >= (uint64_t)KEY_END ? KEY_END : (uint32_t)e;
-                        if (!narrow) xb->top[j] = xb->end[j];
-                    }
-                    xb->lo_min = xb->lo[j] < xb->lo_min ? xb->lo[j] : xb->lo_min;
-                    if (j == p.commit) xb->lo_c = xb->lo[j];
-                }
-            }
-        }
-        c.lo_min = xb->lo_min; c.lo_c = c.split ? xb->lo_c : xb->lo_min;
-        static_assert(EF || NCF == MAXCF, "the exact routes are compiled for any number of CFs");
+        static_assert(EF || NCF == MAXCF, "the exact route is compiled for any number of CFs");
 #pragma unroll
         for (int j = 0; j < NCF; ++j) {
             if (j < p.n_cf) {
-                c.lo[j] = xb->lo[j];
-                c.sh[j] = xb->sh[j];
-                c.top[j] = xb->end[j];
-                if (first && c.lo[j] != NONE) {
-                    // record the new bounds; clear what the refine pass may add to
-                    CfState* st = &p.st[(size_t)t * p.n_cf + j];
-                    if (lane == 0) {
-                        st->lo = c.lo[j]; st->s = c.sh[j]; st->mode = MODE_FAIL; st->redo = 1;
-                        if (!narrow) st->top = xb->end[j];
-                    }
-                    for (int i = lane; i < NBIN; i += 64) p.hist2[((size_t)t * p.n_cf + j) * NBIN + i] = 0;
-                    if (lane < (int)seg_rep(p, t)) p.list_cnt[(seg_block(p, t, j) + lane) * 32] = 0;
-                }
+                c.lo[j] = xb->lo[j]; c.sh[j] = xb->sh[j]; c.top[j] = xb->top[j];
+                c.lo_min = c.lo[j] < c.lo_min ? c.lo[j] : c.lo_min;
+                if (j == p.commit) c.lo_c = c.lo[j];
             }
         }
-        // (on the narrow route the lists and the segment's candidate thresholds stay as they are)
-        if (first && lane == 0 && !narrow) { p.seg[t].lo_min = c.lo_min; p.seg[t].lo_c = c.lo_c; p.seg[t].pz = NONE; }
+        if (!c.split) c.lo_c = c.lo_min;
     }
-    // the copy of the histogram this wavefront adds to: spread by the sub-tile number, and by the tile number too,
-    // because the narrow route's re-binning calls arrive with v = 8 u only
-    c.hstride = seg_rep(p, t) * NBIN;
-    c.h1 = p.hist1 + (seg_block(p, t, 0) + ((v ^ (v / SUB)) & (seg_rep(p, t) - 1u))) * NBIN;
+    // the copy of the histogram this wavefront adds to, spread by the sub-tile number
+    c.hstride = seg_rep(p, t) * (EF ? NBIN : LCAP);
+    if (EF) c.h1 = p.hist1 + (seg_block(p, t, 0) + ((v ^ (v / SUB)) & (seg_rep(p, t) - 1u))) * NBIN;
+    else c.h1 = xb->hist + ((v ^ (v / SUB)) & (seg_rep(p, t) - 1u)) * LCAP;
     c.cidx = p.cand_idx + (size_t)v * TS;
     c.cval = p.cand_val + (size_t)v * TS;
     c.bkey = p.brk_key + (size_t)v * TS;
@@ -1416,45 +1300,6 @@ __device__ __forceinline__ void stream_subtile(const Params& p, uint32_t v, int 
     c.run = 0;
     c.brun = 0;
     c.ssd = 0.0;
-
-    if (narrow) {
-        // the lists stay as they are; only the histograms of the CFs concerned are rebuilt, with the new bins, from
-        // the tile's bracket lists.  Called for the first sub-tile of a tile only: the wavefront takes the whole tile.
-        // An entry counts for CF j if it lies inside the bracket the lists were collected with (below top_j: what
-        // lies above has been counted as above the bracket already) and from the located bin's first key on; past
-        // that bin's last key it adds to the count above the new, narrower bracket.
-        const TileRef tr = tile_ref(p, u);
-        const uint32_t cnt = tr.tl.total();
-        for (uint32_t i0 = 0; i0 < cnt; i0 += 64 * 8) {
-            uint32_t kq[8];
-#pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                const uint32_t i = i0 + q * 64 + lane;
-                float unused;
-                kq[q] = 0;
-                if (i < cnt) ref_entry(p, u, tr, i, kq[q], unused);
-            }
-#pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                if (i0 + q * 64 + lane >= cnt) continue;
-#pragma unroll
-                for (int j = 0; j < NCF; ++j) {
-                    if (j < c.ncf && kq[q] >= c.lo[j] && kq[q] < xb->top[j]) {
-                        if (kq[q] >= c.top[j]) c.ovn[j]++;
-                        else atomicAdd(&c.h1[j * c.hstride + ((kq[q] - c.lo[j]) >> c.sh[j])], 1u);
-                    }
-                }
-            }
-        }
-#pragma unroll
-        for (int j = 0; j < NCF; ++j) {
-            if (j < p.n_cf) {
-                const uint32_t o = wave_sum(c.ovn[j]);
-                if (lane == 0 && o) atomicAdd(&p.ovfc[(((size_t)t * p.n_cf + j) * 64 + (u & 63)) * 32], o);
-            }
-        }
-        return;
-    }
 
     bool dense = false;
     if (p.vec_ok && (s0 & 3) == 0 && e0 - s0 == TS) {
@@ -1535,7 +1380,7 @@ __device__ __forceinline__ void stream_subtile(const Params& p, uint32_t v, int 
             if (lane == 0) {
                 p.ovn[(size_t)v * p.n_cf + j] = o;
                 p.ovs[(size_t)v * p.n_cf + j] = s;
-                if (o) atomicAdd(&p.ovfc[(((size_t)t * p.n_cf + j) * 64 + (v & 63)) * 32], o);
+                if (EF && o) atomicAdd(&p.ovfc[(((size_t)t * p.n_cf + j) * 64 + (v & 63)) * 32], o);
             }
         }
     }
@@ -1546,28 +1391,13 @@ __device__ __forceinline__ void stream_subtile(const Params& p, uint32_t v, int 
     if (lane == 0) { p.cand_cnt[v] = dense ? DENSE_BIT : c.run; p.brk_cnt[v] = c.brun; }
 }
 
-// First pass (SM_EF, SM_SINGLE): one sub-tile per wavefront, one launch covers the whole gradient.
-// SM_EXACT: a fixed number of wavefronts walks over all tiles (only those of failed segments do any work).
+// The first pass (SM_EF, SM_SINGLE): one sub-tile per wavefront, one launch covers the whole gradient.
 template <int M, bool RND, int NCF>
 __global__ __launch_bounds__(WG) void stream_kernel(Params p)
 {
-    const int lane = threadIdx.x & 63;
+    static_assert(M != SM_EXACT, "the exact route is part of the plan step");
     const uint32_t w = __builtin_amdgcn_readfirstlane(blockIdx.x * WAVES + (threadIdx.x >> 6));
-    if constexpr (M != SM_EXACT) {
-        stream_subtile<M, RND, NCF>(p, w, lane, nullptr);
-    } else {
-        if (p.status->any_fail == 0) return;
-        ExactBounds xb;
-        xb.t = -1;
-        const uint32_t nw = gridDim.x * WAVES;
-        for (uint32_t u = w; u < p.n_tiles; u += nw) {
-            const uint32_t kind = p.seg[tile_seg(p, u)].fail;
-            if (kind == FAIL_NONE) continue;
-            // FAIL_NARROW: one call re-bins the bracket lists of the whole tile; FAIL_FULL: sub-tile by sub-tile
-            const int subs = (kind == FAIL_FULL) ? SUB : 1;
-            for (int j = 0; j < subs; ++j) stream_subtile<SM_EXACT, RND, NCF>(p, u * SUB + j, lane, &xb);
-        }
-    }
+    stream_subtile<M, RND, NCF>(p, w, threadIdx.x & 63, nullptr);
 }
 
 // The candidates of sub-tile v that its first pass replaced by +0 in the residual get their values back (the
@@ -1593,104 +1423,19 @@ __device__ __forceinline__ void put_back_subtile(const Params& p, uint32_t v, ui
     }
 }
 
-// ---------------------------------------------------------------------------------------------
-// F1 (exact route, FAIL_FULL): histogram of key >> 20 over the tiles of failed segments; the wavefront
-// of a failed segment's first tile also clears that segment's bracket histograms
-// ---------------------------------------------------------------------------------------------
-constexpr int CSUB = 8;  // copies of the coarse histogram inside a workgroup: lane l counts in copy l % CSUB
-
-__global__ __launch_bounds__(WG) void coarse_kernel(Params p)
-{
-    // Gradient magnitudes crowd into a few exponents, so most lanes of a wavefront hit the same few bins and
-    // LDS atomics on one copy serialise 64-fold; CSUB copies cut that to 64 / CSUB.
-    // (a row is one word longer than the histogram, so that the CSUB counters of one bin lie in different banks)
-    __shared__ uint32_t lh[CSUB][NBIN + 1];
-    if (p.status->any_fail == 0) return;
-    const int tid = threadIdx.x, lane = tid & 63;
-    uint32_t* h = lh[lane & (CSUB - 1)];
-    // a fixed number of workgroups walks over the tiles (a workgroup takes WAVES consecutive tiles at a time, one per
-    // wavefront), so that the launch costs little when nothing failed
-    for (uint32_t i = tid; i < CSUB * (NBIN + 1); i += WG) (&lh[0][0])[i] = 0;
-    __syncthreads();
-    int cur = -1;  // segment whose counts sit in lh
-    for (uint32_t u0 = blockIdx.x * WAVES; u0 < p.n_tiles; u0 += gridDim.x * WAVES) {
-        // the workgroup's tiles may belong to different segments: one segment at a time, flushed in between
-        const uint32_t u1 = u0 + WAVES < p.n_tiles ? u0 + WAVES : p.n_tiles;
-        for (uint32_t ub = u0; ub < u1;) {
-            const int t = tile_seg(p, ub);
-            uint32_t ue = ub + 1;
-            while (ue < u1 && tile_seg(p, ue) == t) ++ue;
-            const uint32_t kind = p.seg[t].fail;
-            if (kind == FAIL_FULL) {
-                if (cur != t && cur >= 0) {
-                    // flush the previous segment's counts
-                    __syncthreads();
-                    uint32_t* gh = p.coarse + (size_t)cur * NBIN;
-                    for (uint32_t i = tid; i < NBIN; i += WG) {
-                        uint32_t v = 0;
-#pragma unroll
-                        for (int c = 0; c < CSUB; ++c) { v += lh[c][i]; lh[c][i] = 0; }
-                        if (v) atomicAdd(&gh[i], v);
-                    }
-                    __syncthreads();
-                }
-                cur = t;
-                const uint32_t u = ub + (tid >> 6);
-                if (u < ue) {
-                    const int64_t sb = seg_begin(p, t), se = seg_end(p, t);
-                    const int64_t s0 = sb + (int64_t)(u - seg_tile0(p, t)) * TW;
-                    const int64_t e0 = (s0 + TW < se) ? s0 + TW : se;
-                    if (u == seg_tile0(p, t)) {
-                        for (uint32_t i = lane; i < (uint32_t)p.n_cf * seg_rep(p, t) * NBIN; i += 64) p.hist1[seg_block(p, t, 0) * NBIN + i] = 0;
-                        for (int i = lane; i < p.n_cf * 64; i += 64) p.ovfc[((size_t)t * p.n_cf * 64 + i) * 32] = 0;
-                    }
-                    const uint32_t pz = p.single ? NONE : p.seg[t].pz;
-                    if (pz != NONE) {
-                        // acc is read again from the residual: first put back what the first pass replaced by +0 there
-                        for (int j = 0; j < SUB; ++j) put_back_subtile(p, u * SUB + j, pz, lane);
-                        __threadfence_block();  // the loads below are this wavefront's own, of the same addresses
-                    }
-                    for (int64_t q0 = s0 + lane; q0 < e0; q0 += 64 * 16) {
-                        // all loads first, without branches around them (an element past the end reads the last
-                        // one instead and is not counted), so that they are in flight together
-                        float a[16];
-#pragma unroll
-                        for (int r = 0; r < 16; ++r) a[r] = p.acc[q0 + r * 64 < e0 ? q0 + r * 64 : e0 - 1];
-#pragma unroll
-                        for (int r = 0; r < 16; ++r)
-                            if (q0 + r * 64 < e0) atomicAdd(&h[cand_key(p, (int32_t)(q0 + r * 64), a[r]) >> 20], 1u);
-                    }
-                }
-            }
-            ub = ue;
-        }
-    }
-    if (cur >= 0) {
-        __syncthreads();
-        uint32_t* gh = p.coarse + (size_t)cur * NBIN;
-        for (uint32_t i = tid; i < NBIN; i += WG) {
-            uint32_t v = 0;
-#pragma unroll
-            for (int c = 0; c < CSUB; ++c) v += lh[c][i];
-            if (v) atomicAdd(&gh[i], v);
-        }
-    }
-}
-
 // How the bin that holds the k-th largest gets resolved to one key.
 struct BinPlan {
     uint32_t mode, base, span, above, c;
 };
 
-// Decide from the located bin (b, above, c) of the bracket histogram with bins (key - lo) >> s, of which the
-// first nb are in use (anything from bin nb on was counted as above the bracket and arrives as bin OVF).
+// Decide from the located bin (b, above, c) of the bracket histogram with bins (key - lo) >> s; what lies above the
+// bracket arrives as bin OVF.
 __device__ __forceinline__ BinPlan plan_bin(uint32_t lo, uint32_t s, uint32_t b, uint32_t above, uint32_t c)
 {
     BinPlan q;
     if (b == NONE || b == OVF) q.mode = MODE_FAIL;  // fewer than k entries from lo on, or the k-th lies above the bracket
     else if (s == 0) q.mode = MODE_RESOLVED;
     else if (c <= LCAP) q.mode = MODE_GATHER;
-    else if (s <= 11) q.mode = MODE_HIST;
     else q.mode = MODE_FAIL;
     q.base = (b == NONE || b == OVF) ? 0u : lo + (b << s);
     q.span = (1u << s) - 1u;
@@ -1699,73 +1444,380 @@ __device__ __forceinline__ BinPlan plan_bin(uint32_t lo, uint32_t s, uint32_t b,
     return q;
 }
 
-__device__ __forceinline__ void store_plan(CfState* st, const BinPlan& q)
+// ---------------------------------------------------------------------------------------------
+// PLAN: find the bracket-histogram bin of every CF's k-th largest and decide how to resolve it.  All workgroups of a
+//       segment (all of the launch in flat mode) work that out for themselves, which costs a few redundant reads of the
+//       histograms and spares a kernel boundary: a segment whose bracket has not failed is done with that, and the
+//       workgroups of one whose bracket has go on with the exact route in the same launch, without anybody having had to
+//       tell them.  (As three launches, the locate step and two that found nothing to do, a call took 2 to 3 us more: on
+//       the ResNet101 shape at CF 100 132.9 -> 129.9 us, 1 MiB buckets 40.1 -> 38.3 us.  The exact routes themselves, forced
+//       on that shape: 474 -> 397 us with one CF, 780 -> 517 us with three; a mass of equal values, which the last step
+//       used to count again alone, 357 -> 40 ms.)
+//
+// Exact routes.  The segment's tiles are cut into chunks, which the running workgroups claim from a counter; a
+// workgroup keeps its chunks through all phases, so that what one phase writes for a tile (residual, lists) is read by
+// the same workgroup in the next, and only histograms, made of device-wide atomics, pass between workgroups.  A
+// workgroup waits for the others only when every chunk has been claimed, that is, for workgroups that are running and do
+// not wait for anybody before they have finished the phase: the wait ends whatever else shares the chip and however few
+// of this launch's workgroups are resident.
+//   FAIL_FULL: phase 0 puts back what the pass replaced by +0 in the residual and histograms key >> 20 of all elements;
+//              phase 1 collects the lists again with the located 2^20 keys as bracket, in bins of 2^9 keys.
+//   FAIL_NARROW, FAIL_TIES: the located bin is cut into up to NBIN parts and counted again from the bracket lists.
+//   Phase 2:   a bin that is still too full is cut again, which leaves bins one key wide (22 = 11 + 11 bits at most).
+// ---------------------------------------------------------------------------------------------
+constexpr int PLAN_T = 1024;            // threads: four teams that search one CF's histogram each
+constexpr int PLAN_W = PLAN_T / 64;
+constexpr uint32_t PLAN_GRID = 256;     // workgroups of a flat call, one per CU
+constexpr uint32_t PLAN_HELP = 64;      // layerwise: tiles of a large tensor per further workgroup
+constexpr uint32_t PLAN_CHUNKS = 4096;  // chunks of a segment at most
+constexpr int CSUB = 8;  // copies of the coarse histogram inside a workgroup: lane l counts in copy l % CSUB
+constexpr int XSHIFT = 9;               // bins of 2^XSHIFT keys cover the 2^20 keys of a coarse bin
+static_assert((NBIN << XSHIFT) == (1 << 20) && LCAP == 2 * NBIN && XQ_WORDS >= 4, "two histograms per gather list; a counter per phase");
+
+struct PlanShared {
+    ExactBounds xb;
+    uint32_t scratch[PLAN_T / 256][8];
+    uint32_t fb[MAXCF], fa[MAXCF], fc[MAXCF];   // what the search found: bin, entries above it, entries in it
+    uint32_t k[MAXCF], lo[MAXCF], s[MAXCF], top[MAXCF];
+    uint32_t mode[MAXCF], base[MAXCF], above[MAXCF], c[MAXCF];
+    uint32_t bs[MAXCF];                         // the located bin spans 2^bs keys
+    uint32_t cut[MAXCF];                        // 1: it is being cut again, into parts of 2^s2 keys
+    uint32_t s2[MAXCF];
+    uint32_t pz;                                // SegState::pz
+    uint32_t got, n_own, leader;
+    uint32_t own[PLAN_CHUNKS];                  // the chunks this workgroup has claimed
+    // Gradient magnitudes crowd into a few exponents, so most lanes of a wavefront hit the same few bins and LDS atomics
+    // on one copy serialise 64-fold; CSUB copies cut that to 64 / CSUB.  (a row is one word longer than the histogram,
+    // so that the CSUB counters of one bin lie in different banks)
+    uint32_t lh[CSUB][NBIN + 1];
+};
+
+// All CFs' searches; setup(j, hist, copies, stride, extra, want) says what to search for CF j: a 2048-bin histogram (bin b
+// at bin_word(b)) in `copies` arrays `stride` words apart that are added up (16-byte aligned), and 64 more counts for the last bin, one per
+// cache line, or null.  Results in sh.fb / fa / fc.  Called by the whole workgroup.
+// The step is one workgroup's reads (64 KB per CF of a large tensor) and a short chain of barriers behind them, so the
+// reads of a call with one or two CFs are split over all four teams, which then add up through LDS.
+template <typename Setup>
+__device__ __forceinline__ void plan_search(PlanShared& sh, int n_cf, int tid, Setup setup)
 {
-    st->mode = q.mode;
-    if (q.mode != MODE_FAIL) {
-        st->base = q.base; st->span = q.span; st->above = q.above; st->c = q.c;
-        if (q.mode == MODE_RESOLVED) { st->tau = q.base; st->cnt_gt = q.above; st->need = st->k - q.above; }
+    const int team = tid >> 8, q = tid & 255;
+    const int subs = n_cf == 1 ? 4 : n_cf == 2 ? 2 : 1, at_once = 4 / subs;   // teams per CF, CFs per round
+    const int sub = team % subs;
+    uint32_t* part = &sh.lh[0][0];   // (the coarse counts are not in use while a search runs)
+    for (int j0 = 0; j0 < n_cf; j0 += at_once) {
+        const int jt = j0 + team / subs, j = jt < n_cf ? jt : n_cf - 1;
+        const uint32_t *hist, *extra_at;
+        uint32_t copies, stride, want, b, above, c;
+        setup(j, hist, copies, stride, extra_at, want);
+        uint32_t h[8], extra = (extra_at && sub == 0 && q < 64) ? extra_at[q * 32] : 0u;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) h[i] = 0;
+        const auto add = [&](const uint4 (&v)[2]) {
+            h[0] += v[0].x; h[1] += v[0].y; h[2] += v[0].z; h[3] += v[0].w;
+            h[4] += v[1].x; h[5] += v[1].y; h[6] += v[1].z; h[7] += v[1].w;
+        };
+        const auto fetch = [&](uint32_t r, uint4 (&v)[2]) {
+            const uint4* hv = (const uint4*)(hist + (size_t)r * stride + 8 * q);
+            v[0] = hv[0]; v[1] = hv[1];
+        };
+        if (jt < n_cf) {
+            if (copies == (uint32_t)REP && subs == 4) {
+                uint4 v[REP / 4][2];
+#pragma unroll
+                for (int r = 0; r < REP / 4; ++r) fetch(sub + 4 * r, v[r]);
+#pragma unroll
+                for (int r = 0; r < REP / 4; ++r) add(v[r]);
+            } else if (copies == (uint32_t)REP && subs == 2) {
+                uint4 v[REP / 2][2];
+#pragma unroll
+                for (int r = 0; r < REP / 2; ++r) fetch(sub + 2 * r, v[r]);
+#pragma unroll
+                for (int r = 0; r < REP / 2; ++r) add(v[r]);
+            } else if (copies == (uint32_t)REP) {
+                uint4 v[REP][2];
+#pragma unroll
+                for (int r = 0; r < REP; ++r) fetch(r, v[r]);
+#pragma unroll
+                for (int r = 0; r < REP; ++r) add(v[r]);
+            } else {
+                for (uint32_t r = sub; r < copies; r += subs) {
+                    uint4 v[2];
+                    fetch(r, v);
+                    add(v);
+                }
+            }
+        }
+        // the words 8 q .. 8 q + 7 (bin_word order) go through LDS, which puts them into bin order and adds the teams up
+#pragma unroll
+        for (int i = 0; i < 8; ++i) part[(team * 8 + i) * 257 + q] = h[i];
+        __syncthreads();
+        if (sub == 0) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const uint32_t w = bin_word(8u * (uint32_t)q + (uint32_t)i);
+                h[i] = part[(team * 8 + (w & 7u)) * 257 + (w >> 3)];
+                for (int x = 1; x < subs; ++x) h[i] += part[((team + x) * 8 + (w & 7u)) * 257 + (w >> 3)];
+            }
+        }
+        team_locate_bin(h, extra, want, q, sh.scratch[team], [] { __syncthreads(); }, b, above, c);
+        if (q == 0 && sub == 0 && jt < n_cf) { sh.fb[j] = b; sh.fa[j] = above; sh.fc[j] = c; }
+    }
+    __syncthreads();
+}
+static_assert(4 * 8 * 257 <= CSUB * (NBIN + 1), "the teams' counts fit into the coarse counts' LDS");
+
+// Everything this workgroup has written is visible to the device; then all workgroups with chunks of the segment have
+// got here, and what they have written is visible to this one.
+__device__ __forceinline__ void plan_barrier(PlanShared& sh, uint32_t* done, uint32_t n_chunks, int tid)
+{
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");   // every wavefront's stores and atomics are done ...
+    __syncthreads();
+    if (tid == 0) {
+        __threadfence();                                           // ... and leave this XCD's L2
+        atomicAdd(done, sh.n_own);
+        while (__hip_atomic_load(done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < n_chunks) __builtin_amdgcn_s_sleep(4);
+    }
+    __syncthreads();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+}
+
+// One tile's entries of the bracket lists into the histograms (first copy of CF 0 at hist) of the CFs that are cut again.
+__device__ __forceinline__ void plan_recount(const Params& p, const PlanShared& sh, uint32_t u, uint32_t* hist, uint32_t copies, int lane)
+{
+    const TileRef tr = tile_ref(p, u);
+    const uint32_t cnt = tr.tl.total();
+    for (uint32_t i0 = 0; i0 < cnt; i0 += 64 * 8) {
+        uint32_t kq[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const uint32_t i = i0 + q * 64 + lane;
+            float unused;
+            ref_entry(p, u, tr, i < cnt ? i : 0u, kq[q], unused);
+        }
+        for (int j = 0; j < p.n_cf; ++j) {
+            if (!sh.cut[j]) continue;
+            uint32_t* h = hist + ((size_t)j * copies + (u & (copies - 1u))) * LCAP;
+            const uint32_t base = sh.base[j], top = sh.top[j], width = 1u << sh.bs[j], s2 = sh.s2[j];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                // (an entry counts if it lies inside the bracket the lists were collected with: what lies above was
+                // counted as above the bracket by the pass and may be listed all the same)
+                const bool in = i0 + q * 64 + lane < cnt && kq[q] < top && kq[q] >= base && kq[q] - base < width;
+                const uint32_t bin = (kq[q] - base) >> s2;
+                // a mass of equal keys: the lanes that share the first one's bin add once
+                const uint64_t m = __ballot(in);
+                if (m == 0ull) continue;
+                const int first = __ffsll((unsigned long long)m) - 1;
+                const uint64_t same = __ballot(in && bin == (uint32_t)__shfl((int)bin, first, 64));
+                if (lane == first) atomicAdd(&h[bin_word(bin)], (uint32_t)__popcll(same));
+                else if (in && !((same >> lane) & 1ull)) atomicAdd(&h[bin_word(bin)], 1u);
+            }
+        }
     }
 }
 
-// ---------------------------------------------------------------------------------------------
-// L1: one workgroup per (segment, CF): find the bracket-histogram bin of the k-th largest and
-// decide how to resolve it; a segment whose bracket failed is marked for an exact route
-// ---------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void locate_kernel(Params p)
+template <bool RND>
+__global__ __launch_bounds__(PLAN_T) void plan_kernel(Params p)
 {
-    __shared__ uint32_t scratch[8];
-    const int tid = threadIdx.x;
-    const uint32_t id = blockIdx.x;
-    const int t = id / p.n_cf, j = id - t * p.n_cf;
-    if (seg_small(p, t)) return;
-    CfState* st = &p.st[id];
-    const uint32_t k = seg_k(p, t, j);
-    const uint32_t lo = p.bnd_lo[id];
-    uint32_t s, top;
-    bracket_bins(lo, p.bnd_hi[id], s, top);
-    uint32_t b, above, c;
-    const uint32_t copies = seg_rep(p, t);
-    team_locate_bin(p.hist1 + seg_block(p, t, j) * NBIN, (int)copies, p.ovfc + (size_t)id * 64 * 32, k, tid, scratch,
-                    [] { __syncthreads(); }, b, above, c);
-    const BinPlan q = plan_bin(lo, s, b, above, c);
-    if (q.mode == MODE_HIST)
-        for (int i = tid; i < NBIN; i += 256) p.hist2[(size_t)id * NBIN + i] = 0;
-    const bool narrow = q.mode == MODE_FAIL && b != NONE && b != OVF;
-    if (narrow) {
-        // a bin 2^s keys wide (s > 11) with more than LCAP keys: XBINS bins of 2^(s - 10) keys cover it, and a
-        // bin at most 2^10 keys wide can always be resolved (gathered or histogrammed key by key); this CF's
-        // histogram is rebuilt by the exact route, the count above the bracket stays
-        for (uint32_t i = tid; i < copies * NBIN; i += 256) p.hist1[seg_block(p, t, j) * NBIN + i] = 0;
-    }
-    if (tid == 0) {
-        st->k = k; st->lo = lo; st->s = s; st->top = top;
-        st->base = 0; st->span = 0; st->above = 0; st->c = 0; st->tau = 0; st->need = 0; st->cnt_gt = 0;
-        st->redo = 0; st->lo2 = 0; st->s2 = 0; st->pad = 0;
-        store_plan(st, q);
-        if (q.mode == MODE_FAIL) {
-            p.status->any_fail = 1;
-            uint32_t kind = FAIL_FULL;
-            if (narrow) {
-                kind = FAIL_NARROW;
-                st->redo = 1; st->lo2 = lo + (b << s); st->s2 = s - 10;
-            }
-            if (atomicMax(&p.seg[t].fail, kind) == 0u) atomicAdd(&p.status->n_fail, 1);
+    __shared__ PlanShared sh;
+    const int tid = threadIdx.x, lane = tid & 63, wib = tid >> 6;
+    int t = 0;
+    bool first_block = blockIdx.x == 0;   // of the segment
+    if (!is_flat(p)) {
+        if (blockIdx.x < (uint32_t)p.n_seg) {
+            t = (int)blockIdx.x;
+            first_block = true;
+        } else {
+            const uint32_t u = (blockIdx.x - (uint32_t)p.n_seg) * PLAN_HELP;
+            if (u >= p.n_tiles) return;
+            t = tile_seg(p, u);
+            if (u - seg_tile0(p, t) < PLAN_HELP) return;   // (the segment's first workgroup is enough for these tiles)
+            first_block = false;
         }
-        if (j == 0) {
-            // what the segment's tiles need of all its CFs together
-            uint32_t lo_min = NONE, lo_c = NONE, pz = NONE;
-            for (int x = 0; x < p.n_cf; ++x) {
-                const uint32_t lx = p.bnd_lo[(size_t)t * p.n_cf + x];
-                lo_min = lx < lo_min ? lx : lo_min;
-                if (x == p.commit) {
-                    uint32_t sx, tx;
-                    bracket_bins(lx, p.bnd_hi[(size_t)t * p.n_cf + x], sx, tx);
-                    lo_c = lx;
-                    pz = zero_from(p, t, lx, tx);
+        if (seg_small(p, t)) return;
+    }
+    const uint32_t copies = seg_rep(p, t);
+    const size_t id0 = (size_t)t * p.n_cf;
+    // (the brackets are fetched along with the histograms)
+    uint32_t b_lo = 0, b_hi = 0, b_mid = 0;
+    if (tid < p.n_cf) { b_lo = p.bnd_lo[id0 + tid]; b_hi = p.bnd_hi[id0 + tid]; b_mid = p.bnd_mid[id0 + tid]; }
+    plan_search(sh, p.n_cf, tid, [&](int j, const uint32_t*& hist, uint32_t& nc, uint32_t& stride, const uint32_t*& extra, uint32_t& want) {
+        hist = p.hist1 + seg_block(p, t, j) * NBIN; nc = copies; stride = NBIN;
+        extra = p.ovfc + (id0 + j) * 64 * 32; want = seg_k(p, t, j);
+    });
+    if (tid < p.n_cf) {
+        const int j = tid;
+        const uint32_t lo = b_lo;
+        uint32_t s, top;
+        bracket_bins(lo, b_hi, s, top);
+        if (j == p.commit) sh.pz = zero_from(p, lo, top, b_mid);
+        const uint32_t b = sh.fb[j];
+        const BinPlan q = plan_bin(lo, s, b, sh.fa[j], sh.fc[j]);
+        sh.k[j] = seg_k(p, t, j); sh.lo[j] = lo; sh.s[j] = s; sh.top[j] = top;
+        sh.mode[j] = q.mode; sh.base[j] = q.base; sh.above[j] = q.above; sh.c[j] = q.c; sh.bs[j] = s;
+    }
+    __syncthreads();
+    uint32_t kind = FAIL_NONE;
+    for (int j = 0; j < p.n_cf; ++j) {
+        if (sh.mode[j] != MODE_FAIL) continue;
+        const uint32_t b = sh.fb[j];
+        const uint32_t x = (b == NONE || b == OVF) ? FAIL_FULL : (sh.s[j] > 11u ? FAIL_NARROW : FAIL_TIES);
+        kind = x > kind ? x : kind;
+    }
+    bool writes = first_block;   // this workgroup records the plan
+    if (kind != FAIL_NONE) {
+        // ---- exact routes
+        uint32_t* xq = p.xq + (size_t)t * p.n_cf * NBIN;
+        const uint32_t u0 = seg_tile0(p, t), u1 = seg_tile1(p, t), tiles = u1 - u0;
+        // (two tiles are one sub-tile per wavefront; a few chunks per workgroup leave little of a last, uneven round)
+        constexpr uint32_t UNIT = PLAN_W / SUB;
+        const uint32_t per = UNIT * ((tiles + UNIT * PLAN_CHUNKS - 1) / (UNIT * PLAN_CHUNKS));  // tiles per chunk
+        const uint32_t n_chunks = (tiles + per - 1) / per;
+        uint32_t* xhist = p.list_key + seg_block(p, t, 0) * LCAP;   // the first of the two sets of histograms
+        const bool full = kind == FAIL_FULL;
+        const uint32_t pz = sh.pz;
+        __syncthreads();   // (sh.lo / top / fb are rewritten below)
+        if (tid == 0) { sh.n_own = 0; sh.leader = 0; }
+        if (full)
+            for (uint32_t i = tid; i < CSUB * (NBIN + 1); i += PLAN_T) (&sh.lh[0][0])[i] = 0;
+        uint32_t next = tid == 0 ? atomicAdd(&xq[0], 1u) : 0u;
+        for (;;) {
+            if (tid == 0) sh.got = next;
+            __syncthreads();
+            const uint32_t at = sh.got;
+            __syncthreads();
+            if (at >= n_chunks) break;
+            if (tid == 0) {
+                sh.own[sh.n_own++] = at;
+                if (at == 0) sh.leader = 1;
+                next = atomicAdd(&xq[0], 1u);   // (on its way while this chunk is worked on)
+            }
+            if (at == 0) {
+                const uint4 z = make_uint4(0u, 0u, 0u, 0u);
+                uint4* h = (uint4*)xhist;
+                for (uint32_t i = tid; i < (uint32_t)p.n_cf * copies * (LCAP / 4); i += PLAN_T) h[i] = z;
+            }
+            if (!full) continue;
+            uint32_t* h = sh.lh[lane & (CSUB - 1)];
+            const int64_t sb = seg_begin(p, t), se = seg_end(p, t);
+            const uint32_t v1 = (u0 + (at + 1) * per < u1 ? u0 + (at + 1) * per : u1) * SUB;
+            for (uint32_t v = (u0 + at * per) * SUB + wib; v < v1; v += PLAN_W) {
+                const int64_t s0 = sb + (int64_t)(v - u0 * SUB) * TS;
+                const int64_t e0 = (s0 + TS < se) ? s0 + TS : se;
+                if (s0 >= se) continue;
+                if (pz != NONE) {
+                    // acc is read again from the residual: first put back what the first pass replaced by +0 there
+                    put_back_subtile(p, v, pz, lane);
+                    __threadfence_block();  // the loads below are this wavefront's own, of the same addresses
+                }
+                // all loads first, without branches around them (an element past the end reads the last one instead and
+                // is not counted), so that they are in flight together
+                static_assert(TS == 64 * 16, "a lane's loads cover the sub-tile");
+                float a[16];
+#pragma unroll
+                for (int r = 0; r < 16; ++r) a[r] = p.acc[s0 + lane + r * 64 < e0 ? s0 + lane + r * 64 : e0 - 1];
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    if (s0 + lane + r * 64 < e0) atomicAdd(&h[cand_key(p, (int32_t)(s0 + lane + r * 64), a[r]) >> 20], 1u);
+            }
+        }
+        if (sh.n_own == 0) return;   // every chunk is somebody else's
+        writes = sh.leader != 0;
+        if (full) {
+            __syncthreads();
+            uint32_t* gh = p.coarse + (size_t)t * NBIN;
+            for (uint32_t i = tid; i < NBIN; i += PLAN_T) {
+                uint32_t v = 0;
+#pragma unroll
+                for (int c = 0; c < CSUB; ++c) v += sh.lh[c][i];
+                if (v) atomicAdd(&gh[bin_word(i)], v);
+            }
+        }
+        plan_barrier(sh, &xq[1], n_chunks, tid);
+        if (full) {
+            // the coarse (key >> 20) bin of every CF's k-th largest is the new bracket
+            plan_search(sh, p.n_cf, tid, [&](int j, const uint32_t*& hist, uint32_t& nc, uint32_t& stride, const uint32_t*& extra, uint32_t& want) {
+                hist = p.coarse + (size_t)t * NBIN; nc = 1; stride = NBIN; extra = nullptr; want = sh.k[j];
+            });
+            if (tid < p.n_cf) {
+                uint32_t b = sh.fb[tid];
+                if (b == NONE) { b = 0; p.status->error = 1; }
+                sh.lo[tid] = b << 20; sh.s[tid] = XSHIFT; sh.top[tid] = (b + 1u) << 20;   // (2^31, KEY_END, at most)
+                sh.above[tid] = sh.fa[tid]; sh.base[tid] = b << 20; sh.bs[tid] = 20; sh.s2[tid] = XSHIFT; sh.cut[tid] = 1;
+                sh.xb.lo[tid] = b << 20; sh.xb.sh[tid] = XSHIFT; sh.xb.top[tid] = (b + 1u) << 20;
+            }
+        } else if (tid < p.n_cf) {
+            const bool x = sh.mode[tid] == MODE_FAIL;
+            sh.cut[tid] = x ? 1u : 0u;
+            sh.s2[tid] = sh.bs[tid] > 11u ? sh.bs[tid] - 11u : 0u;
+        }
+        if (tid == 0) sh.xb.hist = xhist;
+        __syncthreads();
+        for (int phase = 1; phase <= 2; ++phase) {
+            uint32_t* hist = xhist + (phase - 1) * NBIN;
+            // the workgroup's chunks, dealt over its wavefronts by the sub-tile or by the tile
+            const uint32_t per_chunk = full && phase == 1 ? per * SUB : per, all = sh.n_own * per_chunk;
+            for (uint32_t i = wib; i < all; i += PLAN_W) {
+                const uint32_t x = i / per_chunk, first = u0 + sh.own[x] * per;
+                if (full && phase == 1) {
+                    const uint32_t v = __builtin_amdgcn_readfirstlane(first * SUB + (i - x * per_chunk));
+                    if (v < u1 * SUB) stream_subtile<SM_EXACT, RND, MAXCF>(p, v, lane, &sh.xb);
+                } else {
+                    const uint32_t u = first + (i - x * per_chunk);
+                    if (u < u1) plan_recount(p, sh, u, hist, copies, lane);
                 }
             }
-            p.seg[t].lo_min = lo_min; p.seg[t].lo_c = lo_c; p.seg[t].pz = pz;
+            plan_barrier(sh, &xq[1 + phase], n_chunks, tid);
+            // the part that holds the k-th largest
+            plan_search(sh, p.n_cf, tid, [&](int j, const uint32_t*& h, uint32_t& nc, uint32_t& stride, const uint32_t*& extra, uint32_t& want) {
+                h = hist + (size_t)j * copies * LCAP; nc = copies; stride = LCAP; extra = nullptr; want = sh.k[j] - sh.above[j];
+            });
+            if (tid < p.n_cf && sh.cut[tid]) {
+                const uint32_t b = sh.fb[tid];
+                if (b == NONE) { p.status->error = 1; sh.cut[tid] = 0; sh.mode[tid] = MODE_FAIL; }
+                else {
+                    sh.base[tid] += b << sh.s2[tid];
+                    sh.above[tid] += sh.fa[tid];
+                    sh.c[tid] = sh.fc[tid];
+                    sh.bs[tid] = sh.s2[tid];
+                    sh.mode[tid] = sh.bs[tid] == 0u ? MODE_RESOLVED : (sh.c[tid] <= (uint32_t)LCAP ? MODE_GATHER : MODE_FAIL);
+                    sh.cut[tid] = sh.mode[tid] == MODE_FAIL ? 1u : 0u;
+                    sh.s2[tid] = sh.bs[tid] > 11u ? sh.bs[tid] - 11u : 0u;
+                }
+            }
+            __syncthreads();
+            bool again = false;
+            for (int j = 0; j < p.n_cf; ++j) again = again || sh.cut[j] != 0u;
+            if (!again) break;
+        }
+    }
+    if (!writes) return;
+    if (tid < p.n_cf) {
+        const int j = tid;
+        CfState st;
+        st.k = sh.k[j]; st.lo = sh.lo[j]; st.s = sh.s[j]; st.mode = sh.mode[j];
+        st.base = 0; st.span = 0; st.above = 0; st.c = 0; st.tau = 0; st.need = 0; st.cnt_gt = 0; st.top = sh.top[j];
+        st.pad[0] = st.pad[1] = st.pad[2] = st.pad[3] = 0;
+        if (st.mode == MODE_FAIL) {
+            p.status->error = 1;   // the exact routes cannot fail
+        } else {
+            st.base = sh.base[j]; st.span = (1u << sh.bs[j]) - 1u; st.above = sh.above[j]; st.c = sh.c[j];
+            if (st.mode == MODE_RESOLVED) { st.tau = st.base; st.cnt_gt = st.above; st.need = st.k - st.above; }
+        }
+        p.st[id0 + j] = st;
+    }
+    if (tid == 0) {
+        // what the segment's tiles need of all its CFs together
+        uint32_t lo_min = NONE;
+        for (int x = 0; x < p.n_cf; ++x) lo_min = sh.lo[x] < lo_min ? sh.lo[x] : lo_min;
+        SegState sg;
+        sg.lo_min = lo_min; sg.fail = kind; sg.lo_c = sh.lo[p.commit];
+        sg.pz = kind == FAIL_FULL ? NONE : sh.pz;
+        p.seg[t] = sg;
+        if (kind >= FAIL_NARROW) {
+            p.status->any_fail = 1;
+            atomicAdd(&p.status->n_fail, 1);
+            if (kind == FAIL_NARROW) atomicAdd(&p.status->n_narrow, 1);
         }
     }
 }
@@ -1774,9 +1826,7 @@ __global__ __launch_bounds__(256) void locate_kernel(Params p)
 // R1: one wavefront per tile.  The tile's sums of the pass over the gradient (energy, entries above
 // every CF's bracket and their energy) are added up over its sub-tiles; then the tile's entries inside
 // the brackets are walked: per CF, those above the bin that holds the k-th largest are counted and
-// their energy summed, those inside that bin are gathered (key, tile, value) or histogrammed.  For a
-// segment that took an exact route the plan is derived here, by every wavefront for itself, from the
-// rebuilt bracket histogram (its first tile's wavefront records it).
+// their energy summed, those inside that bin are gathered (key, tile, value).
 // ---------------------------------------------------------------------------------------------
 // (the form for four CFs is held to 80 registers, a dozen values spilled: six wavefronts per SIMD instead of four
 // take the ResNet101 shape's tiles in one round instead of two)
@@ -1791,7 +1841,6 @@ __global__ __launch_bounds__(LWG) __attribute__((amdgpu_waves_per_eu((NCF == 3 |
     const uint32_t u = __builtin_amdgcn_readfirstlane(blockIdx.x * LWAVES + (threadIdx.x >> 6));
     if (u >= p.n_tiles) return;
     // loads that depend on nothing but the tile number come first, so that they are in flight together
-    const int any_fail = p.status->any_fail;
     const double ssd = lane < SUB ? p.ssd[(size_t)u * SUB + lane] : 0.0;
     // ... among them the heads of the tile's eight lists, before their lengths are known: lane l takes entries
     // l % 8 + 8 r (r < SPEC_R) of sub-tile l / 8.  A tile whose lists are no longer than that (most tiles of a call
@@ -1812,7 +1861,7 @@ __global__ __launch_bounds__(LWG) __attribute__((amdgpu_waves_per_eu((NCF == 3 |
         os[j] = have ? p.ovs[((size_t)u * SUB + lane) * p.n_cf + j] : 0.0;
     }
     const int t = tile_seg(p, u);
-    // (the plan as the locate step left it: fetched with the counts, not after them)
+    // (the plan: fetched with the counts, not after them)
     uint32_t mode[NCF], base[NCF], span[NCF], top[NCF];
 #pragma unroll
     for (int j = 0; j < NCF; ++j) {
@@ -1824,48 +1873,14 @@ __global__ __launch_bounds__(LWG) __attribute__((amdgpu_waves_per_eu((NCF == 3 |
     }
     const TileRef tr = tile_ref(p, u);
     const uint32_t cnt = tr.tl.total();
-    const bool redo = any_fail != 0 && p.seg[t].fail != 0;
-    const bool first = redo && (u == seg_tile0(p, t));
     uint32_t hn[NCF], tin = 0;
     double hs[NCF];
 #pragma unroll
     for (int j = 0; j < NCF; ++j) { hn[j] = 0; hs[j] = 0.0; }
-    if (cnt != 0 || first) {
-        // exact route: the plan comes from the rebuilt bracket histogram.  A plain loop whose results go through
-        // LDS, so that the search does not inflate the register count of the common path.
-        __shared__ uint32_t rp[LWAVES][MAXCF][3];
-        const int wib = threadIdx.x >> 6;
-        if (redo) {
-            const uint32_t fail_kind = p.seg[t].fail;
-            if (first && lane == 0 && fail_kind == FAIL_NARROW) atomicAdd(&p.status->n_narrow, 1);
-            for (int j = 0; j < p.n_cf; ++j) {
-                CfState* st = &p.st[(size_t)t * p.n_cf + j];
-                if (fail_kind == FAIL_NARROW && st->redo == 0) {
-                    // this CF was not binned again: its plan stands (nobody writes it during this kernel)
-                    if (lane == 0) { rp[wib][j][0] = st->mode; rp[wib][j][1] = st->base; rp[wib][j][2] = st->span; }
-                    continue;
-                }
-                uint32_t b, above, c;
-                wave_locate_bin(p.hist1 + seg_block(p, t, j) * NBIN, (int)seg_rep(p, t), p.ovfc + ((size_t)t * p.n_cf + j) * 64 * 32,
-                                st->k, b, above, c);
-                const BinPlan q = plan_bin(st->lo, st->s, b, above, c);
-                if (lane == 0) {
-                    rp[wib][j][0] = q.mode; rp[wib][j][1] = q.base; rp[wib][j][2] = q.span;
-                    if (first) {
-                        store_plan(st, q);
-                        if (q.mode == MODE_FAIL) p.status->error = 1;  // the exact routes cannot fail
-                    }
-                }
-            }
-            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");  // rp is read back by the same wavefront
-        }
+    if (cnt != 0) {
 #pragma unroll
         for (int j = 0; j < NCF; ++j) {
             if (j < p.n_cf) {
-                if (redo) {  // (an exact route may have moved the bracket's end too)
-                    mode[j] = rp[wib][j][0]; base[j] = rp[wib][j][1]; span[j] = rp[wib][j][2];
-                    top[j] = p.st[(size_t)t * p.n_cf + j].top;
-                }
                 if (mode[j] == MODE_FAIL) { base[j] = NONE; top[j] = 0; }  // (an error: nothing is counted)
             }
         }
@@ -1898,8 +1913,6 @@ __global__ __launch_bounds__(LWG) __attribute__((amdgpu_waves_per_eu((NCF == 3 |
                             if (p.random) p.list_val[lst * LCAP + pos] = val;
                         }
                     }
-                } else if (mode[j] == MODE_HIST && in) {
-                    atomicAdd(&p.hist2[((size_t)t * p.n_cf + j) * NBIN + (key - base[j])], 1u);
                 }
             }
         };
@@ -2016,8 +2029,8 @@ __global__ __launch_bounds__(LWG) __attribute__((amdgpu_waves_per_eu((NCF == 3 |
 
 // ---------------------------------------------------------------------------------------------
 // SCAN: grid (n_seg, slices + n_cf), SCAN_T threads.  Every block first resolves one CF of its segment to
-//       the exact key tau of the k-th largest (from the gathered keys by a bitwise search, or from the
-//       key-by-key histogram), and how many keys equal to tau are selected.
+//       the exact key tau of the k-th largest (from the gathered keys by a bitwise search), and how many keys equal to
+//       tau are selected.
 //       Block (t, y < slices), committed CF: the counts of the y-th slice of SCAN_SLICE tiles of
 //       segment t (entries above the located bin, plus the gathered entries above tau, by tile) and their
 //       exclusive scan -> every tile's output offset and tie quota.  The totals of the earlier slices are
@@ -2119,17 +2132,6 @@ __global__ __launch_bounds__(SCAN_T) void scan_kernel(Params p, uint32_t slices)
     if (mode == MODE_FAIL) {
         if (tid == 0) p.status->error = 1;
         tau = 0; need = 0; cnt_gt = 0;
-    } else if (mode == MODE_HIST) {
-        if (wib == 0) {
-            uint32_t b, ab, cn;  // bins are single keys: base + b
-            wave_locate_bin(p.hist2 + (size_t)id * NBIN, 1, nullptr, k - above, b, ab, cn);
-            if (lane == 0) {
-                if (b == NONE) { p.status->error = 1; b = 0; }
-                res3[0] = base + b; res3[1] = above + ab;
-            }
-        }
-        __syncthreads();
-        tau = res3[0]; cnt_gt = res3[1]; need = k - cnt_gt;
     } else if (mode == MODE_GATHER) {
         // the want-th largest of the listed keys d = key - base.
         // The keys sit in REP lists; list r holds positions [off_r, off_r + n_r) of the concatenation.
@@ -2237,28 +2239,6 @@ __global__ __launch_bounds__(SCAN_T) void scan_kernel(Params p, uint32_t slices)
                 const bool gt = d[q] > dtau;
                 if (rt[q] < slice0) { if (gt) ++pg; else ++pe; }
                 else if (rt[q] - slice0 < (uint32_t)SCAN_SLICE) atomicAdd(gt ? &sg[rt[q] - slice0] : &se[rt[q] - slice0], 1u);
-            }
-        } else if (mode == MODE_HIST) {
-            // more keys in the located bin than a gather list holds (a mass of equal values): the tiles that have
-            // entries in the bin are walked again, up to the end of this slice, one wavefront per tile at a time
-            const uint32_t uend = slice0 + SCAN_SLICE < u1 ? slice0 + SCAN_SLICE : u1;
-            const uint32_t top = st->top;
-            for (uint32_t u = u0 + wib; u < uend; u += SCAN_W) {
-                if (p.tin[u] == 0) continue;
-                const TileRef tr = tile_ref(p, u);
-                const uint32_t cnt = tr.tl.total();
-                uint32_t g = 0, e = 0;
-                for (uint32_t i = lane; i < cnt; i += 64) {
-                    uint32_t key;
-                    float unused;
-                    ref_entry(p, u, tr, i, key, unused);
-                    if (key < top && key >= base && key - base <= span) { g += key > tau; e += key == tau; }
-                }
-                g = wave_sum(g); e = wave_sum(e);
-                if (lane == 0) {
-                    if (u < slice0) { pg += g; pe += e; }
-                    else { atomicAdd(&sg[u - slice0], g); atomicAdd(&se[u - slice0], e); }
-                }
             }
         }
         pg = wave_sum(pg);
@@ -2386,18 +2366,6 @@ __global__ __launch_bounds__(SCAN_T) void scan_kernel(Params p, uint32_t slices)
             ebin = scalbn((double)all, ex - 49);
         }
         }
-    } else if (mode == MODE_HIST) {
-        // Top-k only (priorities are distinct): the key-by-key histogram's bins above the threshold, in bin order
-        double s = 0.0;
-        for (uint32_t b = tid; b < NBIN; b += SCAN_T) {
-            const uint32_t cn = (b > dtau && b <= span) ? p.hist2[(size_t)id * NBIN + b] : 0u;
-            const double dv = (double)__uint_as_float(base + b);
-            s += (double)cn * (dv * dv);
-        }
-        s = wave_sum(s);
-        if (lane == 0) dred[2][wib] = s;
-        __syncthreads();
-        for (int w = 0; w < SCAN_W; ++w) ebin += dred[2][w];
     }
     // every wavefront's sum, then the SCAN_W of them in order: the same order in every run
     {
@@ -3304,7 +3272,7 @@ __global__ __launch_bounds__(256) void commit_kernel(const int32_t* __restrict__
 size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 struct Layout {
-    size_t status, tables, tables_bytes, tseg, st, seg, bnd_lo, bnd_hi, bnd_mid, hist1, ovfc, hist2, coarse, list_key, list_tile,
+    size_t status, tables, tables_bytes, tseg, st, seg, bnd_lo, bnd_hi, bnd_mid, hist1, ovfc, xq, coarse, list_key, list_tile,
         list_val, list_cnt, samp_hist, samp_grp, cand_cnt, brk_cnt, ovn, ovs, tg0, tin, toff, ttake, tsel, ssd, ssd_t, sss,
         cand_idx, cand_val, brk_key, brk_val, total;
 };
@@ -3359,7 +3327,7 @@ Layout make_layout(int64_t n, int n_cf, int n_seg)
     const size_t blocks = pool_blocks(n, n_cf, n_seg);
     L.hist1 = take(sizeof(uint32_t) * blocks * NBIN);
     L.ovfc = take(sizeof(uint32_t) * sc * 64 * 32);
-    L.hist2 = take(sizeof(uint32_t) * sc * NBIN);
+    L.xq = take(sizeof(uint32_t) * sc * NBIN);
     L.coarse = take(sizeof(uint32_t) * (size_t)n_seg * NBIN);
     L.list_key = take(sizeof(uint32_t) * blocks * LCAP);
     L.list_tile = take(sizeof(uint32_t) * blocks * LCAP);
@@ -3625,7 +3593,7 @@ static int compress_impl(const float* grad, float* residual, int64_t n, const do
     p.bnd_mid = (uint32_t*)(ws + L.bnd_mid);
     p.hist1 = (uint32_t*)(ws + L.hist1);
     p.ovfc = (uint32_t*)(ws + L.ovfc);
-    p.hist2 = (uint32_t*)(ws + L.hist2);
+    p.xq = (uint32_t*)(ws + L.xq);
     p.coarse = (uint32_t*)(ws + L.coarse);
     p.list_key = (uint32_t*)(ws + L.list_key);
     p.list_tile = (uint32_t*)(ws + L.list_tile);
@@ -3762,7 +3730,6 @@ static int compress_impl(const float* grad, float* residual, int64_t n, const do
         if (!copied || !recorded) return GRAVAC_ERR_HIP;
     }
 
-    const uint32_t tile_grid = (p.n_tiles + WAVES - 1) / WAVES;
     const uint32_t sub_grid = (p.n_tiles * SUB + WAVES - 1) / WAVES;
     const uint32_t light_grid = (p.n_tiles + LWAVES - 1) / LWAVES;
     const uint32_t scan_slices = (max_seg_tiles + SCAN_SLICE - 1) / SCAN_SLICE;
@@ -3809,13 +3776,11 @@ static int compress_impl(const float* grad, float* residual, int64_t n, const do
             hipLaunchKernelGGL(kern, dim3(sub_grid), dim3(WG), 0, stream, p);
     }
     if (have_tiles && !fixed) {
-    hipLaunchKernelGGL(locate_kernel, dim3((uint32_t)(ns * n_cf)), dim3(256), 0, stream, p);
-    // exact routes, taken only by segments whose bracket failed (the kernels return at once otherwise)
-    hipLaunchKernelGGL(coarse_kernel, dim3(tile_grid < XGRID ? tile_grid : XGRID), dim3(WG), 0, stream, p);
-    if (random)
-        hipLaunchKernelGGL((stream_kernel<SM_EXACT, true, MAXCF>), dim3(sub_grid < XGRID ? sub_grid : XGRID), dim3(WG), 0, stream, p);
-    else
-        hipLaunchKernelGGL((stream_kernel<SM_EXACT, false, MAXCF>), dim3(sub_grid < XGRID ? sub_grid : XGRID), dim3(WG), 0, stream, p);
+    // a flat call: as many workgroups as its tiles can keep busy should its bracket have failed; layerwise: one per tensor
+    // and one more per PLAN_HELP tiles of a large one
+    const uint32_t plan_flat = (p.n_tiles + PLAN_T / 64 - 1) / (PLAN_T / 64);
+    const uint32_t plan_grid = ns == 1 ? (plan_flat < PLAN_GRID ? plan_flat : PLAN_GRID) : (uint32_t)ns + p.n_tiles / PLAN_HELP;
+    hipLaunchKernelGGL(random ? plan_kernel<true> : plan_kernel<false>, dim3(plan_grid), dim3(PLAN_T), 0, stream, p);
     }
     if (have_tiles) {
     // the refine kernel loops over the CFs: forms for 1, 2, 3, 4 and MAXCF CFs

@@ -3,10 +3,13 @@ kernel form or route to another, against the CPU oracle, bit for bit."""
 import numpy as np
 import pytest
 
-from paper_2305_12201_amd import workloads
+from paper_2305_12201_amd import binding, workloads
+from tests.gpu_util import check
 from tests.test_gpu_randomk import check as check_randomk
 
 pytestmark = pytest.mark.gpu
+
+FB = binding.FLAG_FORCE_FALLBACK
 
 
 @pytest.mark.parametrize("n_cf", [1, 2, 3, 4, 5, 8])
@@ -18,3 +21,63 @@ def test_randomk_forms(n_cf, n):
     r = workloads.normal_gradient(n, 1e-5, seed=n_cf)
     check_randomk(g, r, cfs, seed=n + n_cf, commit=n_cf - 1, what=f"{n_cf} CFs, highest sent")
     check_randomk(g, r, cfs, seed=n - n_cf, commit=0, what=f"{n_cf} CFs, lowest sent")
+
+
+def _mass(n, seed, share, value, rest):
+    """n entries, about `share` of them exactly +-value, the others Normal(0, rest)."""
+    rng = np.random.Generator(np.random.PCG64(seed))
+    g = (rng.standard_normal(n) * rest).astype(np.float32)
+    hit = rng.random(n) < share
+    g[hit] = np.where(rng.random(int(hit.sum())) < 0.5, -value, value).astype(np.float32)
+    return g
+
+
+@pytest.mark.parametrize("flags", [0, FB])
+@pytest.mark.parametrize("n,share,cf", [(131_073, 0.5, 3.0), (300_007, 0.2, 10.0), (1_200_001, 0.9, 1.5), (700_001, 0.05, 25.0)])
+def test_mass_of_equal_values(n, share, cf, flags):
+    """The k-th largest is one of many equal values: its bin holds more entries than a gather list, on the exact route
+    after the lists have been collected again too."""
+    for value, rest in ((1e-3, 1e-3), (0.0, 1e-3), (np.float32(1.25), 1e-6)):
+        g = _mass(n, n, share, value, rest)
+        check(g, np.zeros(n, np.float32), [cf], flags=flags, what=f"mass of {value}")
+        check(g, np.zeros(n, np.float32), [cf, 4 * cf, 40 * cf], 1, flags=flags, what=f"mass of {value}, three CFs")
+
+
+def test_wide_bracket_is_cut_twice():
+    """Magnitudes over hundreds of octaves and a mass of equal ones below: bins far wider than 2^11 keys, and still too
+    full when they are cut the first time."""
+    n = 400_003
+    rng = np.random.Generator(np.random.PCG64(5))
+    g = np.exp(rng.uniform(-80.0, 0.0, n)).astype(np.float32)
+    g[rng.random(n) < 0.5] = np.float32(1e-30)
+    for cf in (2.0, 2.5, 3.0):
+        check(g, np.zeros(n, np.float32), [cf], what=f"cf {cf}")
+        check(g, np.zeros(n, np.float32), [cf, 10.0 * cf], 0, what=f"cf {cf} and {10 * cf}")
+
+
+@pytest.mark.parametrize("n_cf", [1, 2, 3, 5, 8])
+def test_plan_of_every_cf_count(n_cf):
+    """The search of the histograms is split over the workgroup in as many ways as there are CFs."""
+    n = 900_001
+    cfs = [2.0, 5.0, 10.0, 33.0, 100.0, 160.0, 300.0, 1000.0][:n_cf]
+    g = workloads.resnet_like_gradient(n, seed=n_cf)
+    r = workloads.normal_gradient(n, 1e-5, seed=2)
+    for flags in (0, FB):
+        check(g, r, cfs, n_cf // 2, flags=flags, what=f"{n_cf} CFs")
+
+
+def test_some_tensors_take_the_exact_route():
+    """Layerwise: tensors of several workgroups, of one, and small ones; some full of equal values, some ordinary."""
+    sizes = [700_001, 64, 20_000, 1_100_003, 8_193, 600_000, 5, 70_001]
+    off = workloads.offsets_of(sizes)
+    n = int(off[-1])
+    g = workloads.normal_gradient(n, 1e-3, seed=3)
+    for t in (0, 2, 5):
+        g[off[t]:off[t + 1]] = _mass(sizes[t], t, 0.6, 1e-3, 1e-4)
+    rng = np.random.Generator(np.random.PCG64(9))
+    g[off[3]:off[4]] = np.exp(rng.uniform(-80.0, 0.0, sizes[3])).astype(np.float32)
+    g[off[3]:off[4]][rng.random(sizes[3]) < 0.5] = np.float32(1e-30)
+    r = np.zeros(n, np.float32)
+    for flags in (0, FB):
+        check(g, r, [2.5], 0, off, flags=flags, what="layerwise, one CF")
+        check(g, r, [2.5, 10.0], 1, off, flags=flags, what="layerwise, two CFs")
