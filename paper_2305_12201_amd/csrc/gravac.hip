@@ -91,6 +91,7 @@ constexpr int DENSE_BLOCKS = 128;        // ... so that there are at most this m
 constexpr int LCAP = 4096;          // keys a gather list can hold
 constexpr int MAXCF = GRAVAC_MAX_CF;
 constexpr double ZMARGIN = 5.0;     // safety margin of the sampled rank, in standard deviations
+constexpr uint32_t CTILES = 64;     // tiles per partial sum of the tiles' counts (csum)
 constexpr int XQ_WORDS = 8;         // a segment's work queue in the plan step: chunks claimed, then chunks done per phase
 constexpr uint32_t NONE = 0xFFFFFFFFu;
 constexpr uint32_t KEY_END = 0x80000000u;  // one past the largest key
@@ -156,7 +157,8 @@ struct SegInfo {
     uint32_t small;          // 1: at most SMALL_MAX elements, handled by one workgroup out of LDS: no tiles, no samples
     uint32_t rep;            // copies of the segment's bracket histograms and gather lists: REP for a large tensor, else 1
     uint32_t pool0;          // its first copy block in hist1 / list_* / list_cnt (n_cf * rep consecutive blocks, CF-major)
-    uint32_t pad[3];
+    uint32_t wg0, wgs;       // its first workgroup in the emit step, and how many
+    uint32_t pad[1];
 };
 static_assert(sizeof(SegInfo) == 64, "SegInfo layout");
 
@@ -217,9 +219,13 @@ struct Params {
     double* ovs;         // [n_tiles][SUB][n_cf] ... and their sum of acc^2
     uint32_t* tg0;       // [n_tiles] entries of the tile above the committed CF's located bin
     uint32_t* tin;       // [n_tiles] entries of the tile inside that bin
+    // a call with a scan step:
     uint32_t* toff;      // [n_tiles] offset of the tile's output inside its segment's message
     uint32_t* ttake;     // [n_tiles] how many of the tile's entries equal to tau(commit) are selected
     uint32_t* tsel;      // [n_tiles] pairs the tile emits
+    // ... and one without (null otherwise):
+    uint64_t* csum;      // [n_tiles / CTILES, rounded up][8] sums of tg0 (high half) and tin over CTILES tiles: word 0 of a cache line
+    uint32_t* wseg;      // [workgroups of the emit step] the segment of each (layerwise; filled by threshold_kernel)
     double* ssd;         // [n_tiles][SUB] sum of acc^2 of every sub-tile
     double* ssd_t;       // [n_tiles] sum of acc^2 of the tile
     double* sss;         // [n_tiles][n_cf] sum of acc^2 over the tile's keys above CF j's located bin
@@ -397,6 +403,17 @@ __device__ __forceinline__ uint32_t wave_scan(uint32_t v)
 __device__ __forceinline__ uint32_t hash32(uint32_t x)
 {
     x ^= x >> 16; x *= 0x7feb352du; x ^= x >> 15; x *= 0x846ca68bu; x ^= x >> 16;
+    return x;
+}
+
+// v[0] out, the others one place down: a rolled loop over registers.  The list kernels are short chains that start with
+// a cold instruction cache, and unrolled copies of their long bodies (50 KB) cost them more than the moves.
+template <typename T, int N>
+__device__ __forceinline__ T pop_front(T (&v)[N])
+{
+    const T x = v[0];
+#pragma unroll
+    for (int i = 0; i + 1 < N; ++i) v[i] = v[i + 1];
     return x;
 }
 
@@ -742,6 +759,8 @@ __global__ __launch_bounds__(256) void sample_kernel(Params p)
         for (uint32_t i = lb * 256 + tid; i < (uint32_t)p.n_cf * 64; i += nbk * 256) p.ovfc[((size_t)t * p.n_cf * 64 + i) * 32] = 0;
         for (uint32_t i = lb * 256 + tid; i < blocks; i += nbk * 256) p.list_cnt[(seg_block(p, t, 0) + i) * 32] = 0;
         if (lb == 0 && tid < XQ_WORDS) p.xq[(size_t)t * p.n_cf * NBIN + tid] = 0;
+        if (p.csum)
+            for (uint32_t i = b * 256 + tid; i < (p.n_tiles + CTILES - 1u) / CTILES; i += gridDim.x * 256) p.csum[(size_t)i * 8] = 0;
     }
     if (p.bounds_from != BOUNDS_SAMPLED) return;
     const int64_t s0 = seg_begin(p, t);
@@ -868,6 +887,8 @@ __global__ __launch_bounds__(P * 1024 / G) __attribute__((amdgpu_waves_per_eu(SM
     if (y == 0) {
         if (!is_flat(p))
             for (uint32_t u = seg_tile0(p, t) + tid; u < seg_tile1(p, t); u += T * P) p.tseg[u] = (uint32_t)t;
+        if (!is_flat(p) && p.wseg)
+            for (uint32_t i = tid; i < p.segs[t].wgs; i += T * P) p.wseg[p.segs[t].wg0 + i] = (uint32_t)t;
     }
     if (tid < p.n_cf) {
         const uint32_t k = seg_k(p, t, tid);
@@ -888,6 +909,8 @@ __global__ __launch_bounds__(P * 1024 / G) __attribute__((amdgpu_waves_per_eu(SM
         // the threshold sparsifier (one flat tensor, one "CF"): an empty bracket at the caller's threshold, so that the
         // pass over the gradient counts and lists what lies at or above it; the later steps find everything resolved:
         // selected <=> key > tau with tau one key below the threshold, no ties to take
+        if (p.csum)
+            for (uint32_t i = tid; i < (p.n_tiles + CTILES - 1u) / CTILES; i += T * P) p.csum[(size_t)i * 8] = 0;
         if (tid == 0) {
             p.bnd_lo[0] = p.fixed_key; p.bnd_hi[0] = p.fixed_key; p.bnd_mid[0] = NONE;
             CfState st;
@@ -1916,9 +1939,7 @@ __global__ __launch_bounds__(LWG) __attribute__((amdgpu_waves_per_eu((NCF == 3 |
                 }
             }
         };
-        // 64 entries per load and lane-row; eight loads in flight per lane where there are that many entries left, two
-        // otherwise (most tiles hold a hundred entries or so, and a round that no lane has an entry for costs as many
-        // instructions as a full one)
+        // 64 entries per load and lane-row, up to eight loads in flight per lane
         uint32_t i0 = 0;
         if constexpr (HEADS) {
             // the lists' heads cover the tile if every list is its sub-tile's expected one and short enough
@@ -1930,10 +1951,11 @@ __global__ __launch_bounds__(LWG) __attribute__((amdgpu_waves_per_eu((NCF == 3 |
                 uint32_t mine_cnt = 0;
 #pragma unroll
                 for (int j = 0; j < SUB; ++j) if ((lane >> 3) == j) mine_cnt = tr.tl.start[j + 1] - tr.tl.start[j];
-#pragma unroll
+#pragma unroll 1
                 for (int r = 0; r < SPEC_R; ++r) {
                     if (__ballot((uint32_t)(lane & 7) + 8u * r < mine_cnt) == 0ull) break;
-                    take(spec[r] & 0x7FFFFFFFu, 0.0f, (uint32_t)(lane & 7) + 8u * r < mine_cnt);
+                    const uint32_t w = pop_front(spec);
+                    take(w & 0x7FFFFFFFu, 0.0f, (uint32_t)(lane & 7) + 8u * r < mine_cnt);
                 }
                 i0 = cnt;
             }
@@ -1960,6 +1982,7 @@ __global__ __launch_bounds__(LWG) __attribute__((amdgpu_waves_per_eu((NCF == 3 |
             uint32_t wq[AHEAD][2];
 #pragma unroll
             for (int a = 0; a < AHEAD; ++a) fetch(a, wq[a]);
+#pragma unroll 1
             for (int j = 0; j < SUB; ++j) {
                 uint32_t w0[2], c;
                 bool fm;
@@ -1969,42 +1992,33 @@ __global__ __launch_bounds__(LWG) __attribute__((amdgpu_waves_per_eu((NCF == 3 |
                 for (int a = 0; a + 1 < AHEAD; ++a) { wq[a][0] = wq[a + 1][0]; wq[a][1] = wq[a + 1][1]; }
                 if (j + AHEAD < SUB) fetch(j + AHEAD, wq[AHEAD - 1]);
                 counts(j, c, fm);
-#pragma unroll
-                for (int q = 0; q < 2; ++q)
-                    if ((uint32_t)q * 64 < c) take(w0[q] & 0x7FFFFFFFu, 0.0f, q * 64 + lane < c);
-                for (uint32_t b0 = 128; b0 < c; b0 += 128) {   // (a sub-tile with more than 128 such entries: rare)
-                    const uint32_t* src = (fm ? (const uint32_t*)p.cand_val : p.brk_key) + (size_t)u * TW + (size_t)j * TS;
-                    uint32_t kq[2];
-#pragma unroll
-                    for (int q = 0; q < 2; ++q) kq[q] = src[(b0 + q * 64 + lane) & (TS - 1)] & 0x7FFFFFFFu;
-#pragma unroll
-                    for (int q = 0; q < 2; ++q)
-                        if (b0 + q * 64 < c) take(kq[q], 0.0f, b0 + q * 64 + lane < c);
+                const uint32_t* src = (fm ? (const uint32_t*)p.cand_val : p.brk_key) + (size_t)u * TW + (size_t)j * TS;
+#pragma unroll 1
+                for (uint32_t b = 0; b < c; b += 64) {   // (more than 128 such entries in a sub-tile: rare)
+                    const uint32_t w = b == 0 ? w0[0] : b == 64 ? w0[1] : src[(b + lane) & (TS - 1)];
+                    take(w & 0x7FFFFFFFu, 0.0f, b + lane < c);
                 }
             }
             i0 = cnt;
         }
-        for (; i0 + 64 * 2 < cnt; i0 += 64 * 8) {
+#pragma unroll 1
+        for (; i0 < cnt; i0 += 64 * 8) {
             uint32_t kq[8];
             float vq[8];
 #pragma unroll
             for (int q = 0; q < 8; ++q) {
-                const uint32_t i = i0 + q * 64 + lane;
-                ref_entry(p, u, tr, i < cnt ? i : 0u, kq[q], vq[q]);
+                kq[q] = 0; vq[q] = 0.0f;
+                if (i0 + q * 64 < cnt) {
+                    const uint32_t i = i0 + q * 64 + lane;
+                    ref_entry(p, u, tr, i < cnt ? i : 0u, kq[q], vq[q]);
+                }
             }
-#pragma unroll
-            for (int q = 0; q < 8; ++q) take(kq[q], vq[q], i0 + q * 64 + lane < cnt);
-        }
-        if (i0 < cnt) {
-            uint32_t kq[2];
-            float vq[2];
-#pragma unroll
-            for (int q = 0; q < 2; ++q) {
-                const uint32_t i = i0 + q * 64 + lane;
-                ref_entry(p, u, tr, i < cnt ? i : 0u, kq[q], vq[q]);
+#pragma unroll 1
+            for (uint32_t i = i0; i < i0 + 64 * 8 && i < cnt; i += 64) {
+                const uint32_t key = pop_front(kq);
+                const float val = pop_front(vq);
+                take(key, val, i + lane < cnt);
             }
-#pragma unroll
-            for (int q = 0; q < 2; ++q) take(kq[q], vq[q], i0 + q * 64 + lane < cnt);
         }
     }
     // the tile's sums: what the pass over the gradient counted above the brackets, plus the above
@@ -2021,7 +2035,10 @@ __global__ __launch_bounds__(LWG) __attribute__((amdgpu_waves_per_eu((NCF == 3 |
             const double e = wave_sum(os[j]) + wave_sum(hs[j]);
             if (lane == 0) {
                 p.sss[(size_t)u * p.n_cf + j] = e;
-                if (j == p.commit) { p.tg0[u] = n; p.tin[u] = tin; }
+                if (j == p.commit) {
+                    p.tg0[u] = n; p.tin[u] = tin;
+                    if (p.csum) atomicAdd((unsigned long long*)&p.csum[(size_t)(u / CTILES) * 8], ((unsigned long long)n << 32) | tin);
+                }
             }
         }
     }
@@ -2043,8 +2060,8 @@ constexpr int SCAN_PER = 4;                  // tiles per thread
 constexpr int SCAN_SLICE = SCAN_T * SCAN_PER;
 constexpr int LPER = LCAP / SCAN_T;          // gathered entries per thread
 constexpr int RW = LPER;
-constexpr int SPEC = SCAN_T / REP;           // threads that fetch the head of one gather list before its length is known
-static_assert(LCAP % SCAN_T == 0 && SCAN_T % REP == 0 && SPEC * LPER <= LCAP && 2 * SCAN_T == NBIN,
+constexpr int SCAN_SPEC = SCAN_T / REP;      // threads that fetch the head of one gather list before its length is known
+static_assert(LCAP % SCAN_T == 0 && SCAN_T % REP == 0 && SCAN_SPEC * LPER <= LCAP && 2 * SCAN_T == NBIN,
               "the gathered entries are dealt evenly; a thread owns two bins of the search's histogram");
 
 __global__ __launch_bounds__(SCAN_T) void scan_kernel(Params p, uint32_t slices)
@@ -2074,15 +2091,15 @@ __global__ __launch_bounds__(SCAN_T) void scan_kernel(Params p, uint32_t slices)
     for (int r = 0; r < REP; ++r) fill[r] = (uint32_t)r < copies ? p.list_cnt[(block0 + r) * 32] : 0u;
     const uint32_t mode = st->mode, k = st->k, above = st->above, base = st->base, span = st->span, c = st->c;
     uint32_t tau = st->tau, need = st->need, cnt_gt = st->cnt_gt;   // valid if the located bin was one key wide
-    // ... and the head of every gather list, SPEC * LPER entries of it, before the fill counts are known: a list is
+    // ... and the head of every gather list, SCAN_SPEC * LPER entries of it, before the fill counts are known: a list is
     // rarely longer than that (the located bin's entries spread over the copies), and a load that waits for the
     // counts would cost this kernel another round trip to memory
-    const uint32_t spec_r = (uint32_t)tid / SPEC;
+    const uint32_t spec_r = (uint32_t)tid / SCAN_SPEC;
     uint32_t sk[LPER], stl[LPER];
     float sv[LPER];
 #pragma unroll
     for (int q = 0; q < LPER; ++q) {
-        const size_t at = (block0 + (spec_r < copies ? spec_r : 0u)) * LCAP + (uint32_t)(tid % SPEC) + (uint32_t)q * SPEC;
+        const size_t at = (block0 + (spec_r < copies ? spec_r : 0u)) * LCAP + (uint32_t)(tid % SCAN_SPEC) + (uint32_t)q * SCAN_SPEC;
         sk[q] = p.list_key[at];
         stl[q] = p.list_tile[at];
         sv[q] = p.random ? p.list_val[at] : 0.0f;
@@ -2146,15 +2163,15 @@ __global__ __launch_bounds__(SCAN_T) void scan_kernel(Params p, uint32_t slices)
         } else {
             bool spec_ok = true;
 #pragma unroll
-            for (int r = 0; r < REP; ++r) spec_ok = spec_ok && fill[r] <= (uint32_t)(SPEC * LPER);
+            for (int r = 0; r < REP; ++r) spec_ok = spec_ok && fill[r] <= (uint32_t)(SCAN_SPEC * LPER);
             if (spec_ok) {
-                // the entries are the ones fetched ahead: list spec_r, slots tid % SPEC + q SPEC
+                // the entries are the ones fetched ahead: list spec_r, slots tid % SCAN_SPEC + q SCAN_SPEC
                 uint32_t my_fill = 0;
 #pragma unroll
                 for (int r = 0; r < REP; ++r) if ((uint32_t)r == spec_r) my_fill = fill[r];   // (0 beyond the segment's copies)
 #pragma unroll
                 for (int q = 0; q < LPER; ++q) {
-                    const uint32_t slot = (uint32_t)(tid % SPEC) + (uint32_t)q * SPEC;
+                    const uint32_t slot = (uint32_t)(tid % SCAN_SPEC) + (uint32_t)q * SCAN_SPEC;
                     d[q] = sk[q]; rt[q] = stl[q]; rv[q] = sv[q];
                     if (slot < my_fill) live |= 1u << q;
                 }
@@ -2390,16 +2407,299 @@ __global__ __launch_bounds__(SCAN_T) void scan_kernel(Params p, uint32_t slices)
 }
 
 // ---------------------------------------------------------------------------------------------
-// K4: one wavefront per tile emits the tile's share of the committed selection in ascending index
-//     order and zeroes its residual slots.  A sub-tile with a candidate list is emitted from the list;
-//     a sub-tile without one (mostly candidates) is read again, 1024 elements, and its residual rewritten.
+// EMIT: the tiles' shares of the committed selection in ascending index order, a wavefront per tile, and zeroes in its
+//       residual slots.  A sub-tile with a candidate list is emitted from the list; a sub-tile without one (mostly
+//       candidates) is read again, 1024 elements, and its residual rewritten.  Two kernels:
+//
+// emit_kernel works from what the scan step has left.
+//
+// resolve_emit_kernel does the scan step's work itself: every workgroup resolves the committed CF of its segment to the
+// exact key tau of the k-th largest from the gathered entries, and adds up what lies before its eight tiles (totals of 64
+// tiles each, which the refine step has added up, and up to 126 single tiles at the ends).  The first n_seg n_cf workgroups
+// of its launch are the statistics of one (segment, CF) each.  The scan step is 6 to 8 us of round trips and barriers in
+// one or a few workgroups; repeated by all of them, part of it overlaps with the tiles' own first loads, and a launch is
+// spared: 1 MiB buckets 38.3 -> 33.8 us, 25 MB 74.7 -> 72.4, ResNet101 CF 100 129.9 -> 126.3, three CFs 197 -> 192, LSTM
+// 156 -> 151 (with the rolled loops of pop_front, which took 1 to 3 us of that).  It holds while all tiles' wavefronts are resident at once (EMIT_RESIDENT: six per SIMD); the VGG16 shape's 2112 workgroups
+// take two to three rounds of it, 386 instead of 381 us at CF 1000 and 439 instead of 417 at CF 10, and stay with the scan step.
 // ---------------------------------------------------------------------------------------------
+constexpr int EWG = 512;                    // threads
+constexpr int EW = EWG / 64;
+constexpr uint32_t EMIT_RESIDENT = 6144;    // tiles (six wavefronts on each of 1024 SIMDs)
+constexpr int SPEC = EWG / REP;             // threads that fetch the head of one gather list before its length is known,
+constexpr int SPEC_Q = 2;                   // ... SPEC_Q entries each
+static_assert(EWG % REP == 0 && SPEC * SPEC_Q <= LCAP && 4 * EWG == NBIN, "a thread owns four bins of the search's histogram");
+
+struct EmitShared {
+    uint32_t hist[NBIN];
+    uint32_t wsum[EW];
+    uint32_t pick[2];
+    uint32_t fg[EW], fe[EW];                // gathered entries above / at the threshold, per tile of the workgroup
+    uint32_t tg[EW], te[EW];                // the tiles' counts, as refine_kernel leaves them
+    uint32_t ws[3][EW];
+    double dred[3][EW];
+    uint64_t ured[EW];
+};
+
+// The located bin of one (segment, CF) and the entries gathered from it.
+struct Gathered {
+    uint32_t mode, k, above, base, span, c;
+    uint32_t tau, need, cnt_gt;             // the result
+    uint32_t fill[REP];
+    size_t block0;                          // first copy block
+    uint32_t sk[SPEC_Q], stl[SPEC_Q];       // heads of the lists
+    float sv[SPEC_Q];
+    uint32_t my_fill;                       // entries in the list whose head this thread has fetched
+    bool spec;                              // the heads are all there is
+};
+
+// The loads that start a resolution; the heads of the gather lists come before their fill counts are known: a list is
+// rarely longer than that (the located bin's entries spread over the copies), and a load that waits for the counts
+// would cost another round trip to memory.
+__device__ __forceinline__ void gathered_load(const Params& p, int t, int j, int tid, Gathered& g)
+{
+    const uint32_t copies = seg_rep(p, t);
+    g.block0 = seg_block(p, t, j);
+    const CfState* st = &p.st[(size_t)t * p.n_cf + j];
+#pragma unroll
+    for (int r = 0; r < REP; ++r) g.fill[r] = (uint32_t)r < copies ? p.list_cnt[(g.block0 + r) * 32] : 0u;
+    const uint32_t r = (uint32_t)tid / SPEC;
+#pragma unroll
+    for (int q = 0; q < SPEC_Q; ++q) {
+        const size_t at = (g.block0 + (r < copies ? r : 0u)) * LCAP + (uint32_t)(tid % SPEC) + (uint32_t)q * SPEC;
+        g.sk[q] = p.list_key[at];
+        g.stl[q] = p.list_tile[at];
+        g.sv[q] = p.random ? p.list_val[at] : 0.0f;
+    }
+    g.mode = st->mode; g.k = st->k; g.above = st->above; g.base = st->base; g.span = st->span; g.c = st->c;
+    g.tau = st->tau; g.need = st->need; g.cnt_gt = st->cnt_gt;   // valid if the located bin was one key wide
+    bool spec = true;
+    uint32_t mine = 0;
+#pragma unroll
+    for (int x = 0; x < REP; ++x) {
+        spec = spec && g.fill[x] <= (uint32_t)(SPEC * SPEC_Q);
+        if ((uint32_t)x == r) mine = g.fill[x];   // (0 beyond the segment's copies)
+    }
+    g.spec = spec;
+    g.my_fill = mine;
+}
+
+// f(key - base, tile, value) for every gathered entry of this thread.
+template <typename F>
+__device__ __forceinline__ void gathered_each(const Params& p, int tid, const Gathered& g, F f)
+{
+    if (g.spec) {
+#pragma unroll
+        for (int q = 0; q < SPEC_Q; ++q)
+            if ((uint32_t)(tid % SPEC) + (uint32_t)q * SPEC < g.my_fill) f(g.sk[q] - g.base, g.stl[q], g.sv[q]);
+        return;
+    }
+    // a long list: the entries are dealt over the workgroup by their position in the concatenation
+    for (uint32_t pos = tid; pos < g.c; pos += EWG) {
+        uint32_t r = 0, before = 0, sum = 0;
+#pragma unroll
+        for (int x = 0; x < REP; ++x) {
+            if (pos >= sum) { r = x; before = sum; }
+            sum += g.fill[x];
+        }
+        const size_t at = (g.block0 + r) * LCAP + (pos - before);
+        f(p.list_key[at] - g.base, p.list_tile[at], p.random ? p.list_val[at] : 0.0f);
+    }
+}
+
+// g.tau / need / cnt_gt: the key of the k-th largest, how many equal to it are selected, how many lie above.
+__device__ __forceinline__ void gathered_resolve(const Params& p, int tid, Gathered& g, EmitShared& sh)
+{
+    const int lane = tid & 63, wib = tid >> 6;
+    if (g.mode == MODE_RESOLVED) return;
+    uint32_t filled = 0;
+#pragma unroll
+    for (int r = 0; r < REP; ++r) filled += g.fill[r];
+    const uint32_t want = g.k - g.above;
+    if (g.mode != MODE_GATHER || filled != g.c || g.c > (uint32_t)LCAP || want == 0 || want > g.c) {
+        if (tid == 0) p.status->error = 1;
+        g.mode = MODE_FAIL;
+        g.tau = g.base; g.need = 0; g.cnt_gt = g.above;
+        return;
+    }
+    // The want-th largest d = key - base: a histogram of 11 bits of d at a time, from the top bits down (one round unless
+    // the located bin is more than 2048 keys wide), among the entries that agree with the bits found so far.
+    // Thread tid owns bins 2047 - 4 tid .. 2044 - 4 tid, so that a scan over the threads runs from the top bin.
+    int nbits = 0;
+    while (nbits < 32 && (g.span >> nbits) != 0u) ++nbits;
+    uint32_t prefix = 0, pmask = 0, gsum = 0, left = want;
+    int shift = nbits > 11 ? nbits - 11 : 0;
+    for (;;) {
+        *(uint4*)&sh.hist[4 * tid] = make_uint4(0u, 0u, 0u, 0u);
+        __syncthreads();
+        gathered_each(p, tid, g, [&](uint32_t d, uint32_t, float) {
+            if ((d & pmask) == prefix) atomicAdd(&sh.hist[(d >> shift) & (NBIN - 1)], 1u);
+        });
+        __syncthreads();
+        const uint4 hv = *(const uint4*)&sh.hist[NBIN - 4 - 4 * tid];
+        const uint32_t hh[4] = {hv.w, hv.z, hv.y, hv.x}, mine = hv.x + hv.y + hv.z + hv.w;
+        const uint32_t incl = wave_scan(mine);
+        if (lane == 63) sh.wsum[wib] = incl;
+        __syncthreads();
+        uint32_t higher = incl - mine;   // entries in the bins above this thread's four
+#pragma unroll
+        for (int w = 0; w < EW; ++w) if (w < wib) higher += sh.wsum[w];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            if (higher < left && higher + hh[e] >= left) { sh.pick[0] = (uint32_t)(NBIN - 1 - 4 * tid - e); sh.pick[1] = higher; }
+            higher += hh[e];
+        }
+        __syncthreads();
+        prefix |= sh.pick[0] << shift;
+        pmask |= (uint32_t)(NBIN - 1) << shift;
+        gsum += sh.pick[1];
+        left -= sh.pick[1];
+        if (shift == 0) break;
+        shift = shift > 11 ? shift - 11 : 0;
+        __syncthreads();   // (pick is rewritten in the next round)
+    }
+    g.tau = g.base + prefix; g.cnt_gt = g.above + gsum; g.need = g.k - g.cnt_gt;
+}
+
+// Statistics of (segment t, CF j), by one workgroup.
+__device__ __forceinline__ void emit_stats(const Params& p, int t, int j, EmitShared& sh)
+{
+    const int tid = threadIdx.x, lane = tid & 63, wib = tid >> 6;
+    const uint32_t u0 = seg_tile0(p, t), u1 = seg_tile1(p, t);
+    Gathered g;
+    gathered_load(p, t, j, tid, g);
+    // the tiles' sums, eight tiles per thread and round, in a fixed order
+    double sd = 0.0, sj = 0.0;
+    uint32_t kept = 0;   // threshold sparsifier: the entries at or above the threshold
+    for (uint32_t v0 = u0 + tid; v0 < u1; v0 += 8 * EWG) {
+        double xd[8], xj[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const uint32_t u = v0 + q * EWG;
+            xd[q] = (u < u1) ? p.ssd_t[u] : 0.0;
+            xj[q] = (u < u1) ? p.sss[(size_t)u * p.n_cf + j] : 0.0;
+        }
+#pragma unroll
+        for (int q = 0; q < 8; ++q) { sd += xd[q]; sj += xj[q]; }
+    }
+    if (p.bounds_from == BOUNDS_FIXED) {
+        for (uint32_t u = u0 + tid; u < u1; u += EWG) kept += p.tg0[u];
+        kept = wave_sum(kept);
+        if (lane == 0) sh.ws[0][wib] = kept;
+    }
+    gathered_resolve(p, tid, g, sh);
+    const uint32_t dtau = g.tau - g.base;  // the threshold inside the located bin
+    // the entries of the located bin above the threshold (Random-k: and the one at it).  Their order in the gather
+    // lists varies from run to run, so their energies are added as integers: every square, exact in binary64, is
+    // scaled by a power of two that puts the largest of them below 2^50 and truncated, the sum of up to LCAP of them
+    // fits 64 bits and does not depend on the order, and it is off by less than 2^-38 of itself.
+    double ebin = 0.0;
+    if (g.mode == MODE_GATHER) {
+        const auto square = [&](uint32_t d, float val) {
+            const bool in = d > dtau || (p.random && d == dtau);
+            const double dv = p.random ? (double)val : (double)__uint_as_float(g.base + d);
+            return in ? dv * dv : 0.0;
+        };
+        const uint32_t kmax = g.base + g.span;   // the located bin's largest key
+        if (!p.random && kmax < 0x7F800000u) {
+            // Top-k keys are magnitudes, and the bin's own bounds say how large a square can get: no look at the
+            // entries for the scale, and nothing can be infinite or NaN
+            if (kmax != 0u) {
+                const double m = (double)__uint_as_float(kmax);
+                const int ex = ilogb(m * m);                  // every square is below 2^(ex + 1)
+                const double sc = scalbn(1.0, 49 - ex);       // (a power of two: the product is exact)
+                uint64_t acc = 0;
+                gathered_each(p, tid, g, [&](uint32_t d, uint32_t, float val) { acc += (uint64_t)(square(d, val) * sc); });  // < 2^50 each
+                acc = wave_sum(acc);
+                if (lane == 0) sh.ured[wib] = acc;
+                __syncthreads();
+                uint64_t all = 0;
+#pragma unroll
+                for (int w = 0; w < EW; ++w) all += sh.ured[w];
+                ebin = scalbn((double)all, ex - 49);
+            }
+        } else {
+            double mx = 0.0, plain = 0.0;
+            bool finite = true;
+            gathered_each(p, tid, g, [&](uint32_t d, uint32_t, float val) {
+                const double x = square(d, val);
+                mx = fmax(mx, x);   // (a NaN square is skipped here and shows in the plain sum)
+                plain += x;
+                finite = finite && (x <= 1.0e300);
+            });
+            mx = wave_max(mx);
+            if (lane == 0) sh.dred[2][wib] = mx;
+            const bool all_finite = __syncthreads_and(finite ? 1 : 0) != 0;
+            mx = 0.0;
+#pragma unroll
+            for (int w = 0; w < EW; ++w) mx = fmax(mx, sh.dred[2][w]);
+            __syncthreads();
+            if (!all_finite) {
+                // an infinite or NaN square: the sum is infinite or NaN in any order
+                plain = wave_sum(plain);
+                if (lane == 0) sh.dred[2][wib] = plain;
+                __syncthreads();
+                for (int w = 0; w < EW; ++w) ebin += sh.dred[2][w];
+            } else if (mx > 0.0) {
+                const int ex = ilogb(mx);                      // 2^ex <= mx < 2^(ex + 1)
+                uint64_t acc = 0;
+                gathered_each(p, tid, g, [&](uint32_t d, uint32_t, float val) { acc += (uint64_t)scalbn(square(d, val), 49 - ex); });  // < 2^50 each
+                acc = wave_sum(acc);
+                if (lane == 0) sh.ured[wib] = acc;
+                __syncthreads();
+                uint64_t all = 0;
+#pragma unroll
+                for (int w = 0; w < EW; ++w) all += sh.ured[w];
+                ebin = scalbn((double)all, ex - 49);
+            }
+        }
+    }
+    // every wavefront's sum, then the EW of them in order: the same order in every run
+    {
+        const double wd = wave_sum(sd), wj = wave_sum(sj);
+        if (lane == 0) { sh.dred[0][wib] = wd; sh.dred[1][wib] = wj; }
+    }
+    __syncthreads();
+    if (tid == 0) {
+        // fourth statistic: the threshold as a magnitude (Top-k) or as a priority (Random-k)
+        const double tauv = p.random ? (double)g.tau : (double)__uint_as_float(g.tau);
+        double ss_dense = 0.0, ss_above = 0.0;
+        for (int w = 0; w < EW; ++w) { ss_dense += sh.dred[0][w]; ss_above += sh.dred[1][w]; }
+        // Top-k: the ties all have magnitude tau; Random-k: the entry at the threshold has been summed
+        const double ss_sel = ss_above + ebin + (p.random ? 0.0 : (double)g.need * tauv * tauv);
+        double* o = p.out_stats + ((size_t)t * p.n_cf + j) * GRAVAC_STATS_PER_CF;
+        o[0] = ss_sel;
+        o[1] = ss_dense;
+        o[2] = (ss_dense == 0.0) ? 1.0 : ss_sel / ss_dense;
+        o[3] = p.bounds_from == BOUNDS_FIXED ? (double)__uint_as_float(p.fixed_key) : tauv;
+        if (p.bounds_from == BOUNDS_FIXED) {
+            uint32_t n = 0;
+            for (int w = 0; w < EW; ++w) n += sh.ws[0][w];
+            p.status->count = (int)n;
+            *p.out_count = (int64_t)n;
+        }
+    }
+}
+
 struct EmitCtx {
     uint32_t tau, take, pz;
     bool put_back;
     bool zero;   // selected entries are removed from the residual (not in a call without commit)
     int64_t pos, lim;
     uint32_t erun;
+    // The first pass has left +0 in the residual of its listed sub-tiles for keys >= pz (not on the full exact route,
+    // which has put acc back).  Those entries need no store here if they are selected, and get acc back if they are
+    // not, which can only be when the threshold turned out to lie at or above pz.
+    __device__ __forceinline__ void set_pz(const Params& p, const SegState& sg, bool single)
+    {
+        pz = (single || sg.fail == FAIL_FULL) ? NONE : sg.pz;
+        put_back = pz != NONE && tau >= pz;
+        zero = !p.no_commit;
+    }
+    __device__ __forceinline__ void set_tau(uint32_t key)
+    {
+        tau = key;
+        put_back = pz != NONE && tau >= pz;
+    }
 };
 
 // One round of up to 64 listed candidates (idx, val), one per lane.
@@ -2445,48 +2745,20 @@ __device__ __forceinline__ void emit_listed(const Params& p, EmitCtx& x, int32_t
 // loads, before the lists' lengths are known; a tile whose lists are no longer than that is emitted from them, a
 // lane's four consecutive candidates at a time, one round trip to memory earlier.  As in the refine kernel this
 // pays where all tiles' wavefronts are resident at once, and the host picks the form by the number of tiles.
+//
+// One tile u of segment t, by one wavefront: x holds the threshold, the tile's tie quota and the place of its pairs; cc
+// are the tile's counts, hi4 / hv4 the heads of its lists.
 template <bool GEN, bool HEADS>
-__global__ __launch_bounds__(LWG) __attribute__((amdgpu_waves_per_eu(HEADS ? 6 : 1, 8))) void emit_kernel(Params p)
+__device__ __forceinline__ void emit_tile(const Params& p, int t, uint32_t u, EmitCtx& x, const uint32_t (&cc)[SUB], const v4i& hi4,
+                                          const v4f& hv4, int32_t* sidx, float* sval)
 {
     static_assert(!(GEN && HEADS), "the early loads exist in the plain form only");
     const bool rnd = GEN && p.random, single = GEN && p.single;  // (known to be off in the plain form)
     const int lane = threadIdx.x & 63;
-    const uint32_t u = __builtin_amdgcn_readfirstlane(blockIdx.x * LWAVES + (threadIdx.x >> 6));
-    if (u >= p.n_tiles) return;
-    v4i hi4 = {0, 0, 0, 0};
-    v4f hv4 = {0.0f, 0.0f, 0.0f, 0.0f};
-    if constexpr (HEADS) {
-        // lane l: candidates 4 (l % 8) .. + 3 of sub-tile l / 8 (16-byte aligned: a sub-tile's slots start at a multiple of TS)
-        const size_t at = (size_t)u * TW + (size_t)(lane >> 3) * TS + 4u * (lane & 7);
-        hi4 = *(const v4i*)(p.cand_idx + at);
-        hv4 = *(const v4f*)(p.cand_val + at);
-    }
-    uint32_t cc[SUB];
     uint32_t dmask = 0;  // bit j: sub-tile j keeps no candidate list
 #pragma unroll
-    for (int j = 0; j < SUB; ++j) { cc[j] = p.cand_cnt[(size_t)u * SUB + j]; dmask |= (cc[j] & DENSE_BIT) ? 1u << j : 0u; }
+    for (int j = 0; j < SUB; ++j) dmask |= (cc[j] & DENSE_BIT) ? 1u << j : 0u;
     const bool any_dense = dmask != 0u;
-    const int t = tile_seg(p, u);
-    EmitCtx x;
-    x.take = p.ttake[u];
-    x.tau = p.st[(size_t)t * p.n_cf + p.commit].tau;
-    // The first pass has left +0 in the residual of its listed sub-tiles for keys >= pz (not on the full exact route,
-    // which has put acc back).  Those entries need no store here if they are selected, and get acc back if they are
-    // not, which can only be when the threshold turned out to lie at or above pz.
-    x.pz = (single || p.seg[t].fail == FAIL_FULL) ? NONE : p.seg[t].pz;
-    x.put_back = x.pz != NONE && x.tau >= x.pz;
-    x.zero = !p.no_commit;
-    if (p.bounds_from == BOUNDS_FIXED && (int64_t)p.status->count > p.total_out) {
-        // threshold sparsifier, more entries kept than the caller's buffers hold: nothing is emitted and nothing removed.
-        // The listed sub-tiles get back the values the pass replaced by +0; the others kept acc.
-        for (int j = 0; j < SUB; ++j) put_back_subtile(p, u * SUB + j, x.pz, lane);
-        return;
-    }
-    if (p.tsel[u] == 0 && !x.put_back) return;
-    const int64_t seg_out = seg_koff(p, t);
-    x.lim = seg_out + (int64_t)seg_k(p, t, p.commit);  // end of this segment's message
-    x.pos = seg_out + (int64_t)p.toff[u];
-    x.erun = 0;
     const float* cv = p.cand_val + (size_t)u * TW;
     const int32_t* ci = p.cand_idx + (size_t)u * TW;
     if constexpr (HEADS) {
@@ -2574,10 +2846,11 @@ __global__ __launch_bounds__(LWG) __attribute__((amdgpu_waves_per_eu(HEADS ? 6 :
                     in[r] = ci[sl];
                 }
             }
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                if (b0 + r * 64 >= cnt) break;  // (a round that no lane has a candidate for costs as much as a full one)
-                emit_listed<GEN>(p, x, iq[r], vq[r], b0 + r * 64 + lane < cnt);
+#pragma unroll 1
+            for (uint32_t b = b0; b < b0 + 64 * 4 && b < cnt; b += 64) {
+                const int32_t idx = pop_front(iq);
+                const float val = pop_front(vq);
+                emit_listed<GEN>(p, x, idx, val, b + lane < cnt);
             }
         }
         return;
@@ -2586,42 +2859,30 @@ __global__ __launch_bounds__(LWG) __attribute__((amdgpu_waves_per_eu(HEADS ? 6 :
         // all sub-tiles listed, at length (a low CF): sub-tile by sub-tile, so that no lane has to search for its
         // candidate's slot, and the first two rounds of every sub-tile are loaded before any is worked on: the
         // wavefront pays one round trip to memory, not one per sub-tile
-        float va[SUB][2];
-        int32_t ia[SUB][2];
+        float va[2 * SUB];
+        int32_t ia[2 * SUB];
 #pragma unroll
+        for (int r = 0; r < 2 * SUB; ++r) { va[r] = cv[(r / 2) * TS + (r & 1) * 64 + lane]; ia[r] = ci[(r / 2) * TS + (r & 1) * 64 + lane]; }
+#pragma unroll 1
         for (int j = 0; j < SUB; ++j) {
+            uint32_t c = 0;
 #pragma unroll
-            for (int r = 0; r < 2; ++r) { va[j][r] = cv[j * TS + r * 64 + lane]; ia[j][r] = ci[j * TS + r * 64 + lane]; }
-        }
-#pragma unroll
-        for (int j = 0; j < SUB; ++j) {
-            const uint32_t c = cc[j];
-#pragma unroll
-            for (int r = 0; r < 2; ++r)
-                if ((uint32_t)r * 64 < c) emit_listed<GEN>(p, x, ia[j][r], va[j][r], r * 64 + lane < c);
-            for (uint32_t b0 = 128; b0 < c; b0 += 128) {   // (more than 128 candidates and still listed)
-                float vq[2];
-                int32_t iq[2];
-#pragma unroll
-                for (int r = 0; r < 2; ++r) {
-                    const uint32_t q = (b0 + r * 64 + lane) & (TS - 1);
-                    vq[r] = cv[j * TS + q];
-                    iq[r] = ci[j * TS + q];
-                }
-#pragma unroll
-                for (int r = 0; r < 2; ++r)
-                    if (b0 + r * 64 < c) emit_listed<GEN>(p, x, iq[r], vq[r], b0 + r * 64 + lane < c);
+            for (int y = 0; y < SUB; ++y) c = y == j ? cc[y] : c;
+            const float v0 = pop_front(va), v1 = pop_front(va);
+            const int32_t i0 = pop_front(ia), i1 = pop_front(ia);
+#pragma unroll 1
+            for (uint32_t b = 0; b < c; b += 64) {   // (more than 128 candidates and still listed: rare)
+                const uint32_t q = (b + lane) & (TS - 1);
+                const float val = b == 0 ? v0 : b == 64 ? v1 : cv[j * TS + q];
+                const int32_t idx = b == 0 ? i0 : b == 64 ? i1 : ci[j * TS + q];
+                emit_listed<GEN>(p, x, idx, val, b + lane < c);
             }
         }
         return;
     }
     // sub-tile by sub-tile: a tile with sub-tiles that keep no list
-    // (two rows of a sub-tile at a time: with room for a whole sub-tile the LDS of a workgroup would limit the
-    // kernel to five wavefronts per SIMD, and the listed tiles of the same launch need the occupancy)
-    __shared__ int32_t stage_idx[LWAVES][TS / 2];   // half a sub-tile's part of the message, per wavefront
-    __shared__ float stage_val[LWAVES][TS / 2];
-    int32_t* sidx = stage_idx[threadIdx.x >> 6];
-    float* sval = stage_val[threadIdx.x >> 6];
+    // (two rows of a sub-tile at a time in LDS, sidx / sval: with room for a whole sub-tile the LDS of a workgroup would
+    // limit the kernel to five wavefronts per SIMD, and the listed tiles of the same launch need the occupancy)
     const int64_t tile0 = seg_begin(p, t) + (int64_t)(u - seg_tile0(p, t)) * TW;
     v4f nxt[ROWS];  // the rows of the next sub-tile without a list
     {
@@ -2634,6 +2895,7 @@ __global__ __launch_bounds__(LWG) __attribute__((amdgpu_waves_per_eu(HEADS ? 6 :
     int32_t inx[2];
 #pragma unroll
     for (int r = 0; r < 2; ++r) { vnx[r] = cv[r * 64 + lane]; inx[r] = ci[r * 64 + lane]; }
+#pragma unroll 1
     for (int j = 0; j < SUB; ++j) {
         float vq[2];
         int32_t iq[2];
@@ -2645,19 +2907,12 @@ __global__ __launch_bounds__(LWG) __attribute__((amdgpu_waves_per_eu(HEADS ? 6 :
         }
         if (!((dmask >> j) & 1u)) {
             const uint32_t c = p.cand_cnt[(size_t)u * SUB + j];
-#pragma unroll
-            for (int r = 0; r < 2; ++r)
-                if ((uint32_t)r * 64 < c) emit_listed<GEN>(p, x, iq[r], vq[r], r * 64 + lane < c);
-            for (uint32_t b0 = 128; b0 < c; b0 += 128) {   // (more than 128 candidates and still listed)
-#pragma unroll
-                for (int r = 0; r < 2; ++r) {
-                    const uint32_t q = (b0 + r * 64 + lane) & (TS - 1);
-                    vq[r] = cv[j * TS + q];
-                    iq[r] = ci[j * TS + q];
-                }
-#pragma unroll
-                for (int r = 0; r < 2; ++r)
-                    if (b0 + r * 64 < c) emit_listed<GEN>(p, x, iq[r], vq[r], b0 + r * 64 + lane < c);
+#pragma unroll 1
+            for (uint32_t b = 0; b < c; b += 64) {   // (more than 128 candidates and still listed: rare)
+                const uint32_t q = (b + lane) & (TS - 1);
+                const float val = b == 0 ? vq[0] : b == 64 ? vq[1] : cv[j * TS + q];
+                const int32_t idx = b == 0 ? iq[0] : b == 64 ? iq[1] : ci[j * TS + q];
+                emit_listed<GEN>(p, x, idx, val, b + lane < c);
             }
             continue;
         }
@@ -2677,10 +2932,11 @@ __global__ __launch_bounds__(LWG) __attribute__((amdgpu_waves_per_eu(HEADS ? 6 :
                 for (int q = 0; q < ROWS; ++q) nxt[q] = *(const v4f*)(p.acc + sn + q * ROW + 4 * lane);
             }
         }
-#pragma unroll
+#pragma unroll 1
         for (int q = 0; q < ROWS; ++q) {
             const int64_t g = s0 + q * ROW + 4 * lane;
-            const float a[4] = {av[q].x, av[q].y, av[q].z, av[q].w};
+            const v4f row = pop_front(av);
+            const float a[4] = {row.x, row.y, row.z, row.w};
             bool gt[4], eq[4], sel[4];
             uint32_t ties_below = 0;   // ties in lower lanes of this row
 #pragma unroll
@@ -2747,6 +3003,157 @@ __global__ __launch_bounds__(LWG) __attribute__((amdgpu_waves_per_eu(HEADS ? 6 :
             }
         }
     }
+}
+
+// After the scan step.
+template <bool GEN>
+__global__ __launch_bounds__(LWG) void emit_kernel(Params p)
+{
+    __shared__ int32_t stage_idx[LWAVES][TS / 2];   // half a sub-tile's part of the message, per wavefront
+    __shared__ float stage_val[LWAVES][TS / 2];
+    const int lane = threadIdx.x & 63, wib = threadIdx.x >> 6;
+    const uint32_t u = __builtin_amdgcn_readfirstlane(blockIdx.x * LWAVES + wib);
+    if (u >= p.n_tiles) return;
+    uint32_t cc[SUB];
+#pragma unroll
+    for (int j = 0; j < SUB; ++j) cc[j] = p.cand_cnt[(size_t)u * SUB + j];
+    const int t = tile_seg(p, u);
+    EmitCtx x;
+    x.take = p.ttake[u];
+    x.tau = p.st[(size_t)t * p.n_cf + p.commit].tau;
+    x.set_pz(p, p.seg[t], GEN && p.single);
+    if (p.bounds_from == BOUNDS_FIXED && (int64_t)p.status->count > p.total_out) {
+        // threshold sparsifier, more entries kept than the caller's buffers hold: nothing is emitted and nothing removed.
+        // The listed sub-tiles get back the values the pass replaced by +0; the others kept acc.
+        for (int j = 0; j < SUB; ++j) put_back_subtile(p, u * SUB + j, x.pz, lane);
+        return;
+    }
+    if (p.tsel[u] == 0 && !x.put_back) return;
+    const int64_t seg_out = seg_koff(p, t);
+    x.lim = seg_out + (int64_t)seg_k(p, t, p.commit);  // end of this segment's message
+    x.pos = seg_out + (int64_t)p.toff[u];
+    x.erun = 0;
+    emit_tile<GEN, false>(p, t, u, x, cc, v4i{0, 0, 0, 0}, v4f{0.0f, 0.0f, 0.0f, 0.0f}, stage_idx[wib], stage_val[wib]);
+}
+
+// Without a scan step.
+template <bool GEN>
+__global__ __launch_bounds__(EWG) __attribute__((amdgpu_waves_per_eu(6, 8))) void resolve_emit_kernel(Params p)
+{
+    constexpr bool HEADS = !GEN;
+    __shared__ EmitShared sh;
+    __shared__ __attribute__((aligned(16))) int32_t stage_idx[EW][TS / 2];   // half a sub-tile's part of the message, per wavefront
+    __shared__ __attribute__((aligned(16))) float stage_val[EW][TS / 2];     // (before that: the heads of the tile's lists)
+    const int tid = threadIdx.x, lane = tid & 63, wib = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const uint32_t n_stats = (uint32_t)p.n_seg * p.n_cf;
+    if (blockIdx.x < n_stats) {
+        const int t = (int)(blockIdx.x / (uint32_t)p.n_cf);
+        if (!seg_small(p, t)) emit_stats(p, t, (int)(blockIdx.x - (uint32_t)t * p.n_cf), sh);
+        return;
+    }
+    // ---- this workgroup's tiles [ub, ue) of segment t, a wavefront each
+    const uint32_t w = blockIdx.x - n_stats;
+    const int t = is_flat(p) ? 0 : (int)p.wseg[w];
+    const uint32_t u0 = seg_tile0(p, t), u1 = seg_tile1(p, t);
+    const uint32_t ub = u0 + (is_flat(p) ? w : w - p.segs[t].wg0) * EW, ue = ub + EW < u1 ? ub + EW : u1;
+    // ---- loads that depend on nothing else, in flight together
+    v4i hi4 = {0, 0, 0, 0};
+    v4f hv4 = {0.0f, 0.0f, 0.0f, 0.0f};
+    uint32_t cc[SUB];
+    {
+        const uint32_t u = ub + wib < ue ? ub + wib : ub;
+        if constexpr (HEADS) {
+            // lane l: candidates 4 (l % 8) .. + 3 of sub-tile l / 8 (16-byte aligned: a sub-tile's slots start at a multiple of TS)
+            const size_t at = (size_t)u * TW + (size_t)(lane >> 3) * TS + 4u * (lane & 7);
+            hi4 = *(const v4i*)(p.cand_idx + at);
+            hv4 = *(const v4f*)(p.cand_val + at);
+        }
+#pragma unroll
+        for (int j = 0; j < SUB; ++j) cc[j] = p.cand_cnt[(size_t)u * SUB + j];
+    }
+    if (tid < EW) {
+        const bool mine = ub + tid < ue;
+        sh.tg[tid] = mine ? p.tg0[ub + tid] : 0u;
+        sh.te[tid] = mine ? p.tin[ub + tid] : 0u;
+        sh.fg[tid] = 0;
+        sh.fe[tid] = 0;
+    }
+    // what lies before the workgroup's tiles in the segment: whole groups of CTILES tiles, and single tiles at both ends
+    uint32_t pg = 0, pe = 0;
+    {
+        const uint32_t g0 = (u0 + CTILES - 1u) / CTILES, g1 = ub / CTILES;   // whole groups, if g0 < g1
+        const uint32_t head = g0 * CTILES < ub ? g0 * CTILES : ub, tail = g1 > g0 ? g1 * CTILES : head;
+        for (uint32_t i = g0 + tid; i < g1; i += EWG) { const uint64_t v = p.csum[(size_t)i * 8]; pg += (uint32_t)(v >> 32); pe += (uint32_t)v; }
+        if (u0 + tid < head) { pg += p.tg0[u0 + tid]; pe += p.tin[u0 + tid]; }
+        if (tail + tid < ub) { pg += p.tg0[tail + tid]; pe += p.tin[tail + tid]; }
+    }
+    const SegState sg = p.seg[t];
+    Gathered g;
+    gathered_load(p, t, p.commit, tid, g);
+    if constexpr (HEADS) {   // (out of the registers while the threshold is resolved)
+        *(v4i*)&stage_idx[wib][4 * lane] = hi4;
+        *(v4f*)&stage_val[wib][4 * lane] = hv4;
+    }
+    EmitCtx x;
+    x.tau = 0;
+    x.set_pz(p, sg, GEN && p.single);
+    if (p.bounds_from == BOUNDS_FIXED) {
+        uint32_t n = 0;
+        for (uint32_t i = tid; i < (p.n_tiles + CTILES - 1u) / CTILES; i += EWG) n += (uint32_t)(p.csum[(size_t)i * 8] >> 32);
+        n = wave_sum(n);
+        if (lane == 0) sh.ws[2][wib] = n;
+        __syncthreads();
+        n = 0;
+#pragma unroll
+        for (int i = 0; i < EW; ++i) n += sh.ws[2][i];
+        if ((int64_t)n > p.total_out) {   // (as in emit_kernel)
+            for (uint32_t v = ub * SUB + wib; v < ue * SUB; v += EW) put_back_subtile(p, v, x.pz, lane);
+            return;
+        }
+    }
+    gathered_resolve(p, tid, g, sh);
+    const uint32_t dtau = g.tau - g.base;  // the threshold inside the located bin
+    // ---- the gathered entries above and at the threshold, by tile.  Entries equal to tau: those inside a located bin
+    // that is one key wide, else the gathered ones
+    const bool one_key = g.mode == MODE_RESOLVED;
+    if (!one_key) pe = 0;
+    if (g.mode == MODE_GATHER) {
+        gathered_each(p, tid, g, [&](uint32_t d, uint32_t tile, float) {
+            if (d < dtau) return;
+            const bool gt = d > dtau;
+            if (tile < ub) { if (gt) ++pg; else ++pe; }
+            else if (tile < ue) atomicAdd(gt ? &sh.fg[tile - ub] : &sh.fe[tile - ub], 1u);
+        });
+    }
+    pg = wave_sum(pg);
+    pe = wave_sum(pe);
+    if (lane == 0) { sh.ws[0][wib] = pg; sh.ws[1][wib] = pe; }
+    __syncthreads();
+    if (ub + wib >= ue) return;
+    // ---- this wavefront's tile: pairs before it, ties before it, its own
+    uint32_t run_g = 0, run_e = 0, tg = 0, te = 0;
+#pragma unroll
+    for (int i = 0; i < EW; ++i) {
+        run_g += sh.ws[0][i];
+        run_e += sh.ws[1][i];
+        const uint32_t gi = sh.tg[i] + sh.fg[i], ei = one_key ? sh.te[i] : sh.fe[i];
+        if (i < wib) { run_g += gi; run_e += ei; }
+        if (i == wib) { tg = gi; te = ei; }
+    }
+    const uint32_t ties_before = run_e < g.need ? run_e : g.need;   // ties selected in earlier tiles
+    const uint32_t left = g.need - ties_before;
+    x.set_tau(__builtin_amdgcn_readfirstlane(g.tau));
+    x.take = __builtin_amdgcn_readfirstlane(left < te ? left : te);
+    if (__builtin_amdgcn_readfirstlane(tg) + x.take == 0 && !x.put_back) return;
+    const int64_t seg_out = seg_koff(p, t);
+    x.lim = seg_out + (int64_t)seg_k(p, t, p.commit);  // end of this segment's message
+    x.pos = seg_out + (int64_t)(uint32_t)__builtin_amdgcn_readfirstlane(run_g + ties_before);
+    x.erun = 0;
+    if constexpr (HEADS) {
+        hi4 = *(const v4i*)&stage_idx[wib][4 * lane];
+        hv4 = *(const v4f*)&stage_val[wib][4 * lane];
+    }
+    emit_tile<GEN, HEADS>(p, t, ub + wib, x, cc, hi4, hv4, stage_idx[wib], stage_val[wib]);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -3341,9 +3748,9 @@ Layout make_layout(int64_t n, int n_cf, int n_seg)
     L.ovs = take(sizeof(double) * nt * SUB * n_cf);
     L.tg0 = take(sizeof(uint32_t) * nt);
     L.tin = take(sizeof(uint32_t) * nt);
-    L.toff = take(sizeof(uint32_t) * nt);
+    L.toff = take(sizeof(uint32_t) * nt);   // (or csum: 64 bytes per CTILES = 64 tiles, a quarter of that)
     L.ttake = take(sizeof(uint32_t) * nt);
-    L.tsel = take(sizeof(uint32_t) * nt);
+    L.tsel = take(sizeof(uint32_t) * nt);   // (or wseg)
     L.ssd = take(sizeof(double) * nt * SUB);
     L.ssd_t = take(sizeof(double) * nt);
     L.sss = take(sizeof(double) * nt * n_cf);
@@ -3621,6 +4028,7 @@ static int compress_impl(const float* grad, float* residual, int64_t n, const do
 
     int64_t total_out = 0;
     uint32_t max_seg_tiles = 1;  // tiles of the largest segment
+    uint32_t emit_wgs = 0;       // workgroups of an emit step without scan that take tiles
     int sample_rounds = 1;       // groups per thread of the sampling kernel
     uint32_t n_small = 0;        // layerwise: tensors of at most SMALL_MAX elements, one workgroup each (not under the
                                  // testing flag, which sends every tensor through the histogram route)
@@ -3632,6 +4040,7 @@ static int compress_impl(const float* grad, float* residual, int64_t n, const do
         p.flat_samples = sample_count((uint64_t)n, cf_min, cf_max, true);
         p.n_tiles = (uint32_t)((n + TW - 1) / TW);
         max_seg_tiles = p.n_tiles;
+        emit_wgs = (p.n_tiles + EW - 1) / EW;
         // more than SAMPLE_MAX samples (never a tensor read whole): 2 or 4 times SAMPLE_BLOCK samples per block, the
         // fewest that leave at most DENSE_BLOCKS blocks (more blocks keep more loads in flight, fewer cost the
         // threshold kernel less)
@@ -3665,6 +4074,11 @@ static int compress_impl(const float* grad, float* residual, int64_t n, const do
         p.n_tiles = (uint32_t)tiles;
         p.n_sample_blocks = (uint32_t)sblocks;
     }
+    const bool with_scan = p.n_tiles > EMIT_RESIDENT;   // see resolve_emit_kernel
+    if (!with_scan) {
+        p.csum = (uint64_t*)p.toff;
+        p.wseg = p.tsel;
+    }
     // nothing has been queued or written up to here; from here on an error return leaves the outputs unspecified
     if (ns > 1 || ev)
         if (const int rc = refuse_capture(stream)) return rc;
@@ -3695,6 +4109,7 @@ static int compress_impl(const float* grad, float* residual, int64_t n, const do
                 small_list[small_at_++] = (uint32_t)t;
             } else {
                 tile_at += (uint32_t)((nt + TW - 1) / TW); g.tile1 = tile_at;
+                g.wg0 = emit_wgs; g.wgs = (g.tile1 - g.tile0 + EW - 1) / EW; emit_wgs += g.wgs;
                 g.samp_cnt = sample_count((uint64_t)nt, cf_min, cf_max, false);
                 const uint32_t nb = (g.samp_cnt + SAMPLE_BLOCK - 1) / SAMPLE_BLOCK;
                 for (uint32_t b = 0; b < nb; ++b) sblock_seg[sb_at + b] = (uint32_t)t;
@@ -3732,7 +4147,6 @@ static int compress_impl(const float* grad, float* residual, int64_t n, const do
 
     const uint32_t sub_grid = (p.n_tiles * SUB + WAVES - 1) / WAVES;
     const uint32_t light_grid = (p.n_tiles + LWAVES - 1) / LWAVES;
-    const uint32_t scan_slices = (max_seg_tiles + SCAN_SLICE - 1) / SCAN_SLICE;
 
     const int ncf_form = n_cf <= 1 ? 0 : n_cf <= 2 ? 1 : n_cf <= 3 ? 2 : n_cf <= 4 ? 3 : 4;
     static_assert(MAXCF >= 4, "forms for 1, 2, 3, 4 and MAXCF CFs");
@@ -3789,14 +4203,16 @@ static int compress_impl(const float* grad, float* residual, int64_t n, const do
     void (*const refine_forms[2][5])(Params) = {
         {refine_kernel<1, false>, refine_kernel<2, false>, refine_kernel<3, false>, refine_kernel<4, false>, refine_kernel<MAXCF, false>},
         {refine_kernel<1, true>, refine_kernel<2, true>, refine_kernel<3, true>, refine_kernel<4, true>, refine_kernel<MAXCF, true>}};
-    const int heads = (!random && p.n_tiles <= 6144u) ? 1 : 0;
+    const int heads = (!random && p.n_tiles <= EMIT_RESIDENT) ? 1 : 0;
     hipLaunchKernelGGL(refine_forms[heads][ncf_form], dim3(light_grid), dim3(LWG), 0, stream, p);
-    hipLaunchKernelGGL(scan_kernel, dim3(ns, scan_slices + n_cf), dim3(SCAN_T), 0, stream, p, scan_slices);
-    {
-        // (the plain call's form with the early loads of the lists' heads if the tiles' wavefronts are all resident at once)
-        void (*emit)(Params) = (p.random || p.single) ? emit_kernel<true, false>
-                                                      : (p.n_tiles <= 6144u ? emit_kernel<false, true> : emit_kernel<false, false>);
-        hipLaunchKernelGGL(emit, dim3(light_grid), dim3(LWG), 0, stream, p);
+    const bool general = p.random || p.single;   // (the plain call has forms of its own)
+    if (with_scan) {
+        const uint32_t scan_slices = (max_seg_tiles + SCAN_SLICE - 1) / SCAN_SLICE;
+        hipLaunchKernelGGL(scan_kernel, dim3(ns, scan_slices + n_cf), dim3(SCAN_T), 0, stream, p, scan_slices);
+        hipLaunchKernelGGL(general ? emit_kernel<true> : emit_kernel<false>, dim3(light_grid), dim3(LWG), 0, stream, p);
+    } else {
+        hipLaunchKernelGGL(general ? resolve_emit_kernel<true> : resolve_emit_kernel<false>, dim3(emit_wgs + (uint32_t)(ns * n_cf)),
+                           dim3(EWG), 0, stream, p);
     }
     }
     if (ev) (void)hipEventRecord((hipEvent_t)ev->call_end, stream);

@@ -81,3 +81,41 @@ def test_some_tensors_take_the_exact_route():
     for flags in (0, FB):
         check(g, r, [2.5], 0, off, flags=flags, what="layerwise, one CF")
         check(g, r, [2.5, 10.0], 1, off, flags=flags, what="layerwise, two CFs")
+
+
+def _coarse(x, bits):
+    """float32 values with only the top `bits` bits of the mantissa: many equal magnitudes, 2^(23 - bits) keys apart."""
+    return (np.ascontiguousarray(x).view(np.uint32) & np.uint32(0xFFFFFFFF << (23 - bits) & 0xFFFFFFFF)).view(np.float32)
+
+
+@pytest.mark.parametrize("n,bits", [(250_007, 5), (1_000_003, 7), (2_500_001, 8)])
+def test_long_gather_lists(n, bits):
+    """Located bins with hundreds to thousands of entries, few distinct keys among them: the gather lists are longer than
+    their heads, and ties are spread over many tiles."""
+    g = _coarse(workloads.normal_gradient(n, 1e-3, seed=n), bits)
+    z = np.zeros(n, np.float32)
+    for cf in (3.0, 10.0, 50.0):
+        check(g, z, [cf], what=f"cf {cf}")
+    check(g, z, [3.0, 10.0, 50.0], 1, what="three CFs")
+    sizes = [8_193, n // 3, 100, n - n // 3 - 8_193 - 100]
+    check(g, z, [10.0], 0, workloads.offsets_of(sizes), what="layerwise")
+
+
+@pytest.mark.parametrize("n", [1, 8_192, 8_193, 8 * 8_192, 8 * 8_192 + 1, 64 * 8_192, 64 * 8_192 + 1, 72 * 8_192 + 5])
+def test_workgroup_and_group_boundaries(n):
+    """Tile counts around a workgroup of the emit step (8 tiles) and around a partial sum of the tiles' counts (64)."""
+    g = workloads.normal_gradient(n, 1e-3, seed=n)
+    r = workloads.normal_gradient(n, 1e-4, seed=n + 1)
+    for cf in (1.0, 10.0, 1000.0):
+        check(g, r, [cf], what=f"n {n} cf {cf}")
+
+
+def test_tensors_that_start_inside_a_group():
+    """Layerwise: tensors of more than 64 tiles that start anywhere between two partial sums."""
+    sizes = [9 * 8_192 + 3, 130 * 8_192 + 1, 5, 64 * 8_192, 8_193, 200 * 8_192 - 7]
+    off = workloads.offsets_of(sizes)
+    n = int(off[-1])
+    g = workloads.resnet_like_gradient(n, seed=1)
+    r = workloads.normal_gradient(n, 1e-5, seed=2)
+    check(g, r, [10.0, 100.0], 0, off, what="lowest sent")
+    check(_coarse(g, 6), np.zeros(n, np.float32), [20.0], 0, off, what="ties")
