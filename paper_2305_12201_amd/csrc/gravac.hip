@@ -3307,7 +3307,7 @@ __global__ __launch_bounds__(256) void decompress_kernel(const int32_t* __restri
                     // a whole tile: all eight loads of a thread in flight together
                     v4f tv[DTILE / 1024];
 #pragma unroll
-                    for (int r = 0; r < DTILE / 1024; ++r) tv[r] = *(const v4f*)(dense + base + r * 1024 + tid * 4);
+                    for (int r = 0; r < DTILE / 1024; ++r) tv[r] = ld_stream((const v4f*)(dense + base + r * 1024 + tid * 4));
 #pragma unroll
                     for (int r = 0; r < DTILE / 1024; ++r) *(v4f*)(acc + r * 1024 + tid * 4) = tv[r];
                 } else {
@@ -3368,7 +3368,7 @@ __global__ __launch_bounds__(256) void decompress_kernel(const int32_t* __restri
             if (vec && len == DTILE) {
 #pragma unroll
                 for (int r = 0; r < DTILE / 1024; ++r)
-                    *(v4f*)(dense + base + r * 1024 + tid * 4) = *(const v4f*)(acc + r * 1024 + tid * 4);
+                    st_stream(*(const v4f*)(acc + r * 1024 + tid * 4), (v4f*)(dense + base + r * 1024 + tid * 4));
             } else {
                 for (int i = tid * 4; i < len; i += 256 * 4) {
                     if (vec && i + 4 <= len) {
@@ -3401,52 +3401,103 @@ __device__ __forceinline__ int64_t tile_of_index(int32_t x, int64_t ntile)
     return t < ntile ? t : ntile;
 }
 
-// grid (pair blocks, workers).  Pair j > 0 of a message starts the tiles (tile of pair j - 1, tile of pair j].
-// A lane with up to 2 tiles to write does it itself, longer runs (gaps in the message) are written by the
-// whole wavefront.
+// grid (pair blocks, workers).  Pair j > 0 of a message starts the tiles (tile of pair j - 1, tile of pair j].  A
+// wavefront takes BPAIRS consecutive rows of 64 pairs, all their loads in flight at once (one row per wavefront and two
+// loads per pair: 10.4 us for 3.6 million pairs).  A lane with up to BGAP tiles to write does it itself, longer runs (gaps
+// in the message) are written by the whole wavefront.
+constexpr int BPAIRS = 4;
+constexpr int BGAP = 8;
+
 __global__ __launch_bounds__(256) void bounds_kernel(const int32_t* __restrict__ idx, WorkerOffsets wo, int64_t ntile,
                                                      uint32_t* __restrict__ bounds)
 {
     const int w = blockIdx.y, lane = threadIdx.x & 63;
     const int64_t a = wo.at[w], cnt = wo.at[w + 1] - a;
     uint32_t* bw = bounds + (size_t)w * (size_t)(ntile + 1);
-    const int64_t j0 = ((int64_t)blockIdx.x * 256 + (threadIdx.x & ~63));  // first pair of this wavefront
+    const int64_t j0 = ((int64_t)blockIdx.x * 256 + (threadIdx.x & ~63)) * BPAIRS;  // first pair of this wavefront
     if (j0 >= cnt) return;
-    const int64_t j = j0 + lane;
-    const bool live = j > 0 && j < cnt;
-    int64_t t_prev = 0, t_cur = 0;  // this lane writes bw[t] = j for t in (t_prev, t_cur]
-    if (live) {
-        t_cur = tile_of_index(idx[a + j], ntile);
-        t_prev = tile_of_index(idx[a + j - 1], ntile);
+    int32_t x[BPAIRS];
+#pragma unroll
+    for (int q = 0; q < BPAIRS; ++q) {
+        const int64_t j = j0 + q * 64 + lane;
+        x[q] = idx[a + (j < cnt ? j : cnt - 1)];
     }
-    const int64_t gap = t_cur - t_prev;  // <= 0 where the indices do not ascend: nothing is written
-    if (live && gap > 0 && gap <= 2) {
-        bw[t_prev + 1] = (uint32_t)j;
-        if (gap == 2) bw[t_prev + 2] = (uint32_t)j;
-    }
-    uint64_t big = __ballot(live && gap > 2);
-    while (big) {
-        const int src = __ffsll((unsigned long long)big) - 1;
-        big &= big - 1;
-        const int64_t tp = __shfl(t_prev, src, 64), tc = __shfl(t_cur, src, 64);
-        const uint32_t v = (uint32_t)(j0 + src);
-        for (int64_t t = tp + 1 + lane; t <= tc; t += 64) bw[t] = v;
+    int32_t last = j0 > 0 ? idx[a + j0 - 1] : 0;   // the pair before the row
+#pragma unroll
+    for (int q = 0; q < BPAIRS; ++q) {
+        const int64_t j = j0 + q * 64 + lane;
+        int32_t prev = __shfl_up(x[q], 1, 64);
+        if (lane == 0) prev = last;
+        last = __builtin_amdgcn_readlane(x[q], 63);
+        const bool live = j > 0 && j < cnt;
+        int64_t t_prev = 0, t_cur = 0;  // this lane writes bw[t] = j for t in (t_prev, t_cur]
+        if (live) {
+            t_cur = tile_of_index(x[q], ntile);
+            t_prev = tile_of_index(prev, ntile);
+        }
+        const int64_t gap = t_cur - t_prev;  // <= 0 where the indices do not ascend: nothing is written
+        if (live && gap > 0 && gap <= BGAP)
+            for (int64_t t = t_prev + 1; t <= t_cur; ++t) bw[t] = (uint32_t)j;
+        uint64_t big = __ballot(live && gap > BGAP);
+        while (big) {
+            const int src = __ffsll((unsigned long long)big) - 1;
+            big &= big - 1;
+            const int64_t tp = __shfl(t_prev, src, 64), tc = __shfl(t_cur, src, 64);
+            const uint32_t v = (uint32_t)(j0 + q * 64 + src);
+            for (int64_t t = tp + 1 + lane; t <= tc; t += 64) bw[t] = v;
+        }
     }
 }
 
 constexpr int DCHUNK = 32;  // tiles whose boundaries a workgroup fetches in one round of loads
 constexpr int DENT = 768;   // (tile, worker) entries of such a chunk
 
+// The tile's pairs in worker-major order, N per thread: place inside the tile, value and worker (-1: none, or an index
+// outside the tile, which a malformed message may have).  Slots past the last pair take the last pair's place.
+template <int N>
+__device__ __forceinline__ void tile_pairs(const int32_t* __restrict__ idx, const float* __restrict__ val, const uint32_t* spre,
+                                           const int64_t* wat, const uint32_t* lo, uint32_t tot, int64_t base, int len, int tid,
+                                           int (&pj)[N], float (&pv)[N], int (&pw)[N])
+{
+    int64_t at[N];
+#pragma unroll
+    for (int q = 0; q < N; ++q) {
+        const uint32_t slot = q * 256 + tid;
+        const uint32_t sc = slot < tot ? slot : tot - 1;
+        int w = 0;
+#pragma unroll
+        for (int step = 32; step >= 1; step >>= 1)
+            if (spre[w + step] <= sc) w += step;   // spre[64] = tot > sc: w stays below 64
+        at[q] = wat[w] + (int64_t)lo[w] + (int64_t)(sc - spre[w]);
+        pw[q] = slot < tot ? w : -1;
+    }
+#pragma unroll
+    for (int q = 0; q < N; ++q) pj[q] = idx[at[q]];
+#pragma unroll
+    for (int q = 0; q < N; ++q) pv[q] = val[at[q]];
+#pragma unroll
+    for (int q = 0; q < N; ++q) {
+        const int64_t j = (int64_t)pj[q] - base;
+        if (j < 0 || j >= len) pw[q] = -1;
+        pj[q] = (int)(j < 0 || j >= len ? 0 : j);
+    }
+}
+
+// (Whole tiles are read and written with non-temporal hints, as in the pass over the gradient: eight messages of CF 100 on
+// the ResNet101 shape, all tiles whole, 385 MB, 76.6 -> 67.0 us.  Moving only the named 64-byte lines of a tile, seven in
+// ten there, was no faster: 128 bytes is what the memory moves.)
 // A workgroup takes the tiles blockIdx.x, blockIdx.x + gridDim.x, ...  It first fetches, for a chunk of its
 // tiles at once, every worker's boundaries (one round of independent loads instead of one dependent round per
 // tile) and then walks over the chunk's tiles; a tile no message has a pair in costs no further memory access.
-__global__ __launch_bounds__(256) void decompress_ws_kernel(const int32_t* __restrict__ idx, const float* __restrict__ val,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) void decompress_ws_kernel(const int32_t* __restrict__ idx, const float* __restrict__ val,
                                                             WorkerOffsets wo, int W, int64_t n, float* dense,
                                                             const uint32_t* __restrict__ bounds, float alpha)
 {
     __shared__ __attribute__((aligned(16))) float acc[DTILE];
     __shared__ uint32_t blo[DENT], bcnt[DENT];      // first pair and number of pairs, per (tile of the chunk, worker)
     __shared__ uint32_t btot[DCHUNK];               // pairs of all workers, per tile of the chunk
+    __shared__ uint32_t bwrk[DCHUNK];               // ... the number of those workers (high half) and the sum of their numbers
+    __shared__ uint32_t tpre[DCHUNK + 1];           // pairs of the chunk's tiles of one worker before each
     __shared__ uint32_t spre[DMAXW + 1];            // a sparse tile's pairs before worker w, in worker-major order
     __shared__ int64_t wat[DMAXW + 1];              // start of every worker's message
     __shared__ int32_t first[DMAXW], last[DMAXW];   // smallest and largest index of every worker's message
@@ -3463,7 +3514,7 @@ __global__ __launch_bounds__(256) void decompress_ws_kernel(const int32_t* __res
     const int tc = DENT / Wp < DCHUNK ? DENT / Wp : DCHUNK;       // tiles per chunk (>= 12: Wp <= 64)
     for (int64_t c0 = blockIdx.x; c0 < ntile; c0 += (int64_t)tc * gridDim.x) {
         __syncthreads();  // first / last / wat are written; the previous chunk's entries are no longer read
-        if (tid < DCHUNK) btot[tid] = 0;
+        if (tid < DCHUNK) { btot[tid] = 0; bwrk[tid] = 0; }
         __syncthreads();
         for (int e = tid; e < tc * Wp; e += 256) {
             const int i = e / Wp, w = e - i * Wp;
@@ -3485,9 +3536,33 @@ __global__ __launch_bounds__(256) void decompress_ws_kernel(const int32_t* __res
             }
             blo[e] = l;
             bcnt[e] = c;
-            if (c) atomicAdd(&btot[i], c);
+            if (c) { atomicAdd(&btot[i], c); atomicAdd(&bwrk[i], 0x10000u + (uint32_t)w); }
         }
         __syncthreads();
+        // The chunk's tiles with few pairs, all of one worker: nothing has to be ordered, so the pairs of all of them are
+        // applied at once, each to its entry (in most of a gradient whose large entries sit elsewhere a tile holds a pair
+        // or two, and a tile at a time would be a chain of round trips each).
+        {
+            if (tid < 64) {
+                const uint32_t c = tid < tc && (bwrk[tid] >> 16) == 1u && btot[tid] <= DSPARSE ? btot[tid] : 0u;
+                const uint32_t inc = wave_scan(c);
+                if (tid < DCHUNK) tpre[tid + 1] = inc;
+                if (tid == 0) tpre[0] = 0;
+            }
+            __syncthreads();
+            const uint32_t all = tpre[DCHUNK];
+            for (uint32_t k = tid; k < all; k += 256) {
+                int i = 0;
+#pragma unroll
+                for (int step = DCHUNK / 2; step >= 1; step >>= 1)
+                    if (tpre[i + step] <= k) i += step;
+                const int w = (int)(bwrk[i] & 0xFFFFu);
+                const int64_t base = (c0 + (int64_t)i * gridDim.x) * DTILE, end = (n - base < DTILE) ? n : base + DTILE;
+                const int64_t at = wat[w] + (int64_t)blo[i * Wp + w] + (int64_t)(k - tpre[i]);
+                const int64_t g = idx[at];
+                if (g >= base && g < end) dense[g] = __fadd_rn(dense[g], __fmul_rn(alpha, val[at]));
+            }
+        }
         for (int i = 0; i < tc; ++i) {
             const int64_t tile = c0 + (int64_t)i * gridDim.x;
             if (tile >= ntile) break;
@@ -3495,6 +3570,7 @@ __global__ __launch_bounds__(256) void decompress_ws_kernel(const int32_t* __res
             const int len = (int)((n - base < DTILE) ? n - base : DTILE);
             const uint32_t tot = btot[i];
             if (tot == 0) continue;  // no message touches the tile
+            if (tot <= DSPARSE && (bwrk[i] >> 16) == 1u) continue;  // done above
             if (tot <= DSPARSE) {
                 // Few pairs: only the entries they name are read and written back, not the whole tile (a scattered
                 // access moves 64 bytes, so this pays up to about one pair per 16 entries).  The entries go through
@@ -3508,30 +3584,7 @@ __global__ __launch_bounds__(256) void decompress_ws_kernel(const int32_t* __res
                 __syncthreads();
                 int pj[DSLOTS], pw[DSLOTS];
                 float pv[DSLOTS], dv[DSLOTS];
-                int64_t at[DSLOTS];
-                // the tile's pairs in worker-major order, DSLOTS per thread (a slot past the last pair takes the last
-                // pair's place and is not applied)
-#pragma unroll
-                for (int q = 0; q < DSLOTS; ++q) {
-                    const uint32_t slot = q * 256 + tid;
-                    const uint32_t sc = slot < tot ? slot : tot - 1;
-                    int w = 0;
-#pragma unroll
-                    for (int step = 32; step >= 1; step >>= 1)
-                        if (spre[w + step] <= sc) w += step;   // spre[64] = tot > sc: w stays below 64
-                    at[q] = wat[w] + (int64_t)blo[i * Wp + w] + (int64_t)(sc - spre[w]);
-                    pw[q] = slot < tot ? w : -1;
-                }
-#pragma unroll
-                for (int q = 0; q < DSLOTS; ++q) pj[q] = idx[at[q]];
-#pragma unroll
-                for (int q = 0; q < DSLOTS; ++q) pv[q] = val[at[q]];
-#pragma unroll
-                for (int q = 0; q < DSLOTS; ++q) {
-                    const int64_t j = (int64_t)pj[q] - base;
-                    if (j < 0 || j >= len) pw[q] = -1;   // an index outside the tile (malformed message) is ignored
-                    pj[q] = (int)(j < 0 || j >= len ? 0 : j);
-                }
+                tile_pairs<DSLOTS>(idx, val, spre, wat, blo + i * Wp, tot, base, len, tid, pj, pv, pw);
 #pragma unroll
                 for (int q = 0; q < DSLOTS; ++q) dv[q] = pw[q] >= 0 ? dense[base + pj[q]] : 0.0f;
 #pragma unroll
@@ -3566,7 +3619,7 @@ __global__ __launch_bounds__(256) void decompress_ws_kernel(const int32_t* __res
                         // a whole tile: all eight loads of a thread in flight together
                         v4f tv[DTILE / 1024];
 #pragma unroll
-                        for (int r = 0; r < DTILE / 1024; ++r) tv[r] = *(const v4f*)(dense + base + r * 1024 + tid * 4);
+                        for (int r = 0; r < DTILE / 1024; ++r) tv[r] = ld_stream((const v4f*)(dense + base + r * 1024 + tid * 4));
 #pragma unroll
                         for (int r = 0; r < DTILE / 1024; ++r) *(v4f*)(acc + r * 1024 + tid * 4) = tv[r];
                     } else {
@@ -3630,7 +3683,7 @@ __global__ __launch_bounds__(256) void decompress_ws_kernel(const int32_t* __res
                 if (vec && len == DTILE) {
 #pragma unroll
                     for (int r = 0; r < DTILE / 1024; ++r)
-                        *(v4f*)(dense + base + r * 1024 + tid * 4) = *(const v4f*)(acc + r * 1024 + tid * 4);
+                        st_stream(*(const v4f*)(acc + r * 1024 + tid * 4), (v4f*)(dense + base + r * 1024 + tid * 4));
                 } else {
                     for (int q = tid * 4; q < len; q += 256 * 4) {
                         if (vec && q + 4 <= len) {
@@ -4339,7 +4392,7 @@ static int decompress_impl(const int32_t* idx, const float* val, const int64_t* 
         if (group == 0) continue;
         if (bounds) {
             // tile boundaries of the group's messages first (the workspace is reused from group to group: stream order)
-            const uint32_t pair_blocks = (uint32_t)((longest + 255) / 256);
+                const uint32_t pair_blocks = (uint32_t)((longest + 256 * BPAIRS - 1) / (256 * BPAIRS));
             hipLaunchKernelGGL(bounds_kernel, dim3(pair_blocks, (uint32_t)wn), dim3(256), 0, stream, idx, wo, ntile,
                                bounds);
             hipLaunchKernelGGL(decompress_ws_kernel, dim3(grid), dim3(256), 0, stream, idx, val, wo, wn, n, dense_out,

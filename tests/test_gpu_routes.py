@@ -2,7 +2,9 @@
 kernel form or route to another, against the CPU oracle, bit for bit."""
 import numpy as np
 import pytest
+import torch
 
+from oracle import oracle
 from paper_2305_12201_amd import binding, workloads
 from tests.gpu_util import check
 from tests.test_gpu_randomk import check as check_randomk
@@ -119,3 +121,36 @@ def test_tensors_that_start_inside_a_group():
     r = workloads.normal_gradient(n, 1e-5, seed=2)
     check(g, r, [10.0, 100.0], 0, off, what="lowest sent")
     check(_coarse(g, 6), np.zeros(n, np.float32), [20.0], 0, off, what="ties")
+
+
+def _gapped(n, count, seed, spread):
+    """Ascending distinct indices in runs: gaps from one entry to many tiles of 8192."""
+    rng = np.random.Generator(np.random.PCG64(seed))
+    step = np.maximum(1, np.exp(rng.uniform(0.0, spread, count))).astype(np.int64)
+    idx = np.cumsum(step) - 1
+    return idx[idx < n].astype(np.int32)
+
+
+@pytest.mark.parametrize("W", [1, 2, 8, 9, 33, 65])
+@pytest.mark.parametrize("n,spread", [(40 * 8_192 + 11, 4.0), (700 * 8_192 - 5, 9.0), (2_000 * 8_192, 12.5)])
+def test_decompression_of_gapped_messages(W, n, spread):
+    """Tile boundaries across gaps of every length; tiles named by no worker, by one (applied together, up to 512 pairs)
+    and by several; entries outside the buffer are ignored; with and without a workspace."""
+    msgs = [_gapped(n + 20_000, 3_000 + 97 * w, 100 * W + w, spread) for w in range(W)]
+    if W > 1:
+        msgs[1] = msgs[1][:0]                                            # a worker without pairs
+        msgs[0] = np.unique(np.concatenate([msgs[0], np.arange(3 * 8_192, 3 * 8_192 + 512),    # exactly 512 pairs of one worker ...
+                                            np.arange(5 * 8_192, 5 * 8_192 + 513)])).astype(np.int32)   # ... and one more
+    rng = np.random.Generator(np.random.PCG64(W))
+    vals = [rng.standard_normal(m.size).astype(np.float32) for m in msgs]
+    base = rng.standard_normal(n).astype(np.float32)
+    idx, val, counts = np.concatenate(msgs), np.concatenate(vals), [m.size for m in msgs]
+    ref = base.copy()
+    keep = [m < n for m in msgs]
+    oracle.decompress_update(np.concatenate([m[k] for m, k in zip(msgs, keep)]), np.concatenate([v[k] for v, k in zip(vals, keep)]),
+                             [int(k.sum()) for k in keep], -0.0125, ref)
+    i, v = torch.from_numpy(idx).cuda(), torch.from_numpy(val).cuda()
+    for ws in (None, torch.empty(binding.gravac_decompress_workspace_bytes(W, n), dtype=torch.uint8, device="cuda")):
+        d = torch.from_numpy(base.copy()).cuda()
+        binding.gravac_decompress_update(i, v, counts, -0.0125, d, workspace=ws)
+        assert np.array_equal(d.cpu().numpy().view(np.uint32), ref.view(np.uint32)), f"workspace {ws is not None}"
