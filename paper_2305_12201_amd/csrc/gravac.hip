@@ -77,10 +77,22 @@ constexpr uint32_t LONG_WALK = 256;   // a tile with at least this many listed e
 constexpr int REP = 8;              // copies of the bracket histogram and of the gather lists
 constexpr int NBIN = 2048;          // bins of the bracket / refine / coarse histograms
 constexpr uint32_t OVF = NBIN - 1;  // bins 0 .. OVF - 1 cover the bracket; bin OVF stands for everything above it
-constexpr int SBIN = 4096;          // bins of the sample histogram: 2^17 keys each (64 per octave, 1.1 % in magnitude)
-constexpr uint32_t SSHIFT = 17;     // from |x| = 2^-48 up to 2^16; smaller magnitudes share bin 0, larger ones the last bin
-constexpr uint32_t SKEY0 = 79u << 23;
-static_assert((uint64_t)SKEY0 + ((uint64_t)SBIN << SSHIFT) <= 0x7F800000ull, "the window lies inside the finite keys");
+// Bins of the sample histogram, in key order: SCOARSE bins of 2^19 keys (16 per octave, 4.4 % in magnitude) from
+// |x| = 2^-48 up to 2^16 (smaller magnitudes share the first, larger ones the last), except that a window of SWIN octaves
+// is cut into bins of 2^15 keys (256 per octave, 0.27 %).  A bracket's ends are bin edges, so a bin's entries are what it
+// has too many.  (4096 bins of 1.1 % everywhere: at CF 10 the bracket held three times the statistically needed entries.)
+constexpr int SBIN = 4096;
+constexpr uint32_t SCSHIFT = 19, SFSHIFT = 15;
+constexpr uint32_t SEXP0 = 79, SOCT = 64;      // exponent field of 2^-48, octaves
+constexpr uint32_t SWIN = 12, SWIN_ABOVE = 2;  // octaves of the window, and how many of them lie above the largest of 256 samples
+// A flat tensor of fewer than SWIN_SMALL elements takes a window from 2^-14 on, unseen: a bracket 4.4 % in magnitude too
+// wide costs it little (23,000 entries at most), and the look at the 256 elements 0.6 us of a 1 MiB bucket's 34.
+constexpr int64_t SWIN_SMALL = 1 << 19;
+constexpr uint32_t SWIN_FIXED = (127u - 14u) << 23;
+constexpr uint32_t SKEY0 = SEXP0 << 23;
+constexpr uint32_t SCOARSE = SOCT << (23 - SCSHIFT), SFINE = SWIN << (23 - SFSHIFT), SLESS = SWIN << (23 - SCSHIFT);
+constexpr uint32_t SUSED = SCOARSE + SFINE - SLESS;   // bins in use
+static_assert(SUSED <= (uint32_t)SBIN && (uint64_t)SKEY0 + ((uint64_t)SOCT << 23) <= 0x7F800000ull, "inside the finite keys");
 constexpr int SGRP = 8;             // the sample bins in SGRP groups: one workgroup of the threshold kernel each
 constexpr int SAMPLE_BLOCK = 1024;  // samples per workgroup of the sampling kernel
 constexpr int SAMPLE_MAX = 65536;   // samples of a flat tensor at most (unless k n is large, see SAMPLE_MAX_FLAT)
@@ -93,6 +105,7 @@ constexpr int MAXCF = GRAVAC_MAX_CF;
 constexpr double ZMARGIN = 5.0;     // safety margin of the sampled rank, in standard deviations
 constexpr uint32_t CTILES = 64;     // tiles per partial sum of the tiles' counts (csum)
 constexpr int XQ_WORDS = 8;         // a segment's work queue in the plan step: chunks claimed, then chunks done per phase
+constexpr int XQ_WIN = XQ_WORDS;    // ... and behind it the first key of its sample histogram's window
 constexpr uint32_t NONE = 0xFFFFFFFFu;
 constexpr uint32_t KEY_END = 0x80000000u;  // one past the largest key
 
@@ -195,6 +208,7 @@ struct Params {
     // the same for one flat tensor
     uint32_t flat_k[MAXCF];
     uint32_t flat_samples;
+    uint32_t fixed_window;   // a small flat tensor: first key of the sample histogram's window (0: found from the data)
     // workspace
     Status* status;
     CfState* st;         // [n_seg][n_cf]
@@ -205,7 +219,7 @@ struct Params {
     uint32_t* hist1;     // [copy blocks][NBIN] bracket histograms: REP copies per CF of a large tensor, one otherwise
     uint32_t* ovfc;      // [n_seg][n_cf][64][32] counts above the bracket (the histogram's last bin), spread over
                          // 64 cache lines; word 0 of each line is used
-    uint32_t* xq;        // [n_seg][n_cf][NBIN], of which a segment's first 8 words are in use: the plan step's work queue (XQ_*)
+    uint32_t* xq;        // [n_seg][n_cf][NBIN], of which a segment's first 9 words are in use (XQ_*)
     uint32_t* coarse;    // [n_seg][NBIN] histogram of key >> 20 (exact route)
     uint32_t* list_key;  // [copy blocks][LCAP] gather lists: key ... (before they are filled: the exact routes' histograms)
     uint32_t* list_tile; //                          ... tile ...
@@ -263,18 +277,27 @@ __device__ __forceinline__ size_t seg_block(const Params& p, int t, int j)
 
 __device__ __forceinline__ uint32_t key_of(float a) { return __float_as_uint(a) & 0x7FFFFFFFu; }
 
-// Bin of the sample histogram a key falls into, and the keys a bin spans.
-__device__ __forceinline__ uint32_t sample_bin(uint32_t key)
+// Bin of the sample histogram a key falls into, and the keys a bin spans; w0: first key of the window (the start of an
+// octave, not of the lowest).
+__device__ __forceinline__ uint32_t sample_bin(uint32_t key, uint32_t w0)
 {
-    if (key < SKEY0) return 0u;
-    const uint32_t b = (key - SKEY0) >> SSHIFT;
-    return b < (uint32_t)SBIN - 1u ? b : (uint32_t)SBIN - 1u;
+    const uint32_t c0 = (w0 - SKEY0) >> SCSHIFT;
+    const uint32_t d = key < SKEY0 ? 0u : key - SKEY0, c = d >> SCSHIFT;
+    const uint32_t f = key - w0;                       // (wraps below the window)
+    if (f < (SWIN << 23)) return c0 + (f >> SFSHIFT);
+    const uint32_t cc = c < SCOARSE - 1u ? c : SCOARSE - 1u;
+    return cc < c0 ? cc : cc + SFINE - SLESS;
 }
-__device__ __forceinline__ uint32_t sample_bin_first(uint32_t b) { return b == 0u ? 0u : SKEY0 + (b << SSHIFT); }
-__device__ __forceinline__ uint32_t sample_bin_end(uint32_t b)
+// first key of bin b; the next bin's is one past its last key
+__device__ __forceinline__ uint32_t sample_bin_first(uint32_t b, uint32_t w0)
 {
-    return b == (uint32_t)SBIN - 1u ? KEY_END : SKEY0 + ((b + 1u) << SSHIFT);
+    const uint32_t c0 = (w0 - SKEY0) >> SCSHIFT;
+    if (b >= SUSED) return KEY_END;
+    if (b >= c0 && b < c0 + SFINE) return w0 + ((b - c0) << SFSHIFT);
+    const uint32_t c = b < c0 ? b : b - (SFINE - SLESS);
+    return c == 0u ? 0u : SKEY0 + (c << SCSHIFT);
 }
+__device__ __forceinline__ uint32_t sample_bin_end(uint32_t b, uint32_t w0) { return sample_bin_first(b + 1u, w0); }
 
 // The bracket histogram of a CF whose bracket is [lo, hi): the shift s is the smallest with which bins 0 .. OVF - 1
 // reach hi, and top is the first key past them (KEY_END if they reach past the largest key).
@@ -733,7 +756,7 @@ __device__ __forceinline__ void small_segment(const Params& p, int t, SmallShare
 
 // ---------------------------------------------------------------------------------------------
 // K0a: sample acc = residual + grad at stratified positions; each workgroup histograms its samples in
-// LDS (SBIN bins of 2^17 keys, see sample_bin) and stores the counts as 16-bit numbers, and the
+// LDS (SBIN bins, see sample_bin) and stores the counts as 16-bit numbers, and the
 // counts per group of SBIN / SGRP bins beside them.  The same launch clears what the later kernels
 // add to (every workgroup a share of its segment's histograms and counters); a call whose brackets
 // do not come from a sample launches it for that alone.
@@ -767,7 +790,15 @@ __global__ __launch_bounds__(256) void sample_kernel(Params p)
     const uint64_t nt = (uint64_t)(seg_end(p, t) - s0);
 #pragma unroll
     for (int q = 0; q < SBIN / 256; ++q) h[q * 256 + tid] = 0;
-    __syncthreads();
+    // The window: every block of the segment looks at the same 256 elements, spread evenly, and takes the exponent of the
+    // largest (an infinite or NaN one does not count).  Their loads are issued before the sample's and arrive with them.
+    const uint64_t wpos = (nt * (2u * tid + 1u)) >> 9;   // (below nt)
+    float wg = 0.0f, wr = 0.0f;
+    if (p.fixed_window == 0u) {
+        wg = p.grad[s0 + (int64_t)wpos];
+        if (!p.single) wr = p.res[s0 + (int64_t)wpos];
+    }
+    __shared__ uint32_t wexp[4];
     // A group is 4 consecutive elements: sample i of the segment is element i % 4 of group i / 4.  A sampled
     // segment (S a multiple of SAMPLE_BLOCK, nt > 2 S) is cut into S / 16 strata of at least 32 elements, and the
     // four groups of a stratum are the 16 elements of one line at a hashed place inside it: a sample costs a
@@ -815,10 +846,28 @@ __global__ __launch_bounds__(256) void sample_kernel(Params p)
             rv[q] = p.res[s0 + (int64_t)pos];
         }
     }
+    uint32_t w0 = p.fixed_window;
+    if (w0 != 0u) {
+        __syncthreads();   // (the histogram is cleared)
+    } else {
+        const uint32_t wk = key_of(p.single ? wg : wr + wg);
+        const double m = wave_max(wk < 0x7F800000u ? (double)(wk >> 23) : 0.0);
+        if ((tid & 63) == 0) wexp[tid >> 6] = (uint32_t)m;
+        __syncthreads();   // (... and the histogram is cleared)
+        uint32_t e = 0;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) e = wexp[w] > e ? wexp[w] : e;
+        // exponents e + SWIN_ABOVE + 1 - SWIN .. e + SWIN_ABOVE, inside the octaves covered
+        // (not the lowest: the first bin holds the keys below them, too)
+        uint32_t b0 = e + SWIN_ABOVE + 1u > SWIN + SEXP0 + 1u ? e + SWIN_ABOVE + 1u - SWIN : SEXP0 + 1u;
+        b0 = b0 > SEXP0 + SOCT - SWIN ? SEXP0 + SOCT - SWIN : b0;
+        w0 = b0 << 23;
+        if (lb == 0 && tid == 0) p.xq[(size_t)t * p.n_cf * NBIN + XQ_WIN] = w0;
+    }
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
         const float acc = p.single ? gv[q] : rv[q] + gv[q];
-        if (live[q]) atomicAdd(&h[sample_bin(key_of(acc))], 1u);
+        if (live[q]) atomicAdd(&h[sample_bin(key_of(acc), w0)], 1u);
     }
     __syncthreads();
     // thread i stores bins 16i .. 16i+15, two counts per word (a count is at most R * SAMPLE_BLOCK < 2^16)
@@ -947,6 +996,7 @@ __global__ __launch_bounds__(P * 1024 / G) __attribute__((amdgpu_waves_per_eu(SM
     // samples in the groups of bins above this workgroup's, and in all
     // (the group counts of up to two blocks per thread are fetched first and added up after the histograms, so that
     // both sets of loads are in flight together)
+    const uint32_t w0 = p.fixed_window ? p.fixed_window : p.xq[(size_t)t * p.n_cf * NBIN + XQ_WIN];
     uint32_t g_above = 0, g_total = 0;
     uint4 ga[2][2];
     static_assert(G == 1 || 2 * (1024 / G) >= 2 * DENSE_BLOCKS, "two blocks' group counts per thread cover a flat sample");
@@ -1026,12 +1076,12 @@ __global__ __launch_bounds__(P * 1024 / G) __attribute__((amdgpu_waves_per_eu(SM
             const uint32_t c = hh[q];
             const uint32_t bin = 4u * (uint32_t)(y * T + ot) + (uint32_t)q;
             // lower edge of the bin of the r_lo-th sample from the top, upper edge of the bin of the r_hi-th
-            if (above < r_lo && above + c >= r_lo) p.bnd_lo[id] = sample_bin_first(bin);
-            if (above < r_hi && above + c >= r_hi) p.bnd_hi[id] = sample_bin_end(bin);
+            if (above < r_lo && above + c >= r_lo) p.bnd_lo[id] = sample_bin_first(bin, w0);
+            if (above < r_hi && above + c >= r_hi) p.bnd_hi[id] = sample_bin_end(bin, w0);
             if (above < r_mid && above + c >= r_mid) {
                 // the r_mid-th sample from the top is the (r_mid - above)-th of the c in this bin: that far down from
                 // the bin's upper edge, as if the bin's samples were spread evenly over its keys
-                const uint32_t first = sample_bin_first(bin), end = sample_bin_end(bin);
+                const uint32_t first = sample_bin_first(bin, w0), end = sample_bin_end(bin, w0);
                 // (an estimate: single precision will do, and keeps a 64-bit division out of this kernel)
                 const uint32_t down = (uint32_t)((float)(end - first) * ((float)(r_mid - above) / (float)c));
                 p.bnd_mid[id] = down >= end - first ? first : end - down;
@@ -2724,7 +2774,7 @@ __device__ __forceinline__ void emit_listed(const Params& p, EmitCtx& x, int32_t
             ov[o] = val;
             if (!single) {
                 oi[o] = idx;
-                if (x.zero && key < x.pz) p.res[idx] = 0.0f;
+                if (x.zero && key < x.pz) __builtin_nontemporal_store(0.0f, &p.res[idx]);
             } else {
                 const int mi = p.map_idx[idx];  // position in the message -> index in the gradient
                 oi[o] = mi;
@@ -2862,7 +2912,12 @@ __device__ __forceinline__ void emit_tile(const Params& p, int t, uint32_t u, Em
         float va[2 * SUB];
         int32_t ia[2 * SUB];
 #pragma unroll
-        for (int r = 0; r < 2 * SUB; ++r) { va[r] = cv[(r / 2) * TS + (r & 1) * 64 + lane]; ia[r] = ci[(r / 2) * TS + (r & 1) * 64 + lane]; }
+        for (int r = 0; r < 2 * SUB; ++r) {
+            // (Random-k at CF 10: 151 -> 147 us with non-temporal loads; in the plain form they cost a 25 MB bucket 2 us)
+            const size_t at = (r / 2) * TS + (r & 1) * 64 + lane;
+            va[r] = GEN ? __builtin_nontemporal_load(&cv[at]) : cv[at];
+            ia[r] = GEN ? __builtin_nontemporal_load(&ci[at]) : ci[at];
+        }
 #pragma unroll 1
         for (int j = 0; j < SUB; ++j) {
             uint32_t c = 0;
@@ -2888,7 +2943,7 @@ __device__ __forceinline__ void emit_tile(const Params& p, int t, uint32_t u, Em
     {
         const int64_t sn = tile0 + (int64_t)(__ffs((int)dmask) - 1) * TS;
 #pragma unroll
-        for (int q = 0; q < ROWS; ++q) nxt[q] = *(const v4f*)(p.acc + sn + q * ROW + 4 * lane);
+        for (int q = 0; q < ROWS; ++q) nxt[q] = ld_stream((const v4f*)(p.acc + sn + q * ROW + 4 * lane));
     }
     // the first two rounds of the next sub-tile's list, loaded while this one is worked on, whatever they hold
     float vnx[2];
@@ -2929,7 +2984,7 @@ __device__ __forceinline__ void emit_tile(const Params& p, int t, uint32_t u, Em
             if (later != 0u) {
                 const int64_t sn = tile0 + (int64_t)(__ffs((int)later) - 1) * TS;
 #pragma unroll
-                for (int q = 0; q < ROWS; ++q) nxt[q] = *(const v4f*)(p.acc + sn + q * ROW + 4 * lane);
+                for (int q = 0; q < ROWS; ++q) nxt[q] = ld_stream((const v4f*)(p.acc + sn + q * ROW + 4 * lane));
             }
         }
 #pragma unroll 1
@@ -2983,7 +3038,7 @@ __device__ __forceinline__ void emit_tile(const Params& p, int t, uint32_t u, Em
                 v4f r;
                 r.x = sel[0] ? 0.0f : a[0]; r.y = sel[1] ? 0.0f : a[1];
                 r.z = sel[2] ? 0.0f : a[2]; r.w = sel[3] ? 0.0f : a[3];
-                *(v4f*)(p.res + g) = r;
+                st_stream(r, (v4f*)(p.res + g));   // (non-temporal, as the loads: VGG16 shape at CF 10 408 -> 398 us)
             }
             staged += tot;
             x.erun += ties_row;
@@ -4094,6 +4149,7 @@ static int compress_impl(const float* grad, float* residual, int64_t n, const do
     if (ns == 1) {
         for (int j = 0; j < n_cf; ++j) p.flat_k[j] = (uint32_t)gravac_topk_count(n, cf_list[j]);
         p.flat_samples = sample_count((uint64_t)n, cf_min, cf_max, true);
+        p.fixed_window = n < SWIN_SMALL ? SWIN_FIXED : 0u;
         p.n_tiles = (uint32_t)((n + TW - 1) / TW);
         max_seg_tiles = p.n_tiles;
         emit_wgs = (p.n_tiles + EW - 1) / EW;

@@ -154,3 +154,18 @@ def test_decompression_of_gapped_messages(W, n, spread):
         d = torch.from_numpy(base.copy()).cuda()
         binding.gravac_decompress_update(i, v, counts, -0.0125, d, workspace=ws)
         assert np.array_equal(d.cpu().numpy().view(np.uint32), ref.view(np.uint32)), f"workspace {ws is not None}"
+
+
+@pytest.mark.parametrize("n", [200_003, (1 << 19) - 1, 1 << 19, 1_500_001])
+@pytest.mark.parametrize("scale", [1e-30, 1e-12, 1e-5, 1.0, 3e4, 1e8])
+def test_sample_window(n, scale):
+    """Magnitudes inside, below and above the finely binned octaves of the sample, whether the window is found from the data
+    or given; thresholds far below the largest entries, and infinities among the entries it is found from."""
+    rng = np.random.Generator(np.random.PCG64(n))
+    g = (rng.standard_normal(n) * scale).astype(np.float32)
+    z = np.zeros(n, np.float32)
+    check(g, z, [10.0, 300.0], 0, what="normal")
+    wide = (np.exp(rng.uniform(-30.0, 0.0, n)) * scale).astype(np.float32)
+    check(wide, z, [1.5, 10.0], 0, what="thirty octaves and a low CF")
+    g[rng.random(n) < 0.02] = np.inf
+    check(g, z, [10.0], 0, what="infinities")
