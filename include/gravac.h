@@ -20,7 +20,9 @@
  *   - Every call is asynchronous on `stream` (a hipStream_t passed as void*; NULL = the null
  *     stream).  Outputs are valid once the stream has been synchronised.
  *   - The library never allocates device memory: scratch space comes from the caller's
- *     `workspace`.  Calls that overlap in time must use different workspaces.
+ *     `workspace`.  Calls that overlap in time must use different workspaces.  (Two that share one give
+ *     unspecified results.  Workgroups of the exact route wait for each other over counters in the workspace;
+ *     where another call has cleared them the wait ends after a minute or two, with the internal-error flag set.)
  *   - The library keeps no state between calls, with one exception: layerwise calls pass their segment tables
  *     through a ring of up to eight pinned host staging buffers that the library allocates on first use
  *     (hipHostMalloc, grown when a larger table arrives, kept until the process ends) and that are shared by all
@@ -71,6 +73,10 @@ extern "C" {
                                          (Alg. 1): compress at theta_min with this flag, derive the candidate CF's message
                                          from that message (gravac_recompress with residual == NULL), then remove the
                                          message that is sent with gravac_commit.  Not accepted by the other calls. */
+#define GRAVAC_FLAG_STALL_FALLBACK 8u /* a testing aid, accepted only together with GRAVAC_FLAG_FORCE_FALLBACK: the
+                                         workgroups of the exact route wait for one more than there are and give up after a
+                                         few polls, so that the call ends with the internal-error flag of
+                                         gravac_read_status set and with unspecified outputs */
 
 /*
  * Number of pairs a call will emit for a tensor of n elements at compression factor cf:
@@ -115,7 +121,7 @@ int gravac_workspace_bytes(int64_t n, int n_cf, int n_seg, size_t* bytes_out);
  *                 |acc| of the smallest selected entry }.
  *   workspace   device, 256-byte aligned, at least gravac_workspace_bytes(n, n_cf, n_seg) bytes.
  *               Contents on entry are irrelevant; contents on exit are unspecified.
- *   flags       0, or GRAVAC_FLAG_FORCE_FALLBACK and / or GRAVAC_FLAG_NO_COMMIT.
+ *   flags       0, or GRAVAC_FLAG_FORCE_FALLBACK and / or GRAVAC_FLAG_NO_COMMIT (tests: GRAVAC_FLAG_STALL_FALLBACK).
  */
 int gravac_compress(const float* grad, float* residual, int64_t n,
                     const double* cf_list, int n_cf, int commit,
@@ -299,9 +305,9 @@ int gravac_decompress_accumulate_static(const int32_t* idx, const float* val,
  * Diagnostics of the last gravac_compress call that used `workspace`: synchronises `stream`
  * and copies 8 int32 to the host pointer out8:
  *   [0] 1 if any segment took the exact-histogram fallback, [1] number of such segments,
- *   [2] internal-error flag (must be 0), [3] number of segments, [4] how many of [1] needed no second
- *   pass over the gradient (the located histogram bin was too coarse and too full and was binned again from the
- *   lists the pass had collected), [5..7] reserved.
+ *   [2] internal-error flag (must be 0; else the call's outputs and residual are not to be used), [3] number of
+ *   segments, [4] how many of [1] needed no second pass over the gradient (the located histogram bin was too coarse
+ *   and too full and was binned again from the lists the pass had collected), [5..7] reserved.
  */
 int gravac_read_status(const void* workspace, void* stream, int32_t* out8);
 

@@ -26,6 +26,7 @@ STATIC_SCRATCH_BYTES = 4 << 20
 MAX_CF = 8
 FLAG_FORCE_FALLBACK = 1
 FLAG_NO_COMMIT = 2
+FLAG_STALL_FALLBACK = 8
 
 EXPORTS = (
     "gravac_topk_count", "gravac_workspace_bytes", "gravac_compress", "gravac_compress_profiled", "gravac_randomk_compress", "gravac_threshold_compress", "gravac_recompress", "gravac_commit",

@@ -106,6 +106,9 @@ constexpr double ZMARGIN = 5.0;     // safety margin of the sampled rank, in sta
 constexpr uint32_t CTILES = 64;     // tiles per partial sum of the tiles' counts (csum)
 constexpr int XQ_WORDS = 8;         // a segment's work queue in the plan step: chunks claimed, then chunks done per phase
 constexpr int XQ_WIN = XQ_WORDS;    // ... and behind it the first key of its sample histogram's window
+constexpr uint32_t WAIT_POLLS = 1u << 26;  // polls after which a workgroup of the plan step gives up on the others: at least
+                                           // half a minute, where the longest wait of a call is milliseconds
+constexpr uint32_t WAIT_POLLS_TEST = 256;  // ... and under GRAVAC_FLAG_STALL_FALLBACK
 constexpr uint32_t NONE = 0xFFFFFFFFu;
 constexpr uint32_t KEY_END = 0x80000000u;  // one past the largest key
 
@@ -190,6 +193,8 @@ struct Params {
                              // list of their own everywhere; 0: a sub-tile's candidate list, where it has one, holds them all
     uint32_t bounds_from;    // BOUNDS_*
     uint32_t fixed_key;      // BOUNDS_FIXED: the key of the caller's threshold; entries with key >= fixed_key are kept
+    uint32_t wait_polls;     // polls after which a workgroup of the plan step stops waiting for the others
+    uint32_t wait_extra;     // arrivals it waits for beyond those that will come: 0 (1 under the testing flag)
     uint32_t rk_s0, rk_s1;   // Random-k: the two 31-bit keys (from the seed)
     int64_t n;
     int n_seg;  // >= 1
@@ -1532,7 +1537,7 @@ __device__ __forceinline__ BinPlan plan_bin(uint32_t lo, uint32_t s, uint32_t b,
 // the same workgroup in the next, and only histograms, made of device-wide atomics, pass between workgroups.  A
 // workgroup waits for the others only when every chunk has been claimed, that is, for workgroups that are running and do
 // not wait for anybody before they have finished the phase: the wait ends whatever else shares the chip and however few
-// of this launch's workgroups are resident.
+// of this launch's workgroups are resident.  (Two calls at a time on one workspace break that; the wait is bounded for them.)
 //   FAIL_FULL: phase 0 puts back what the pass replaced by +0 in the residual and histograms key >> 20 of all elements;
 //              phase 1 collects the lists again with the located 2^20 keys as bracket, in bins of 2^9 keys.
 //   FAIL_NARROW, FAIL_TIES: the located bin is cut into up to NBIN parts and counted again from the bracket lists.
@@ -1557,7 +1562,7 @@ struct PlanShared {
     uint32_t cut[MAXCF];                        // 1: it is being cut again, into parts of 2^s2 keys
     uint32_t s2[MAXCF];
     uint32_t pz;                                // SegState::pz
-    uint32_t got, n_own, leader;
+    uint32_t got, n_own, leader, arrived;
     uint32_t own[PLAN_CHUNKS];                  // the chunks this workgroup has claimed
     // Gradient magnitudes crowd into a few exponents, so most lanes of a wavefront hit the same few bins and LDS atomics
     // on one copy serialise 64-fold; CSUB copies cut that to 64 / CSUB.  (a row is one word longer than the histogram,
@@ -1640,18 +1645,27 @@ __device__ __forceinline__ void plan_search(PlanShared& sh, int n_cf, int tid, S
 static_assert(4 * 8 * 257 <= CSUB * (NBIN + 1), "the teams' counts fit into the coarse counts' LDS");
 
 // Everything this workgroup has written is visible to the device; then all workgroups with chunks of the segment have
-// got here, and what they have written is visible to this one.
-__device__ __forceinline__ void plan_barrier(PlanShared& sh, uint32_t* done, uint32_t n_chunks, int tid)
+// got here, and what they have written is visible to this one.  False (to every thread): they have not, after as many
+// polls as the call allows.  That takes a second call on the same workspace, which clears this one's counters or claims
+// its chunks; the wait must not hold the GPU for ever then.
+__device__ __forceinline__ bool plan_barrier(const Params& p, PlanShared& sh, uint32_t* done, uint32_t n_chunks, int tid)
 {
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");   // every wavefront's stores and atomics are done ...
     __syncthreads();
     if (tid == 0) {
         __threadfence();                                           // ... and leave this XCD's L2
         atomicAdd(done, sh.n_own);
-        while (__hip_atomic_load(done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < n_chunks) __builtin_amdgcn_s_sleep(4);
+        uint32_t polls = 0;
+        while (polls < p.wait_polls &&
+               __hip_atomic_load(done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < n_chunks + p.wait_extra) {
+            __builtin_amdgcn_s_sleep(4);
+            ++polls;
+        }
+        sh.arrived = polls < p.wait_polls ? 1u : 0u;
     }
     __syncthreads();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    return sh.arrived != 0u;
 }
 
 // One tile's entries of the bracket lists into the histograms (first copy of CF 0 at hist) of the CFs that are cut again.
@@ -1737,7 +1751,7 @@ __global__ __launch_bounds__(PLAN_T) void plan_kernel(Params p)
         const uint32_t x = (b == NONE || b == OVF) ? FAIL_FULL : (sh.s[j] > 11u ? FAIL_NARROW : FAIL_TIES);
         kind = x > kind ? x : kind;
     }
-    bool writes = first_block;   // this workgroup records the plan
+    bool writes = first_block, counts = true;   // this workgroup records the plan, and counts the segment
     if (kind != FAIL_NONE) {
         // ---- exact routes
         uint32_t* xq = p.xq + (size_t)t * p.n_cf * NBIN;
@@ -1755,7 +1769,7 @@ __global__ __launch_bounds__(PLAN_T) void plan_kernel(Params p)
             for (uint32_t i = tid; i < CSUB * (NBIN + 1); i += PLAN_T) (&sh.lh[0][0])[i] = 0;
         uint32_t next = tid == 0 ? atomicAdd(&xq[0], 1u) : 0u;
         for (;;) {
-            if (tid == 0) sh.got = next;
+            if (tid == 0) sh.got = sh.n_own < PLAN_CHUNKS ? next : NONE;   // (more are not to be had, unless the counter was cleared)
             __syncthreads();
             const uint32_t at = sh.got;
             __syncthreads();
@@ -1806,8 +1820,8 @@ __global__ __launch_bounds__(PLAN_T) void plan_kernel(Params p)
                 if (v) atomicAdd(&gh[bin_word(i)], v);
             }
         }
-        plan_barrier(sh, &xq[1], n_chunks, tid);
-        if (full) {
+        bool arrived = plan_barrier(p, sh, &xq[1], n_chunks, tid);
+        if (full && arrived) {
             // the coarse (key >> 20) bin of every CF's k-th largest is the new bracket
             plan_search(sh, p.n_cf, tid, [&](int j, const uint32_t*& hist, uint32_t& nc, uint32_t& stride, const uint32_t*& extra, uint32_t& want) {
                 hist = p.coarse + (size_t)t * NBIN; nc = 1; stride = NBIN; extra = nullptr; want = sh.k[j];
@@ -1819,14 +1833,14 @@ __global__ __launch_bounds__(PLAN_T) void plan_kernel(Params p)
                 sh.above[tid] = sh.fa[tid]; sh.base[tid] = b << 20; sh.bs[tid] = 20; sh.s2[tid] = XSHIFT; sh.cut[tid] = 1;
                 sh.xb.lo[tid] = b << 20; sh.xb.sh[tid] = XSHIFT; sh.xb.top[tid] = (b + 1u) << 20;
             }
-        } else if (tid < p.n_cf) {
+        } else if (!full && tid < p.n_cf) {
             const bool x = sh.mode[tid] == MODE_FAIL;
             sh.cut[tid] = x ? 1u : 0u;
             sh.s2[tid] = sh.bs[tid] > 11u ? sh.bs[tid] - 11u : 0u;
         }
         if (tid == 0) sh.xb.hist = xhist;
         __syncthreads();
-        for (int phase = 1; phase <= 2; ++phase) {
+        for (int phase = 1; phase <= 2 && arrived; ++phase) {
             uint32_t* hist = xhist + (phase - 1) * NBIN;
             // the workgroup's chunks, dealt over its wavefronts by the sub-tile or by the tile
             const uint32_t per_chunk = full && phase == 1 ? per * SUB : per, all = sh.n_own * per_chunk;
@@ -1840,7 +1854,8 @@ __global__ __launch_bounds__(PLAN_T) void plan_kernel(Params p)
                     if (u < u1) plan_recount(p, sh, u, hist, copies, lane);
                 }
             }
-            plan_barrier(sh, &xq[1 + phase], n_chunks, tid);
+            arrived = plan_barrier(p, sh, &xq[1 + phase], n_chunks, tid);
+            if (!arrived) break;
             // the part that holds the k-th largest
             plan_search(sh, p.n_cf, tid, [&](int j, const uint32_t*& h, uint32_t& nc, uint32_t& stride, const uint32_t*& extra, uint32_t& want) {
                 h = hist + (size_t)j * copies * LCAP; nc = copies; stride = LCAP; extra = nullptr; want = sh.k[j] - sh.above[j];
@@ -1863,6 +1878,13 @@ __global__ __launch_bounds__(PLAN_T) void plan_kernel(Params p)
             for (int j = 0; j < p.n_cf; ++j) again = again || sh.cut[j] != 0u;
             if (!again) break;
         }
+        if (!arrived) {
+            // whichever workgroup gives up records a plan that selects nothing inside the brackets: the later steps stay
+            // inside their buffers, and the call's internal-error flag says that its results are not to be used
+            counts = writes;
+            writes = true;
+            if (tid < p.n_cf) sh.mode[tid] = MODE_FAIL;
+        }
     }
     if (!writes) return;
     if (tid < p.n_cf) {
@@ -1872,7 +1894,7 @@ __global__ __launch_bounds__(PLAN_T) void plan_kernel(Params p)
         st.base = 0; st.span = 0; st.above = 0; st.c = 0; st.tau = 0; st.need = 0; st.cnt_gt = 0; st.top = sh.top[j];
         st.pad[0] = st.pad[1] = st.pad[2] = st.pad[3] = 0;
         if (st.mode == MODE_FAIL) {
-            p.status->error = 1;   // the exact routes cannot fail
+            p.status->error = 1;   // the exact routes cannot fail, except by giving up a wait
         } else {
             st.base = sh.base[j]; st.span = (1u << sh.bs[j]) - 1u; st.above = sh.above[j]; st.c = sh.c[j];
             if (st.mode == MODE_RESOLVED) { st.tau = st.base; st.cnt_gt = st.above; st.need = st.k - st.above; }
@@ -1887,7 +1909,7 @@ __global__ __launch_bounds__(PLAN_T) void plan_kernel(Params p)
         sg.lo_min = lo_min; sg.fail = kind; sg.lo_c = sh.lo[p.commit];
         sg.pz = kind == FAIL_FULL ? NONE : sh.pz;
         p.seg[t] = sg;
-        if (kind >= FAIL_NARROW) {
+        if (kind >= FAIL_NARROW && counts) {
             p.status->any_fail = 1;
             atomicAdd(&p.status->n_fail, 1);
             if (kind == FAIL_NARROW) atomicAdd(&p.status->n_narrow, 1);
@@ -4053,7 +4075,9 @@ static int compress_impl(const float* grad, float* residual, int64_t n, const do
     if ((!out_idx || !out_val) && !(fixed && out_capacity == 0)) return GRAVAC_ERR_INVALID_ARG;
     if (n <= 0 || n > 2147483647LL || n_cf < 1 || n_cf > MAXCF || commit < 0 || commit >= n_cf) return GRAVAC_ERR_INVALID_ARG;
     if (((uintptr_t)grad & 3) || ((uintptr_t)residual & 3) || ((uintptr_t)map_idx & 3)) return GRAVAC_ERR_INVALID_ARG;
-    if (flags & ~(unsigned)(GRAVAC_FLAG_FORCE_FALLBACK | GRAVAC_FLAG_NO_COMMIT)) return GRAVAC_ERR_INVALID_ARG;
+    if (flags & ~(unsigned)(GRAVAC_FLAG_FORCE_FALLBACK | GRAVAC_FLAG_NO_COMMIT | GRAVAC_FLAG_STALL_FALLBACK)) return GRAVAC_ERR_INVALID_ARG;
+    const bool stall = (flags & GRAVAC_FLAG_STALL_FALLBACK) != 0;
+    if (stall && !(flags & GRAVAC_FLAG_FORCE_FALLBACK)) return GRAVAC_ERR_INVALID_ARG;
     if ((flags & GRAVAC_FLAG_NO_COMMIT) && (single || fixed)) return GRAVAC_ERR_INVALID_ARG;
     if (n_seg < 0 || (n_seg > 0 && !seg_offsets) || (int64_t)n_seg > n) return GRAVAC_ERR_INVALID_ARG;
     if (ev && (!ev->call_begin || !ev->pass_begin || !ev->pass_end || !ev->call_end)) return GRAVAC_ERR_INVALID_ARG;
@@ -4086,6 +4110,8 @@ static int compress_impl(const float* grad, float* residual, int64_t n, const do
     p.split = (cf_list[commit] > cf_min || random) ? 1 : 0;
     p.no_commit = (flags & GRAVAC_FLAG_NO_COMMIT) ? 1 : 0;
     p.bounds_from = (flags & GRAVAC_FLAG_FORCE_FALLBACK) ? BOUNDS_FORCED : (random ? BOUNDS_RANDOM : BOUNDS_SAMPLED);
+    p.wait_polls = stall ? WAIT_POLLS_TEST : WAIT_POLLS;
+    p.wait_extra = stall ? 1u : 0u;
     if (fixed) {
         p.bounds_from = BOUNDS_FIXED;
         std::memcpy(&p.fixed_key, tau, sizeof(uint32_t));   // positive and finite: the bit pattern is the key

@@ -6,7 +6,7 @@ import torch
 
 from oracle import oracle
 from paper_2305_12201_amd import binding, workloads
-from tests.gpu_util import check
+from tests.gpu_util import assert_same, check, gpu_compress, oracle_compress
 from tests.test_gpu_randomk import check as check_randomk
 
 pytestmark = pytest.mark.gpu
@@ -83,6 +83,25 @@ def test_some_tensors_take_the_exact_route():
     for flags in (0, FB):
         check(g, r, [2.5], 0, off, flags=flags, what="layerwise, one CF")
         check(g, r, [2.5, 10.0], 1, off, flags=flags, what="layerwise, two CFs")
+
+
+def test_exact_route_gives_up_a_wait_that_cannot_end():
+    """The workgroups of the exact route wait for each other.  With an arrival that never comes every kernel still ends and
+    the call reports an internal error; the next call on the same workspace is right again."""
+    stall = FB | binding.FLAG_STALL_FALLBACK
+    n = 600_001
+    g, z = workloads.normal_gradient(n, 1e-3, seed=1), np.zeros(n, np.float32)
+    off = workloads.offsets_of([200_000, 5, 8_193, n - 208_198])
+    for cfs, commit, seg in (([10.0], 0, None), ([10.0, 100.0, 1000.0], 2, None), ([10.0, 100.0], 0, off)):
+        comp = binding.Compressor(n, cfs, commit, seg)
+        for run in (lambda r, f: comp(torch.from_numpy(g).cuda(), r, flags=f), lambda r, f: comp.randomk(torch.from_numpy(g).cuda(), r, seed=7, flags=f)):
+            run(torch.zeros(n, device="cuda"), stall)
+            assert comp.status()["internal_error"] == 1
+        got = gpu_compress(g, z, cfs, commit, seg, flags=FB, comp=comp)
+        assert got[4]["internal_error"] == 0
+        assert_same(got, oracle_compress(g, z, cfs, commit, seg), "the call after")
+    with pytest.raises(binding.GravacError):
+        comp(torch.from_numpy(g).cuda(), torch.zeros(n, device="cuda"), flags=binding.FLAG_STALL_FALLBACK)
 
 
 def _coarse(x, bits):
