@@ -3287,6 +3287,49 @@ __device__ __forceinline__ void lower_bounds_32(const int32_t* idx, int64_t a, i
     h = a1;
 }
 
+// How whole tiles are moved: six of their eight rows of 1024 floats are read with non-temporal hints and seven are written
+// with them; in a buffer of up to PLAIN_BYTES none is written with them.  Microseconds, eight messages of CF 100 unless
+// said, with a workspace; rows hinted (read, written):  0, 0    8, 0    8, 8    8, 6    6, 7
+//   178 MB, three buffers in turn                        85.5    82.4    73.6    70.7    70.2
+//   178 MB, the same buffer again                        67.2    68.5    73.4    69.1    67.9
+//   178 MB, the buffer just cleared                      69.4    69.8    81.8*   68.6    68.6
+//   178 MB, caches flushed                               93.5    90.8    83.3    85.3    86.7
+//   178 MB, caches flushed, the buffer cleared           79.1    72.0    92.4    79.3    72.4
+//   553 MB                                              255     246     225     232     198
+//   80 MB, the same buffer again                         33.7    34.2    36.0    35.9    35.9
+//   VGG16 shape at CF 1000, 59 of 553 MB, in the step    31.6    31.6    34.4    33.9    33.8
+//   ... the step with it, one buffer / three in turn    344/360 346/360 348/348 348/350 348/349
+// (*: 68.3 until something else has filled the 256 MB last-level cache once.)  What the hints gain is the cache's evictions
+// of dirty lines, which a later kernel pays for unless the same lines are written again soon; with every row hinted a
+// buffer that would fit is never taken in again, not even by a clear.  In the last two rows the plain stores only move the
+// time from the decompression to the pass over the gradient, as soon as anything else gets into the cache.
+// Without a workspace all rows are hinted, read and written, or in such a small buffer read (178 MB, three in turn, the
+// same again, cleared, flushed: 0, 0: 87, 76, 79, 108; 8, 0: 83, 76, 79, 98; 6, 7: 79, 82, 77, 100; 8, 8: 78, 82, 77, 95).
+constexpr int64_t PLAIN_BYTES = 96ll << 20;
+
+template <int NT>  // rows read with hints
+__device__ __forceinline__ void load_tile(const float* from, float* acc, int tid)
+{
+    // (all loads of a thread in flight together)
+    v4f tv[DTILE / 1024];
+#pragma unroll
+    for (int r = 0; r < NT; ++r) tv[r] = ld_stream((const v4f*)(from + r * 1024 + tid * 4));
+#pragma unroll
+    for (int r = NT; r < DTILE / 1024; ++r) tv[r] = *(const v4f*)(from + r * 1024 + tid * 4);
+#pragma unroll
+    for (int r = 0; r < DTILE / 1024; ++r) *(v4f*)(acc + r * 1024 + tid * 4) = tv[r];
+}
+
+template <int NT>  // rows written with hints
+__device__ __forceinline__ void store_tile(const float* acc, float* to, int tid)
+{
+#pragma unroll
+    for (int r = 0; r < NT; ++r) st_stream(*(const v4f*)(acc + r * 1024 + tid * 4), (v4f*)(to + r * 1024 + tid * 4));
+#pragma unroll
+    for (int r = NT; r < DTILE / 1024; ++r) *(v4f*)(to + r * 1024 + tid * 4) = *(const v4f*)(acc + r * 1024 + tid * 4);
+}
+
+template <int NT>  // rows of a whole tile written with non-temporal hints
 __global__ __launch_bounds__(256) void decompress_kernel(const int32_t* __restrict__ idx, const float* __restrict__ val,
                                                          WorkerOffsets wo, int W, int64_t n, float* dense, float alpha)
 {
@@ -3381,12 +3424,7 @@ __global__ __launch_bounds__(256) void decompress_kernel(const int32_t* __restri
             }
             if (!loaded) {
                 if (vec && len == DTILE) {
-                    // a whole tile: all eight loads of a thread in flight together
-                    v4f tv[DTILE / 1024];
-#pragma unroll
-                    for (int r = 0; r < DTILE / 1024; ++r) tv[r] = ld_stream((const v4f*)(dense + base + r * 1024 + tid * 4));
-#pragma unroll
-                    for (int r = 0; r < DTILE / 1024; ++r) *(v4f*)(acc + r * 1024 + tid * 4) = tv[r];
+                    load_tile<DTILE / 1024>(dense + base, acc, tid);
                 } else {
                     for (int i = tid * 4; i < len; i += 256 * 4) {
                         if (vec && i + 4 <= len) {
@@ -3443,9 +3481,7 @@ __global__ __launch_bounds__(256) void decompress_kernel(const int32_t* __restri
         if (loaded) {
             __syncthreads();
             if (vec && len == DTILE) {
-#pragma unroll
-                for (int r = 0; r < DTILE / 1024; ++r)
-                    st_stream(*(const v4f*)(acc + r * 1024 + tid * 4), (v4f*)(dense + base + r * 1024 + tid * 4));
+                store_tile<NT>(acc, dense + base, tid);
             } else {
                 for (int i = tid * 4; i < len; i += 256 * 4) {
                     if (vec && i + 4 <= len) {
@@ -3560,14 +3596,12 @@ __device__ __forceinline__ void tile_pairs(const int32_t* __restrict__ idx, cons
     }
 }
 
-// (Whole tiles are read and written with non-temporal hints, as in the pass over the gradient: eight messages of CF 100 on
-// the ResNet101 shape, all tiles whole, 385 MB, 76.6 -> 67.0 us.  Moving only the named 64-byte lines of a tile, seven in
-// ten there, was no faster: 128 bytes is what the memory moves.  Hints on the loads or the stores alone: 81 and 84 us for
-// the call against 73 with both and 88 without; after a clear of the buffer, clear and call together 94.2 -> 89.5 us; only
-// a buffer that the call before has left in the last-level cache loses, 70.6 -> 73.5 us.)
+// (Moving only the named 64-byte lines of a whole tile, seven in ten with eight messages of CF 100, was no faster: 128
+// bytes is what the memory moves.)
 // A workgroup takes the tiles blockIdx.x, blockIdx.x + gridDim.x, ...  It first fetches, for a chunk of its
 // tiles at once, every worker's boundaries (one round of independent loads instead of one dependent round per
 // tile) and then walks over the chunk's tiles; a tile no message has a pair in costs no further memory access.
+template <int NT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) void decompress_ws_kernel(const int32_t* __restrict__ idx, const float* __restrict__ val,
                                                             WorkerOffsets wo, int W, int64_t n, float* dense,
                                                             const uint32_t* __restrict__ bounds, float alpha)
@@ -3695,12 +3729,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
                 if (total == 0) continue;  // no message of this group touches the tile
                 if (!loaded) {
                     if (vec && len == DTILE) {
-                        // a whole tile: all eight loads of a thread in flight together
-                        v4f tv[DTILE / 1024];
-#pragma unroll
-                        for (int r = 0; r < DTILE / 1024; ++r) tv[r] = ld_stream((const v4f*)(dense + base + r * 1024 + tid * 4));
-#pragma unroll
-                        for (int r = 0; r < DTILE / 1024; ++r) *(v4f*)(acc + r * 1024 + tid * 4) = tv[r];
+                        load_tile<6>(dense + base, acc, tid);
                     } else {
                         for (int q = tid * 4; q < len; q += 256 * 4) {
                             if (vec && q + 4 <= len) {
@@ -3760,9 +3789,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
             if (loaded) {
                 __syncthreads();
                 if (vec && len == DTILE) {
-#pragma unroll
-                    for (int r = 0; r < DTILE / 1024; ++r)
-                        st_stream(*(const v4f*)(acc + r * 1024 + tid * 4), (v4f*)(dense + base + r * 1024 + tid * 4));
+                    store_tile<NT>(acc, dense + base, tid);
                 } else {
                     for (int q = tid * 4; q < len; q += 256 * 4) {
                         if (vec && q + 4 <= len) {
@@ -4461,6 +4488,7 @@ static int decompress_impl(const int32_t* idx, const float* val, const int64_t* 
     if (total == 0) return GRAVAC_OK;
     const int64_t ntile = (n + DTILE - 1) / DTILE;
     const uint32_t grid = (uint32_t)(ntile < 1024 ? ntile : 1024);  // 4 workgroups (4 x 32 KiB LDS) on each of 256 CUs
+    const bool plain = 4 * n <= PLAIN_BYTES;                        // see store_tile
     int64_t at = 0;
     for (int w0 = 0; w0 < W; w0 += DMAXW) {
         const int wn = (W - w0 < DMAXW) ? W - w0 : DMAXW;
@@ -4476,13 +4504,14 @@ static int decompress_impl(const int32_t* idx, const float* val, const int64_t* 
         if (group == 0) continue;
         if (bounds) {
             // tile boundaries of the group's messages first (the workspace is reused from group to group: stream order)
-                const uint32_t pair_blocks = (uint32_t)((longest + 256 * BPAIRS - 1) / (256 * BPAIRS));
+            const uint32_t pair_blocks = (uint32_t)((longest + 256 * BPAIRS - 1) / (256 * BPAIRS));
             hipLaunchKernelGGL(bounds_kernel, dim3(pair_blocks, (uint32_t)wn), dim3(256), 0, stream, idx, wo, ntile,
                                bounds);
-            hipLaunchKernelGGL(decompress_ws_kernel, dim3(grid), dim3(256), 0, stream, idx, val, wo, wn, n, dense_out,
-                               (const uint32_t*)bounds, alpha);
+            hipLaunchKernelGGL(plain ? decompress_ws_kernel<0> : decompress_ws_kernel<7>,
+                               dim3(grid), dim3(256), 0, stream, idx, val, wo, wn, n, dense_out, (const uint32_t*)bounds, alpha);
         } else {
-            hipLaunchKernelGGL(decompress_kernel, dim3(grid), dim3(256), 0, stream, idx, val, wo, wn, n, dense_out, alpha);
+            hipLaunchKernelGGL(plain ? decompress_kernel<0> : decompress_kernel<DTILE / 1024>,
+                               dim3(grid), dim3(256), 0, stream, idx, val, wo, wn, n, dense_out, alpha);
         }
     }
     if (hipGetLastError() != hipSuccess) return GRAVAC_ERR_HIP;

@@ -175,6 +175,29 @@ def test_decompression_of_gapped_messages(W, n, spread):
         assert np.array_equal(d.cpu().numpy().view(np.uint32), ref.view(np.uint32)), f"workspace {ws is not None}"
 
 
+@pytest.mark.parametrize("n", [4_000_001, 24 * 1024 * 1024, 24 * 1024 * 1024 + 1])
+@pytest.mark.parametrize("W", [2, 9])
+def test_decompression_of_whole_tiles(n, W):
+    """Tiles moved whole, in buffers on both sides of the size from which most of their rows are stored past the caches; the
+    last tile ragged, a buffer that starts off a 16-byte boundary moved element by element."""
+    step = 6 * W
+    msgs = [np.arange(w, n, step, dtype=np.int32) for w in range(W - 1)] + [np.arange(0, n, step, dtype=np.int32)]
+    rng = np.random.Generator(np.random.PCG64(n + W))
+    vals = [rng.random(m.size, dtype=np.float32) - np.float32(0.5) for m in msgs]
+    base = rng.random(n + 1, dtype=np.float32)
+    idx, val, counts = np.concatenate(msgs), np.concatenate(vals), [m.size for m in msgs]
+    ref = base[1:].copy()
+    oracle.decompress_update(idx, val, counts, -0.0125, ref)
+    i, v = torch.from_numpy(idx).cuda(), torch.from_numpy(val).cuda()
+    ws = torch.empty(binding.gravac_decompress_workspace_bytes(W, n), dtype=torch.uint8, device="cuda")
+    for w in (None, ws):
+        for off in ((0, 1) if n < 5_000_000 else (0,)):
+            d = torch.empty(n + off, device="cuda")[off:]
+            d.copy_(torch.from_numpy(base[1:]))
+            binding.gravac_decompress_update(i, v, counts, -0.0125, d, workspace=w)
+            assert np.array_equal(d.cpu().numpy().view(np.uint32), ref.view(np.uint32)), f"workspace {w is not None}, offset {off}"
+
+
 @pytest.mark.parametrize("n", [200_003, (1 << 19) - 1, 1 << 19, 1_500_001])
 @pytest.mark.parametrize("scale", [1e-30, 1e-12, 1e-5, 1.0, 3e4, 1e8])
 def test_sample_window(n, scale):
