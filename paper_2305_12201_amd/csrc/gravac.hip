@@ -3654,11 +3654,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
         __syncthreads();
         // The chunk's tiles with few pairs, all of one worker: nothing has to be ordered, so the pairs of all of them are
         // applied at once, each to its entry (in most of a gradient whose large entries sit elsewhere a tile holds a pair
-        // or two, and a tile at a time would be a chain of round trips each).
-        {
+        // or two, and a tile at a time would be a chain of round trips each).  Every wavefront sees for itself whether the
+        // chunk has such tiles; if not, no barrier is spent on them, and the block is kept out of the way of the code around
+        // it (eight CF 1000 messages spread evenly over the ResNet101 shape, none such: 24.0 -> 23.4 us, 23.3 without the
+        // block; one message of CF 1000 over the VGG16 shape, nothing else: 15.0, 32.5 without the block).
+        const int cl = tid & 63;
+        const uint32_t cone = cl < tc && (bwrk[cl] >> 16) == 1u && btot[cl] <= DSPARSE ? btot[cl] : 0u;
+        if (__builtin_expect(__ballot(cone != 0u) != 0ull, 0)) {
             if (tid < 64) {
-                const uint32_t c = tid < tc && (bwrk[tid] >> 16) == 1u && btot[tid] <= DSPARSE ? btot[tid] : 0u;
-                const uint32_t inc = wave_scan(c);
+                const uint32_t inc = wave_scan(cone);
                 if (tid < DCHUNK) tpre[tid + 1] = inc;
                 if (tid == 0) tpre[0] = 0;
             }
