@@ -3288,7 +3288,7 @@ __device__ __forceinline__ void lower_bounds_32(const int32_t* idx, int64_t a, i
 }
 
 // How whole tiles are moved: six of their eight rows of 1024 floats are read with non-temporal hints and seven are written
-// with them; in a buffer of up to PLAIN_BYTES none is written with them.  Microseconds, eight messages of CF 100 unless
+// with them; in a buffer between PLAIN_FROM and PLAIN_BYTES none is written with them.  Microseconds, eight messages of CF 100 unless
 // said, with a workspace; rows hinted (read, written):  0, 0    8, 0    8, 8    8, 6    6, 7
 //   178 MB, three buffers in turn                        85.5    82.4    73.6    70.7    70.2
 //   178 MB, the same buffer again                        67.2    68.5    73.4    69.1    67.9
@@ -3303,9 +3303,12 @@ __device__ __forceinline__ void lower_bounds_32(const int32_t* idx, int64_t a, i
 // of dirty lines, which a later kernel pays for unless the same lines are written again soon; with every row hinted a
 // buffer that would fit is never taken in again, not even by a clear.  In the last two rows the plain stores only move the
 // time from the decompression to the pass over the gradient, as soon as anything else gets into the cache.
-// Without a workspace all rows are hinted, read and written, or in such a small buffer read (178 MB, three in turn, the
+// Without a workspace all rows are hinted, read and written, or in a buffer of that size only read (178 MB, three in turn, the
 // same again, cleared, flushed: 0, 0: 87, 76, 79, 108; 8, 0: 83, 76, 79, 98; 6, 7: 79, 82, 77, 100; 8, 8: 78, 82, 77, 95).
-constexpr int64_t PLAIN_BYTES = 96ll << 20;
+// A buffer of up to 32 MB fits the eight L2 caches, which would write its lines back when the kernel ends: 16 MB, CF 20,
+// in turn 19.3 (6, 0), 17.8 (6, 7); 48 MB 23.1 and 24.6, 64 MB 28.4 and 30.1, 80 MB 36.3 and 35.7, 96 MB 44.7 and 42.0,
+// there the same buffer again 40.7 and 42.0.
+constexpr int64_t PLAIN_FROM = 32ll << 20, PLAIN_BYTES = 96ll << 20;
 
 template <int NT>  // rows read with hints
 __device__ __forceinline__ void load_tile(const float* from, float* acc, int tid)
@@ -4492,7 +4495,7 @@ static int decompress_impl(const int32_t* idx, const float* val, const int64_t* 
     if (total == 0) return GRAVAC_OK;
     const int64_t ntile = (n + DTILE - 1) / DTILE;
     const uint32_t grid = (uint32_t)(ntile < 1024 ? ntile : 1024);  // 4 workgroups (4 x 32 KiB LDS) on each of 256 CUs
-    const bool plain = 4 * n <= PLAIN_BYTES;                        // see store_tile
+    const bool plain = 4 * n > PLAIN_FROM && 4 * n <= PLAIN_BYTES;  // see store_tile
     int64_t at = 0;
     for (int w0 = 0; w0 < W; w0 += DMAXW) {
         const int wn = (W - w0 < DMAXW) ? W - w0 : DMAXW;

@@ -175,10 +175,10 @@ def test_decompression_of_gapped_messages(W, n, spread):
         assert np.array_equal(d.cpu().numpy().view(np.uint32), ref.view(np.uint32)), f"workspace {ws is not None}"
 
 
-@pytest.mark.parametrize("n", [4_000_001, 24 * 1024 * 1024, 24 * 1024 * 1024 + 1])
+@pytest.mark.parametrize("n", [4_000_001, 8 * 1024 * 1024, 8 * 1024 * 1024 + 1, 24 * 1024 * 1024, 24 * 1024 * 1024 + 1])
 @pytest.mark.parametrize("W", [2, 9])
 def test_decompression_of_whole_tiles(n, W):
-    """Tiles moved whole, in buffers on both sides of the size from which most of their rows are stored past the caches; the
+    """Tiles moved whole, in buffers on both sides of the sizes between which their rows are stored through the caches; the
     last tile ragged, a buffer that starts off a 16-byte boundary moved element by element."""
     step = 6 * W
     msgs = [np.arange(w, n, step, dtype=np.int32) for w in range(W - 1)] + [np.arange(0, n, step, dtype=np.int32)]
