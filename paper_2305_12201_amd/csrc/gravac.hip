@@ -3518,29 +3518,32 @@ __device__ __forceinline__ int64_t tile_of_index(int32_t x, int64_t ntile)
 }
 
 // grid (pair blocks, workers).  Pair j > 0 of a message starts the tiles (tile of pair j - 1, tile of pair j].  A
-// wavefront takes BPAIRS consecutive rows of 64 pairs, all their loads in flight at once (one row per wavefront and two
-// loads per pair: 10.4 us for 3.6 million pairs).  A lane with up to BGAP tiles to write does it itself, longer runs (gaps
-// in the message) are written by the whole wavefront.
-constexpr int BPAIRS = 4;
+// wavefront takes BP consecutive rows of 64 pairs, all their loads in flight at once.  A lane with up to BGAP tiles to
+// write does it itself, longer runs (gaps in the message) are written by the whole wavefront.
 constexpr int BGAP = 8;
+// Four rows from this many pairs of a call on, one row below (whole calls, one row and four): 3.6 million pairs 76.5 and
+// 73.4 us, 1.6 million 18.4 and 17.5, 0.8 million 14.2 and 14.3, 0.32 million 15.7 and 16.2, 84,000 14.5 and 15.0 (the
+// chains are longer and the code is four times as much, on a chip that is not full).
+constexpr int64_t BROWS_PAIRS = 1 << 19;
 
+template <int BP>
 __global__ __launch_bounds__(256) void bounds_kernel(const int32_t* __restrict__ idx, WorkerOffsets wo, int64_t ntile,
                                                      uint32_t* __restrict__ bounds)
 {
     const int w = blockIdx.y, lane = threadIdx.x & 63;
     const int64_t a = wo.at[w], cnt = wo.at[w + 1] - a;
     uint32_t* bw = bounds + (size_t)w * (size_t)(ntile + 1);
-    const int64_t j0 = ((int64_t)blockIdx.x * 256 + (threadIdx.x & ~63)) * BPAIRS;  // first pair of this wavefront
+    const int64_t j0 = ((int64_t)blockIdx.x * 256 + (threadIdx.x & ~63)) * BP;  // first pair of this wavefront
     if (j0 >= cnt) return;
-    int32_t x[BPAIRS];
+    int32_t x[BP];
 #pragma unroll
-    for (int q = 0; q < BPAIRS; ++q) {
+    for (int q = 0; q < BP; ++q) {
         const int64_t j = j0 + q * 64 + lane;
         x[q] = idx[a + (j < cnt ? j : cnt - 1)];
     }
     int32_t last = j0 > 0 ? idx[a + j0 - 1] : 0;   // the pair before the row
 #pragma unroll
-    for (int q = 0; q < BPAIRS; ++q) {
+    for (int q = 0; q < BP; ++q) {
         const int64_t j = j0 + q * 64 + lane;
         int32_t prev = __shfl_up(x[q], 1, 64);
         if (lane == 0) prev = last;
@@ -4511,9 +4514,10 @@ static int decompress_impl(const int32_t* idx, const float* val, const int64_t* 
         if (group == 0) continue;
         if (bounds) {
             // tile boundaries of the group's messages first (the workspace is reused from group to group: stream order)
-            const uint32_t pair_blocks = (uint32_t)((longest + 256 * BPAIRS - 1) / (256 * BPAIRS));
-            hipLaunchKernelGGL(bounds_kernel, dim3(pair_blocks, (uint32_t)wn), dim3(256), 0, stream, idx, wo, ntile,
-                               bounds);
+            const int bp = group < BROWS_PAIRS ? 1 : 4;
+            const uint32_t pair_blocks = (uint32_t)((longest + 256 * bp - 1) / (256 * bp));
+            hipLaunchKernelGGL(bp == 1 ? bounds_kernel<1> : bounds_kernel<4>, dim3(pair_blocks, (uint32_t)wn), dim3(256), 0,
+                               stream, idx, wo, ntile, bounds);
             hipLaunchKernelGGL(plain ? decompress_ws_kernel<0> : decompress_ws_kernel<7>,
                                dim3(grid), dim3(256), 0, stream, idx, val, wo, wn, n, dense_out, (const uint32_t*)bounds, alpha);
         } else {

@@ -175,6 +175,23 @@ def test_decompression_of_gapped_messages(W, n, spread):
         assert np.array_equal(d.cpu().numpy().view(np.uint32), ref.view(np.uint32)), f"workspace {ws is not None}"
 
 
+@pytest.mark.parametrize("count", [65_535, 65_536])
+def test_tile_boundaries_on_both_sides_of_their_two_forms(count):
+    """Eight messages with gaps from one entry to a tile, 2^19 pairs together and eight fewer: boundaries found four rows of
+    pairs and one row at a time."""
+    n, W = 70_000_000, 8
+    msgs = [_gapped(n, count, w, 9.0) for w in range(W)]
+    assert all(m.size == count for m in msgs)
+    rng = np.random.Generator(np.random.PCG64(count))
+    val = rng.standard_normal(W * count).astype(np.float32)
+    ref = np.zeros(n, np.float32)
+    oracle.decompress_update(np.concatenate(msgs), val, [count] * W, 0.5, ref)
+    d = torch.zeros(n, device="cuda")
+    ws = torch.empty(binding.gravac_decompress_workspace_bytes(W, n), dtype=torch.uint8, device="cuda")
+    binding.gravac_decompress_update(torch.from_numpy(np.concatenate(msgs)).cuda(), torch.from_numpy(val).cuda(), [count] * W, 0.5, d, workspace=ws)
+    assert np.array_equal(d.cpu().numpy().view(np.uint32), ref.view(np.uint32))
+
+
 @pytest.mark.parametrize("n", [4_000_001, 8 * 1024 * 1024, 8 * 1024 * 1024 + 1, 24 * 1024 * 1024, 24 * 1024 * 1024 + 1])
 @pytest.mark.parametrize("W", [2, 9])
 def test_decompression_of_whole_tiles(n, W):
