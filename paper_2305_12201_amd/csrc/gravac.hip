@@ -85,10 +85,9 @@ constexpr int SBIN = 4096;
 constexpr uint32_t SCSHIFT = 19, SFSHIFT = 15;
 constexpr uint32_t SEXP0 = 79, SOCT = 64;      // exponent field of 2^-48, octaves
 constexpr uint32_t SWIN = 12, SWIN_ABOVE = 2;  // octaves of the window, and how many of them lie above the largest of 256 samples
-// A flat tensor of fewer than SWIN_SMALL elements takes a window from 2^-14 on, unseen: a bracket 4.4 % in magnitude too
-// wide costs it little (23,000 entries at most), and the look at the 256 elements 0.6 us of a 1 MiB bucket's 34.
-constexpr int64_t SWIN_SMALL = 1 << 19;
-constexpr uint32_t SWIN_FIXED = (127u - 14u) << 23;
+// (The look at the 256 elements costs a 1 MiB bucket 0.4 of 33.4 us.  A window given by the host for small tensors, 2^-14
+// to 2^-2, spared it for magnitudes of 1e-4 to 1e-1 alone: 33.0 us for Normal(0, 1e-3), but 38.4 for 1e-7 and 37.4 for 1;
+// equal bins of 1.1 %, 33.9 for all.)
 constexpr uint32_t SKEY0 = SEXP0 << 23;
 constexpr uint32_t SCOARSE = SOCT << (23 - SCSHIFT), SFINE = SWIN << (23 - SFSHIFT), SLESS = SWIN << (23 - SCSHIFT);
 constexpr uint32_t SUSED = SCOARSE + SFINE - SLESS;   // bins in use
@@ -213,7 +212,6 @@ struct Params {
     // the same for one flat tensor
     uint32_t flat_k[MAXCF];
     uint32_t flat_samples;
-    uint32_t fixed_window;   // a small flat tensor: first key of the sample histogram's window (0: found from the data)
     // workspace
     Status* status;
     CfState* st;         // [n_seg][n_cf]
@@ -798,11 +796,7 @@ __global__ __launch_bounds__(256) void sample_kernel(Params p)
     // The window: every block of the segment looks at the same 256 elements, spread evenly, and takes the exponent of the
     // largest (an infinite or NaN one does not count).  Their loads are issued before the sample's and arrive with them.
     const uint64_t wpos = (nt * (2u * tid + 1u)) >> 9;   // (below nt)
-    float wg = 0.0f, wr = 0.0f;
-    if (p.fixed_window == 0u) {
-        wg = p.grad[s0 + (int64_t)wpos];
-        if (!p.single) wr = p.res[s0 + (int64_t)wpos];
-    }
+    const float wg = p.grad[s0 + (int64_t)wpos], wr = p.single ? 0.0f : p.res[s0 + (int64_t)wpos];
     __shared__ uint32_t wexp[4];
     // A group is 4 consecutive elements: sample i of the segment is element i % 4 of group i / 4.  A sampled
     // segment (S a multiple of SAMPLE_BLOCK, nt > 2 S) is cut into S / 16 strata of at least 32 elements, and the
@@ -851,24 +845,19 @@ __global__ __launch_bounds__(256) void sample_kernel(Params p)
             rv[q] = p.res[s0 + (int64_t)pos];
         }
     }
-    uint32_t w0 = p.fixed_window;
-    if (w0 != 0u) {
-        __syncthreads();   // (the histogram is cleared)
-    } else {
-        const uint32_t wk = key_of(p.single ? wg : wr + wg);
-        const double m = wave_max(wk < 0x7F800000u ? (double)(wk >> 23) : 0.0);
-        if ((tid & 63) == 0) wexp[tid >> 6] = (uint32_t)m;
-        __syncthreads();   // (... and the histogram is cleared)
-        uint32_t e = 0;
+    const uint32_t wk = key_of(p.single ? wg : wr + wg);
+    const double m = wave_max(wk < 0x7F800000u ? (double)(wk >> 23) : 0.0);
+    if ((tid & 63) == 0) wexp[tid >> 6] = (uint32_t)m;
+    __syncthreads();   // (... and the histogram is cleared)
+    uint32_t e = 0;
 #pragma unroll
-        for (int w = 0; w < 4; ++w) e = wexp[w] > e ? wexp[w] : e;
-        // exponents e + SWIN_ABOVE + 1 - SWIN .. e + SWIN_ABOVE, inside the octaves covered
-        // (not the lowest: the first bin holds the keys below them, too)
-        uint32_t b0 = e + SWIN_ABOVE + 1u > SWIN + SEXP0 + 1u ? e + SWIN_ABOVE + 1u - SWIN : SEXP0 + 1u;
-        b0 = b0 > SEXP0 + SOCT - SWIN ? SEXP0 + SOCT - SWIN : b0;
-        w0 = b0 << 23;
-        if (lb == 0 && tid == 0) p.xq[(size_t)t * p.n_cf * NBIN + XQ_WIN] = w0;
-    }
+    for (int w = 0; w < 4; ++w) e = wexp[w] > e ? wexp[w] : e;
+    // exponents e + SWIN_ABOVE + 1 - SWIN .. e + SWIN_ABOVE, inside the octaves covered
+    // (not the lowest: the first bin holds the keys below them, too)
+    uint32_t b0 = e + SWIN_ABOVE + 1u > SWIN + SEXP0 + 1u ? e + SWIN_ABOVE + 1u - SWIN : SEXP0 + 1u;
+    b0 = b0 > SEXP0 + SOCT - SWIN ? SEXP0 + SOCT - SWIN : b0;
+    const uint32_t w0 = b0 << 23;
+    if (lb == 0 && tid == 0) p.xq[(size_t)t * p.n_cf * NBIN + XQ_WIN] = w0;
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
         const float acc = p.single ? gv[q] : rv[q] + gv[q];
@@ -1001,7 +990,7 @@ __global__ __launch_bounds__(P * 1024 / G) __attribute__((amdgpu_waves_per_eu(SM
     // samples in the groups of bins above this workgroup's, and in all
     // (the group counts of up to two blocks per thread are fetched first and added up after the histograms, so that
     // both sets of loads are in flight together)
-    const uint32_t w0 = p.fixed_window ? p.fixed_window : p.xq[(size_t)t * p.n_cf * NBIN + XQ_WIN];
+    const uint32_t w0 = p.xq[(size_t)t * p.n_cf * NBIN + XQ_WIN];
     uint32_t g_above = 0, g_total = 0;
     uint4 ga[2][2];
     static_assert(G == 1 || 2 * (1024 / G) >= 2 * DENSE_BLOCKS, "two blocks' group counts per thread cover a flat sample");
@@ -4214,7 +4203,6 @@ static int compress_impl(const float* grad, float* residual, int64_t n, const do
     if (ns == 1) {
         for (int j = 0; j < n_cf; ++j) p.flat_k[j] = (uint32_t)gravac_topk_count(n, cf_list[j]);
         p.flat_samples = sample_count((uint64_t)n, cf_min, cf_max, true);
-        p.fixed_window = n < SWIN_SMALL ? SWIN_FIXED : 0u;
         p.n_tiles = (uint32_t)((n + TW - 1) / TW);
         max_seg_tiles = p.n_tiles;
         emit_wgs = (p.n_tiles + EW - 1) / EW;

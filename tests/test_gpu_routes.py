@@ -218,8 +218,8 @@ def test_decompression_of_whole_tiles(n, W):
 @pytest.mark.parametrize("n", [200_003, (1 << 19) - 1, 1 << 19, 1_500_001])
 @pytest.mark.parametrize("scale", [1e-30, 1e-12, 1e-5, 1.0, 3e4, 1e8])
 def test_sample_window(n, scale):
-    """Magnitudes inside, below and above the finely binned octaves of the sample, whether the window is found from the data
-    or given; thresholds far below the largest entries, and infinities among the entries it is found from."""
+    """Magnitudes inside, below and above the finely binned octaves of the sample, of tensors read whole and of sampled ones;
+    thresholds far below the largest entries, and infinities among the entries the octaves are found from."""
     rng = np.random.Generator(np.random.PCG64(n))
     g = (rng.standard_normal(n) * scale).astype(np.float32)
     z = np.zeros(n, np.float32)
