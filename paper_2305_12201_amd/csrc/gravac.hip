@@ -793,9 +793,11 @@ __global__ __launch_bounds__(256) void sample_kernel(Params p)
     const uint64_t nt = (uint64_t)(seg_end(p, t) - s0);
 #pragma unroll
     for (int q = 0; q < SBIN / 256; ++q) h[q * 256 + tid] = 0;
-    // The window: every block of the segment looks at the same 256 elements, spread evenly, and takes the exponent of the
-    // largest (an infinite or NaN one does not count).  Their loads are issued before the sample's and arrive with them.
-    const uint64_t wpos = (nt * (2u * tid + 1u)) >> 9;   // (below nt)
+    // The window: every block of the segment looks at the same 256 elements, 64 groups of four spread evenly, and takes the
+    // exponent of the largest (an infinite or NaN one does not count).  Their loads are issued before the sample's and
+    // arrive with them.  (256 single elements are four times the memory the sample itself takes: a call with 1000 tensors of
+    // 20,000 elements spent 55 us here instead of 28, and all together 191 instead of 171.)
+    const uint64_t wat = ((nt * (2u * (tid >> 2) + 1u)) >> 7) + (tid & 3u), wpos = wat < nt ? wat : nt - 1u;
     const float wg = p.grad[s0 + (int64_t)wpos], wr = p.single ? 0.0f : p.res[s0 + (int64_t)wpos];
     __shared__ uint32_t wexp[4];
     // A group is 4 consecutive elements: sample i of the segment is element i % 4 of group i / 4.  A sampled
