@@ -122,6 +122,25 @@ def test_long_gather_lists(n, bits):
     check(g, z, [10.0], 0, workloads.offsets_of(sizes), what="layerwise")
 
 
+@pytest.mark.parametrize("n", [3 * 8_192 + 5, 200_003])
+@pytest.mark.parametrize("cf", [1.2, 2.0, 2.8, 4.0, 6.0])
+def test_lists_of_many_rounds(n, cf):
+    """Sub-tiles with up to 383 listed candidates, and in buffers off a 16-byte boundary, where every sub-tile keeps its list,
+    with up to 1024."""
+    g = workloads.normal_gradient(n, 1e-3, seed=n)
+    r = workloads.normal_gradient(n, 1e-4, seed=n + 1)
+    check(g, r, [cf], what="one CF")
+    check(_coarse(g, 7), np.zeros(n, np.float32), [cf, 10.0 * cf], 0, what="ties, two CFs")
+    check_randomk(g, r, [cf], seed=n, commit=0, what="Random-k")
+    dg = torch.empty(n + 1, device="cuda")[1:]
+    dr = torch.empty(n + 1, device="cuda")[1:]
+    dg.copy_(torch.from_numpy(g))
+    dr.copy_(torch.from_numpy(r))
+    idx, val, stats = binding.Compressor(n, [cf], 0)(dg, dr)
+    got = (idx.cpu().numpy(), val.cpu().numpy(), stats.cpu().numpy(), dr.cpu().numpy())
+    assert_same(got, oracle_compress(g, r, [cf]), "off a 16-byte boundary")
+
+
 @pytest.mark.parametrize("n", [1, 8_192, 8_193, 8 * 8_192, 8 * 8_192 + 1, 64 * 8_192, 64 * 8_192 + 1, 72 * 8_192 + 5])
 def test_workgroup_and_group_boundaries(n):
     """Tile counts around a workgroup of the emit step (8 tiles) and around a partial sum of the tiles' counts (64)."""
