@@ -560,9 +560,10 @@ def test_buffers_at_any_float_boundary(off_g, off_r):
 
 
 def test_mass_of_equal_values_at_the_threshold_over_several_scan_slices():
-    """More ties at the threshold than a gather list holds, in a gradient long enough for several slices of the
-    scan (4096 tiles each): the located bin is histogrammed key by key and the tiles' ties are counted again."""
-    n = 40_000_000
+    """More ties at the threshold than a gather list holds, in a gradient long enough for a scan step of its own (more
+    than 6144 tiles) with several slices (4096 tiles each): the located bin is one key wide or gets counted key by key, and
+    the tiles' ties are dealt out by the scan."""
+    n = 52_000_003
     rng = np.random.default_rng(123)
     g = (rng.integers(-3, 4, n) * 0.25).astype(np.float32)
     r = np.zeros(n, np.float32)
