@@ -105,6 +105,7 @@ constexpr double ZMARGIN = 5.0;     // safety margin of the sampled rank, in sta
 constexpr uint32_t CTILES = 64;     // tiles per partial sum of the tiles' counts (csum)
 constexpr int XQ_WORDS = 8;         // a segment's work queue in the plan step: chunks claimed, then chunks done per phase
 constexpr int XQ_WIN = XQ_WORDS;    // ... and behind it the first key of its sample histogram's window
+constexpr int XQ_LINE = 32;         // words between two segments' queues: a cache line
 constexpr uint32_t WAIT_POLLS = 1u << 26;  // polls after which a workgroup of the plan step gives up on the others: at least
                                            // half a minute, where the longest wait of a call is milliseconds
 constexpr uint32_t WAIT_POLLS_TEST = 256;  // ... and under GRAVAC_FLAG_STALL_FALLBACK
@@ -142,11 +143,9 @@ struct CfState {
 static_assert(sizeof(CfState) == 64, "CfState layout");
 
 struct SegState {
-    uint32_t lo_min;  // smallest lo over the CFs: keys below it concern no CF
     uint32_t fail;    // FAIL_*: whether a bracket failed and the segment takes an exact route, and which
     uint32_t pz;      // sparse sub-tiles: the first pass has stored +0 instead of acc for keys >= pz: the upper end of the
                       // committed CF's bracket, above which an entry is selected unless the bracket fails (NONE: none)
-    uint32_t lo_c;    // the committed CF's lo: keys from here on are candidates for the message
 };
 
 struct Status {
@@ -206,8 +205,6 @@ struct Params {
     const SegInfo* segs;           // [n_seg] built on the host
     const uint32_t* ktab;          // [n_seg][n_cf] built on the host
     const uint32_t* sblock_seg;    // [n_sample_blocks] segment of every sample block, built on the host
-    const uint32_t* small_list;    // [n_small] the segments handled by one workgroup each, built on the host
-    uint32_t n_small;
     uint32_t* tseg;                // [n_tiles] segment of every tile, filled by threshold_kernel
     // the same for one flat tensor
     uint32_t flat_k[MAXCF];
@@ -222,7 +219,7 @@ struct Params {
     uint32_t* hist1;     // [copy blocks][NBIN] bracket histograms: REP copies per CF of a large tensor, one otherwise
     uint32_t* ovfc;      // [n_seg][n_cf][64][32] counts above the bracket (the histogram's last bin), spread over
                          // 64 cache lines; word 0 of each line is used
-    uint32_t* xq;        // [n_seg][n_cf][NBIN], of which a segment's first 9 words are in use (XQ_*)
+    uint32_t* xq;        // [n_seg][XQ_LINE] the plan step's work queue of every segment (XQ_*)
     uint32_t* coarse;    // [n_seg][NBIN] histogram of key >> 20 (exact route)
     uint32_t* list_key;  // [copy blocks][LCAP] gather lists: key ... (before they are filled: the exact routes' histograms)
     uint32_t* list_tile; //                          ... tile ...
@@ -784,7 +781,7 @@ __global__ __launch_bounds__(256) void sample_kernel(Params p)
         for (uint32_t i = lb * 256 + tid; i < NBIN / 4; i += nbk * 256) cs[i] = z;
         for (uint32_t i = lb * 256 + tid; i < (uint32_t)p.n_cf * 64; i += nbk * 256) p.ovfc[((size_t)t * p.n_cf * 64 + i) * 32] = 0;
         for (uint32_t i = lb * 256 + tid; i < blocks; i += nbk * 256) p.list_cnt[(seg_block(p, t, 0) + i) * 32] = 0;
-        if (lb == 0 && tid < XQ_WORDS) p.xq[(size_t)t * p.n_cf * NBIN + tid] = 0;
+        if (lb == 0 && tid < XQ_WORDS) p.xq[(size_t)t * XQ_LINE + tid] = 0;
         if (p.csum)
             for (uint32_t i = b * 256 + tid; i < (p.n_tiles + CTILES - 1u) / CTILES; i += gridDim.x * 256) p.csum[(size_t)i * 8] = 0;
     }
@@ -859,7 +856,7 @@ __global__ __launch_bounds__(256) void sample_kernel(Params p)
     uint32_t b0 = e + SWIN_ABOVE + 1u > SWIN + SEXP0 + 1u ? e + SWIN_ABOVE + 1u - SWIN : SEXP0 + 1u;
     b0 = b0 > SEXP0 + SOCT - SWIN ? SEXP0 + SOCT - SWIN : b0;
     const uint32_t w0 = b0 << 23;
-    if (lb == 0 && tid == 0) p.xq[(size_t)t * p.n_cf * NBIN + XQ_WIN] = w0;
+    if (lb == 0 && tid == 0) p.xq[(size_t)t * XQ_LINE + XQ_WIN] = w0;
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
         const float acc = p.single ? gv[q] : rv[q] + gv[q];
@@ -964,7 +961,7 @@ __global__ __launch_bounds__(P * 1024 / G) __attribute__((amdgpu_waves_per_eu(SM
             st.top = p.fixed_key; st.pad[0] = st.pad[1] = st.pad[2] = st.pad[3] = 0;
             p.st[0] = st;
             SegState sg;
-            sg.lo_min = p.fixed_key; sg.fail = FAIL_NONE; sg.pz = p.single ? NONE : p.fixed_key; sg.lo_c = p.fixed_key;
+            sg.fail = FAIL_NONE; sg.pz = p.single ? NONE : p.fixed_key;
             p.seg[0] = sg;
         }
         return;
@@ -992,7 +989,7 @@ __global__ __launch_bounds__(P * 1024 / G) __attribute__((amdgpu_waves_per_eu(SM
     // samples in the groups of bins above this workgroup's, and in all
     // (the group counts of up to two blocks per thread are fetched first and added up after the histograms, so that
     // both sets of loads are in flight together)
-    const uint32_t w0 = p.xq[(size_t)t * p.n_cf * NBIN + XQ_WIN];
+    const uint32_t w0 = p.xq[(size_t)t * XQ_LINE + XQ_WIN];
     uint32_t g_above = 0, g_total = 0;
     uint4 ga[2][2];
     static_assert(G == 1 || 2 * (1024 / G) >= 2 * DENSE_BLOCKS, "two blocks' group counts per thread cover a flat sample");
@@ -1745,7 +1742,7 @@ __global__ __launch_bounds__(PLAN_T) void plan_kernel(Params p)
     bool writes = first_block, counts = true;   // this workgroup records the plan, and counts the segment
     if (kind != FAIL_NONE) {
         // ---- exact routes
-        uint32_t* xq = p.xq + (size_t)t * p.n_cf * NBIN;
+        uint32_t* xq = p.xq + (size_t)t * XQ_LINE;
         const uint32_t u0 = seg_tile0(p, t), u1 = seg_tile1(p, t), tiles = u1 - u0;
         // (two tiles are one sub-tile per wavefront; a few chunks per workgroup leave little of a last, uneven round)
         constexpr uint32_t UNIT = PLAN_W / SUB;
@@ -1894,10 +1891,8 @@ __global__ __launch_bounds__(PLAN_T) void plan_kernel(Params p)
     }
     if (tid == 0) {
         // what the segment's tiles need of all its CFs together
-        uint32_t lo_min = NONE;
-        for (int x = 0; x < p.n_cf; ++x) lo_min = sh.lo[x] < lo_min ? sh.lo[x] : lo_min;
         SegState sg;
-        sg.lo_min = lo_min; sg.fail = kind; sg.lo_c = sh.lo[p.commit];
+        sg.fail = kind;
         sg.pz = kind == FAIL_FULL ? NONE : sh.pz;
         p.seg[t] = sg;
         if (kind >= FAIL_NARROW && counts) {
@@ -3895,8 +3890,8 @@ Layout make_layout(int64_t n, int n_cf, int n_seg)
     const uint64_t nt = max_tiles(n, n_seg), nsb = max_sample_blocks(n, n_seg);
     const size_t sc = (size_t)n_seg * n_cf;
     L.status = take(sizeof(Status));
-    // host-built tables, one piece: SegInfo[n_seg], ktab[n_seg][n_cf], sblock_seg[sample blocks], small_list[n_seg]
-    L.tables_bytes = sizeof(SegInfo) * n_seg + sizeof(uint32_t) * sc + sizeof(uint32_t) * nsb + sizeof(uint32_t) * n_seg;
+    // host-built tables, one piece: SegInfo[n_seg], ktab[n_seg][n_cf], sblock_seg[sample blocks]
+    L.tables_bytes = sizeof(SegInfo) * n_seg + sizeof(uint32_t) * sc + sizeof(uint32_t) * nsb;
     L.tables = take(L.tables_bytes);
     L.tseg = take(sizeof(uint32_t) * nt);
     L.st = take(sizeof(CfState) * sc);
@@ -3907,7 +3902,7 @@ Layout make_layout(int64_t n, int n_cf, int n_seg)
     const size_t blocks = pool_blocks(n, n_cf, n_seg);
     L.hist1 = take(sizeof(uint32_t) * blocks * NBIN);
     L.ovfc = take(sizeof(uint32_t) * sc * 64 * 32);
-    L.xq = take(sizeof(uint32_t) * sc * NBIN);
+    L.xq = take(sizeof(uint32_t) * (size_t)n_seg * XQ_LINE);
     L.coarse = take(sizeof(uint32_t) * (size_t)n_seg * NBIN);
     L.list_key = take(sizeof(uint32_t) * blocks * LCAP);
     L.list_tile = take(sizeof(uint32_t) * blocks * LCAP);
@@ -4264,19 +4259,15 @@ static int compress_impl(const float* grad, float* residual, int64_t n, const do
         if (const int rc = refuse_capture(stream)) return rc;
     (void)hipGetLastError();  // an error left behind by earlier work of the process is not this call's
     if (ns > 1) {
-        table_bytes = sizeof(SegInfo) * ns + sizeof(uint32_t) * (size_t)ns * n_cf + sizeof(uint32_t) * p.n_sample_blocks +
-                      sizeof(uint32_t) * n_small;
+        table_bytes = sizeof(SegInfo) * ns + sizeof(uint32_t) * (size_t)ns * n_cf + sizeof(uint32_t) * p.n_sample_blocks;
         table_bytes = (table_bytes + 15) & ~(size_t)15;   // (moved 16 bytes at a time; the workspace's part is that long)
         slot = staging_acquire(table_bytes);
         if (!slot) return GRAVAC_ERR_HIP;
         SegInfo* segs = (SegInfo*)slot->mem;
         uint32_t* ktab = (uint32_t*)(slot->mem + sizeof(SegInfo) * ns);
         uint32_t* sblock_seg = ktab + (size_t)ns * n_cf;
-        uint32_t* small_list = sblock_seg + p.n_sample_blocks;
-        p.small_list = p.sblock_seg + p.n_sample_blocks;
-        p.n_small = n_small;
         int64_t koff = 0;
-        uint32_t tile_at = 0, sb_at = 0, small_at_ = 0, block_at = 0;
+        uint32_t tile_at = 0, sb_at = 0, block_at = 0;
         for (int t = 0; t < ns; ++t) {
             const int64_t nt = seg_offsets[t + 1] - seg_offsets[t];
             SegInfo& g = segs[t];
@@ -4286,7 +4277,6 @@ static int compress_impl(const float* grad, float* residual, int64_t n, const do
             g.rep = seg_copies(nt, false); g.pool0 = block_at; block_at += (uint32_t)n_cf * g.rep;
             if (small_ok && nt <= SMALL_MAX) {
                 g.small = 1;
-                small_list[small_at_++] = (uint32_t)t;
             } else {
                 tile_at += (uint32_t)((nt + TW - 1) / TW); g.tile1 = tile_at;
                 g.wg0 = emit_wgs; g.wgs = (g.tile1 - g.tile0 + EW - 1) / EW; emit_wgs += g.wgs;
