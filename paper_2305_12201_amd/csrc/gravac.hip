@@ -24,11 +24,17 @@
 //
 // Units of work.  A tile is TW consecutive elements; the streaming pass gives each of its SUB
 // sub-tiles to one 64-lane wavefront, which owns that sub-tile's slots of the list arrays, so
-// ordered compaction needs no communication between wavefronts and no list can overflow.  No kernel
-// waits on another workgroup: cross-tile results (histograms, output offsets) are combined at kernel
-// boundaries.  Global atomics complete at a rate of roughly one per cache line per 10 ns on this part,
-// so the bracket histogram and the gather lists exist in REP copies (picked from the sub-tile,
-// tile or workgroup number) and nothing else uses global atomics.
+// ordered compaction needs no communication between wavefronts and no list can overflow.  Cross-tile
+// results (histograms, output offsets) are combined at kernel boundaries, and no workgroup waits for
+// another, except on the exact routes: they run inside the plan step, whose workgroups wait for each
+// other over counters in the workspace.  Such a workgroup works on one segment, waits only once every
+// chunk of it has been claimed, hence only for workgroups that are running and wait for nobody before
+// they have arrived, and gives up after a number of polls (plan_barrier).  Global atomics complete at a
+// rate of roughly one per cache line per 10 ns on this part, so what takes many of them is spread: the
+// bracket histogram and the gather lists' fill counts exist in REP copies (picked from the sub-tile,
+// tile or workgroup number), the counts above the brackets lie on 64 lines.  The others are few: a
+// tile's counts added to those of its 64-tile group, the exact routes' histograms (one add per workgroup
+// and bin, or per wavefront and bin) and queue counters, the status record.
 
 #include <hip/hip_runtime.h>
 #include <hip/hip_ext.h>
@@ -2479,8 +2485,9 @@ __global__ __launch_bounds__(SCAN_T) void scan_kernel(Params p, uint32_t slices)
 // of its launch are the statistics of one (segment, CF) each.  The scan step is 6 to 8 us of round trips and barriers in
 // one or a few workgroups; repeated by all of them, part of it overlaps with the tiles' own first loads, and a launch is
 // spared: 1 MiB buckets 38.3 -> 33.8 us, 25 MB 74.7 -> 72.4, ResNet101 CF 100 129.9 -> 126.3, three CFs 197 -> 192, LSTM
-// 156 -> 151 (with the rolled loops of pop_front, which took 1 to 3 us of that).  It holds while all tiles' wavefronts are resident at once (EMIT_RESIDENT: six per SIMD); the VGG16 shape's 2112 workgroups
-// take two to three rounds of it, 386 instead of 381 us at CF 1000 and 439 instead of 417 at CF 10, and stay with the scan step.
+// 156 -> 151 (with the rolled loops of pop_front, which took 1 to 3 us of that).  It holds while all tiles' wavefronts are
+// resident at once (EMIT_RESIDENT: six per SIMD); the VGG16 shape's 2112 workgroups take two to three rounds of it, 386
+// instead of 381 us at CF 1000 and 439 instead of 417 at CF 10, and stay with the scan step.
 // ---------------------------------------------------------------------------------------------
 constexpr int EWG = 512;                    // threads
 constexpr int EW = EWG / 64;
