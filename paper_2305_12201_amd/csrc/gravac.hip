@@ -2487,7 +2487,8 @@ __global__ __launch_bounds__(SCAN_T) void scan_kernel(Params p, uint32_t slices)
 // spared: 1 MiB buckets 38.3 -> 33.8 us, 25 MB 74.7 -> 72.4, ResNet101 CF 100 129.9 -> 126.3, three CFs 197 -> 192, LSTM
 // 156 -> 151 (with the rolled loops of pop_front, which took 1 to 3 us of that).  It holds while all tiles' wavefronts are
 // resident at once (EMIT_RESIDENT: six per SIMD); the VGG16 shape's 2112 workgroups take two to three rounds of it, 386
-// instead of 381 us at CF 1000 and 439 instead of 417 at CF 10, and stay with the scan step.
+// instead of 381 us at CF 1000 and 439 instead of 417 at CF 10, and stay with the scan step.  (Normal gradients of 50 to 100
+// million elements: within 1.5 % either way, 137.8 against 138.8 us just below the limit and 139.4 against 140.5 just above.)
 // ---------------------------------------------------------------------------------------------
 constexpr int EWG = 512;                    // threads
 constexpr int EW = EWG / 64;
@@ -3668,11 +3669,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
         // applied at once, each to its entry (in most of a gradient whose large entries sit elsewhere a tile holds a pair
         // or two, and a tile at a time would be a chain of round trips each).  Every wavefront sees for itself whether the
         // chunk has such tiles; if not, no barrier is spent on them, and the block is kept out of the way of the code around
-        // it (eight CF 1000 messages spread evenly over the ResNet101 shape, none such: 24.0 -> 23.4 us, 23.3 without the
-        // block; one message of CF 1000 over the VGG16 shape, nothing else: 15.0, 32.5 without the block).
+        // it (eight CF 1000 messages spread evenly over the ResNet101 shape, none such, caches flushed: 33.6 -> 32.5 us,
+        // 32.1 without the block; one message of CF 1000 over the VGG16 shape, nothing else: 13.6, 32.3 without the block).
         const int cl = tid & 63;
         const uint32_t cone = cl < tc && (bwrk[cl] >> 16) == 1u && btot[cl] <= DSPARSE ? btot[cl] : 0u;
-        if (__builtin_expect(__ballot(cone != 0u) != 0ull, 0)) {
+        static_assert(DCHUNK <= 32, "a bit per tile of a chunk");
+        const uint32_t ones = (uint32_t)__ballot(cone != 0u);   // bit i: the chunk's tile i is such a one
+        if (__builtin_expect(ones != 0u, 0)) {
             if (tid < 64) {
                 const uint32_t inc = wave_scan(cone);
                 if (tid < DCHUNK) tpre[tid + 1] = inc;
@@ -3699,7 +3702,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
             const int len = (int)((n - base < DTILE) ? n - base : DTILE);
             const uint32_t tot = btot[i];
             if (tot == 0) continue;  // no message touches the tile
-            if (tot <= DSPARSE && (bwrk[i] >> 16) == 1u) continue;  // done above
+            if ((ones >> i) & 1u) continue;  // done above
             if (tot <= DSPARSE) {
                 // Few pairs: only the entries they name are read and written back, not the whole tile (a scattered
                 // access moves 64 bytes, so this pays up to about one pair per 16 entries).  The entries go through
