@@ -193,8 +193,6 @@ struct Params {
     int random;              // 1 = Random-k: the order is that of a keyed priority of the index, not of |acc|
     int no_commit;           // 1: nothing is removed from the residual (it keeps acc); the caller commits a message later
     int vec_ok;              // 1 if every buffer the kernels read or write with 16-byte accesses is aligned to 16 bytes
-    int split;               // 1 if the committed CF is not the lowest of the list: the entries inside the brackets then get a
-                             // list of their own everywhere; 0: a sub-tile's candidate list, where it has one, holds them all
     uint32_t bounds_from;    // BOUNDS_*
     uint32_t fixed_key;      // BOUNDS_FIXED: the key of the caller's threshold; entries with key >= fixed_key are kept
     uint32_t wait_polls;     // polls after which a workgroup of the plan step stops waiting for the others
@@ -463,62 +461,17 @@ struct TileLists {
     }
 };
 
-// from the per-sub-tile counts cnt[u * SUB ..]; a count's DENSE_BIT is masked off (such a sub-tile lists nothing)
+// from the per-sub-tile counts cnt[u * SUB ..]
 __device__ __forceinline__ TileLists tile_lists(const uint32_t* cnt, uint32_t u)
 {
     TileLists c;
     c.start[0] = 0;
 #pragma unroll
     for (int j = 0; j < SUB; ++j) {
-        const uint32_t x = cnt[(size_t)u * SUB + j];
-        c.start[j + 1] = c.start[j] + ((x & DENSE_BIT) ? 0u : x);
+        c.start[j + 1] = c.start[j] + cnt[(size_t)u * SUB + j];
     }
     return c;
 }
-
-// The entries of a tile that the steps after the pass over the gradient look at one by one: all that lie inside
-// some CF's bracket.  They are the sub-tile's bracket list, or, where the committed CF is the lowest of the call and
-// the sub-tile keeps a candidate list, that list (which then holds them all, next to entries above the brackets).
-struct TileRef {
-    TileLists tl;        // such entries per sub-tile
-    uint32_t main_mask;  // bit j: sub-tile j's are its candidate list
-};
-
-__device__ __forceinline__ TileRef tile_ref(const Params& p, uint32_t u)
-{
-    TileRef r;
-    r.tl.start[0] = 0;
-    r.main_mask = 0;
-#pragma unroll
-    for (int j = 0; j < SUB; ++j) {
-        const uint32_t cc = p.cand_cnt[(size_t)u * SUB + j], bc = p.brk_cnt[(size_t)u * SUB + j];
-        const bool use_main = !p.split && !(cc & DENSE_BIT);
-        if (use_main) r.main_mask |= 1u << j;
-        r.tl.start[j + 1] = r.tl.start[j] + (use_main ? cc : bc);
-    }
-    return r;
-}
-
-// Key (and value: needed for Random-k only, else 0) of the tile's i-th such entry, i < r.tl.total().
-__device__ __forceinline__ void ref_entry(const Params& p, uint32_t u, const TileRef& r, uint32_t i, uint32_t& key, float& val)
-{
-    const uint32_t sl = r.tl.slot(i);
-    const bool from_main = (r.main_mask >> (sl / TS)) & 1u;
-    const size_t at = (size_t)u * TW + sl;
-    if (!p.random) {
-        // the bits of |acc| either way: a candidate's value with its sign, or the key itself
-        const uint32_t* src = from_main ? (const uint32_t*)p.cand_val : p.brk_key;
-        key = src[at] & 0x7FFFFFFFu;
-        val = 0.0f;
-    } else if (from_main) {
-        key = priority_of(p.rk_s0, p.rk_s1, (uint32_t)p.cand_idx[at]);
-        val = p.cand_val[at];
-    } else {
-        key = p.brk_key[at];
-        val = p.brk_val[at];
-    }
-}
-
 
 // Four wavefronts (threads q = 0..255 of a 256-thread team; `q` is the thread's number inside the team, `scratch` 8
 // words of LDS owned by the team) search a 2048-bin histogram for the bin of the k-th largest: thread q holds the
@@ -1115,15 +1068,22 @@ __device__ __forceinline__ uint32_t zero_from(const Params& p, uint32_t lo, uint
     return mid < lo ? lo : (mid > top ? top : mid);
 }
 
+// Entries of a sub-tile that some bracket concerns (key >= lo_min) go through LDS on their way to the lists, compacted in
+// index order, so that what has to be done for each of them (per CF a count and an energy, a histogram update; the list
+// stores) is done 64 entries at a time by full wavefronts.  Done where the entries lie, an element at a time, the pass
+// over the ResNet101 shape with CFs 10, 100 and 1000 took 800 vector instructions and 61 stores and atomics per sub-tile, a
+// few lanes each, and 120 us instead of 106 (the LSTM shape with two CFs 107 -> 103 us).  16 KB per workgroup leave the occupancy to the registers.
+constexpr uint32_t STAGE = 512;   // entries a wavefront can hold
+static_assert(STAGE >= 2 * ROW && DENSE_SUB <= STAGE, "a row fits behind another, and a sub-tile with a candidate list in one piece");
+
 template <int NCF>  // compiled for calls with up to NCF CFs: the loops over the CFs are unrolled
 struct SubCtx {
     uint32_t lo_min, lo_c, pz;
     uint32_t lo[NCF];
     uint32_t sh[NCF];
     uint32_t top[NCF];
-    uint32_t ovn[NCF];     // entries above CF j's bracket ...
-    double ovs[NCF];       // ... and their sum of acc^2
-    bool split;            // the entries inside the brackets get a list of their own in every sub-tile
+    uint32_t ovn[NCF];     // entries above CF j's bracket (the same in all lanes) ...
+    double ovs[NCF];       // ... and their sum of acc^2 (this lane's share)
     uint32_t* h1;   // this wavefront's copy of the bracket histograms of the tile's segment ...
     uint32_t hstride;  // ... whose CFs are this many words apart
     int32_t* cidx;  // candidate-list slots of this sub-tile
@@ -1135,29 +1095,9 @@ struct SubCtx {
     double ssd;
     int ncf;
     uint32_t s0, s1;  // Random-k keys
+    uint2* stage;     // this wavefront's entries in LDS: index and value ...
+    uint32_t staged;  // ... and their number
 };
-
-// What one entry with key >= lo_min adds: per CF whose bracket starts at or below it, a count above the bracket or
-// a histogram update inside it.  Returns whether it lies inside some CF's bracket.
-template <int NCF>
-__device__ __forceinline__ bool bracket_count(SubCtx<NCF>& c, uint32_t key, float a)
-{
-    bool inside = false;
-#pragma unroll
-    for (int j = 0; j < NCF; ++j) {
-        if ((j == 0 || j < c.ncf) && key >= c.lo[j]) {
-            if (key >= c.top[j]) {
-                const double d = (double)a;
-                c.ovn[j]++;
-                c.ovs[j] += d * d;
-            } else {
-                atomicAdd(&c.h1[j * c.hstride + bin_word((key - c.lo[j]) >> c.sh[j])], 1u);
-                inside = true;
-            }
-        }
-    }
-    return inside;
-}
 
 __device__ __forceinline__ v4f ld_stream(const v4f* q)
 {
@@ -1185,67 +1125,99 @@ __device__ __forceinline__ void keys_of_row(const SubCtx<NCF>& c, const float a[
     for (int e = 0; e < 4; ++e) key[e] = RND ? priority_of(c.s0, c.s1, (uint32_t)(g + e)) : key_of(a[e]);
 }
 
-// One lane's four consecutive elements a[0..3] with keys key[0..3] at global index g; vm = validity bits;
-// listed = whether the sub-tile keeps a candidate list (the same for all lanes).
-template <bool SSD, bool RND, int NCF>
-__device__ __forceinline__ void consume(SubCtx<NCF>& c, const float a[4], const uint32_t key[4], int64_t g, unsigned vm, bool listed)
+// One lane's four consecutive elements a[0..3] with keys key[0..3] at global index g; vm = validity bits: those that some
+// bracket concerns are staged behind what is there (index order: lanes, then a lane's elements).
+template <int NCF>
+__device__ __forceinline__ void stage_row(SubCtx<NCF>& c, const float a[4], const uint32_t key[4], int64_t g, unsigned vm)
 {
     bool f[4];
+    uint64_t m[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-        const bool valid = (vm >> e) & 1u;
-        f[e] = valid && key[e] >= c.lo_min;
-        if (SSD) {
-            const double d = valid ? (double)a[e] : 0.0;
-            c.ssd += d * d;
-        }
+        f[e] = ((vm >> e) & 1u) && key[e] >= c.lo_min;
+        m[e] = __ballot(f[e]);
     }
-    if (__ballot(f[0] | f[1] | f[2] | f[3]) == 0ull) return;
-    bool fb[4], fm[4];
+    if ((m[0] | m[1] | m[2] | m[3]) == 0ull) return;
+    uint32_t w = c.staged;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) w += lanes_below(m[e]);
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-        fb[e] = f[e] ? bracket_count(c, key[e], a[e]) : false;
-        fm[e] = listed && f[e] && key[e] >= c.lo_c;
-    }
-    if (__ballot(fm[0] | fm[1] | fm[2] | fm[3]) != 0ull) {
-        uint32_t pre = 0, tot = 0;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const uint64_t m = __ballot(fm[e]);
-            pre += lanes_below(m);
-            tot += (uint32_t)__popcll(m);
+        if (f[e]) {
+            c.stage[w] = make_uint2((uint32_t)(g + e), __float_as_uint(a[e]));
+            ++w;
         }
-        uint32_t w = c.run + pre;
+        c.staged += (uint32_t)__popcll(m[e]);
+    }
+}
+
+// The same for a row of a sub-tile that keeps no candidate list.  Most of its entries lie above the bracket, which is all
+// there is to know of them: they are counted here, and only those inside it are staged (the VGG16 shape at CF 10, whose
+// convolutions are such sub-tiles: 397 -> 394 us).  For one CF: with more, the code costs every call registers (three CFs on
+// the ResNet101 shape 164 -> 168 us), and all entries are staged.
+__device__ __forceinline__ void stage_dense_row(SubCtx<1>& c, const float a[4], const uint32_t key[4], int64_t g)
+{
+    unsigned in = 0;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            if (fm[e]) {
-                c.cidx[w] = (int32_t)(g + e);
-                c.cval[w] = a[e];
-                ++w;
+    for (int e = 0; e < 4; ++e) {
+        const double d = (double)a[e], dd = d * d;
+        const bool from = key[e] >= c.lo[0], above = from && key[e] >= c.top[0];
+        c.ovn[0] += (uint32_t)__popcll(__ballot(above));
+        c.ovs[0] += above ? dd : 0.0;
+        in |= (from && !above) ? 1u << e : 0u;
+    }
+    stage_row<1>(c, a, key, g, in);
+}
+
+// The staged entries, 64 at a time: per CF a count and the energy of those above its bracket and a histogram update for
+// those inside it; into the lists.  listed = whether the sub-tile keeps a candidate list; counted = whether the entries above
+// the bracket have been counted.
+template <bool RND, int NCF>
+__device__ __forceinline__ void flush_stage(SubCtx<NCF>& c, bool listed, bool counted, int lane)
+{
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");  // the wavefront's own LDS writes, read back by other lanes
+#pragma unroll 1
+    for (uint32_t b = 0; b < c.staged; b += 64) {
+        const bool live = b + lane < c.staged;
+        const uint2 s = c.stage[b + lane];   // (b + lane < STAGE, a multiple of 64)
+        const float val = __uint_as_float(s.y);
+        const uint32_t key = RND ? priority_of(c.s0, c.s1, s.x) : key_of(val);
+        const double d = (double)val, dd = d * d;
+        bool inside = false;
+#pragma unroll
+        for (int j = 0; j < NCF; ++j) {
+            if (j == 0 || j < c.ncf) {
+                const bool from = live && key >= c.lo[j], above = from && key >= c.top[j];
+                if (!counted) {
+                    c.ovn[j] += (uint32_t)__popcll(__ballot(above));
+                    c.ovs[j] += above ? dd : 0.0;
+                }
+                if (from && !above) {
+                    atomicAdd(&c.h1[j * c.hstride + bin_word((key - c.lo[j]) >> c.sh[j])], 1u);
+                    inside = true;
+                }
             }
         }
-        c.run += tot;
-    }
-    // the entries inside the brackets: a list of their own, unless the candidate list holds them all
-    if ((c.split || !listed) && __ballot(fb[0] | fb[1] | fb[2] | fb[3]) != 0ull) {
-        uint32_t pre = 0, tot = 0;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const uint64_t m = __ballot(fb[e]);
-            pre += lanes_below(m);
-            tot += (uint32_t)__popcll(m);
-        }
-        uint32_t w = c.brun + pre;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            if (fb[e]) {
-                c.bkey[w] = key[e];
-                if (RND) c.bval[w] = a[e];
-                ++w;
+        if (listed) {
+            const bool cand = live && key >= c.lo_c;
+            const uint64_t m = __ballot(cand);
+            if (cand) {
+                const uint32_t w = c.run + lanes_below(m);
+                c.cidx[w] = (int32_t)s.x;
+                c.cval[w] = val;
             }
+            c.run += (uint32_t)__popcll(m);
         }
-        c.brun += tot;
+        const uint64_t m = __ballot(inside);
+        if (inside) {
+            const uint32_t w = c.brun + lanes_below(m);
+            c.bkey[w] = key;
+            if (RND) c.bval[w] = val;
+        }
+        c.brun += (uint32_t)__popcll(m);
     }
+    c.staged = 0;
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");  // read before the next entries overwrite them
 }
 
 // Modes of the pass.
@@ -1308,9 +1280,9 @@ struct ExactBounds {
     uint32_t* hist;        // the histograms' first copy of CF 0; LCAP words between copies
 };
 
-// One sub-tile v, by one wavefront.
+// One sub-tile v, by one wavefront; stage: STAGE entries of LDS of its own.
 template <int M, bool RND, int NCF>
-__device__ __forceinline__ void stream_subtile(const Params& p, uint32_t v, int lane, const ExactBounds* xb)
+__device__ __forceinline__ void stream_subtile(const Params& p, uint32_t v, int lane, const ExactBounds* xb, uint2* stage)
 {
     constexpr bool EF = (M != SM_EXACT);  // a first pass: sums acc^2, takes the brackets from the threshold kernel
     const uint32_t u = v / SUB;  // tile
@@ -1327,7 +1299,6 @@ __device__ __forceinline__ void stream_subtile(const Params& p, uint32_t v, int 
 
     SubCtx<NCF> c;
     c.ncf = p.n_cf;
-    c.split = p.split != 0;
     c.s0 = p.rk_s0; c.s1 = p.rk_s1;
     c.lo_min = NONE; c.lo_c = NONE; c.pz = NONE;
 #pragma unroll
@@ -1348,7 +1319,6 @@ __device__ __forceinline__ void stream_subtile(const Params& p, uint32_t v, int 
                 }
             }
         }
-        if (!c.split) c.lo_c = c.lo_min;  // the candidate list takes every entry that concerns some CF
     } else {
         static_assert(EF || NCF == MAXCF, "the exact route is compiled for any number of CFs");
 #pragma unroll
@@ -1359,7 +1329,6 @@ __device__ __forceinline__ void stream_subtile(const Params& p, uint32_t v, int 
                 if (j == p.commit) c.lo_c = c.lo[j];
             }
         }
-        if (!c.split) c.lo_c = c.lo_min;
     }
     // the copy of the histogram this wavefront adds to, spread by the sub-tile number
     c.hstride = seg_rep(p, t) * (EF ? NBIN : LCAP);
@@ -1372,17 +1341,23 @@ __device__ __forceinline__ void stream_subtile(const Params& p, uint32_t v, int 
     c.run = 0;
     c.brun = 0;
     c.ssd = 0.0;
+    c.stage = stage;
+    c.staged = 0;
 
     bool dense = false;
-    if (p.vec_ok && (s0 & 3) == 0 && e0 - s0 == TS) {
-        // a whole sub-tile: the loads of all its rows first, then the arithmetic
+    const bool whole = p.vec_ok && (s0 & 3) == 0 && e0 - s0 == TS;
+    const int64_t row0 = s0 & ~(int64_t)3;   // rows start at a multiple of 4 elements
+    float a[ROWS][4];
+    uint32_t rk[RND ? ROWS : 1][4];  // Random-k: the priorities, each computed once (four quarter-rate multiplications)
+    bool at_once = false;            // all rows are staged before the entries are worked on
+    int parts = (int)((e0 - row0 + ROW - 1) / ROW);
+    if (whole) {
+        // the loads of all rows first, then the arithmetic
         v4f x[ROWS], y[ROWS];
         v4i m[ROWS];
 #pragma unroll
         for (int q = 0; q < ROWS; ++q) row_load<M>(p, s0 + q * ROW + 4 * lane, x[q], y[q], m[q]);
-        float a[ROWS][4];
-        uint32_t rk[RND ? ROWS : 1][4];  // Random-k: the priorities, each computed once (four quarter-rate multiplications)
-        uint32_t nc = 0;  // candidates for the message in this sub-tile
+        uint32_t nc = 0, nm = 0;  // candidates for the message in this sub-tile, entries that some bracket concerns
 #pragma unroll
         for (int q = 0; q < ROWS; ++q) {
             row_finish<M>(p, x[q], y[q], m[q], a[q]);
@@ -1392,62 +1367,101 @@ __device__ __forceinline__ void stream_subtile(const Params& p, uint32_t v, int 
             for (int e = 0; e < 4; ++e) {
                 if (RND) rk[q][e] = key[e];
                 nc += (uint32_t)__popcll(__ballot(key[e] >= c.lo_c));
+                if (NCF > 1) nm += (uint32_t)__popcll(__ballot(key[e] >= c.lo_min));
+                if (EF) {
+                    const double d = (double)a[q][e];   // (the square is exact in binary64: rounded once, as a sum of its own)
+                    c.ssd = __builtin_fma(d, d, c.ssd);
+                }
             }
         }
+        if (NCF == 1) nm = nc;
         dense = nc >= DENSE_SUB;
+        if (M == SM_EF) {
+            // acc goes back into the residual; in a sub-tile that keeps a candidate list an entry above the committed
+            // CF's bracket leaves +0 there already: it is selected unless the bracket fails (the list keeps its value,
+            // and the exact route puts it back), which spares the emit step a scattered store per selected entry
+            const uint32_t z = dense ? NONE : c.pz;   // (a key is less than NONE)
 #pragma unroll
-        for (int q = 0; q < ROWS; ++q) {
-            const int64_t g = s0 + q * ROW + 4 * lane;
-            uint32_t key[4];
-            if (RND) {
+            for (int q = 0; q < ROWS; ++q) {
+                uint32_t key[4];
+                if (RND) {
 #pragma unroll
-                for (int e = 0; e < 4; ++e) key[e] = rk[q][e];
-            } else {
-                keys_of_row<RND, NCF>(c, a[q], g, key);
-            }
-            if (M == SM_EF) {
-                // acc goes back into the residual; in a sub-tile that keeps a candidate list an entry above the committed
-                // CF's bracket leaves +0 there already: it is selected unless the bracket fails (the list keeps its value,
-                // and the exact route puts it back), which spares the emit step a scattered store per selected entry
+                    for (int e = 0; e < 4; ++e) key[e] = rk[q][e];
+                } else {
+                    keys_of_row<RND, NCF>(c, a[q], 0, key);
+                }
                 v4f o;
-                o.x = (!dense && key[0] >= c.pz) ? 0.0f : a[q][0];
-                o.y = (!dense && key[1] >= c.pz) ? 0.0f : a[q][1];
-                o.z = (!dense && key[2] >= c.pz) ? 0.0f : a[q][2];
-                o.w = (!dense && key[3] >= c.pz) ? 0.0f : a[q][3];
-                st_stream(o, (v4f*)(p.res + g));
+                o.x = key[0] >= z ? 0.0f : a[q][0];
+                o.y = key[1] >= z ? 0.0f : a[q][1];
+                o.z = key[2] >= z ? 0.0f : a[q][2];
+                o.w = key[3] >= z ? 0.0f : a[q][3];
+                st_stream(o, (v4f*)(p.res + s0 + q * ROW + 4 * lane));
             }
-            consume<EF, RND, NCF>(c, a[q], key, g, 0xFu, !dense);
         }
-    } else {
-        // a ragged or unaligned sub-tile: element-wise, guarded; rows start at a multiple of 4 elements
-        for (int64_t rb = s0 & ~(int64_t)3; rb < e0; rb += ROW) {
-            const int64_t g = rb + 4 * lane;
-            float a[4];
-            unsigned vm = 0;
+        at_once = nm <= STAGE && !(NCF == 1 && dense);
+        parts = nm == 0u ? 0 : (at_once ? 1 : ROWS);
+    }
+#pragma unroll 1
+    for (int part = 0; part < parts; ++part) {
+        if (at_once) {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int64_t q = g + e;
-                a[e] = 0.0f;
-                if (q >= s0 && q < e0) {
-                    vm |= 1u << e;
-                    a[e] = element_load<M>(p, q);
+            for (int q = 0; q < ROWS; ++q) {
+                uint32_t key[4];
+                if (RND) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) key[e] = rk[q][e];
+                } else {
+                    keys_of_row<RND, NCF>(c, a[q], 0, key);
+                }
+                stage_row<NCF>(c, a[q], key, s0 + q * ROW + 4 * lane, 0xFu);
+            }
+        } else {
+            // a row at a time: one of many entries' rows, or the next of a ragged or unaligned sub-tile, element-wise, guarded
+            const int64_t g = row0 + part * ROW + 4 * lane;
+            unsigned vm = whole ? 0xFu : 0u;
+            if (!whole) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int64_t q = g + e;
+                    a[0][e] = 0.0f;
+                    if (q >= s0 && q < e0) {
+                        vm |= 1u << e;
+                        a[0][e] = element_load<M>(p, q);
+                    }
                 }
             }
             uint32_t key[4];
-            keys_of_row<RND, NCF>(c, a, g, key);
-            if (M == SM_EF) {
+            keys_of_row<RND, NCF>(c, a[0], g, key);
+            if (!whole) {
 #pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    if ((vm >> e) & 1u) p.res[g + e] = key[e] >= c.pz ? 0.0f : a[e];
+                for (int e = 0; e < 4; ++e) {
+                    if (!((vm >> e) & 1u)) continue;
+                    if (M == SM_EF) p.res[g + e] = key[e] >= c.pz ? 0.0f : a[0][e];
+                    if (EF) {
+                        const double d = (double)a[0][e];
+                        c.ssd = __builtin_fma(d, d, c.ssd);
+                    }
+                }
             }
-            consume<EF, RND, NCF>(c, a, key, g, vm, true);
+            if constexpr (NCF == 1) {
+                if (dense) stage_dense_row(c, a[0], key, g);
+                else stage_row<NCF>(c, a[0], key, g, vm);
+            } else {
+                stage_row<NCF>(c, a[0], key, g, vm);
+            }
+#pragma unroll
+            for (int q = 0; q + 1 < ROWS; ++q) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) a[q][e] = a[q + 1][e];
+            }
         }
+        if (part == parts - 1 || c.staged > STAGE - ROW) flush_stage<RND, NCF>(c, !dense, NCF == 1 && dense, lane);
     }
 
 #pragma unroll
     for (int j = 0; j < NCF; ++j) {
         if (j < p.n_cf) {
-            const uint32_t o = wave_sum(c.ovn[j]);
+            const uint32_t o = c.ovn[j];
             const double s = wave_sum(c.ovs[j]);
             if (lane == 0) {
                 p.ovn[(size_t)v * p.n_cf + j] = o;
@@ -1468,8 +1482,9 @@ template <int M, bool RND, int NCF>
 __global__ __launch_bounds__(WG) void stream_kernel(Params p)
 {
     static_assert(M != SM_EXACT, "the exact route is part of the plan step");
+    __shared__ uint2 stage[WAVES][STAGE];
     const uint32_t w = __builtin_amdgcn_readfirstlane(blockIdx.x * WAVES + (threadIdx.x >> 6));
-    stream_subtile<M, RND, NCF>(p, w, threadIdx.x & 63, nullptr);
+    stream_subtile<M, RND, NCF>(p, w, threadIdx.x & 63, nullptr, stage[threadIdx.x >> 6]);
 }
 
 // The candidates of sub-tile v that its first pass replaced by +0 in the residual get their values back (the
@@ -1561,8 +1576,10 @@ struct PlanShared {
     // Gradient magnitudes crowd into a few exponents, so most lanes of a wavefront hit the same few bins and LDS atomics
     // on one copy serialise 64-fold; CSUB copies cut that to 64 / CSUB.  (a row is one word longer than the histogram,
     // so that the CSUB counters of one bin lie in different banks)
-    uint32_t lh[CSUB][NBIN + 1];
+    // (once they are counted: the wavefronts' staged entries while the lists are collected again)
+    __attribute__((aligned(16))) uint32_t lh[CSUB][NBIN + 1];
 };
+static_assert(sizeof(uint32_t) * CSUB * (NBIN + 1) >= sizeof(uint2) * STAGE * PLAN_W, "the staged entries fit into the coarse counts' LDS");
 
 // All CFs' searches; setup(j, hist, copies, stride, extra, want) says what to search for CF j: a 2048-bin histogram (bin b
 // at bin_word(b)) in `copies` arrays `stride` words apart that are added up (16-byte aligned), and 64 more counts for the last bin, one per
@@ -1665,15 +1682,14 @@ __device__ __forceinline__ bool plan_barrier(const Params& p, PlanShared& sh, ui
 // One tile's entries of the bracket lists into the histograms (first copy of CF 0 at hist) of the CFs that are cut again.
 __device__ __forceinline__ void plan_recount(const Params& p, const PlanShared& sh, uint32_t u, uint32_t* hist, uint32_t copies, int lane)
 {
-    const TileRef tr = tile_ref(p, u);
-    const uint32_t cnt = tr.tl.total();
+    const TileLists tl = tile_lists(p.brk_cnt, u);
+    const uint32_t cnt = tl.total();
     for (uint32_t i0 = 0; i0 < cnt; i0 += 64 * 8) {
         uint32_t kq[8];
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
             const uint32_t i = i0 + q * 64 + lane;
-            float unused;
-            ref_entry(p, u, tr, i < cnt ? i : 0u, kq[q], unused);
+            kq[q] = p.brk_key[(size_t)u * TW + tl.slot(i < cnt ? i : 0u)];
         }
         for (int j = 0; j < p.n_cf; ++j) {
             if (!sh.cut[j]) continue;
@@ -1842,7 +1858,7 @@ __global__ __launch_bounds__(PLAN_T) void plan_kernel(Params p)
                 const uint32_t x = i / per_chunk, first = u0 + sh.own[x] * per;
                 if (full && phase == 1) {
                     const uint32_t v = __builtin_amdgcn_readfirstlane(first * SUB + (i - x * per_chunk));
-                    if (v < u1 * SUB) stream_subtile<SM_EXACT, RND, MAXCF>(p, v, lane, &sh.xb);
+                    if (v < u1 * SUB) stream_subtile<SM_EXACT, RND, MAXCF>(p, v, lane, &sh.xb, (uint2*)&sh.lh[0][0] + wib * STAGE);
                 } else {
                     const uint32_t u = first + (i - x * per_chunk);
                     if (u < u1) plan_recount(p, sh, u, hist, copies, lane);
@@ -1935,7 +1951,7 @@ __global__ __launch_bounds__(LWG) __attribute__((amdgpu_waves_per_eu((NCF == 3 |
     constexpr int SPEC_R = HEADS ? 4 : 1;
     uint32_t spec[SPEC_R];
     if constexpr (HEADS) {
-        const uint32_t* src = (p.split ? p.brk_key : (const uint32_t*)p.cand_val) + (size_t)u * TW + (size_t)(lane >> 3) * TS + (lane & 7);
+        const uint32_t* src = p.brk_key + (size_t)u * TW + (size_t)(lane >> 3) * TS + (lane & 7);
 #pragma unroll
         for (int r = 0; r < SPEC_R; ++r) spec[r] = src[8 * r];
     }
@@ -1958,8 +1974,8 @@ __global__ __launch_bounds__(LWG) __attribute__((amdgpu_waves_per_eu((NCF == 3 |
             mode[j] = st->mode; base[j] = st->base; span[j] = st->span; top[j] = st->top;
         }
     }
-    const TileRef tr = tile_ref(p, u);
-    const uint32_t cnt = tr.tl.total();
+    const TileLists tl = tile_lists(p.brk_cnt, u);
+    const uint32_t cnt = tl.total();
     uint32_t hn[NCF], tin = 0;
     double hs[NCF];
 #pragma unroll
@@ -2006,20 +2022,19 @@ __global__ __launch_bounds__(LWG) __attribute__((amdgpu_waves_per_eu((NCF == 3 |
         // 64 entries per load and lane-row, up to eight loads in flight per lane
         uint32_t i0 = 0;
         if constexpr (HEADS) {
-            // the lists' heads cover the tile if every list is its sub-tile's expected one and short enough
+            // the lists' heads cover the tile if every list is short enough
             bool heads = !p.random;
-            const uint32_t expect = p.split ? 0u : 0xFFu;
 #pragma unroll
-            for (int j = 0; j < SUB; ++j) heads = heads && tr.tl.start[j + 1] - tr.tl.start[j] <= 8u * SPEC_R;
-            if (heads && tr.main_mask == expect) {
+            for (int j = 0; j < SUB; ++j) heads = heads && tl.start[j + 1] - tl.start[j] <= 8u * SPEC_R;
+            if (heads) {
                 uint32_t mine_cnt = 0;
 #pragma unroll
-                for (int j = 0; j < SUB; ++j) if ((lane >> 3) == j) mine_cnt = tr.tl.start[j + 1] - tr.tl.start[j];
+                for (int j = 0; j < SUB; ++j) if ((lane >> 3) == j) mine_cnt = tl.start[j + 1] - tl.start[j];
 #pragma unroll 1
                 for (int r = 0; r < SPEC_R; ++r) {
                     if (__ballot((uint32_t)(lane & 7) + 8u * r < mine_cnt) == 0ull) break;
                     const uint32_t w = pop_front(spec);
-                    take(w & 0x7FFFFFFFu, 0.0f, (uint32_t)(lane & 7) + 8u * r < mine_cnt);
+                    take(w, 0.0f, (uint32_t)(lane & 7) + 8u * r < mine_cnt);
                 }
                 i0 = cnt;
             }
@@ -2032,14 +2047,8 @@ __global__ __launch_bounds__(LWG) __attribute__((amdgpu_waves_per_eu((NCF == 3 |
             // (decoded at once, the loads would be waited for at once).  The counts are the ones fetched with the
             // tile's first loads.
             constexpr int AHEAD = 4;
-            const auto counts = [&](int j, uint32_t& c, bool& from_main) {
-                c = 0;
-#pragma unroll
-                for (int x = 0; x < SUB; ++x) c = (x == j) ? tr.tl.start[x + 1] - tr.tl.start[x] : c;
-                from_main = (tr.main_mask >> j) & 1u;
-            };
             const auto fetch = [&](int j, uint32_t (&w)[2]) {
-                const uint32_t* src = (((tr.main_mask >> j) & 1u) ? (const uint32_t*)p.cand_val : p.brk_key) + (size_t)u * TW + (size_t)j * TS;
+                const uint32_t* src = p.brk_key + (size_t)u * TW + (size_t)j * TS;
 #pragma unroll
                 for (int q = 0; q < 2; ++q) w[q] = src[q * 64 + lane];
             };
@@ -2048,21 +2057,21 @@ __global__ __launch_bounds__(LWG) __attribute__((amdgpu_waves_per_eu((NCF == 3 |
             for (int a = 0; a < AHEAD; ++a) fetch(a, wq[a]);
 #pragma unroll 1
             for (int j = 0; j < SUB; ++j) {
-                uint32_t w0[2], c;
-                bool fm;
+                uint32_t w0[2], c = 0;
 #pragma unroll
                 for (int q = 0; q < 2; ++q) w0[q] = wq[0][q];
 #pragma unroll
                 for (int a = 0; a + 1 < AHEAD; ++a) { wq[a][0] = wq[a + 1][0]; wq[a][1] = wq[a + 1][1]; }
                 if (j + AHEAD < SUB) fetch(j + AHEAD, wq[AHEAD - 1]);
-                counts(j, c, fm);
-                const uint32_t* src = (fm ? (const uint32_t*)p.cand_val : p.brk_key) + (size_t)u * TW + (size_t)j * TS;
+#pragma unroll
+                for (int x = 0; x < SUB; ++x) c = (x == j) ? tl.start[x + 1] - tl.start[x] : c;
+                const uint32_t* src = p.brk_key + (size_t)u * TW + (size_t)j * TS;
 #pragma unroll 1
                 for (uint32_t b = 0; b < c; b += 64) {
                     const uint32_t w = w0[0];
                     w0[0] = w0[1];
                     if (b + 128 < c) w0[1] = src[(b + 128 + lane) & (TS - 1)];   // (the round after the next one)
-                    take(w & 0x7FFFFFFFu, 0.0f, b + lane < c);
+                    take(w, 0.0f, b + lane < c);
                 }
             }
             i0 = cnt;
@@ -2076,7 +2085,9 @@ __global__ __launch_bounds__(LWG) __attribute__((amdgpu_waves_per_eu((NCF == 3 |
                 kq[q] = 0; vq[q] = 0.0f;
                 if (i0 + q * 64 < cnt) {
                     const uint32_t i = i0 + q * 64 + lane;
-                    ref_entry(p, u, tr, i < cnt ? i : 0u, kq[q], vq[q]);
+                    const size_t at = (size_t)u * TW + tl.slot(i < cnt ? i : 0u);
+                    kq[q] = p.brk_key[at];
+                    if (p.random) vq[q] = p.brk_val[at];
                 }
             }
 #pragma unroll 1
@@ -4150,10 +4161,6 @@ static int compress_impl(const float* grad, float* residual, int64_t n, const do
     p.map_idx = map_idx; p.restore = restore; p.n_restore = restore ? n_restore : 0; p.single = single ? 1 : 0;
     // 16-byte accesses need 16-byte aligned buffers; anything else is read and written element by element
     p.vec_ok = (((uintptr_t)grad & 15) == 0 && ((uintptr_t)residual & 15) == 0 && ((uintptr_t)map_idx & 15) == 0) ? 1 : 0;
-    // (Random-k's brackets follow from k alone and hold few entries, 21,000 at CF 10 on the ResNet101 shape where the candidate
-    // lists hold 4.5 million: with a list of their own the refine step takes 7 us there instead of 23.  For Top-k at CF 10,
-    // whose brackets are a fifth as long as the candidate lists, it gained 6 to 12 us and the pass lost 7 to 13.)
-    p.split = (cf_list[commit] > cf_min || random) ? 1 : 0;
     p.no_commit = (flags & GRAVAC_FLAG_NO_COMMIT) ? 1 : 0;
     p.bounds_from = (flags & GRAVAC_FLAG_FORCE_FALLBACK) ? BOUNDS_FORCED : (random ? BOUNDS_RANDOM : BOUNDS_SAMPLED);
     p.wait_polls = stall ? WAIT_POLLS_TEST : WAIT_POLLS;
