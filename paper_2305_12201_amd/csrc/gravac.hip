@@ -232,7 +232,7 @@ struct Params {
     uint32_t* samp_hist; // [n_sample_blocks][SBIN / 2] sample histograms, two 16-bit counts per word
     uint32_t* samp_grp;  // [n_sample_blocks][SGRP] samples per group of SBIN / SGRP bins
     uint32_t* cand_cnt;  // [n_tiles][SUB] listed candidates of every sub-tile (| DENSE_BIT: none listed, the sub-tile is read again)
-    uint32_t* brk_cnt;   // [n_tiles][SUB] bracket-list entries of every sub-tile
+    uint32_t* brk_cnt;   // [n_tiles][SUB] bracket-list entries of every sub-tile (| zeros counted instead of listed << ZERO_SHIFT)
     uint32_t* ovn;       // [n_tiles][SUB][n_cf] entries of the sub-tile above CF j's bracket
     double* ovs;         // [n_tiles][SUB][n_cf] ... and their sum of acc^2
     uint32_t* tg0;       // [n_tiles] entries of the tile above the committed CF's located bin
@@ -303,15 +303,20 @@ __device__ __forceinline__ uint32_t sample_bin_first(uint32_t b, uint32_t w0)
 }
 __device__ __forceinline__ uint32_t sample_bin_end(uint32_t b, uint32_t w0) { return sample_bin_first(b + 1u, w0); }
 
-// The bracket histogram of a CF whose bracket is [lo, hi): the shift s is the smallest with which bins 0 .. OVF - 1
-// reach hi, and top is the first key past them (KEY_END if they reach past the largest key).
-__device__ __forceinline__ void bracket_bins(uint32_t lo, uint32_t hi, uint32_t& s, uint32_t& top)
+// The bracket histogram of a CF whose bracket is [lo, hi): bin (key - org) >> s, the shift the smallest with which bins
+// 0 .. OVF - 1 reach hi, and top the first key past them (KEY_END if they reach past the largest key).  org is lo, unless
+// the bracket starts at zero: then bin 0 is the key 0 alone.  Zeros are the one value that a gradient is likely to have a
+// mass of, and a k-th largest among them is resolved with the bin.
+__device__ __forceinline__ void bracket_bins(uint32_t lo, uint32_t hi, uint32_t& s, uint32_t& org, uint32_t& top)
 {
     const uint32_t span = hi > lo ? hi - lo : 0u;
     s = 0;
+    org = lo;
     if (span == 0u) { top = lo; return; }  // an empty bracket: every key from lo on counts as above it
-    while ((span >> s) > OVF - 1u) ++s;
-    const uint64_t t = (uint64_t)lo + ((uint64_t)OVF << s);
+    const uint32_t last = lo == 0u ? OVF - 2u : OVF - 1u;
+    while ((span >> s) > last) ++s;
+    if (lo == 0u) org = 1u - (1u << s);    // (wraps: (0 - org) >> s is 0, (1 - org) >> s is 1)
+    const uint64_t t = (uint64_t)lo + ((uint64_t)OVF << s) - (lo == 0u ? (1u << s) - 1u : 0u);
     top = t >= (uint64_t)KEY_END ? KEY_END : (uint32_t)t;
 }
 
@@ -444,9 +449,14 @@ __device__ __forceinline__ T pop_front(T (&v)[N])
     return x;
 }
 
+// A sub-tile's word in brk_cnt: entries in its bracket list, and the number of zeros that were counted instead of listed.
+constexpr uint32_t ZERO_SHIFT = 16, LISTED = (1u << ZERO_SHIFT) - 1u;
+static_assert(TS <= (int)LISTED, "both fit");
+
 // The entries of a tile's lists are the concatenation of its SUB sub-tile lists.
 struct TileLists {
     uint32_t start[SUB + 1];  // start[j] = entries in sub-tiles before j; start[SUB] = all
+    uint32_t zeros;           // the bracket lists: zeros that are not in them
     __device__ __forceinline__ uint32_t total() const { return start[SUB]; }
     // slot (relative to the tile's first slot) of the tile's i-th entry
     __device__ __forceinline__ uint32_t slot(uint32_t i) const
@@ -461,14 +471,17 @@ struct TileLists {
     }
 };
 
-// from the per-sub-tile counts cnt[u * SUB ..]
-__device__ __forceinline__ TileLists tile_lists(const uint32_t* cnt, uint32_t u)
+// the bracket lists
+__device__ __forceinline__ TileLists bracket_lists(const Params& p, uint32_t u)
 {
     TileLists c;
     c.start[0] = 0;
+    c.zeros = 0;
 #pragma unroll
     for (int j = 0; j < SUB; ++j) {
-        c.start[j + 1] = c.start[j] + cnt[(size_t)u * SUB + j];
+        const uint32_t x = p.brk_cnt[(size_t)u * SUB + j];
+        c.start[j + 1] = c.start[j] + (x & LISTED);
+        c.zeros += x >> ZERO_SHIFT;
     }
     return c;
 }
@@ -1080,6 +1093,7 @@ template <int NCF>  // compiled for calls with up to NCF CFs: the loops over the
 struct SubCtx {
     uint32_t lo_min, lo_c, pz;
     uint32_t lo[NCF];
+    uint32_t org[NCF];
     uint32_t sh[NCF];
     uint32_t top[NCF];
     uint32_t ovn[NCF];     // entries above CF j's bracket (the same in all lanes) ...
@@ -1161,7 +1175,7 @@ __device__ __forceinline__ void stage_dense_row(SubCtx<1>& c, const float a[4], 
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
         const double d = (double)a[e], dd = d * d;
-        const bool from = key[e] >= c.lo[0], above = from && key[e] >= c.top[0];
+        const bool from = key[e] >= c.lo_min, above = from && key[e] >= c.top[0];
         c.ovn[0] += (uint32_t)__popcll(__ballot(above));
         c.ovs[0] += above ? dd : 0.0;
         in |= (from && !above) ? 1u << e : 0u;
@@ -1192,10 +1206,11 @@ __device__ __forceinline__ void flush_stage(SubCtx<NCF>& c, bool listed, bool co
                     c.ovn[j] += (uint32_t)__popcll(__ballot(above));
                     c.ovs[j] += above ? dd : 0.0;
                 }
-                if (from && !above) {
-                    atomicAdd(&c.h1[j * c.hstride + bin_word((key - c.lo[j]) >> c.sh[j])], 1u);
-                    inside = true;
-                }
+                const bool in = from && !above;
+                const uint64_t m = __ballot(in);
+                if (m == 0ull) continue;
+                if (in) atomicAdd(&c.h1[j * c.hstride + bin_word((key - c.org[j]) >> c.sh[j])], 1u);
+                inside = inside || in;
             }
         }
         if (listed) {
@@ -1304,14 +1319,14 @@ __device__ __forceinline__ void stream_subtile(const Params& p, uint32_t v, int 
 #pragma unroll
     for (int j = 0; j < NCF; ++j) {
         c.ovn[j] = 0; c.ovs[j] = 0.0;
-        c.lo[j] = NONE; c.sh[j] = 0; c.top[j] = KEY_END;
+        c.lo[j] = NONE; c.org[j] = NONE; c.sh[j] = 0; c.top[j] = KEY_END;
     }
     if (EF) {
 #pragma unroll
         for (int j = 0; j < NCF; ++j) {
             if (j < p.n_cf) {
                 c.lo[j] = p.bnd_lo[(size_t)t * p.n_cf + j];
-                bracket_bins(c.lo[j], p.bnd_hi[(size_t)t * p.n_cf + j], c.sh[j], c.top[j]);
+                bracket_bins(c.lo[j], p.bnd_hi[(size_t)t * p.n_cf + j], c.sh[j], c.org[j], c.top[j]);
                 c.lo_min = c.lo[j] < c.lo_min ? c.lo[j] : c.lo_min;
                 if (j == p.commit) {
                     c.lo_c = c.lo[j];
@@ -1324,7 +1339,7 @@ __device__ __forceinline__ void stream_subtile(const Params& p, uint32_t v, int 
 #pragma unroll
         for (int j = 0; j < NCF; ++j) {
             if (j < p.n_cf) {
-                c.lo[j] = xb->lo[j]; c.sh[j] = xb->sh[j]; c.top[j] = xb->top[j];
+                c.lo[j] = c.org[j] = xb->lo[j]; c.sh[j] = xb->sh[j]; c.top[j] = xb->top[j];
                 c.lo_min = c.lo[j] < c.lo_min ? c.lo[j] : c.lo_min;
                 if (j == p.commit) c.lo_c = c.lo[j];
             }
@@ -1350,6 +1365,11 @@ __device__ __forceinline__ void stream_subtile(const Params& p, uint32_t v, int 
     float a[ROWS][4];
     uint32_t rk[RND ? ROWS : 1][4];  // Random-k: the priorities, each computed once (four quarter-rate multiplications)
     bool at_once = false;            // all rows are staged before the entries are worked on
+    // Zeros inside a bracket are only counted, not listed (whole sub-tiles of Top-k's first pass).  Where they may be
+    // selected, the committed CF's bracket starts at zero, all of the sub-tile are candidates and it keeps no list.
+    const bool skip_zeros = EF && !RND && whole && c.lo_min == 0u;
+    if (skip_zeros) c.lo_min = 1u;
+    uint32_t zeros = 0;
     int parts = (int)((e0 - row0 + ROW - 1) / ROW);
     if (whole) {
         // the loads of all rows first, then the arithmetic
@@ -1366,15 +1386,16 @@ __device__ __forceinline__ void stream_subtile(const Params& p, uint32_t v, int 
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 if (RND) rk[q][e] = key[e];
-                nc += (uint32_t)__popcll(__ballot(key[e] >= c.lo_c));
-                if (NCF > 1) nm += (uint32_t)__popcll(__ballot(key[e] >= c.lo_min));
+                nm += (uint32_t)__popcll(__ballot(key[e] >= c.lo_min));
+                if (NCF > 1) nc += (uint32_t)__popcll(__ballot(key[e] >= c.lo_c));
                 if (EF) {
                     const double d = (double)a[q][e];   // (the square is exact in binary64: rounded once, as a sum of its own)
                     c.ssd = __builtin_fma(d, d, c.ssd);
                 }
             }
         }
-        if (NCF == 1) nm = nc;
+        zeros = skip_zeros ? (uint32_t)TS - nm : 0u;
+        if (NCF == 1) nc = nm + zeros;
         dense = nc >= DENSE_SUB;
         if (M == SM_EF) {
             // acc goes back into the residual; in a sub-tile that keeps a candidate list an entry above the committed
@@ -1474,7 +1495,12 @@ __device__ __forceinline__ void stream_subtile(const Params& p, uint32_t v, int 
         const double s = wave_sum(c.ssd);
         if (lane == 0) p.ssd[v] = s;
     }
-    if (lane == 0) { p.cand_cnt[v] = dense ? DENSE_BIT : c.run; p.brk_cnt[v] = c.brun; }
+    if (zeros != 0u && lane == 0) {
+#pragma unroll
+        for (int j = 0; j < NCF; ++j)   // (a sampled bracket is not empty: zeros are inside one that starts there)
+            if (c.lo[j] == 0u) atomicAdd(&c.h1[j * c.hstride + bin_word(0u)], zeros);
+    }
+    if (lane == 0) { p.cand_cnt[v] = dense ? DENSE_BIT : c.run; p.brk_cnt[v] = c.brun | (zeros << ZERO_SHIFT); }
 }
 
 // The first pass (SM_EF, SM_SINGLE): one sub-tile per wavefront, one launch covers the whole gradient.
@@ -1512,20 +1538,21 @@ __device__ __forceinline__ void put_back_subtile(const Params& p, uint32_t v, ui
 
 // How the bin that holds the k-th largest gets resolved to one key.
 struct BinPlan {
-    uint32_t mode, base, span, above, c;
+    uint32_t mode, base, bits, above, c;   // (the bin spans 2^bits keys)
 };
 
-// Decide from the located bin (b, above, c) of the bracket histogram with bins (key - lo) >> s; what lies above the
+// Decide from the located bin (b, above, c) of the bracket histogram with bins (key - org) >> s; what lies above the
 // bracket arrives as bin OVF.
-__device__ __forceinline__ BinPlan plan_bin(uint32_t lo, uint32_t s, uint32_t b, uint32_t above, uint32_t c)
+__device__ __forceinline__ BinPlan plan_bin(uint32_t lo, uint32_t org, uint32_t s, uint32_t b, uint32_t above, uint32_t c)
 {
     BinPlan q;
+    const bool zero = lo == 0u && b == 0u;          // the bin of the key 0
     if (b == NONE || b == OVF) q.mode = MODE_FAIL;  // fewer than k entries from lo on, or the k-th lies above the bracket
-    else if (s == 0) q.mode = MODE_RESOLVED;
+    else if (s == 0 || zero) q.mode = MODE_RESOLVED;
     else if (c <= LCAP) q.mode = MODE_GATHER;
     else q.mode = MODE_FAIL;
-    q.base = (b == NONE || b == OVF) ? 0u : lo + (b << s);
-    q.span = (1u << s) - 1u;
+    q.base = (b == NONE || b == OVF || zero) ? 0u : org + (b << s);
+    q.bits = zero ? 0u : s;
     q.above = above;
     q.c = c;
     return q;
@@ -1682,7 +1709,7 @@ __device__ __forceinline__ bool plan_barrier(const Params& p, PlanShared& sh, ui
 // One tile's entries of the bracket lists into the histograms (first copy of CF 0 at hist) of the CFs that are cut again.
 __device__ __forceinline__ void plan_recount(const Params& p, const PlanShared& sh, uint32_t u, uint32_t* hist, uint32_t copies, int lane)
 {
-    const TileLists tl = tile_lists(p.brk_cnt, u);
+    const TileLists tl = bracket_lists(p, u);
     const uint32_t cnt = tl.total();
     for (uint32_t i0 = 0; i0 < cnt; i0 += 64 * 8) {
         uint32_t kq[8];
@@ -1745,13 +1772,13 @@ __global__ __launch_bounds__(PLAN_T) void plan_kernel(Params p)
     if (tid < p.n_cf) {
         const int j = tid;
         const uint32_t lo = b_lo;
-        uint32_t s, top;
-        bracket_bins(lo, b_hi, s, top);
+        uint32_t s, org, top;
+        bracket_bins(lo, b_hi, s, org, top);
         if (j == p.commit) sh.pz = zero_from(p, lo, top, b_mid);
         const uint32_t b = sh.fb[j];
-        const BinPlan q = plan_bin(lo, s, b, sh.fa[j], sh.fc[j]);
+        const BinPlan q = plan_bin(lo, org, s, b, sh.fa[j], sh.fc[j]);
         sh.k[j] = seg_k(p, t, j); sh.lo[j] = lo; sh.s[j] = s; sh.top[j] = top;
-        sh.mode[j] = q.mode; sh.base[j] = q.base; sh.above[j] = q.above; sh.c[j] = q.c; sh.bs[j] = s;
+        sh.mode[j] = q.mode; sh.base[j] = q.base; sh.above[j] = q.above; sh.c[j] = q.c; sh.bs[j] = q.bits;
     }
     __syncthreads();
     uint32_t kind = FAIL_NONE;
@@ -1974,7 +2001,7 @@ __global__ __launch_bounds__(LWG) __attribute__((amdgpu_waves_per_eu((NCF == 3 |
             mode[j] = st->mode; base[j] = st->base; span[j] = st->span; top[j] = st->top;
         }
     }
-    const TileLists tl = tile_lists(p.brk_cnt, u);
+    const TileLists tl = bracket_lists(p, u);
     const uint32_t cnt = tl.total();
     uint32_t hn[NCF], tin = 0;
     double hs[NCF];
@@ -2098,6 +2125,10 @@ __global__ __launch_bounds__(LWG) __attribute__((amdgpu_waves_per_eu((NCF == 3 |
             }
         }
     }
+    // zeros that the pass has counted and not listed are inside the located bin if that is theirs alone
+#pragma unroll
+    for (int j = 0; j < NCF; ++j)
+        if (j < p.n_cf && j == p.commit && mode[j] == MODE_RESOLVED && base[j] == 0u && lane == 0) tin += tl.zeros;
     // the tile's sums: what the pass over the gradient counted above the brackets, plus the above
     {
         const double x = wave_sum(ssd);
