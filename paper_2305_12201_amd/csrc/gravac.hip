@@ -166,6 +166,11 @@ struct Status {
 
 typedef float v4f __attribute__((ext_vector_type(4)));
 typedef int v4i __attribute__((ext_vector_type(4)));
+// The same at any address of a float: a gfx950 load or store of 16 bytes needs no more than 4-byte alignment, and a tensor
+// of a layerwise call starts anywhere (38 million elements as 387 tensors, three in four of which start off a multiple of four
+// elements: 153 us, with their elements one by one 213).
+typedef v4f v4fu __attribute__((aligned(4)));
+typedef v4i v4iu __attribute__((aligned(4)));
 
 // One tensor of a layerwise call.
 struct SegInfo {
@@ -192,7 +197,6 @@ struct Params {
     int single;              // 1 = single-source mode (second-level compression of a message)
     int random;              // 1 = Random-k: the order is that of a keyed priority of the index, not of |acc|
     int no_commit;           // 1: nothing is removed from the residual (it keeps acc); the caller commits a message later
-    int vec_ok;              // 1 if every buffer the kernels read or write with 16-byte accesses is aligned to 16 bytes
     uint32_t bounds_from;    // BOUNDS_*
     uint32_t fixed_key;      // BOUNDS_FIXED: the key of the caller's threshold; entries with key >= fixed_key are kept
     uint32_t wait_polls;     // polls after which a workgroup of the plan step stops waiting for the others
@@ -314,7 +318,8 @@ __device__ __forceinline__ void bracket_bins(uint32_t lo, uint32_t hi, uint32_t&
     org = lo;
     if (span == 0u) { top = lo; return; }  // an empty bracket: every key from lo on counts as above it
     const uint32_t last = lo == 0u ? OVF - 2u : OVF - 1u;
-    while ((span >> s) > last) ++s;
+    s = span >> 11 ? 21u - (uint32_t)__clz((int)span) : 0u;   // span >> s < 2^11
+    if ((span >> s) > last) ++s;
     if (lo == 0u) org = 1u - (1u << s);    // (wraps: (0 - org) >> s is 0, (1 - org) >> s is 1)
     const uint64_t t = (uint64_t)lo + ((uint64_t)OVF << s) - (lo == 0u ? (1u << s) - 1u : 0u);
     top = t >= (uint64_t)KEY_END ? KEY_END : (uint32_t)t;
@@ -1113,7 +1118,7 @@ struct SubCtx {
     uint32_t staged;  // ... and their number
 };
 
-__device__ __forceinline__ v4f ld_stream(const v4f* q)
+__device__ __forceinline__ v4f ld_stream(const v4fu* q)
 {
 #if GV_NT
     return __builtin_nontemporal_load(q);
@@ -1122,7 +1127,7 @@ __device__ __forceinline__ v4f ld_stream(const v4f* q)
 #endif
 }
 
-__device__ __forceinline__ void st_stream(v4f v, v4f* q)
+__device__ __forceinline__ void st_stream(v4f v, v4fu* q)
 {
 #if GV_NT
     __builtin_nontemporal_store(v, q);
@@ -1245,11 +1250,11 @@ enum { SM_EF = 0,      // acc = residual + grad, written back into residual
 template <int M>
 __device__ __forceinline__ void row_load(const Params& p, int64_t g, v4f& x, v4f& y, v4i& m)
 {
-    if (M == SM_EF) { x = ld_stream((const v4f*)(p.res + g)); y = ld_stream((const v4f*)(p.grad + g)); }
-    if (M == SM_EXACT) x = ld_stream((const v4f*)(p.acc + g));
+    if (M == SM_EF) { x = ld_stream((const v4fu*)(p.res + g)); y = ld_stream((const v4fu*)(p.grad + g)); }
+    if (M == SM_EXACT) x = ld_stream((const v4fu*)(p.acc + g));
     if (M == SM_SINGLE) {
-        y = ld_stream((const v4f*)(p.grad + g));
-        if (p.restore) m = *(const v4i*)(p.map_idx + g);
+        y = ld_stream((const v4fu*)(p.grad + g));
+        if (p.restore) m = *(const v4iu*)(p.map_idx + g);
     }
 }
 
@@ -1273,7 +1278,7 @@ __device__ __forceinline__ void row_finish(const Params& p, const v4f& x, const 
     }
 }
 
-// One element of a row that is not handled with 16-byte accesses.
+// One element of a ragged sub-tile's row.
 template <int M>
 __device__ __forceinline__ float element_load(const Params& p, int64_t q)
 {
@@ -1360,8 +1365,7 @@ __device__ __forceinline__ void stream_subtile(const Params& p, uint32_t v, int 
     c.staged = 0;
 
     bool dense = false;
-    const bool whole = p.vec_ok && (s0 & 3) == 0 && e0 - s0 == TS;
-    const int64_t row0 = s0 & ~(int64_t)3;   // rows start at a multiple of 4 elements
+    const bool whole = e0 - s0 == TS;
     float a[ROWS][4];
     uint32_t rk[RND ? ROWS : 1][4];  // Random-k: the priorities, each computed once (four quarter-rate multiplications)
     bool at_once = false;            // all rows are staged before the entries are worked on
@@ -1370,17 +1374,17 @@ __device__ __forceinline__ void stream_subtile(const Params& p, uint32_t v, int 
     const bool skip_zeros = EF && !RND && whole && c.lo_min == 0u;
     if (skip_zeros) c.lo_min = 1u;
     uint32_t zeros = 0;
-    int parts = (int)((e0 - row0 + ROW - 1) / ROW);
+    int parts = (int)((e0 - s0 + ROW - 1) / ROW);
     if (whole) {
         // the loads of all rows first, then the arithmetic
         v4f x[ROWS], y[ROWS];
-        v4i m[ROWS];
+        v4i mi[ROWS];
 #pragma unroll
-        for (int q = 0; q < ROWS; ++q) row_load<M>(p, s0 + q * ROW + 4 * lane, x[q], y[q], m[q]);
+        for (int q = 0; q < ROWS; ++q) row_load<M>(p, s0 + q * ROW + 4 * lane, x[q], y[q], mi[q]);
         uint32_t nc = 0, nm = 0;  // candidates for the message in this sub-tile, entries that some bracket concerns
 #pragma unroll
         for (int q = 0; q < ROWS; ++q) {
-            row_finish<M>(p, x[q], y[q], m[q], a[q]);
+            row_finish<M>(p, x[q], y[q], mi[q], a[q]);
             uint32_t key[4];
             keys_of_row<RND, NCF>(c, a[q], s0 + q * ROW + 4 * lane, key);
 #pragma unroll
@@ -1416,7 +1420,7 @@ __device__ __forceinline__ void stream_subtile(const Params& p, uint32_t v, int 
                 o.y = key[1] >= z ? 0.0f : a[q][1];
                 o.z = key[2] >= z ? 0.0f : a[q][2];
                 o.w = key[3] >= z ? 0.0f : a[q][3];
-                st_stream(o, (v4f*)(p.res + s0 + q * ROW + 4 * lane));
+                st_stream(o, (v4fu*)(p.res + s0 + q * ROW + 4 * lane));
             }
         }
         at_once = nm <= STAGE && !(NCF == 1 && dense);
@@ -1437,15 +1441,15 @@ __device__ __forceinline__ void stream_subtile(const Params& p, uint32_t v, int 
                 stage_row<NCF>(c, a[q], key, s0 + q * ROW + 4 * lane, 0xFu);
             }
         } else {
-            // a row at a time: one of many entries' rows, or the next of a ragged or unaligned sub-tile, element-wise, guarded
-            const int64_t g = row0 + part * ROW + 4 * lane;
+            // a row at a time: one of many entries' rows, or the next of a ragged sub-tile, element-wise, guarded
+            const int64_t g = s0 + part * ROW + 4 * lane;
             unsigned vm = whole ? 0xFu : 0u;
             if (!whole) {
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     const int64_t q = g + e;
                     a[0][e] = 0.0f;
-                    if (q >= s0 && q < e0) {
+                    if (q < e0) {
                         vm |= 1u << e;
                         a[0][e] = element_load<M>(p, q);
                     }
@@ -3010,7 +3014,7 @@ __device__ __forceinline__ void emit_tile(const Params& p, int t, uint32_t u, Em
     {
         const int64_t sn = tile0 + (int64_t)(__ffs((int)dmask) - 1) * TS;
 #pragma unroll
-        for (int q = 0; q < ROWS; ++q) nxt[q] = ld_stream((const v4f*)(p.acc + sn + q * ROW + 4 * lane));
+        for (int q = 0; q < ROWS; ++q) nxt[q] = ld_stream((const v4fu*)(p.acc + sn + q * ROW + 4 * lane));
     }
     // the first two rounds of the next sub-tile's list, loaded while this one is worked on, whatever they hold
     float vnx[2];
@@ -3055,7 +3059,7 @@ __device__ __forceinline__ void emit_tile(const Params& p, int t, uint32_t u, Em
             if (later != 0u) {
                 const int64_t sn = tile0 + (int64_t)(__ffs((int)later) - 1) * TS;
 #pragma unroll
-                for (int q = 0; q < ROWS; ++q) nxt[q] = ld_stream((const v4f*)(p.acc + sn + q * ROW + 4 * lane));
+                for (int q = 0; q < ROWS; ++q) nxt[q] = ld_stream((const v4fu*)(p.acc + sn + q * ROW + 4 * lane));
             }
         }
 #pragma unroll 1
@@ -3109,7 +3113,7 @@ __device__ __forceinline__ void emit_tile(const Params& p, int t, uint32_t u, Em
                 v4f r;
                 r.x = sel[0] ? 0.0f : a[0]; r.y = sel[1] ? 0.0f : a[1];
                 r.z = sel[2] ? 0.0f : a[2]; r.w = sel[3] ? 0.0f : a[3];
-                st_stream(r, (v4f*)(p.res + g));   // (non-temporal, as the loads: VGG16 shape at CF 10 408 -> 398 us)
+                st_stream(r, (v4fu*)(p.res + g));   // (non-temporal, as the loads: VGG16 shape at CF 10 408 -> 398 us)
             }
             staged += tot;
             x.erun += ties_row;
@@ -3365,7 +3369,7 @@ __device__ __forceinline__ void load_tile(const float* from, float* acc, int tid
     // (all loads of a thread in flight together)
     v4f tv[DTILE / 1024];
 #pragma unroll
-    for (int r = 0; r < NT; ++r) tv[r] = ld_stream((const v4f*)(from + r * 1024 + tid * 4));
+    for (int r = 0; r < NT; ++r) tv[r] = ld_stream((const v4fu*)(from + r * 1024 + tid * 4));
 #pragma unroll
     for (int r = NT; r < DTILE / 1024; ++r) tv[r] = *(const v4f*)(from + r * 1024 + tid * 4);
 #pragma unroll
@@ -3376,7 +3380,7 @@ template <int NT>  // rows written with hints
 __device__ __forceinline__ void store_tile(const float* acc, float* to, int tid)
 {
 #pragma unroll
-    for (int r = 0; r < NT; ++r) st_stream(*(const v4f*)(acc + r * 1024 + tid * 4), (v4f*)(to + r * 1024 + tid * 4));
+    for (int r = 0; r < NT; ++r) st_stream(*(const v4f*)(acc + r * 1024 + tid * 4), (v4fu*)(to + r * 1024 + tid * 4));
 #pragma unroll
     for (int r = NT; r < DTILE / 1024; ++r) *(v4f*)(to + r * 1024 + tid * 4) = *(const v4f*)(acc + r * 1024 + tid * 4);
 }
@@ -4190,8 +4194,6 @@ static int compress_impl(const float* grad, float* residual, int64_t n, const do
     std::memset(&p, 0, sizeof(p));
     p.grad = grad; p.res = residual; p.acc = single ? grad : residual;
     p.map_idx = map_idx; p.restore = restore; p.n_restore = restore ? n_restore : 0; p.single = single ? 1 : 0;
-    // 16-byte accesses need 16-byte aligned buffers; anything else is read and written element by element
-    p.vec_ok = (((uintptr_t)grad & 15) == 0 && ((uintptr_t)residual & 15) == 0 && ((uintptr_t)map_idx & 15) == 0) ? 1 : 0;
     p.no_commit = (flags & GRAVAC_FLAG_NO_COMMIT) ? 1 : 0;
     p.bounds_from = (flags & GRAVAC_FLAG_FORCE_FALLBACK) ? BOUNDS_FORCED : (random ? BOUNDS_RANDOM : BOUNDS_SAMPLED);
     p.wait_polls = stall ? WAIT_POLLS_TEST : WAIT_POLLS;
