@@ -99,6 +99,7 @@ constexpr uint32_t SCOARSE = SOCT << (23 - SCSHIFT), SFINE = SWIN << (23 - SFSHI
 constexpr uint32_t SUSED = SCOARSE + SFINE - SLESS;   // bins in use
 static_assert(SUSED <= (uint32_t)SBIN && (uint64_t)SKEY0 + ((uint64_t)SOCT << 23) <= 0x7F800000ull, "inside the finite keys");
 constexpr int SGRP = 8;             // the sample bins in SGRP groups: one workgroup of the threshold kernel each
+constexpr int RGRP = 64;            // ... and in RGRP groups, one wavefront of a flat call's pass each (bracket_role)
 constexpr int SAMPLE_BLOCK = 1024;  // samples per workgroup of the sampling kernel
 constexpr int SAMPLE_MAX = 65536;   // samples of a flat tensor at most (unless k n is large, see SAMPLE_MAX_FLAT)
 constexpr int SAMPLE_MAX_SEG = 32768;  // layerwise: samples per tensor at most (a tensor of up to twice that is read whole)
@@ -112,6 +113,8 @@ constexpr uint32_t CTILES = 64;     // tiles per partial sum of the tiles' count
 constexpr int XQ_WORDS = 8;         // a segment's work queue in the plan step: chunks claimed, then chunks done per phase
 constexpr int XQ_WIN = XQ_WORDS;    // ... and behind it the first key of its sample histogram's window
 constexpr int XQ_LINE = 32;         // words between two segments' queues: a cache line
+constexpr int BND_WORDS = 32;       // words of a segment's brackets, a cache line: lo, hi, mid and a spare one per CF
+static_assert(4 * GRAVAC_MAX_CF <= BND_WORDS, "a bracket per CF");
 constexpr uint32_t WAIT_POLLS = 1u << 26;  // polls after which a workgroup of the plan step gives up on the others: at least
                                            // half a minute, where the longest wait of a call is milliseconds
 constexpr uint32_t WAIT_POLLS_TEST = 256;  // ... and under GRAVAC_FLAG_STALL_FALLBACK
@@ -221,9 +224,8 @@ struct Params {
     Status* status;
     CfState* st;         // [n_seg][n_cf]
     SegState* seg;       // [n_seg]
-    uint32_t* bnd_lo;    // [n_seg][n_cf] the bracket of every CF as the threshold kernel found it: first key ...
-    uint32_t* bnd_hi;    // [n_seg][n_cf] ... and one past its last key (at most KEY_END)
-    uint32_t* bnd_mid;   // [n_seg][n_cf] the key the sample puts the k-th largest at (NONE: no estimate)
+    uint32_t* bnd;       // [n_seg][BND_WORDS] the bracket of every CF: first key, one past the last key (at most KEY_END), the key
+                         // the sample puts the k-th largest at (NONE: no estimate)
     uint32_t* hist1;     // [copy blocks][NBIN] bracket histograms: REP copies per CF of a large tensor, one otherwise
     uint32_t* ovfc;      // [n_seg][n_cf][64][32] counts above the bracket (the histogram's last bin), spread over
                          // 64 cache lines; word 0 of each line is used
@@ -234,7 +236,7 @@ struct Params {
     float* list_val;     //                          ... and value (written for Random-k only) of the listed entries
     uint32_t* list_cnt;  // [copy blocks][32] fill counts of the gather lists, one cache line each
     uint32_t* samp_hist; // [n_sample_blocks][SBIN / 2] sample histograms, two 16-bit counts per word
-    uint32_t* samp_grp;  // [n_sample_blocks][SGRP] samples per group of SBIN / SGRP bins
+    uint16_t* samp_above;  // [n_sample_blocks][RGRP] the block's samples above each group of SBIN / RGRP bins
     uint32_t* cand_cnt;  // [n_tiles][SUB] listed candidates of every sub-tile (| DENSE_BIT: none listed, the sub-tile is read again)
     uint32_t* brk_cnt;   // [n_tiles][SUB] bracket-list entries of every sub-tile (| zeros counted instead of listed << ZERO_SHIFT)
     uint32_t* ovn;       // [n_tiles][SUB][n_cf] entries of the sub-tile above CF j's bracket
@@ -731,6 +733,58 @@ __device__ __forceinline__ void small_segment(const Params& p, int t, SmallShare
     }
 }
 
+// A call's status record and, where the host knows it, the number of pairs: by one workgroup of its first kernel that has
+// something to do for every call of its kind.
+__device__ __forceinline__ void reset_status(const Params& p, uint32_t tid)
+{
+    if (tid != 0) return;
+    p.status->any_fail = 0; p.status->n_fail = 0; p.status->error = 0; p.status->n_seg = p.n_seg;
+    p.status->n_narrow = 0; p.status->count = 0;
+    if (p.out_count && p.bounds_from != BOUNDS_FIXED) *p.out_count = p.total_out;  // (else the last step knows it)
+}
+
+// The bracket of CF j of segment t where no sample is needed: it follows from k alone (Random-k) or is left empty (every
+// segment takes the exact route).  w: lo, hi, mid.
+__device__ __forceinline__ void known_bracket(const Params& p, int t, int j, uint32_t* w)
+{
+    uint32_t lo = NONE, hi = NONE, mid = NONE;
+    if (p.bounds_from == BOUNDS_RANDOM) {
+        // priorities are a keyed permutation of the 31-bit integers: the number of a tensor's nt indices
+        // with priority >= x is as good as binomial (nt, 1 - x / 2^31), so the bounds follow from k alone:
+        // x with k + ZMARGIN sqrt(k) + 2 expected above it, and x with k - ZMARGIN sqrt(k) - 2
+        const uint64_t nt = (uint64_t)(seg_end(p, t) - seg_begin(p, t));
+        const double k = (double)seg_k(p, t, j), w0 = ZMARGIN * sqrt(k) + 2.0;
+        const double q_lo = (k + w0) / (double)nt, q_hi = (k - w0) / (double)nt;
+        lo = q_lo >= 1.0 ? 0u : (uint32_t)floor(2147483648.0 * (1.0 - q_lo));
+        hi = q_hi <= 0.0 ? KEY_END : (uint32_t)ceil(2147483648.0 * (1.0 - q_hi));
+        mid = (uint32_t)floor(2147483648.0 * (1.0 - (k >= (double)nt ? 1.0 : k / (double)nt)));
+    }
+    w[0] = lo; w[1] = hi; w[2] = mid;
+}
+
+// Ranks in the sample, S of nt elements, whose keys are a bracket's ends and the estimate of the k-th largest.
+__device__ __forceinline__ void sampled_ranks(uint32_t k, uint32_t S, uint64_t nt, uint32_t& r_lo, uint32_t& r_hi, uint32_t& r_mid)
+{
+    r_lo = r_hi = r_mid = k;
+    if ((uint64_t)S == nt) return;   // the whole segment was read
+    // expected number of sampled keys among the k largest, widened by ZMARGIN standard deviations
+    const double m = (double)k * (double)S / (double)nt, sd = sqrt(m);
+    const double a = ceil(m + ZMARGIN * sd + 2.0), b = floor(m - ZMARGIN * sd - 2.0);
+    r_lo = (a >= 4.0e9) ? NONE : (uint32_t)a;
+    r_hi = (b < 1.0) ? 1u : (uint32_t)b;
+    r_mid = (m < 1.0) ? 1u : (m >= 4.0e9 ? NONE : (uint32_t)(m + 0.5));
+}
+
+// The r_mid-th sample from the top is the (r_mid - above)-th of the c in sample bin `bin`: that far down from the bin's upper
+// edge, as if the bin's samples were spread evenly over its keys.
+__device__ __forceinline__ uint32_t key_inside(uint32_t bin, uint32_t w0, uint32_t down_of, uint32_t c)
+{
+    const uint32_t first = sample_bin_first(bin, w0), end = sample_bin_end(bin, w0);
+    // (an estimate: single precision will do, and keeps a 64-bit division out of the kernel)
+    const uint32_t down = (uint32_t)((float)(end - first) * ((float)down_of / (float)c));
+    return down >= end - first ? first : end - down;
+}
+
 // ---------------------------------------------------------------------------------------------
 // K0a: sample acc = residual + grad at stratified positions; each workgroup histograms its samples in
 // LDS (SBIN bins, see sample_bin) and stores the counts as 16-bit numbers, and the
@@ -746,7 +800,7 @@ __global__ __launch_bounds__(256) void sample_kernel(Params p)
     const int t = is_flat(p) ? 0 : (int)p.sblock_seg[b];
     const uint32_t lb = b - (is_flat(p) ? 0u : p.segs[t].samp0);
     const uint32_t S = is_flat(p) ? p.flat_samples : p.segs[t].samp_cnt;
-    {
+    const auto clear = [&]() {
         // the segment's sample blocks share the clearing: block lb of nbk takes every nbk-th 16-byte piece
         const uint32_t per = SAMPLE_BLOCK * R;
         const uint32_t nbk = is_flat(p) ? p.n_sample_blocks : (S + per - 1) / per;
@@ -759,14 +813,20 @@ __global__ __launch_bounds__(256) void sample_kernel(Params p)
         for (uint32_t i = lb * 256 + tid; i < (uint32_t)p.n_cf * 64; i += nbk * 256) p.ovfc[((size_t)t * p.n_cf * 64 + i) * 32] = 0;
         for (uint32_t i = lb * 256 + tid; i < blocks; i += nbk * 256) p.list_cnt[(seg_block(p, t, 0) + i) * 32] = 0;
         if (lb == 0 && tid < XQ_WORDS) p.xq[(size_t)t * XQ_LINE + tid] = 0;
+        if (is_flat(p)) {
+            // what a flat call has no threshold step for
+            if (b == 0) reset_status(p, tid);
+            if (b == 0 && p.bounds_from != BOUNDS_SAMPLED && tid < p.n_cf) known_bracket(p, 0, tid, p.bnd + 4 * tid);
+        }
         if (p.csum)
             for (uint32_t i = b * 256 + tid; i < (p.n_tiles + CTILES - 1u) / CTILES; i += gridDim.x * 256) p.csum[(size_t)i * 8] = 0;
+    };
+    if (p.bounds_from != BOUNDS_SAMPLED) {
+        clear();
+        return;
     }
-    if (p.bounds_from != BOUNDS_SAMPLED) return;
     const int64_t s0 = seg_begin(p, t);
     const uint64_t nt = (uint64_t)(seg_end(p, t) - s0);
-#pragma unroll
-    for (int q = 0; q < SBIN / 256; ++q) h[q * 256 + tid] = 0;
     // The window: every block of the segment looks at the same 256 elements, 64 groups of four spread evenly, and takes the
     // exponent of the largest (an infinite or NaN one does not count).  Their loads are issued before the sample's and
     // arrive with them.  (256 single elements are four times the memory the sample itself takes: a call with 1000 tensors of
@@ -783,11 +843,12 @@ __global__ __launch_bounds__(256) void sample_kernel(Params p)
     constexpr int Q = 4 * R;
     uint64_t gpos[R];
     bool live[Q];
-    // stratum g16 of G = S / 16 spans [g16 nt / G, (g16 + 1) nt / G): with nt = G qd + rm that is g16 qd + g16 rm / G, one
-    // 64-bit division per thread and 32-bit ones per stratum (g16 rm < G^2 <= 2^30) instead of 64-bit ones throughout
+    // stratum g of G = S / 16 spans [g step / 2^32, (g + 1) step / 2^32) with step = 2^32 nt / G, which is off by less than 2^10
+    // and G less than 2^15: the last stratum ends at nt or just before.  (64-bit and 32-bit divisions for the exact ends and the
+    // place inside took 1 us before the first load.)
     const uint32_t G = S / 16 ? S / 16 : 1u;
-    const uint64_t qd = nt / G;
-    const uint32_t rm = (uint32_t)(nt - qd * G);
+    static_assert(SAMPLE_MAX_FLAT / 16 <= 1 << 15, "g step fits 64 bits: nt < 2^31");
+    const uint64_t step = (uint64_t)((double)nt * 4294967296.0 / (double)G);
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         const uint32_t g = (lb * R + r) * (SAMPLE_BLOCK / 4) + tid;  // group
@@ -796,10 +857,10 @@ __global__ __launch_bounds__(256) void sample_kernel(Params p)
             // four neighbouring threads share one stratum and one run of 16 elements in it that starts at a multiple
             // of 16 in the flat buffer (a 64-byte line if the buffer is aligned to that)
             const uint32_t g16 = g >> 2;
-            const uint64_t a = (uint64_t)g16 * qd + (g16 * rm) / G, e = (uint64_t)(g16 + 1) * qd + ((g16 + 1) * rm) / G;  // e - a >= 32
+            const uint64_t a = (g16 * step) >> 32, e = ((g16 + 1u) * step) >> 32;     // e - a >= 32 (nt > 32 G), e <= nt
             const uint64_t first = ((uint64_t)s0 + a + 15) & ~15ull;                 // first such run inside the stratum
             const uint32_t runs = (uint32_t)(((uint64_t)s0 + e - first) / 16);        // >= 1
-            const uint64_t at = first + 16ull * (hash32(g16 * 0x9E3779B9u + 0x85EBCA6Bu) % runs);
+            const uint64_t at = first + 16ull * __umulhi(hash32(g16 * 0x9E3779B9u + 0x85EBCA6Bu), runs);
             gpos[r] = (at - (uint64_t)s0) + 4u * (g & 3u);                            // gpos + 3 < e <= nt
         }
 #pragma unroll
@@ -821,6 +882,10 @@ __global__ __launch_bounds__(256) void sample_kernel(Params p)
             rv[q] = p.res[s0 + (int64_t)pos];
         }
     }
+    // while they are on their way
+    clear();
+#pragma unroll
+    for (int q = 0; q < SBIN / 256; ++q) h[q * 256 + tid] = 0;
     const uint32_t wk = key_of(p.single ? wg : wr + wg);
     const double m = wave_max(wk < 0x7F800000u ? (double)(wk >> 23) : 0.0);
     if ((tid & 63) == 0) wexp[tid >> 6] = (uint32_t)m;
@@ -854,16 +919,20 @@ __global__ __launch_bounds__(256) void sample_kernel(Params p)
     uint4* dst = (uint4*)(p.samp_hist + (size_t)b * (SBIN / 2) + 8 * tid);
     dst[0] = w[0];
     dst[1] = w[1];
-    // a group of SBIN / SGRP = 512 bins is what 32 neighbouring threads hold: half a wavefront
-    static_assert(SBIN / SGRP == 32 * 16 && SGRP == 8, "one group per half wavefront");
+    // what lies above each group of SBIN / RGRP = 64 bins, four neighbouring threads' (a block's samples fit 16 bits)
+    static_assert(SBIN / RGRP == 4 * 16, "four threads per group");
+    const uint32_t incl = wave_scan(mine);
+    if ((tid & 63) == 63) wexp[tid >> 6] = incl;   // (read before the last barrier)
+    __syncthreads();
+    uint32_t above = last_lane(incl) - incl;
 #pragma unroll
-    for (int o = 16; o > 0; o >>= 1) mine += __shfl_xor(mine, o, 64);
-    if ((tid & 31) == 0) p.samp_grp[(size_t)b * SGRP + (tid >> 5)] = mine;
+    for (uint32_t w = 0; w < 4; ++w) above += w > (tid >> 6) ? wexp[w] : 0u;
+    if ((tid & 3) == 3) p.samp_above[(size_t)b * RGRP + (tid >> 2)] = (uint16_t)above;
 }
 
 // ---------------------------------------------------------------------------------------------
-// K0b: per segment, add up the sample histograms and turn the sampled ranks into a bracket of keys per
-// CF.  G workgroups per segment; workgroup y adds up the bins [y, y + 1) * SBIN / G of all the
+// K0b: layerwise, per segment, add up the sample histograms and turn the sampled ranks into a bracket of keys per
+// CF.  (A flat call's pass over the gradient does that itself, bracket_role.)  G workgroups per segment; workgroup y adds up the bins [y, y + 1) * SBIN / G of all the
 // segment's sample blocks (what lies above them it knows from the blocks' group counts) and writes the
 // bracket ends that fall into its bins, so that no workgroup waits for another.  The kernels that
 // use the brackets derive the histogram shift and the rest from them (bracket_bins).
@@ -879,16 +948,12 @@ __global__ __launch_bounds__(P * 1024 / G) __attribute__((amdgpu_waves_per_eu(SM
     static_assert(P * 1024 / G <= 1024 && (G > 1 || P == 1), "threads of a workgroup");
     constexpr int NW = T / 64;
     static_assert(G == 1 || G == SGRP, "one workgroup per group of bins, or one for all");
-    __shared__ uint32_t wtot[NW], gab[NW], gto[NW];
+    __shared__ uint32_t wtot[NW], gab[NW];
     __shared__ uint32_t rank_lo[MAXCF], rank_hi[MAXCF], rank_mid[MAXCF];
     __shared__ uint32_t hx[P > 1 ? P - 1 : 1][P > 1 ? T : 1][4];
     const int t = blockIdx.x, y = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wib = tid >> 6;
     const int part = tid / T, ot = tid - part * T;
-    if (t == 0 && y == 0 && tid == 0) {
-        p.status->any_fail = 0; p.status->n_fail = 0; p.status->error = 0; p.status->n_seg = p.n_seg;
-        p.status->n_narrow = 0; p.status->count = 0;
-        if (p.out_count && p.bounds_from != BOUNDS_FIXED) *p.out_count = p.total_out;  // (else the scan knows it)
-    }
+    if (t == 0 && y == 0) reset_status(p, (uint32_t)tid);
     if constexpr (SMALL) {
         static_assert(G == 1 && SM_T == 1024, "the small tensors' workgroups are this kernel's");
         __shared__ SmallShared small;
@@ -897,87 +962,26 @@ __global__ __launch_bounds__(P * 1024 / G) __attribute__((amdgpu_waves_per_eu(SM
             return;
         }
     }
-    const uint32_t S = is_flat(p) ? p.flat_samples : p.segs[t].samp_cnt;
-    const uint32_t sb0 = is_flat(p) ? 0u : p.segs[t].samp0;
-    const uint32_t nb = is_flat(p) ? p.n_sample_blocks : (S + SAMPLE_BLOCK - 1) / SAMPLE_BLOCK;
+    const uint32_t S = p.segs[t].samp_cnt;
+    const uint32_t sb0 = p.segs[t].samp0;
+    const uint32_t nb = (S + SAMPLE_BLOCK - 1) / SAMPLE_BLOCK;
     const uint64_t nt = (uint64_t)(seg_end(p, t) - seg_begin(p, t));
-    const bool whole = ((uint64_t)S == nt);
-    const bool sampled = p.bounds_from == BOUNDS_SAMPLED;
+    uint32_t* bnd = p.bnd + (size_t)t * BND_WORDS;
     if (y == 0) {
-        if (!is_flat(p))
-            for (uint32_t u = seg_tile0(p, t) + tid; u < seg_tile1(p, t); u += T * P) p.tseg[u] = (uint32_t)t;
-        if (!is_flat(p) && p.wseg)
+        for (uint32_t u = seg_tile0(p, t) + tid; u < seg_tile1(p, t); u += T * P) p.tseg[u] = (uint32_t)t;
+        if (p.wseg)
             for (uint32_t i = tid; i < p.segs[t].wgs; i += T * P) p.wseg[p.segs[t].wg0 + i] = (uint32_t)t;
     }
-    if (tid < p.n_cf) {
-        const uint32_t k = seg_k(p, t, tid);
-        uint32_t r_lo, r_hi, r_mid;
-        if (whole) {
-            r_lo = r_hi = r_mid = k;
-        } else {
-            // expected number of sampled keys among the k largest, widened by ZMARGIN standard deviations
-            const double m = (double)k * (double)S / (double)nt, sd = sqrt(m);
-            const double a = ceil(m + ZMARGIN * sd + 2.0), b = floor(m - ZMARGIN * sd - 2.0);
-            r_lo = (a >= 4.0e9) ? NONE : (uint32_t)a;
-            r_hi = (b < 1.0) ? 1u : (uint32_t)b;
-            r_mid = (m < 1.0) ? 1u : (m >= 4.0e9 ? NONE : (uint32_t)(m + 0.5));
-        }
-        rank_lo[tid] = r_lo; rank_hi[tid] = r_hi; rank_mid[tid] = r_mid;
-    }
-    if (p.bounds_from == BOUNDS_FIXED) {
-        // the threshold sparsifier (one flat tensor, one "CF"): an empty bracket at the caller's threshold, so that the
-        // pass over the gradient counts and lists what lies at or above it; the later steps find everything resolved:
-        // selected <=> key > tau with tau one key below the threshold, no ties to take
-        if (p.csum)
-            for (uint32_t i = tid; i < (p.n_tiles + CTILES - 1u) / CTILES; i += T * P) p.csum[(size_t)i * 8] = 0;
-        if (tid == 0) {
-            p.bnd_lo[0] = p.fixed_key; p.bnd_hi[0] = p.fixed_key; p.bnd_mid[0] = NONE;
-            CfState st;
-            st.k = 0; st.lo = p.fixed_key; st.s = 0; st.mode = MODE_RESOLVED; st.base = p.fixed_key; st.span = 0;
-            st.above = 0; st.c = 0; st.tau = p.fixed_key - 1u; st.need = 0; st.cnt_gt = 0;
-            st.top = p.fixed_key; st.pad[0] = st.pad[1] = st.pad[2] = st.pad[3] = 0;
-            p.st[0] = st;
-            SegState sg;
-            sg.fail = FAIL_NONE; sg.pz = p.single ? NONE : p.fixed_key;
-            p.seg[0] = sg;
-        }
+    if (p.bounds_from != BOUNDS_SAMPLED) {
+        if (y == 0 && tid < p.n_cf) known_bracket(p, t, tid, bnd + 4 * tid);
         return;
     }
-    if (!sampled) {
-        // no sample: the brackets follow from k alone (Random-k) or are left empty (every segment takes the exact route)
-        if (y == 0 && tid < p.n_cf) {
-            uint32_t lo = NONE, hi = NONE, mid = NONE;
-            if (p.bounds_from == BOUNDS_RANDOM) {
-                // priorities are a keyed permutation of the 31-bit integers: the number of a tensor's nt indices
-                // with priority >= x is as good as binomial (nt, 1 - x / 2^31), so the bounds follow from k alone:
-                // x with k + ZMARGIN sqrt(k) + 2 expected above it, and x with k - ZMARGIN sqrt(k) - 2
-                const double k = (double)seg_k(p, t, tid), w = ZMARGIN * sqrt(k) + 2.0;
-                const double q_lo = (k + w) / (double)nt, q_hi = (k - w) / (double)nt;
-                lo = q_lo >= 1.0 ? 0u : (uint32_t)floor(2147483648.0 * (1.0 - q_lo));
-                hi = q_hi <= 0.0 ? KEY_END : (uint32_t)ceil(2147483648.0 * (1.0 - q_hi));
-                mid = (uint32_t)floor(2147483648.0 * (1.0 - (k >= (double)nt ? 1.0 : k / (double)nt)));
-            }
-            p.bnd_lo[(size_t)t * p.n_cf + tid] = lo;
-            p.bnd_hi[(size_t)t * p.n_cf + tid] = hi;
-            p.bnd_mid[(size_t)t * p.n_cf + tid] = mid;
-        }
-        return;
-    }
-    // samples in the groups of bins above this workgroup's, and in all
-    // (the group counts of up to two blocks per thread are fetched first and added up after the histograms, so that
-    // both sets of loads are in flight together)
+    if (tid < p.n_cf) sampled_ranks(seg_k(p, t, tid), S, nt, rank_lo[tid], rank_hi[tid], rank_mid[tid]);
+    // samples in the groups of bins above this workgroup's (fetched first and added up after the histograms)
     const uint32_t w0 = p.xq[(size_t)t * XQ_LINE + XQ_WIN];
-    uint32_t g_above = 0, g_total = 0;
-    uint4 ga[2][2];
-    static_assert(G == 1 || 2 * (1024 / G) >= 2 * DENSE_BLOCKS, "two blocks' group counts per thread cover a flat sample");
-    if (G > 1 && part == 0) {
-#pragma unroll
-        for (int x = 0; x < 2; ++x) {
-            const uint32_t b = ot + x * T;
-            const uint4* gp = (const uint4*)(p.samp_grp + (size_t)(sb0 + (b < nb ? b : 0u)) * SGRP);
-            ga[x][0] = gp[0]; ga[x][1] = gp[1];
-        }
-    }
+    uint32_t g_above = 0;
+    static_assert(G == 1 || 1024 / G >= SAMPLE_MAX_SEG * 2 / SAMPLE_BLOCK, "a block's count per thread covers a tensor's sample");
+    if (G > 1 && part == 0 && (uint32_t)ot < nb) g_above = p.samp_above[(size_t)(sb0 + ot) * RGRP + (y + 1) * (RGRP / SGRP) - 1];
     uint32_t h0 = 0, h1 = 0, h2 = 0, h3 = 0;
     {
         const uint2* src = (const uint2*)(p.samp_hist + (size_t)sb0 * (SBIN / 2)) + (y * T + ot);
@@ -1006,19 +1010,8 @@ __global__ __launch_bounds__(P * 1024 / G) __attribute__((amdgpu_waves_per_eu(SM
         }
     }
     if (G > 1 && part == 0) {
-#pragma unroll
-        for (int x = 0; x < 2; ++x) {
-            if (ot + x * T >= nb) continue;
-            const uint32_t v[8] = {ga[x][0].x, ga[x][0].y, ga[x][0].z, ga[x][0].w, ga[x][1].x, ga[x][1].y, ga[x][1].z, ga[x][1].w};
-#pragma unroll
-            for (int g = 0; g < 8; ++g) {
-                g_total += v[g];
-                if (g > y) g_above += v[g];
-            }
-        }
         g_above = wave_sum(g_above);
-        g_total = wave_sum(g_total);
-        if (lane == 0) { gab[wib] = g_above; gto[wib] = g_total; }
+        if (lane == 0) gab[wib] = g_above;
     }
     const uint32_t mine = h0 + h1 + h2 + h3;
     const uint32_t incl = wave_scan(mine);
@@ -1026,44 +1019,95 @@ __global__ __launch_bounds__(P * 1024 / G) __attribute__((amdgpu_waves_per_eu(SM
     __syncthreads();
     if (part != 0) return;   // (no barrier follows)
     uint32_t local = 0, before = 0;
-    g_above = 0; g_total = 0;
+    g_above = 0;
 #pragma unroll
     for (int w = 0; w < NW; ++w) {
         const uint32_t x = wtot[w];
         local += x;
         if (w < wib) before += x;
-        if (G > 1) { g_above += gab[w]; g_total += gto[w]; }
+        if (G > 1) g_above += gab[w];
     }
-    if (G == 1) g_total = local;
     const uint32_t above0 = g_above + local - (before + incl);  // samples in bins above this thread's four
     const uint32_t hh[4] = {h0, h1, h2, h3};
     for (int j = 0; j < p.n_cf; ++j) {
         const uint32_t r_lo = rank_lo[j], r_hi = rank_hi[j], r_mid = rank_mid[j];
-        const size_t id = (size_t)t * p.n_cf + j;
         uint32_t above = above0;
 #pragma unroll
         for (int q = 3; q >= 0; --q) {
             const uint32_t c = hh[q];
             const uint32_t bin = 4u * (uint32_t)(y * T + ot) + (uint32_t)q;
             // lower edge of the bin of the r_lo-th sample from the top, upper edge of the bin of the r_hi-th
-            if (above < r_lo && above + c >= r_lo) p.bnd_lo[id] = sample_bin_first(bin, w0);
-            if (above < r_hi && above + c >= r_hi) p.bnd_hi[id] = sample_bin_end(bin, w0);
-            if (above < r_mid && above + c >= r_mid) {
-                // the r_mid-th sample from the top is the (r_mid - above)-th of the c in this bin: that far down from
-                // the bin's upper edge, as if the bin's samples were spread evenly over its keys
-                const uint32_t first = sample_bin_first(bin, w0), end = sample_bin_end(bin, w0);
-                // (an estimate: single precision will do, and keeps a 64-bit division out of this kernel)
-                const uint32_t down = (uint32_t)((float)(end - first) * ((float)(r_mid - above) / (float)c));
-                p.bnd_mid[id] = down >= end - first ? first : end - down;
-            }
+            if (above < r_lo && above + c >= r_lo) bnd[4 * j] = sample_bin_first(bin, w0);
+            if (above < r_hi && above + c >= r_hi) bnd[4 * j + 1] = sample_bin_end(bin, w0);
+            if (above < r_mid && above + c >= r_mid) bnd[4 * j + 2] = key_inside(bin, w0, r_mid - above, c);
             above += c;
         }
         // fewer samples than a rank: the bracket is open on that side
         if (y == 0 && tid == 0) {
-            if (g_total < r_lo) p.bnd_lo[id] = 0u;
-            if (g_total < r_hi) p.bnd_hi[id] = KEY_END;
-            if (g_total < r_mid) p.bnd_mid[id] = NONE;
+            if (S < r_lo) bnd[4 * j] = 0u;
+            if (S < r_hi) bnd[4 * j + 1] = KEY_END;
+            if (S < r_mid) bnd[4 * j + 2] = NONE;
         }
+    }
+}
+
+// A flat call's brackets: RGRP wavefronts, each of which adds up one group of bins of all sample blocks' histograms (what
+// lies above them it knows from the blocks themselves) and writes the bracket ends that fall into its bins.  No wavefront
+// waits for another, and up to 64 blocks are one round trip to memory.
+// (As a part of the pass, whose other wavefronts waited for it with their loads on their way, it was no faster: under the
+// pass's own traffic the round trips take two to three times as long.  25 MB buckets 64 -> 66 us, the ResNet101 shape 123.4
+// -> 121.7 at CF 100 and 164 -> 167 with three CFs.)
+__global__ __launch_bounds__(64) void bracket_kernel(Params p)
+{
+    const uint32_t role = blockIdx.x, nb = p.n_sample_blocks, S = p.flat_samples;
+    const int lane = threadIdx.x;
+    // (one round trip for up to 64 blocks: what lies above the group in block `lane`, two bins of every second block)
+    const uint32_t w0 = p.xq[XQ_WIN], k = p.flat_k[lane < p.n_cf ? lane : 0];
+    uint32_t g_above = 0;
+    for (uint32_t b = lane; b < nb; b += 64) g_above += p.samp_above[b * RGRP + role];
+    static_assert(SBIN / RGRP == 64 && RGRP == 64, "half a wavefront covers a group's words, two bins each");
+    const uint32_t half = (uint32_t)lane >> 5;
+    const uint32_t* src = p.samp_hist + (size_t)role * 32u + (lane & 31);
+    uint32_t h0 = 0, h1 = 0;
+    constexpr uint32_t NB = 32;   // loads in flight
+#pragma unroll 1
+    for (uint32_t b0 = 0; b0 < nb; b0 += 2 * NB) {
+        uint32_t w[NB];
+#pragma unroll
+        for (uint32_t q = 0; q < NB; ++q) {
+            const uint32_t b = b0 + 2 * q + half;
+            w[q] = src[(b < nb ? b : nb - 1u) * (SBIN / 2)];
+        }
+#pragma unroll
+        for (uint32_t q = 0; q < NB; ++q)
+            if (b0 + 2 * q + half < nb) { h0 += w[q] & 0xFFFFu; h1 += w[q] >> 16; }
+    }
+    uint32_t rank_lo, rank_hi, rank_mid;
+    sampled_ranks(k, S, (uint64_t)p.n, rank_lo, rank_hi, rank_mid);
+    h0 += __shfl_xor(h0, 32, 64);
+    h1 += __shfl_xor(h1, 32, 64);
+    if (half != 0u) h0 = h1 = 0;
+    g_above = wave_sum(g_above);
+    const uint32_t incl = wave_scan(h0 + h1);
+    const uint32_t above1 = g_above + last_lane(incl) - incl, above0 = above1 + h1;   // samples above each of this lane's bins
+    const uint32_t bin0 = 2u * (role * 32u + (uint32_t)(lane & 31));
+    for (int j = 0; j < p.n_cf; ++j) {
+        const auto find = [&](uint32_t ranks, uint32_t word, uint32_t none, auto key) {
+            // the bin of the rank-th sample from the top, if it is one of this wavefront's
+            const uint32_t rank = (uint32_t)__builtin_amdgcn_readlane((int)ranks, j);
+            const bool in1 = above1 < rank && above1 + h1 >= rank, in0 = above0 < rank && above0 + h0 >= rank;
+            const uint64_t m = __ballot(in1 || in0);
+            if (m != 0ull) {
+                const uint32_t value = key(in1 ? bin0 + 1u : bin0, rank - (in1 ? above1 : above0), in1 ? h1 : h0);
+                if (in1 || in0) p.bnd[4 * j + word] = value;
+            } else if (role == 0u && S < rank) {
+                if (lane == 0) p.bnd[4 * j + word] = none;   // fewer samples than a rank: the bracket is open on that side
+            }
+        };
+        // lower edge of the bin of the rank_lo-th sample from the top, upper edge of the bin of the rank_hi-th
+        find(rank_lo, 0u, 0u, [&](uint32_t bin, uint32_t, uint32_t) { return sample_bin_first(bin, w0); });
+        find(rank_hi, 1u, KEY_END, [&](uint32_t bin, uint32_t, uint32_t) { return sample_bin_end(bin, w0); });
+        find(rank_mid, 2u, NONE, [&](uint32_t bin, uint32_t down, uint32_t c) { return key_inside(bin, w0, down, c); });
     }
 }
 
@@ -1311,6 +1355,24 @@ __device__ __forceinline__ void stream_subtile(const Params& p, uint32_t v, int 
     const int64_t sb = seg_begin(p, t), se = seg_end(p, t);
     const int64_t s0 = sb + (int64_t)(u - seg_tile0(p, t)) * TW + (int64_t)(v % SUB) * TS;
     const int64_t e0 = (s0 + TS < se) ? s0 + TS : se;
+    const bool whole = e0 - s0 == TS;
+    const uint32_t rep = seg_rep(p, t);
+    const size_t block0 = seg_block(p, t, 0);
+    // the brackets' load, then all rows': on their way together
+    uint32_t word = NONE;   // lane 4 j + i: word i of CF j's bracket
+    if (EF) {
+        if (p.bounds_from == BOUNDS_FIXED) word = (lane & 3) == 2 ? NONE : p.fixed_key;   // an empty bracket at the caller's threshold
+        else word = p.bnd[(size_t)t * BND_WORDS + (lane & (BND_WORDS - 1))];
+    }
+    float a[ROWS][4];
+    if (whole) {
+        v4f x[ROWS], y[ROWS];
+        v4i mi[ROWS];
+#pragma unroll
+        for (int q = 0; q < ROWS; ++q) row_load<M>(p, s0 + q * ROW + 4 * lane, x[q], y[q], mi[q]);
+#pragma unroll
+        for (int q = 0; q < ROWS; ++q) row_finish<M>(p, x[q], y[q], mi[q], a[q]);
+    }
     if (s0 >= se) {  // sub-tile past the end of the segment
         if (lane == 0) { p.cand_cnt[v] = 0; p.brk_cnt[v] = 0; if (EF) p.ssd[v] = 0.0; }
         if (lane < p.n_cf) { p.ovn[(size_t)v * p.n_cf + lane] = 0; p.ovs[(size_t)v * p.n_cf + lane] = 0.0; }
@@ -1330,12 +1392,12 @@ __device__ __forceinline__ void stream_subtile(const Params& p, uint32_t v, int 
 #pragma unroll
         for (int j = 0; j < NCF; ++j) {
             if (j < p.n_cf) {
-                c.lo[j] = p.bnd_lo[(size_t)t * p.n_cf + j];
-                bracket_bins(c.lo[j], p.bnd_hi[(size_t)t * p.n_cf + j], c.sh[j], c.org[j], c.top[j]);
+                c.lo[j] = (uint32_t)__builtin_amdgcn_readlane((int)word, 4 * j);
+                bracket_bins(c.lo[j], (uint32_t)__builtin_amdgcn_readlane((int)word, 4 * j + 1), c.sh[j], c.org[j], c.top[j]);
                 c.lo_min = c.lo[j] < c.lo_min ? c.lo[j] : c.lo_min;
                 if (j == p.commit) {
                     c.lo_c = c.lo[j];
-                    if (M == SM_EF) c.pz = zero_from(p, c.lo[j], c.top[j], p.bnd_mid[(size_t)t * p.n_cf + j]);
+                    if (M == SM_EF) c.pz = zero_from(p, c.lo[j], c.top[j], (uint32_t)__builtin_amdgcn_readlane((int)word, 4 * j + 2));
                 }
             }
         }
@@ -1351,9 +1413,9 @@ __device__ __forceinline__ void stream_subtile(const Params& p, uint32_t v, int 
         }
     }
     // the copy of the histogram this wavefront adds to, spread by the sub-tile number
-    c.hstride = seg_rep(p, t) * (EF ? NBIN : LCAP);
-    if (EF) c.h1 = p.hist1 + (seg_block(p, t, 0) + ((v ^ (v / SUB)) & (seg_rep(p, t) - 1u))) * NBIN;
-    else c.h1 = xb->hist + ((v ^ (v / SUB)) & (seg_rep(p, t) - 1u)) * LCAP;
+    c.hstride = rep * (EF ? NBIN : LCAP);
+    if (EF) c.h1 = p.hist1 + (block0 + ((v ^ (v / SUB)) & (rep - 1u))) * NBIN;
+    else c.h1 = xb->hist + ((v ^ (v / SUB)) & (rep - 1u)) * LCAP;
     c.cidx = p.cand_idx + (size_t)v * TS;
     c.cval = p.cand_val + (size_t)v * TS;
     c.bkey = p.brk_key + (size_t)v * TS;
@@ -1365,8 +1427,6 @@ __device__ __forceinline__ void stream_subtile(const Params& p, uint32_t v, int 
     c.staged = 0;
 
     bool dense = false;
-    const bool whole = e0 - s0 == TS;
-    float a[ROWS][4];
     uint32_t rk[RND ? ROWS : 1][4];  // Random-k: the priorities, each computed once (four quarter-rate multiplications)
     bool at_once = false;            // all rows are staged before the entries are worked on
     // Zeros inside a bracket are only counted, not listed (whole sub-tiles of Top-k's first pass).  Where they may be
@@ -1376,15 +1436,9 @@ __device__ __forceinline__ void stream_subtile(const Params& p, uint32_t v, int 
     uint32_t zeros = 0;
     int parts = (int)((e0 - s0 + ROW - 1) / ROW);
     if (whole) {
-        // the loads of all rows first, then the arithmetic
-        v4f x[ROWS], y[ROWS];
-        v4i mi[ROWS];
-#pragma unroll
-        for (int q = 0; q < ROWS; ++q) row_load<M>(p, s0 + q * ROW + 4 * lane, x[q], y[q], mi[q]);
         uint32_t nc = 0, nm = 0;  // candidates for the message in this sub-tile, entries that some bracket concerns
 #pragma unroll
         for (int q = 0; q < ROWS; ++q) {
-            row_finish<M>(p, x[q], y[q], mi[q], a[q]);
             uint32_t key[4];
             keys_of_row<RND, NCF>(c, a[q], s0 + q * ROW + 4 * lane, key);
 #pragma unroll
@@ -1515,6 +1569,23 @@ __global__ __launch_bounds__(WG) void stream_kernel(Params p)
     __shared__ uint2 stage[WAVES][STAGE];
     const uint32_t w = __builtin_amdgcn_readfirstlane(blockIdx.x * WAVES + (threadIdx.x >> 6));
     stream_subtile<M, RND, NCF>(p, w, threadIdx.x & 63, nullptr, stage[threadIdx.x >> 6]);
+    if (p.bounds_from == BOUNDS_FIXED) {
+        // the threshold sparsifier's first kernel.  The later steps find everything resolved: selected <=> key > tau with tau
+        // one key below the threshold, no ties to take
+        const uint32_t i = blockIdx.x * WG + threadIdx.x;
+        if (p.csum && i < (p.n_tiles + CTILES - 1u) / CTILES) p.csum[(size_t)i * 8] = 0;
+        if (i == 0) {
+            reset_status(p, 0);
+            CfState st;
+            st.k = 0; st.lo = p.fixed_key; st.s = 0; st.mode = MODE_RESOLVED; st.base = p.fixed_key; st.span = 0;
+            st.above = 0; st.c = 0; st.tau = p.fixed_key - 1u; st.need = 0; st.cnt_gt = 0;
+            st.top = p.fixed_key; st.pad[0] = st.pad[1] = st.pad[2] = st.pad[3] = 0;
+            p.st[0] = st;
+            SegState sg;
+            sg.fail = FAIL_NONE; sg.pz = p.single ? NONE : p.fixed_key;
+            p.seg[0] = sg;
+        }
+    }
 }
 
 // The candidates of sub-tile v that its first pass replaced by +0 in the residual get their values back (the
@@ -1768,7 +1839,7 @@ __global__ __launch_bounds__(PLAN_T) void plan_kernel(Params p)
     const size_t id0 = (size_t)t * p.n_cf;
     // (the brackets are fetched along with the histograms)
     uint32_t b_lo = 0, b_hi = 0, b_mid = 0;
-    if (tid < p.n_cf) { b_lo = p.bnd_lo[id0 + tid]; b_hi = p.bnd_hi[id0 + tid]; b_mid = p.bnd_mid[id0 + tid]; }
+    if (tid < p.n_cf) { const uint32_t* b = p.bnd + (size_t)t * BND_WORDS + 4 * tid; b_lo = b[0]; b_hi = b[1]; b_mid = b[2]; }
     plan_search(sh, p.n_cf, tid, [&](int j, const uint32_t*& hist, uint32_t& nc, uint32_t& stride, const uint32_t*& extra, uint32_t& want) {
         hist = p.hist1 + seg_block(p, t, j) * NBIN; nc = copies; stride = NBIN;
         extra = p.ovfc + (id0 + j) * 64 * 32; want = seg_k(p, t, j);
@@ -3903,8 +3974,8 @@ __global__ __launch_bounds__(256) void commit_kernel(const int32_t* __restrict__
 size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 struct Layout {
-    size_t status, tables, tables_bytes, tseg, st, seg, bnd_lo, bnd_hi, bnd_mid, hist1, ovfc, xq, coarse, list_key, list_tile,
-        list_val, list_cnt, samp_hist, samp_grp, cand_cnt, brk_cnt, ovn, ovs, tg0, tin, toff, ttake, tsel, ssd, ssd_t, sss,
+    size_t status, tables, tables_bytes, tseg, st, seg, bnd, hist1, ovfc, xq, coarse, list_key, list_tile,
+        list_val, list_cnt, samp_hist, samp_above, cand_cnt, brk_cnt, ovn, ovs, tg0, tin, toff, ttake, tsel, ssd, ssd_t, sss,
         cand_idx, cand_val, brk_key, brk_val, total;
 };
 
@@ -3952,9 +4023,7 @@ Layout make_layout(int64_t n, int n_cf, int n_seg)
     L.tseg = take(sizeof(uint32_t) * nt);
     L.st = take(sizeof(CfState) * sc);
     L.seg = take(sizeof(SegState) * n_seg);
-    L.bnd_lo = take(sizeof(uint32_t) * sc);
-    L.bnd_hi = take(sizeof(uint32_t) * sc);
-    L.bnd_mid = take(sizeof(uint32_t) * sc);
+    L.bnd = take(sizeof(uint32_t) * BND_WORDS * (size_t)n_seg);
     const size_t blocks = pool_blocks(n, n_cf, n_seg);
     L.hist1 = take(sizeof(uint32_t) * blocks * NBIN);
     L.ovfc = take(sizeof(uint32_t) * sc * 64 * 32);
@@ -3965,7 +4034,7 @@ Layout make_layout(int64_t n, int n_cf, int n_seg)
     L.list_val = take(sizeof(float) * blocks * LCAP);
     L.list_cnt = take(sizeof(uint32_t) * blocks * 32);
     L.samp_hist = take(sizeof(uint32_t) * nsb * (SBIN / 2));
-    L.samp_grp = take(sizeof(uint32_t) * nsb * SGRP);
+    L.samp_above = take(sizeof(uint16_t) * nsb * RGRP);
     L.cand_cnt = take(sizeof(uint32_t) * nt * SUB);
     L.brk_cnt = take(sizeof(uint32_t) * nt * SUB);
     L.ovn = take(sizeof(uint32_t) * nt * SUB * n_cf);
@@ -4220,9 +4289,7 @@ static int compress_impl(const float* grad, float* residual, int64_t n, const do
     p.tseg = (uint32_t*)(ws + L.tseg);
     p.st = (CfState*)(ws + L.st);
     p.seg = (SegState*)(ws + L.seg);
-    p.bnd_lo = (uint32_t*)(ws + L.bnd_lo);
-    p.bnd_hi = (uint32_t*)(ws + L.bnd_hi);
-    p.bnd_mid = (uint32_t*)(ws + L.bnd_mid);
+    p.bnd = (uint32_t*)(ws + L.bnd);
     p.hist1 = (uint32_t*)(ws + L.hist1);
     p.ovfc = (uint32_t*)(ws + L.ovfc);
     p.xq = (uint32_t*)(ws + L.xq);
@@ -4232,7 +4299,7 @@ static int compress_impl(const float* grad, float* residual, int64_t n, const do
     p.list_val = (float*)(ws + L.list_val);
     p.list_cnt = (uint32_t*)(ws + L.list_cnt);
     p.samp_hist = (uint32_t*)(ws + L.samp_hist);
-    p.samp_grp = (uint32_t*)(ws + L.samp_grp);
+    p.samp_above = (uint16_t*)(ws + L.samp_above);
     p.cand_cnt = (uint32_t*)(ws + L.cand_cnt);
     p.brk_cnt = (uint32_t*)(ws + L.brk_cnt);
     p.ovn = (uint32_t*)(ws + L.ovn);
@@ -4380,16 +4447,13 @@ static int compress_impl(const float* grad, float* residual, int64_t n, const do
     }
     // a layerwise call's small tensors are done by their workgroups of this launch; few segments (none of them small):
     // their sample histograms are added up by SGRP workgroups each; many: by one each
-    if (n_small)
+    if (ns == 1 && p.bounds_from == BOUNDS_SAMPLED)
+        hipLaunchKernelGGL(bracket_kernel, dim3(RGRP), dim3(64), 0, stream, p);
+    else if (n_small)
         hipLaunchKernelGGL((threshold_kernel<1, true>), dim3(ns, 1), dim3(1024), 0, stream, p);
-    else if (ns <= 32 && p.bounds_from == BOUNDS_SAMPLED)
-    {
-        if (p.n_sample_blocks > 64u * (uint32_t)ns)
-            hipLaunchKernelGGL((threshold_kernel<SGRP, false, 4>), dim3(ns, SGRP), dim3(4096 / SGRP), 0, stream, p);
-        else
-            hipLaunchKernelGGL((threshold_kernel<SGRP, false, 2>), dim3(ns, SGRP), dim3(2048 / SGRP), 0, stream, p);
-    }
-    else
+    else if (ns > 1 && ns <= 32 && p.bounds_from == BOUNDS_SAMPLED)
+        hipLaunchKernelGGL((threshold_kernel<SGRP, false, 2>), dim3(ns, SGRP), dim3(2048 / SGRP), 0, stream, p);
+    else if (ns > 1)
         hipLaunchKernelGGL((threshold_kernel<1, false>), dim3(ns, 1), dim3(1024), 0, stream, p);
     {
         // the pass exists in forms for 1, 2, 3, 4 and MAXCF CFs (its loops over the CFs are unrolled)
