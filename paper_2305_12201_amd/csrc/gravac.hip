@@ -109,7 +109,8 @@ constexpr int DENSE_BLOCKS = 128;        // ... so that there are at most this m
 constexpr int LCAP = 4096;          // keys a gather list can hold
 constexpr int MAXCF = GRAVAC_MAX_CF;
 constexpr double ZMARGIN = 5.0;     // safety margin of the sampled rank, in standard deviations
-constexpr uint32_t CTILES = 64;     // tiles per partial sum of the tiles' counts (csum)
+constexpr uint32_t CTILES = 64;     // units per partial sum of the units' counts (csum)
+constexpr int FINE = 2, MIDDLE = 4; // sub-tiles per wavefront of the list kernels where a tile each leaves the chip idle (units_per_tile)
 constexpr int XQ_WORDS = 8;         // a segment's work queue in the plan step: chunks claimed, then chunks done per phase
 constexpr int XQ_WIN = XQ_WORDS;    // ... and behind it the first key of its sample histogram's window
 constexpr int XQ_LINE = 32;         // words between two segments' queues: a cache line
@@ -249,6 +250,7 @@ struct Params {
     uint32_t* tsel;      // [n_tiles] pairs the tile emits
     // ... and one without (null otherwise):
     uint64_t* csum;      // [n_tiles / CTILES, rounded up][8] sums of tg0 (high half) and tin over CTILES tiles: word 0 of a cache line
+    uint32_t n_csum;     // their number
     uint32_t* wseg;      // [workgroups of the emit step] the segment of each (layerwise; filled by threshold_kernel)
     double* ssd;         // [n_tiles][SUB] sum of acc^2 of every sub-tile
     double* ssd_t;       // [n_tiles] sum of acc^2 of the tile
@@ -460,33 +462,37 @@ __device__ __forceinline__ T pop_front(T (&v)[N])
 constexpr uint32_t ZERO_SHIFT = 16, LISTED = (1u << ZERO_SHIFT) - 1u;
 static_assert(TS <= (int)LISTED, "both fit");
 
-// The entries of a tile's lists are the concatenation of its SUB sub-tile lists.
-struct TileLists {
-    uint32_t start[SUB + 1];  // start[j] = entries in sub-tiles before j; start[SUB] = all
-    uint32_t zeros;           // the bracket lists: zeros that are not in them
-    __device__ __forceinline__ uint32_t total() const { return start[SUB]; }
-    // slot (relative to the tile's first slot) of the tile's i-th entry
+// What a wavefront of the list kernels works on, a unit: the U sub-tiles from U u on, U = SUB (a tile) or, in calls of few
+// tiles, MIDDLE or FINE (units_per_tile).  The entries of a unit's lists are the concatenation of
+// its sub-tile lists.
+template <int U>
+struct UnitLists {
+    uint32_t start[U + 1];  // start[j] = entries in sub-tiles before j; start[U] = all
+    uint32_t zeros;         // the bracket lists: zeros that are not in them
+    __device__ __forceinline__ uint32_t total() const { return start[U]; }
+    // slot (relative to the unit's first slot) of the unit's i-th entry
     __device__ __forceinline__ uint32_t slot(uint32_t i) const
     {
         uint32_t j = 0;
 #pragma unroll
-        for (int x = 1; x < SUB; ++x) j += (i >= start[x]);
+        for (int x = 1; x < U; ++x) j += (i >= start[x]);
         uint32_t s = 0;
 #pragma unroll
-        for (int x = 1; x < SUB; ++x) if ((uint32_t)x == j) s = start[x];
+        for (int x = 1; x < U; ++x) if ((uint32_t)x == j) s = start[x];
         return j * TS + (i - s);
     }
 };
 
 // the bracket lists
-__device__ __forceinline__ TileLists bracket_lists(const Params& p, uint32_t u)
+template <int U>
+__device__ __forceinline__ UnitLists<U> bracket_lists(const Params& p, uint32_t u)
 {
-    TileLists c;
+    UnitLists<U> c;
     c.start[0] = 0;
     c.zeros = 0;
 #pragma unroll
-    for (int j = 0; j < SUB; ++j) {
-        const uint32_t x = p.brk_cnt[(size_t)u * SUB + j];
+    for (int j = 0; j < U; ++j) {
+        const uint32_t x = p.brk_cnt[(size_t)u * U + j];
         c.start[j + 1] = c.start[j] + (x & LISTED);
         c.zeros += x >> ZERO_SHIFT;
     }
@@ -819,7 +825,7 @@ __global__ __launch_bounds__(256) void sample_kernel(Params p)
             if (b == 0 && p.bounds_from != BOUNDS_SAMPLED && tid < p.n_cf) known_bracket(p, 0, tid, p.bnd + 4 * tid);
         }
         if (p.csum)
-            for (uint32_t i = b * 256 + tid; i < (p.n_tiles + CTILES - 1u) / CTILES; i += gridDim.x * 256) p.csum[(size_t)i * 8] = 0;
+            for (uint32_t i = b * 256 + tid; i < p.n_csum; i += gridDim.x * 256) p.csum[(size_t)i * 8] = 0;
     };
     if (p.bounds_from != BOUNDS_SAMPLED) {
         clear();
@@ -1573,7 +1579,7 @@ __global__ __launch_bounds__(WG) void stream_kernel(Params p)
         // the threshold sparsifier's first kernel.  The later steps find everything resolved: selected <=> key > tau with tau
         // one key below the threshold, no ties to take
         const uint32_t i = blockIdx.x * WG + threadIdx.x;
-        if (p.csum && i < (p.n_tiles + CTILES - 1u) / CTILES) p.csum[(size_t)i * 8] = 0;
+        if (p.csum && i < p.n_csum) p.csum[(size_t)i * 8] = 0;
         if (i == 0) {
             reset_status(p, 0);
             CfState st;
@@ -1784,7 +1790,7 @@ __device__ __forceinline__ bool plan_barrier(const Params& p, PlanShared& sh, ui
 // One tile's entries of the bracket lists into the histograms (first copy of CF 0 at hist) of the CFs that are cut again.
 __device__ __forceinline__ void plan_recount(const Params& p, const PlanShared& sh, uint32_t u, uint32_t* hist, uint32_t copies, int lane)
 {
-    const TileLists tl = bracket_lists(p, u);
+    const UnitLists<SUB> tl = bracket_lists<SUB>(p, u);
     const uint32_t cnt = tl.total();
     for (uint32_t i0 = 0; i0 < cnt; i0 += 64 * 8) {
         uint32_t kq[8];
@@ -2039,33 +2045,33 @@ __global__ __launch_bounds__(PLAN_T) void plan_kernel(Params p)
 // wavefronts are resident at once and the kernel's time is one wavefront's chain of round trips to memory (the
 // ResNet101 shape: 10.1 -> 7.9 us); with more tiles than that the chip is busy either way, and the extra loads and
 // registers cost (the VGG16 shape: 10 -> 14 us), so the host picks the form by the number of tiles.
-template <int NCF, bool HEADS>  // compiled for calls with up to NCF CFs: the loops over the CFs are unrolled
+template <int NCF, bool HEADS, int U>  // compiled for calls with up to NCF CFs: the loops over the CFs are unrolled
 __global__ __launch_bounds__(LWG) __attribute__((amdgpu_waves_per_eu((NCF == 3 || NCF == 4) ? 6 : 1, 8))) void refine_kernel(Params p)
 {
     const int lane = threadIdx.x & 63;
     const uint32_t u = __builtin_amdgcn_readfirstlane(blockIdx.x * LWAVES + (threadIdx.x >> 6));
-    if (u >= p.n_tiles) return;
+    if (u >= p.n_tiles * (SUB / U)) return;
     // loads that depend on nothing but the tile number come first, so that they are in flight together
-    const double ssd = lane < SUB ? p.ssd[(size_t)u * SUB + lane] : 0.0;
-    // ... among them the heads of the tile's eight lists, before their lengths are known: lane l takes entries
-    // l % 8 + 8 r (r < SPEC_R) of sub-tile l / 8.  A tile whose lists are no longer than that (most tiles of a call
+    const double ssd = lane < U ? p.ssd[(size_t)u * U + lane] : 0.0;
+    // ... among them the heads of the unit's lists, before their lengths are known: lane l takes entries
+    // l % H + H r (r < SPEC_R) of sub-tile l / H, H = 64 / U.  A tile whose lists are no longer than that (most tiles of a call
     // with a CF of 100 or more) is done with one round trip to memory less.  Top-k keys only.
-    constexpr int SPEC_R = HEADS ? 4 : 1;
+    constexpr int H = 64 / U, SPEC_R = HEADS ? (U == SUB ? 4 : U == MIDDLE ? 3 : 2) : 1;
     uint32_t spec[SPEC_R];
     if constexpr (HEADS) {
-        const uint32_t* src = p.brk_key + (size_t)u * TW + (size_t)(lane >> 3) * TS + (lane & 7);
+        const uint32_t* src = p.brk_key + (size_t)u * (U * TS) + (size_t)(lane / H) * TS + (lane % H);
 #pragma unroll
-        for (int r = 0; r < SPEC_R; ++r) spec[r] = src[8 * r];
+        for (int r = 0; r < SPEC_R; ++r) spec[r] = src[H * r];
     }
     uint32_t on[NCF];
     double os[NCF];
 #pragma unroll
     for (int j = 0; j < NCF; ++j) {
-        const bool have = lane < SUB && j < p.n_cf;
-        on[j] = have ? p.ovn[((size_t)u * SUB + lane) * p.n_cf + j] : 0u;
-        os[j] = have ? p.ovs[((size_t)u * SUB + lane) * p.n_cf + j] : 0.0;
+        const bool have = lane < U && j < p.n_cf;
+        on[j] = have ? p.ovn[((size_t)u * U + lane) * p.n_cf + j] : 0u;
+        os[j] = have ? p.ovs[((size_t)u * U + lane) * p.n_cf + j] : 0.0;
     }
-    const int t = tile_seg(p, u);
+    const int t = tile_seg(p, u / (SUB / U));
     // (the plan: fetched with the counts, not after them)
     uint32_t mode[NCF], base[NCF], span[NCF], top[NCF];
 #pragma unroll
@@ -2076,7 +2082,7 @@ __global__ __launch_bounds__(LWG) __attribute__((amdgpu_waves_per_eu((NCF == 3 |
             mode[j] = st->mode; base[j] = st->base; span[j] = st->span; top[j] = st->top;
         }
     }
-    const TileLists tl = bracket_lists(p, u);
+    const UnitLists<U> tl = bracket_lists<U>(p, u);
     const uint32_t cnt = tl.total();
     uint32_t hn[NCF], tin = 0;
     double hs[NCF];
@@ -2127,16 +2133,16 @@ __global__ __launch_bounds__(LWG) __attribute__((amdgpu_waves_per_eu((NCF == 3 |
             // the lists' heads cover the tile if every list is short enough
             bool heads = !p.random;
 #pragma unroll
-            for (int j = 0; j < SUB; ++j) heads = heads && tl.start[j + 1] - tl.start[j] <= 8u * SPEC_R;
+            for (int j = 0; j < U; ++j) heads = heads && tl.start[j + 1] - tl.start[j] <= (uint32_t)(H * SPEC_R);
             if (heads) {
                 uint32_t mine_cnt = 0;
 #pragma unroll
-                for (int j = 0; j < SUB; ++j) if ((lane >> 3) == j) mine_cnt = tl.start[j + 1] - tl.start[j];
+                for (int j = 0; j < U; ++j) if (lane / H == j) mine_cnt = tl.start[j + 1] - tl.start[j];
 #pragma unroll 1
                 for (int r = 0; r < SPEC_R; ++r) {
-                    if (__ballot((uint32_t)(lane & 7) + 8u * r < mine_cnt) == 0ull) break;
+                    if (__ballot((uint32_t)(lane % H + H * r) < mine_cnt) == 0ull) break;
                     const uint32_t w = pop_front(spec);
-                    take(w, 0.0f, (uint32_t)(lane & 7) + 8u * r < mine_cnt);
+                    take(w, 0.0f, (uint32_t)(lane % H + H * r) < mine_cnt);
                 }
                 i0 = cnt;
             }
@@ -2148,9 +2154,9 @@ __global__ __launch_bounds__(LWG) __attribute__((amdgpu_waves_per_eu((NCF == 3 |
             // worked on, whatever they hold; the words are carried as loaded and decoded where they are used
             // (decoded at once, the loads would be waited for at once).  The counts are the ones fetched with the
             // tile's first loads.
-            constexpr int AHEAD = 4;
+            constexpr int AHEAD = U < 4 ? U : 4;
             const auto fetch = [&](int j, uint32_t (&w)[2]) {
-                const uint32_t* src = p.brk_key + (size_t)u * TW + (size_t)j * TS;
+                const uint32_t* src = p.brk_key + (size_t)u * (U * TS) + (size_t)j * TS;
 #pragma unroll
                 for (int q = 0; q < 2; ++q) w[q] = src[q * 64 + lane];
             };
@@ -2158,16 +2164,16 @@ __global__ __launch_bounds__(LWG) __attribute__((amdgpu_waves_per_eu((NCF == 3 |
 #pragma unroll
             for (int a = 0; a < AHEAD; ++a) fetch(a, wq[a]);
 #pragma unroll 1
-            for (int j = 0; j < SUB; ++j) {
+            for (int j = 0; j < U; ++j) {
                 uint32_t w0[2], c = 0;
 #pragma unroll
                 for (int q = 0; q < 2; ++q) w0[q] = wq[0][q];
 #pragma unroll
                 for (int a = 0; a + 1 < AHEAD; ++a) { wq[a][0] = wq[a + 1][0]; wq[a][1] = wq[a + 1][1]; }
-                if (j + AHEAD < SUB) fetch(j + AHEAD, wq[AHEAD - 1]);
+                if (j + AHEAD < U) fetch(j + AHEAD, wq[AHEAD - 1]);
 #pragma unroll
-                for (int x = 0; x < SUB; ++x) c = (x == j) ? tl.start[x + 1] - tl.start[x] : c;
-                const uint32_t* src = p.brk_key + (size_t)u * TW + (size_t)j * TS;
+                for (int x = 0; x < U; ++x) c = (x == j) ? tl.start[x + 1] - tl.start[x] : c;
+                const uint32_t* src = p.brk_key + (size_t)u * (U * TS) + (size_t)j * TS;
 #pragma unroll 1
                 for (uint32_t b = 0; b < c; b += 64) {
                     const uint32_t w = w0[0];
@@ -2187,7 +2193,7 @@ __global__ __launch_bounds__(LWG) __attribute__((amdgpu_waves_per_eu((NCF == 3 |
                 kq[q] = 0; vq[q] = 0.0f;
                 if (i0 + q * 64 < cnt) {
                     const uint32_t i = i0 + q * 64 + lane;
-                    const size_t at = (size_t)u * TW + tl.slot(i < cnt ? i : 0u);
+                    const size_t at = (size_t)u * (U * TS) + tl.slot(i < cnt ? i : 0u);
                     kq[q] = p.brk_key[at];
                     if (p.random) vq[q] = p.brk_val[at];
                 }
@@ -2746,13 +2752,14 @@ __device__ __forceinline__ void gathered_resolve(const Params& p, int tid, Gathe
 }
 
 // Statistics of (segment t, CF j), by one workgroup.
+template <int U>
 __device__ __forceinline__ void emit_stats(const Params& p, int t, int j, EmitShared& sh)
 {
     const int tid = threadIdx.x, lane = tid & 63, wib = tid >> 6;
-    const uint32_t u0 = seg_tile0(p, t), u1 = seg_tile1(p, t);
+    const uint32_t u0 = seg_tile0(p, t) * (SUB / U), u1 = seg_tile1(p, t) * (SUB / U);
     Gathered g;
     gathered_load(p, t, j, tid, g);
-    // the tiles' sums, eight tiles per thread and round, in a fixed order
+    // the units' sums, eight units per thread and round, in a fixed order
     double sd = 0.0, sj = 0.0;
     uint32_t kept = 0;   // threshold sparsifier: the entries at or above the threshold
     for (uint32_t v0 = u0 + tid; v0 < u1; v0 += 8 * EWG) {
@@ -2933,8 +2940,8 @@ __device__ __forceinline__ void emit_listed(const Params& p, EmitCtx& x, int32_t
 //
 // One tile u of segment t, by one wavefront: x holds the threshold, the tile's tie quota and the place of its pairs; cc
 // are the tile's counts, hi4 / hv4 the heads of its lists.
-template <bool GEN, bool HEADS>
-__device__ __forceinline__ void emit_tile(const Params& p, int t, uint32_t u, EmitCtx& x, const uint32_t (&cc)[SUB], const v4i& hi4,
+template <bool GEN, bool HEADS, int U>
+__device__ __forceinline__ void emit_unit(const Params& p, int t, uint32_t u, EmitCtx& x, const uint32_t (&cc)[U], const v4i& hi4,
                                           const v4f& hv4, int32_t* sidx, float* sval)
 {
     static_assert(!(GEN && HEADS), "the early loads exist in the plain form only");
@@ -2942,17 +2949,18 @@ __device__ __forceinline__ void emit_tile(const Params& p, int t, uint32_t u, Em
     const int lane = threadIdx.x & 63;
     uint32_t dmask = 0;  // bit j: sub-tile j keeps no candidate list
 #pragma unroll
-    for (int j = 0; j < SUB; ++j) dmask |= (cc[j] & DENSE_BIT) ? 1u << j : 0u;
+    for (int j = 0; j < U; ++j) dmask |= (cc[j] & DENSE_BIT) ? 1u << j : 0u;
     const bool any_dense = dmask != 0u;
-    const float* cv = p.cand_val + (size_t)u * TW;
-    const int32_t* ci = p.cand_idx + (size_t)u * TW;
+    const float* cv = p.cand_val + (size_t)u * (U * TS);
+    const int32_t* ci = p.cand_idx + (size_t)u * (U * TS);
     if constexpr (HEADS) {
+        constexpr int H = 64 / U;   // lanes per sub-tile
         bool covered = !any_dense;
         uint32_t cj = 0;  // candidates of this lane's sub-tile
 #pragma unroll
-        for (int j = 0; j < SUB; ++j) {
-            covered = covered && cc[j] <= 32u;
-            if ((lane >> 3) == j) cj = cc[j];
+        for (int j = 0; j < U; ++j) {
+            covered = covered && cc[j] <= 4u * H;
+            if (lane / H == j) cj = cc[j];
         }
         if (covered) {
             const int32_t ia[4] = {hi4.x, hi4.y, hi4.z, hi4.w};
@@ -2962,7 +2970,7 @@ __device__ __forceinline__ void emit_tile(const Params& p, int t, uint32_t u, Em
             uint32_t n_eq = 0;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                live[e] = 4u * (lane & 7) + e < cj;
+                live[e] = 4u * (lane % H) + e < cj;
                 key[e] = key_of(va[e]);
                 sel[e] = live[e] && key[e] > x.tau;
                 n_eq += (live[e] && key[e] == x.tau) ? 1u : 0u;
@@ -2978,7 +2986,7 @@ __device__ __forceinline__ void emit_tile(const Params& p, int t, uint32_t u, Em
             const uint32_t n_sel = (sel[0] ? 1u : 0u) + (sel[1] ? 1u : 0u) + (sel[2] ? 1u : 0u) + (sel[3] ? 1u : 0u);
             uint32_t o = wave_scan(n_sel) - n_sel;       // pairs of lower lanes
             const int64_t left = x.lim - x.pos;
-            const uint32_t room = left >= (int64_t)TW ? (uint32_t)TW : (left > 0 ? (uint32_t)left : 0u);
+            const uint32_t room = left >= (int64_t)(U * TS) ? (uint32_t)(U * TS) : (left > 0 ? (uint32_t)left : 0u);
             float* ov = p.out_val + x.pos;
             int32_t* oi = p.out_idx + x.pos;
 #pragma unroll
@@ -2999,10 +3007,10 @@ __device__ __forceinline__ void emit_tile(const Params& p, int t, uint32_t u, Em
             return;
         }
     }
-    TileLists tl;
+    UnitLists<U> tl;
     tl.start[0] = 0;
 #pragma unroll
-    for (int j = 0; j < SUB; ++j) tl.start[j + 1] = tl.start[j] + (cc[j] & ~DENSE_BIT);
+    for (int j = 0; j < U; ++j) tl.start[j + 1] = tl.start[j] + (cc[j] & ~DENSE_BIT);
     if (!any_dense && tl.total() < LONG_WALK) {
         // all sub-tiles listed, and shortly: their lists are walked as one, 64 candidates per round.  The loads of
         // the next rounds are issued before this round is worked on (an absent candidate reads slot 0 and is not
@@ -3047,20 +3055,20 @@ __device__ __forceinline__ void emit_tile(const Params& p, int t, uint32_t u, Em
         // about 7) have the round after the next one on its way while one is worked on (loaded when it is due: 85 instead
         // of 76 us for 2 million elements at CF 3; four rounds at once cost a wavefront per SIMD, 284 instead of 242 us for
         // 60 million at CF 5)
-        float va[2 * SUB];
-        int32_t ia[2 * SUB];
+        float va[2 * U];
+        int32_t ia[2 * U];
 #pragma unroll
-        for (int r = 0; r < 2 * SUB; ++r) {
+        for (int r = 0; r < 2 * U; ++r) {
             // (Random-k at CF 10: 151 -> 147 us with non-temporal loads; in the plain form they cost a 25 MB bucket 2 us)
             const size_t at = (r / 2) * TS + (r & 1) * 64 + lane;
             va[r] = GEN ? __builtin_nontemporal_load(&cv[at]) : cv[at];
             ia[r] = GEN ? __builtin_nontemporal_load(&ci[at]) : ci[at];
         }
 #pragma unroll 1
-        for (int j = 0; j < SUB; ++j) {
+        for (int j = 0; j < U; ++j) {
             uint32_t c = 0;
 #pragma unroll
-            for (int y = 0; y < SUB; ++y) c = y == j ? cc[y] : c;
+            for (int y = 0; y < U; ++y) c = y == j ? cc[y] : c;
             float v0 = pop_front(va), v1 = pop_front(va);
             int32_t i0 = pop_front(ia), i1 = pop_front(ia);
 #pragma unroll 1
@@ -3080,7 +3088,7 @@ __device__ __forceinline__ void emit_tile(const Params& p, int t, uint32_t u, Em
     // sub-tile by sub-tile: a tile with sub-tiles that keep no list
     // (two rows of a sub-tile at a time in LDS, sidx / sval: with room for a whole sub-tile the LDS of a workgroup would
     // limit the kernel to five wavefronts per SIMD, and the listed tiles of the same launch need the occupancy)
-    const int64_t tile0 = seg_begin(p, t) + (int64_t)(u - seg_tile0(p, t)) * TW;
+    const int64_t tile0 = seg_begin(p, t) + (int64_t)(u - seg_tile0(p, t) * (SUB / U)) * (U * TS);
     v4f nxt[ROWS];  // the rows of the next sub-tile without a list
     {
         const int64_t sn = tile0 + (int64_t)(__ffs((int)dmask) - 1) * TS;
@@ -3093,17 +3101,17 @@ __device__ __forceinline__ void emit_tile(const Params& p, int t, uint32_t u, Em
 #pragma unroll
     for (int r = 0; r < 2; ++r) { vnx[r] = cv[r * 64 + lane]; inx[r] = ci[r * 64 + lane]; }
 #pragma unroll 1
-    for (int j = 0; j < SUB; ++j) {
+    for (int j = 0; j < U; ++j) {
         float vq[2];
         int32_t iq[2];
 #pragma unroll
         for (int r = 0; r < 2; ++r) { vq[r] = vnx[r]; iq[r] = inx[r]; }
-        if (j + 1 < SUB) {
+        if (j + 1 < U) {
 #pragma unroll
             for (int r = 0; r < 2; ++r) { vnx[r] = cv[(j + 1) * TS + r * 64 + lane]; inx[r] = ci[(j + 1) * TS + r * 64 + lane]; }
         }
         if (!((dmask >> j) & 1u)) {
-            const uint32_t c = p.cand_cnt[(size_t)u * SUB + j];
+            const uint32_t c = p.cand_cnt[(size_t)u * U + j];
 #pragma unroll 1
             for (uint32_t b = 0; b < c; b += 64) {
                 const float val = vq[0];
@@ -3234,14 +3242,15 @@ __global__ __launch_bounds__(LWG) void emit_kernel(Params p)
     x.lim = seg_out + (int64_t)seg_k(p, t, p.commit);  // end of this segment's message
     x.pos = seg_out + (int64_t)p.toff[u];
     x.erun = 0;
-    emit_tile<GEN, false>(p, t, u, x, cc, v4i{0, 0, 0, 0}, v4f{0.0f, 0.0f, 0.0f, 0.0f}, stage_idx[wib], stage_val[wib]);
+    emit_unit<GEN, false, SUB>(p, t, u, x, cc, v4i{0, 0, 0, 0}, v4f{0.0f, 0.0f, 0.0f, 0.0f}, stage_idx[wib], stage_val[wib]);
 }
 
 // Without a scan step.
-template <bool GEN>
+template <bool GEN, int U>
 __global__ __launch_bounds__(EWG) __attribute__((amdgpu_waves_per_eu(6, 8))) void resolve_emit_kernel(Params p)
 {
     constexpr bool HEADS = !GEN;
+    constexpr int H = 64 / U;   // lanes per sub-tile's list
     __shared__ EmitShared sh;
     __shared__ __attribute__((aligned(16))) int32_t stage_idx[EW][TS / 2];   // half a sub-tile's part of the message, per wavefront
     __shared__ __attribute__((aligned(16))) float stage_val[EW][TS / 2];     // (before that: the heads of the tile's lists)
@@ -3249,28 +3258,28 @@ __global__ __launch_bounds__(EWG) __attribute__((amdgpu_waves_per_eu(6, 8))) voi
     const uint32_t n_stats = (uint32_t)p.n_seg * p.n_cf;
     if (blockIdx.x < n_stats) {
         const int t = (int)(blockIdx.x / (uint32_t)p.n_cf);
-        if (!seg_small(p, t)) emit_stats(p, t, (int)(blockIdx.x - (uint32_t)t * p.n_cf), sh);
+        if (!seg_small(p, t)) emit_stats<U>(p, t, (int)(blockIdx.x - (uint32_t)t * p.n_cf), sh);
         return;
     }
     // ---- this workgroup's tiles [ub, ue) of segment t, a wavefront each
     const uint32_t w = blockIdx.x - n_stats;
     const int t = is_flat(p) ? 0 : (int)p.wseg[w];
-    const uint32_t u0 = seg_tile0(p, t), u1 = seg_tile1(p, t);
+    const uint32_t u0 = seg_tile0(p, t) * (SUB / U), u1 = seg_tile1(p, t) * (SUB / U);
     const uint32_t ub = u0 + (is_flat(p) ? w : w - p.segs[t].wg0) * EW, ue = ub + EW < u1 ? ub + EW : u1;
     // ---- loads that depend on nothing else, in flight together
     v4i hi4 = {0, 0, 0, 0};
     v4f hv4 = {0.0f, 0.0f, 0.0f, 0.0f};
-    uint32_t cc[SUB];
+    uint32_t cc[U];
     {
         const uint32_t u = ub + wib < ue ? ub + wib : ub;
         if constexpr (HEADS) {
-            // lane l: candidates 4 (l % 8) .. + 3 of sub-tile l / 8 (16-byte aligned: a sub-tile's slots start at a multiple of TS)
-            const size_t at = (size_t)u * TW + (size_t)(lane >> 3) * TS + 4u * (lane & 7);
+            // lane l: candidates 4 (l % H) .. + 3 of sub-tile l / H (16-byte aligned: a sub-tile's slots start at a multiple of TS)
+            const size_t at = (size_t)u * (U * TS) + (size_t)(lane / H) * TS + 4u * (lane % H);
             hi4 = *(const v4i*)(p.cand_idx + at);
             hv4 = *(const v4f*)(p.cand_val + at);
         }
 #pragma unroll
-        for (int j = 0; j < SUB; ++j) cc[j] = p.cand_cnt[(size_t)u * SUB + j];
+        for (int j = 0; j < U; ++j) cc[j] = p.cand_cnt[(size_t)u * U + j];
     }
     if (tid < EW) {
         const bool mine = ub + tid < ue;
@@ -3300,7 +3309,7 @@ __global__ __launch_bounds__(EWG) __attribute__((amdgpu_waves_per_eu(6, 8))) voi
     x.set_pz(p, sg, GEN && p.single);
     if (p.bounds_from == BOUNDS_FIXED) {
         uint32_t n = 0;
-        for (uint32_t i = tid; i < (p.n_tiles + CTILES - 1u) / CTILES; i += EWG) n += (uint32_t)(p.csum[(size_t)i * 8] >> 32);
+        for (uint32_t i = tid; i < (p.n_tiles * (SUB / U) + CTILES - 1u) / CTILES; i += EWG) n += (uint32_t)(p.csum[(size_t)i * 8] >> 32);
         n = wave_sum(n);
         if (lane == 0) sh.ws[2][wib] = n;
         __syncthreads();
@@ -3308,7 +3317,7 @@ __global__ __launch_bounds__(EWG) __attribute__((amdgpu_waves_per_eu(6, 8))) voi
 #pragma unroll
         for (int i = 0; i < EW; ++i) n += sh.ws[2][i];
         if ((int64_t)n > p.total_out) {   // (as in emit_kernel)
-            for (uint32_t v = ub * SUB + wib; v < ue * SUB; v += EW) put_back_subtile(p, v, x.pz, lane);
+            for (uint32_t v = ub * U + wib; v < ue * U; v += EW) put_back_subtile(p, v, x.pz, lane);
             return;
         }
     }
@@ -3354,7 +3363,7 @@ __global__ __launch_bounds__(EWG) __attribute__((amdgpu_waves_per_eu(6, 8))) voi
         hi4 = *(const v4i*)&stage_idx[wib][4 * lane];
         hv4 = *(const v4f*)&stage_val[wib][4 * lane];
     }
-    emit_tile<GEN, HEADS>(p, t, ub + wib, x, cc, hi4, hv4, stage_idx[wib], stage_val[wib]);
+    emit_unit<GEN, HEADS, U>(p, t, ub + wib, x, cc, hi4, hv4, stage_idx[wib], stage_val[wib]);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -3982,6 +3991,25 @@ struct Layout {
 // Upper bounds that depend only on (n, n_seg).
 uint64_t max_tiles(int64_t n, int n_seg) { return (uint64_t)((n + TW - 1) / TW) + (uint64_t)n_seg; }
 
+// Units of the list kernels per tile.  A wavefront per tile is a thousand wavefronts for 8 million elements, each with a long
+// walk if many entries are selected; smaller units are shorter walks, but every workgroup of the emit step resolves the
+// threshold for itself, so few entries in them are not worth it.  Microseconds with 1, 2 and 4 units per tile, Normal gradients
+// (in brackets: with a part whose entries are a hundred times larger, where they crowd):
+//    4 million, CF 10   51.4  46.0  44.2  (71.0  55.5  47.9)    CF 100   40.1  39.8  40.3  (46.5  42.2  40.0)
+//    8 million, CF 10   60.7  55.4  55.2  (80.6  65.6  58.1)    CF 100   48.3  48.5  49.9  (55.2  51.3  49.6)
+//   12 million, CF 10   71.0  66.7  67.0  (89.7  75.1  68.4)    CF 100   57.2  58.0  60.3  (63.8  59.8  59.6)
+//   24 million, CF 10   99.1  94.9        (113.6  99.6)         CF 100   80.7  82.1        (86.5  83.0)
+constexpr uint64_t FINE_ANY = 512, FINE_MANY = 1536, MIDDLE_ANY = 1024, MIDDLE_MANY = 3072;   // tiles
+constexpr int64_t MANY_CF = 40;   // "many": at least every 40th entry is selected
+static_assert(FINE_MANY * (SUB / FINE) <= EMIT_RESIDENT && MIDDLE_MANY * (SUB / MIDDLE) <= EMIT_RESIDENT,
+              "the wavefronts of such a call are resident at once");
+uint32_t units_per_tile(int64_t n, int n_seg, bool many)
+{
+    const uint64_t tiles = max_tiles(n, n_seg);
+    if (tiles <= (many ? FINE_MANY : FINE_ANY)) return SUB / FINE;
+    return tiles <= (many ? MIDDLE_MANY : MIDDLE_ANY) ? SUB / MIDDLE : 1;
+}
+
 uint64_t max_sample_blocks(int64_t n, int n_seg)
 {
     static_assert(DENSE_BLOCKS * SAMPLE_BLOCK <= 2 * SAMPLE_MAX && SAMPLE_MAX_FLAT <= DENSE_BLOCKS * SAMPLE_BLOCK * DENSE_ROUNDS,
@@ -4014,7 +4042,7 @@ Layout make_layout(int64_t n, int n_cf, int n_seg)
     Layout L;
     size_t at = 0;
     auto take = [&](size_t bytes) { size_t o = at; at = align_up(at + bytes, 256); return o; };
-    const uint64_t nt = max_tiles(n, n_seg), nsb = max_sample_blocks(n, n_seg);
+    const uint64_t nt = max_tiles(n, n_seg), nsb = max_sample_blocks(n, n_seg), nu = nt * units_per_tile(n, n_seg, true);   // (with fewer selected entries there are no more)
     const size_t sc = (size_t)n_seg * n_cf;
     L.status = take(sizeof(Status));
     // host-built tables, one piece: SegInfo[n_seg], ktab[n_seg][n_cf], sblock_seg[sample blocks]
@@ -4039,14 +4067,14 @@ Layout make_layout(int64_t n, int n_cf, int n_seg)
     L.brk_cnt = take(sizeof(uint32_t) * nt * SUB);
     L.ovn = take(sizeof(uint32_t) * nt * SUB * n_cf);
     L.ovs = take(sizeof(double) * nt * SUB * n_cf);
-    L.tg0 = take(sizeof(uint32_t) * nt);
-    L.tin = take(sizeof(uint32_t) * nt);
-    L.toff = take(sizeof(uint32_t) * nt);   // (or csum: 64 bytes per CTILES = 64 tiles, a quarter of that)
+    L.tg0 = take(sizeof(uint32_t) * nu);
+    L.tin = take(sizeof(uint32_t) * nu);
+    L.toff = take(sizeof(uint32_t) * nu);   // (or csum: 64 bytes per CTILES = 64 tiles, a quarter of that)
     L.ttake = take(sizeof(uint32_t) * nt);
-    L.tsel = take(sizeof(uint32_t) * nt);   // (or wseg)
+    L.tsel = take(sizeof(uint32_t) * nu);   // (or wseg)
     L.ssd = take(sizeof(double) * nt * SUB);
-    L.ssd_t = take(sizeof(double) * nt);
-    L.sss = take(sizeof(double) * nt * n_cf);
+    L.ssd_t = take(sizeof(double) * nu);
+    L.sss = take(sizeof(double) * nu * n_cf);
     L.cand_idx = take(sizeof(int32_t) * nt * TW);
     L.cand_val = take(sizeof(float) * nt * TW);
     L.brk_key = take(sizeof(uint32_t) * nt * TW);
@@ -4320,7 +4348,7 @@ static int compress_impl(const float* grad, float* residual, int64_t n, const do
 
     int64_t total_out = 0;
     uint32_t max_seg_tiles = 1;  // tiles of the largest segment
-    uint32_t emit_wgs = 0;       // workgroups of an emit step without scan that take tiles
+    uint32_t emit_wgs = 0;       // workgroups of an emit step without scan that take units
     int sample_rounds = 1;       // groups per thread of the sampling kernel
     uint32_t n_small = 0;        // layerwise: tensors of at most SMALL_MAX elements, one workgroup each (not under the
                                  // testing flag, which sends every tensor through the histogram route)
@@ -4332,7 +4360,6 @@ static int compress_impl(const float* grad, float* residual, int64_t n, const do
         p.flat_samples = sample_count((uint64_t)n, cf_min, cf_max, true);
         p.n_tiles = (uint32_t)((n + TW - 1) / TW);
         max_seg_tiles = p.n_tiles;
-        emit_wgs = (p.n_tiles + EW - 1) / EW;
         // more than SAMPLE_MAX samples (never a tensor read whole): 2 or 4 times SAMPLE_BLOCK samples per block, the
         // fewest that leave at most DENSE_BLOCKS blocks (more blocks keep more loads in flight, fewer cost the
         // threshold kernel less)
@@ -4366,9 +4393,13 @@ static int compress_impl(const float* grad, float* residual, int64_t n, const do
         p.n_tiles = (uint32_t)tiles;
         p.n_sample_blocks = (uint32_t)sblocks;
     }
+    // (the threshold sparsifier's count is not known: few)
+    const uint32_t upt = units_per_tile(n, ns, !fixed && total_out >= n / MANY_CF);
+    if (ns == 1) emit_wgs = (p.n_tiles * upt + EW - 1) / EW;
     const bool with_scan = p.n_tiles > EMIT_RESIDENT;   // see resolve_emit_kernel
     if (!with_scan) {
         p.csum = (uint64_t*)p.toff;
+        p.n_csum = (p.n_tiles * upt + CTILES - 1u) / CTILES;
         p.wseg = p.tsel;
     }
     // nothing has been queued or written up to here; from here on an error return leaves the outputs unspecified
@@ -4396,7 +4427,7 @@ static int compress_impl(const float* grad, float* residual, int64_t n, const do
                 g.small = 1;
             } else {
                 tile_at += (uint32_t)((nt + TW - 1) / TW); g.tile1 = tile_at;
-                g.wg0 = emit_wgs; g.wgs = (g.tile1 - g.tile0 + EW - 1) / EW; emit_wgs += g.wgs;
+                g.wg0 = emit_wgs; g.wgs = ((g.tile1 - g.tile0) * upt + EW - 1) / EW; emit_wgs += g.wgs;
                 g.samp_cnt = sample_count((uint64_t)nt, cf_min, cf_max, false);
                 const uint32_t nb = (g.samp_cnt + SAMPLE_BLOCK - 1) / SAMPLE_BLOCK;
                 for (uint32_t b = 0; b < nb; ++b) sblock_seg[sb_at + b] = (uint32_t)t;
@@ -4433,7 +4464,7 @@ static int compress_impl(const float* grad, float* residual, int64_t n, const do
     }
 
     const uint32_t sub_grid = (p.n_tiles * SUB + WAVES - 1) / WAVES;
-    const uint32_t light_grid = (p.n_tiles + LWAVES - 1) / LWAVES;
+    const uint32_t light_grid = (p.n_tiles * upt + LWAVES - 1) / LWAVES;
 
     const int ncf_form = n_cf <= 1 ? 0 : n_cf <= 2 ? 1 : n_cf <= 3 ? 2 : n_cf <= 4 ? 3 : 4;
     static_assert(MAXCF >= 4, "forms for 1, 2, 3, 4 and MAXCF CFs");
@@ -4484,18 +4515,24 @@ static int compress_impl(const float* grad, float* residual, int64_t n, const do
     // the refine kernel loops over the CFs: forms for 1, 2, 3, 4 and MAXCF CFs
     // (... and with or without the early loads of the lists' heads: with them if the tiles' wavefronts are all resident
     // at once, six per SIMD on 1024 SIMDs)
-    void (*const refine_forms[2][5])(Params) = {
-        {refine_kernel<1, false>, refine_kernel<2, false>, refine_kernel<3, false>, refine_kernel<4, false>, refine_kernel<MAXCF, false>},
-        {refine_kernel<1, true>, refine_kernel<2, true>, refine_kernel<3, true>, refine_kernel<4, true>, refine_kernel<MAXCF, true>}};
+#define REFINE_FORMS(heads, u) {refine_kernel<1, heads, u>, refine_kernel<2, heads, u>, refine_kernel<3, heads, u>, refine_kernel<4, heads, u>, refine_kernel<MAXCF, heads, u>}
+    void (*const refine_forms[3][2][5])(Params) = {{REFINE_FORMS(false, SUB), REFINE_FORMS(true, SUB)},
+                                                   {REFINE_FORMS(false, MIDDLE), REFINE_FORMS(true, MIDDLE)},
+                                                   {REFINE_FORMS(false, FINE), REFINE_FORMS(true, FINE)}};
+#undef REFINE_FORMS
+    const int fine = upt == 1 ? 0 : upt == SUB / MIDDLE ? 1 : 2;
     const int heads = (!random && p.n_tiles <= EMIT_RESIDENT) ? 1 : 0;
-    hipLaunchKernelGGL(refine_forms[heads][ncf_form], dim3(light_grid), dim3(LWG), 0, stream, p);
+    hipLaunchKernelGGL(refine_forms[fine][heads][ncf_form], dim3(light_grid), dim3(LWG), 0, stream, p);
     const bool general = p.random || p.single;   // (the plain call has forms of its own)
     if (with_scan) {
         const uint32_t scan_slices = (max_seg_tiles + SCAN_SLICE - 1) / SCAN_SLICE;
         hipLaunchKernelGGL(scan_kernel, dim3(ns, scan_slices + n_cf), dim3(SCAN_T), 0, stream, p, scan_slices);
         hipLaunchKernelGGL(general ? emit_kernel<true> : emit_kernel<false>, dim3(light_grid), dim3(LWG), 0, stream, p);
     } else {
-        hipLaunchKernelGGL(general ? resolve_emit_kernel<true> : resolve_emit_kernel<false>, dim3(emit_wgs + (uint32_t)(ns * n_cf)),
+        void (*const emit_forms[3][2])(Params) = {{resolve_emit_kernel<false, SUB>, resolve_emit_kernel<true, SUB>},
+                                                  {resolve_emit_kernel<false, MIDDLE>, resolve_emit_kernel<true, MIDDLE>},
+                                                  {resolve_emit_kernel<false, FINE>, resolve_emit_kernel<true, FINE>}};
+        hipLaunchKernelGGL(emit_forms[fine][general ? 1 : 0], dim3(emit_wgs + (uint32_t)(ns * n_cf)),
                            dim3(EWG), 0, stream, p);
     }
     }
