@@ -80,6 +80,13 @@ constexpr uint32_t LONG_WALK = 256;   // a tile with at least this many listed e
 #ifndef GV_NT
 #define GV_NT 1                     // non-temporal hints on the streaming loads and stores
 #endif
+// A flat Top-k call of at most this many elements is direct: the sampling kernel histograms all of them, so the brackets are
+// the bins that hold the k-th largest, what lies above them is known, and the pass gathers their entries itself; the plan and
+// refine steps are left out.
+#ifndef GV_DIRECT
+#define GV_DIRECT 524288
+#endif
+constexpr int64_t DIRECT_MAX = GV_DIRECT;
 constexpr int REP = 8;              // copies of the bracket histogram and of the gather lists
 constexpr int NBIN = 2048;          // bins of the bracket / refine / coarse histograms
 constexpr uint32_t OVF = NBIN - 1;  // bins 0 .. OVF - 1 cover the bracket; bin OVF stands for everything above it
@@ -96,7 +103,7 @@ constexpr uint32_t SWIN = 12, SWIN_ABOVE = 2;  // octaves of the window, and how
 // equal bins of 1.1 %, 33.9 for all.)
 constexpr uint32_t SKEY0 = SEXP0 << 23;
 constexpr uint32_t SCOARSE = SOCT << (23 - SCSHIFT), SFINE = SWIN << (23 - SFSHIFT), SLESS = SWIN << (23 - SCSHIFT);
-constexpr uint32_t SUSED = SCOARSE + SFINE - SLESS;   // bins in use
+constexpr uint32_t SUSED = 1 + SCOARSE + SFINE - SLESS;   // bins in use: the first is the key 0 alone
 static_assert(SUSED <= (uint32_t)SBIN && (uint64_t)SKEY0 + ((uint64_t)SOCT << 23) <= 0x7F800000ull, "inside the finite keys");
 constexpr int SGRP = 8;             // the sample bins in SGRP groups: one workgroup of the threshold kernel each
 constexpr int RGRP = 64;            // ... and in RGRP groups, one wavefront of a flat call's pass each (bracket_role)
@@ -122,7 +129,9 @@ constexpr uint32_t WAIT_POLLS_TEST = 256;  // ... and under GRAVAC_FLAG_STALL_FA
 constexpr uint32_t NONE = 0xFFFFFFFFu;
 constexpr uint32_t KEY_END = 0x80000000u;  // one past the largest key
 
-enum : uint32_t { MODE_RESOLVED = 0, MODE_GATHER = 1, MODE_FAIL = 3 };
+enum : uint32_t { MODE_RESOLVED = 0, MODE_GATHER = 1,
+                  MODE_WIDE = 2,   // a direct call's bin that is too full to gather or too wide: resolved from the bracket lists
+                  MODE_FAIL = 3 };
 // What the plan step found for a segment, the heaviest kind over its CFs:
 //   FAIL_TIES    the bin that holds the k-th largest is at most 2^11 keys wide and too full to gather (a mass of equal
 //                values): it is counted key by key, from the bracket lists;
@@ -202,6 +211,7 @@ struct Params {
     int random;              // 1 = Random-k: the order is that of a keyed priority of the index, not of |acc|
     int no_commit;           // 1: nothing is removed from the residual (it keeps acc); the caller commits a message later
     uint32_t bounds_from;    // BOUNDS_*
+    uint32_t direct;         // 1: the sample is the whole tensor, and its histogram says which bin holds the k-th largest
     uint32_t fixed_key;      // BOUNDS_FIXED: the key of the caller's threshold; entries with key >= fixed_key are kept
     uint32_t wait_polls;     // polls after which a workgroup of the plan step stops waiting for the others
     uint32_t wait_extra;     // arrivals it waits for beyond those that will come: 0 (1 under the testing flag)
@@ -296,18 +306,19 @@ __device__ __forceinline__ uint32_t sample_bin(uint32_t key, uint32_t w0)
     const uint32_t c0 = (w0 - SKEY0) >> SCSHIFT;
     const uint32_t d = key < SKEY0 ? 0u : key - SKEY0, c = d >> SCSHIFT;
     const uint32_t f = key - w0;                       // (wraps below the window)
-    if (f < (SWIN << 23)) return c0 + (f >> SFSHIFT);
+    if (f < (SWIN << 23)) return 1u + c0 + (f >> SFSHIFT);
     const uint32_t cc = c < SCOARSE - 1u ? c : SCOARSE - 1u;
-    return cc < c0 ? cc : cc + SFINE - SLESS;
+    return cc < c0 ? cc + (key != 0u ? 1u : 0u) : 1u + cc + SFINE - SLESS;   // (the window does not start at the lowest octave: 0 < c0)
 }
 // first key of bin b; the next bin's is one past its last key
-__device__ __forceinline__ uint32_t sample_bin_first(uint32_t b, uint32_t w0)
+__device__ __forceinline__ uint32_t sample_bin_first(uint32_t bin, uint32_t w0)
 {
     const uint32_t c0 = (w0 - SKEY0) >> SCSHIFT;
-    if (b >= SUSED) return KEY_END;
+    if (bin >= SUSED) return KEY_END;
+    if (bin <= 1u) return bin;
+    const uint32_t b = bin - 1u;
     if (b >= c0 && b < c0 + SFINE) return w0 + ((b - c0) << SFSHIFT);
-    const uint32_t c = b < c0 ? b : b - (SFINE - SLESS);
-    return c == 0u ? 0u : SKEY0 + (c << SCSHIFT);
+    return SKEY0 + ((b < c0 ? b : b - (SFINE - SLESS)) << SCSHIFT);
 }
 __device__ __forceinline__ uint32_t sample_bin_end(uint32_t b, uint32_t w0) { return sample_bin_first(b + 1u, w0); }
 
@@ -812,18 +823,16 @@ __global__ __launch_bounds__(256) void sample_kernel(Params p)
         const uint32_t nbk = is_flat(p) ? p.n_sample_blocks : (S + per - 1) / per;
         const uint4 z = make_uint4(0u, 0u, 0u, 0u);
         const uint32_t blocks = (uint32_t)p.n_cf * seg_rep(p, t);  // the segment's copy blocks
+        for (uint32_t i = lb * 256 + tid; i < blocks; i += nbk * 256) p.list_cnt[(seg_block(p, t, 0) + i) * 32] = 0;
+        if (is_flat(p) && b == 0) reset_status(p, tid);   // (a flat call has no threshold step)
+        if (p.direct) return;
         uint4* h1 = (uint4*)(p.hist1 + seg_block(p, t, 0) * NBIN);
         for (uint32_t i = lb * 256 + tid; i < blocks * NBIN / 4; i += nbk * 256) h1[i] = z;
         uint4* cs = (uint4*)(p.coarse + (size_t)t * NBIN);
         for (uint32_t i = lb * 256 + tid; i < NBIN / 4; i += nbk * 256) cs[i] = z;
         for (uint32_t i = lb * 256 + tid; i < (uint32_t)p.n_cf * 64; i += nbk * 256) p.ovfc[((size_t)t * p.n_cf * 64 + i) * 32] = 0;
-        for (uint32_t i = lb * 256 + tid; i < blocks; i += nbk * 256) p.list_cnt[(seg_block(p, t, 0) + i) * 32] = 0;
         if (lb == 0 && tid < XQ_WORDS) p.xq[(size_t)t * XQ_LINE + tid] = 0;
-        if (is_flat(p)) {
-            // what a flat call has no threshold step for
-            if (b == 0) reset_status(p, tid);
-            if (b == 0 && p.bounds_from != BOUNDS_SAMPLED && tid < p.n_cf) known_bracket(p, 0, tid, p.bnd + 4 * tid);
-        }
+        if (is_flat(p) && b == 0 && p.bounds_from != BOUNDS_SAMPLED && tid < p.n_cf) known_bracket(p, 0, tid, p.bnd + 4 * tid);
         if (p.csum)
             for (uint32_t i = b * 256 + tid; i < p.n_csum; i += gridDim.x * 256) p.csum[(size_t)i * 8] = 0;
     };
@@ -1057,6 +1066,19 @@ __global__ __launch_bounds__(P * 1024 / G) __attribute__((amdgpu_waves_per_eu(SM
     }
 }
 
+// From which key on the pass over the gradient stores +0 instead of acc in a sub-tile that lists its candidates
+// (NONE: nowhere): the key the sample puts the committed CF's k-th largest at, kept inside that CF's bracket
+// [lo, top).  Entries from there on are in the candidate list, and most of them are selected: the emit step then has
+// a scattered store only for the entries between this key and the threshold, selected ones below it (+0) or
+// unselected ones at or above it (acc put back), instead of one for every selected entry of the bracket; a
+// scattered 4-byte store costs the memory a read and a write of its 64 bytes, 34 us per million of them.
+__device__ __forceinline__ uint32_t zero_from(const Params& p, uint32_t lo, uint32_t top, uint32_t mid)  // mid: bnd_mid
+{
+    if (p.single || p.no_commit || top == KEY_END) return NONE;
+    if (mid == NONE) return top;
+    return mid < lo ? lo : (mid > top ? top : mid);
+}
+
 // A flat call's brackets: RGRP wavefronts, each of which adds up one group of bins of all sample blocks' histograms (what
 // lies above them it knows from the blocks themselves) and writes the bracket ends that fall into its bins.  No wavefront
 // waits for another, and up to 64 blocks are one round trip to memory.
@@ -1098,6 +1120,29 @@ __global__ __launch_bounds__(64) void bracket_kernel(Params p)
     const uint32_t above1 = g_above + last_lane(incl) - incl, above0 = above1 + h1;   // samples above each of this lane's bins
     const uint32_t bin0 = 2u * (role * 32u + (uint32_t)(lane & 31));
     for (int j = 0; j < p.n_cf; ++j) {
+        if (p.direct) {
+            // all ranks are k, and all elements are counted: the bin of the k-th largest and what lies above it
+            const uint32_t kj = (uint32_t)__builtin_amdgcn_readlane((int)rank_lo, j);
+            const bool in1 = above1 < kj && above1 + h1 >= kj, in0 = above0 < kj && above0 + h0 >= kj;
+            if (!in1 && !in0) continue;
+            const uint32_t bin = in1 ? bin0 + 1u : bin0, above = in1 ? above1 : above0, c = in1 ? h1 : h0;
+            const uint32_t lo = sample_bin_first(bin, w0), end = sample_bin_end(bin, w0), mid = key_inside(bin, w0, kj - above, c);
+            p.bnd[4 * j] = lo; p.bnd[4 * j + 1] = end; p.bnd[4 * j + 2] = mid;
+            CfState st;
+            st.k = kj; st.lo = lo; st.s = 0; st.base = lo; st.span = end - lo - 1u; st.above = above; st.c = c; st.top = end;
+            // (the first and the last bin span many octaves, too many for sums scaled by the bin's bounds)
+            st.mode = st.span == 0u ? MODE_RESOLVED : (c <= (uint32_t)LCAP && st.span < (1u << SCSHIFT) ? MODE_GATHER : MODE_WIDE);
+            st.tau = lo; st.cnt_gt = above; st.need = kj - above;   // (if resolved)
+            st.pad[0] = st.pad[1] = st.pad[2] = st.pad[3] = 0;
+            p.st[j] = st;
+            if (st.mode == MODE_WIDE) { p.status->any_fail = 1; p.status->n_fail = 1; p.status->n_narrow = 1; }
+            if (j == p.commit) {
+                SegState sg;
+                sg.fail = FAIL_NONE; sg.pz = zero_from(p, lo, end, mid);
+                p.seg[0] = sg;
+            }
+            continue;
+        }
         const auto find = [&](uint32_t ranks, uint32_t word, uint32_t none, auto key) {
             // the bin of the rank-th sample from the top, if it is one of this wavefront's
             const uint32_t rank = (uint32_t)__builtin_amdgcn_readlane((int)ranks, j);
@@ -1123,19 +1168,6 @@ __global__ __launch_bounds__(64) void bracket_kernel(Params p)
 //     SM_EXACT (exact route, failed segments only): read acc from residual; the brackets come from the
 //     coarse histogram.  Both collect the lists of the sub-tile in index order.
 // ---------------------------------------------------------------------------------------------
-// From which key on the pass over the gradient stores +0 instead of acc in a sub-tile that lists its candidates
-// (NONE: nowhere): the key the sample puts the committed CF's k-th largest at, kept inside that CF's bracket
-// [lo, top).  Entries from there on are in the candidate list, and most of them are selected: the emit step then has
-// a scattered store only for the entries between this key and the threshold, selected ones below it (+0) or
-// unselected ones at or above it (acc put back), instead of one for every selected entry of the bracket; a
-// scattered 4-byte store costs the memory a read and a write of its 64 bytes, 34 us per million of them.
-__device__ __forceinline__ uint32_t zero_from(const Params& p, uint32_t lo, uint32_t top, uint32_t mid)  // mid: bnd_mid
-{
-    if (p.single || p.no_commit || top == KEY_END) return NONE;
-    if (mid == NONE) return top;
-    return mid < lo ? lo : (mid > top ? top : mid);
-}
-
 // Entries of a sub-tile that some bracket concerns (key >= lo_min) go through LDS on their way to the lists, compacted in
 // index order, so that what has to be done for each of them (per CF a count and an energy, a histogram update; the list
 // stores) is done 64 entries at a time by full wavefronts.  Done where the entries lie, an element at a time, the pass
@@ -1241,8 +1273,9 @@ __device__ __forceinline__ void stage_dense_row(SubCtx<1>& c, const float a[4], 
 // The staged entries, 64 at a time: per CF a count and the energy of those above its bracket and a histogram update for
 // those inside it; into the lists.  listed = whether the sub-tile keeps a candidate list; counted = whether the entries above
 // the bracket have been counted.
-template <bool RND, int NCF>
-__device__ __forceinline__ void flush_stage(SubCtx<NCF>& c, bool listed, bool counted, int lane)
+// D (a direct call): those inside a bracket go to the gather lists; zeros are counted where they are found.
+template <bool RND, bool D, int NCF>
+__device__ __forceinline__ void flush_stage(const Params& p, uint32_t v, SubCtx<NCF>& c, bool listed, bool counted, int lane)
 {
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");  // the wavefront's own LDS writes, read back by other lanes
 #pragma unroll 1
@@ -1261,10 +1294,22 @@ __device__ __forceinline__ void flush_stage(SubCtx<NCF>& c, bool listed, bool co
                     c.ovn[j] += (uint32_t)__popcll(__ballot(above));
                     c.ovs[j] += above ? dd : 0.0;
                 }
-                const bool in = from && !above;
+                const bool in = from && !above && !(D && key == 0u);
                 const uint64_t m = __ballot(in);
                 if (m == 0ull) continue;
-                if (in) atomicAdd(&c.h1[j * c.hstride + bin_word((key - c.org[j]) >> c.sh[j])], 1u);
+                if constexpr (D) {
+                    const uint32_t lst = (uint32_t)j * REP + (blockIdx.x & (REP - 1u));
+                    const int leader = __ffsll((unsigned long long)m) - 1;
+                    uint32_t at = 0;
+                    if (lane == leader) at = atomicAdd(&p.list_cnt[lst * 32], (uint32_t)__popcll(m));
+                    const uint32_t pos = (uint32_t)__builtin_amdgcn_readlane((int)at, leader) + lanes_below(m);
+                    if (in && pos < LCAP) {
+                        p.list_key[lst * LCAP + pos] = key;
+                        p.list_tile[lst * LCAP + pos] = v / FINE;
+                    }
+                } else {
+                    if (in) atomicAdd(&c.h1[j * c.hstride + bin_word((key - c.org[j]) >> c.sh[j])], 1u);
+                }
                 inside = inside || in;
             }
         }
@@ -1351,7 +1396,7 @@ struct ExactBounds {
 };
 
 // One sub-tile v, by one wavefront; stage: STAGE entries of LDS of its own.
-template <int M, bool RND, int NCF>
+template <int M, bool RND, bool D, int NCF>
 __device__ __forceinline__ void stream_subtile(const Params& p, uint32_t v, int lane, const ExactBounds* xb, uint2* stage)
 {
     constexpr bool EF = (M != SM_EXACT);  // a first pass: sums acc^2, takes the brackets from the threshold kernel
@@ -1401,6 +1446,7 @@ __device__ __forceinline__ void stream_subtile(const Params& p, uint32_t v, int 
                 c.lo[j] = (uint32_t)__builtin_amdgcn_readlane((int)word, 4 * j);
                 bracket_bins(c.lo[j], (uint32_t)__builtin_amdgcn_readlane((int)word, 4 * j + 1), c.sh[j], c.org[j], c.top[j]);
                 c.lo_min = c.lo[j] < c.lo_min ? c.lo[j] : c.lo_min;
+                if (D) c.top[j] = (uint32_t)__builtin_amdgcn_readlane((int)word, 4 * j + 1);   // (the bin, no more)
                 if (j == p.commit) {
                     c.lo_c = c.lo[j];
                     if (M == SM_EF) c.pz = zero_from(p, c.lo[j], c.top[j], (uint32_t)__builtin_amdgcn_readlane((int)word, 4 * j + 2));
@@ -1437,7 +1483,7 @@ __device__ __forceinline__ void stream_subtile(const Params& p, uint32_t v, int 
     bool at_once = false;            // all rows are staged before the entries are worked on
     // Zeros inside a bracket are only counted, not listed (whole sub-tiles of Top-k's first pass).  Where they may be
     // selected, the committed CF's bracket starts at zero, all of the sub-tile are candidates and it keeps no list.
-    const bool skip_zeros = EF && !RND && whole && c.lo_min == 0u;
+    const bool count_zeros = EF && !RND && c.lo_min == 0u, skip_zeros = count_zeros && whole;
     if (skip_zeros) c.lo_min = 1u;
     uint32_t zeros = 0;
     int parts = (int)((e0 - s0 + ROW - 1) / ROW);
@@ -1527,6 +1573,10 @@ __device__ __forceinline__ void stream_subtile(const Params& p, uint32_t v, int 
                         c.ssd = __builtin_fma(d, d, c.ssd);
                     }
                 }
+                if (D && count_zeros) {   // (they are listed as candidates, if they are, but not as the bracket's)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) zeros += (uint32_t)__popcll(__ballot(((vm >> e) & 1u) && key[e] == 0u));
+                }
             }
             if constexpr (NCF == 1) {
                 if (dense) stage_dense_row(c, a[0], key, g);
@@ -1540,7 +1590,7 @@ __device__ __forceinline__ void stream_subtile(const Params& p, uint32_t v, int 
                 for (int e = 0; e < 4; ++e) a[q][e] = a[q + 1][e];
             }
         }
-        if (part == parts - 1 || c.staged > STAGE - ROW) flush_stage<RND, NCF>(c, !dense, NCF == 1 && dense, lane);
+        if (part == parts - 1 || c.staged > STAGE - ROW) flush_stage<RND, D, NCF>(p, v, c, !dense, NCF == 1 && dense, lane);
     }
 
 #pragma unroll
@@ -1551,7 +1601,7 @@ __device__ __forceinline__ void stream_subtile(const Params& p, uint32_t v, int 
             if (lane == 0) {
                 p.ovn[(size_t)v * p.n_cf + j] = o;
                 p.ovs[(size_t)v * p.n_cf + j] = s;
-                if (EF && o) atomicAdd(&p.ovfc[(((size_t)t * p.n_cf + j) * 64 + (v & 63)) * 32], o);
+                if (EF && !D && o) atomicAdd(&p.ovfc[(((size_t)t * p.n_cf + j) * 64 + (v & 63)) * 32], o);
             }
         }
     }
@@ -1559,7 +1609,7 @@ __device__ __forceinline__ void stream_subtile(const Params& p, uint32_t v, int 
         const double s = wave_sum(c.ssd);
         if (lane == 0) p.ssd[v] = s;
     }
-    if (zeros != 0u && lane == 0) {
+    if (!D && zeros != 0u && lane == 0) {
 #pragma unroll
         for (int j = 0; j < NCF; ++j)   // (a sampled bracket is not empty: zeros are inside one that starts there)
             if (c.lo[j] == 0u) atomicAdd(&c.h1[j * c.hstride + bin_word(0u)], zeros);
@@ -1568,13 +1618,13 @@ __device__ __forceinline__ void stream_subtile(const Params& p, uint32_t v, int 
 }
 
 // The first pass (SM_EF, SM_SINGLE): one sub-tile per wavefront, one launch covers the whole gradient.
-template <int M, bool RND, int NCF>
+template <int M, bool RND, bool D, int NCF>
 __global__ __launch_bounds__(WG) void stream_kernel(Params p)
 {
     static_assert(M != SM_EXACT, "the exact route is part of the plan step");
     __shared__ uint2 stage[WAVES][STAGE];
     const uint32_t w = __builtin_amdgcn_readfirstlane(blockIdx.x * WAVES + (threadIdx.x >> 6));
-    stream_subtile<M, RND, NCF>(p, w, threadIdx.x & 63, nullptr, stage[threadIdx.x >> 6]);
+    stream_subtile<M, RND, D, NCF>(p, w, threadIdx.x & 63, nullptr, stage[threadIdx.x >> 6]);
     if (p.bounds_from == BOUNDS_FIXED) {
         // the threshold sparsifier's first kernel.  The later steps find everything resolved: selected <=> key > tau with tau
         // one key below the threshold, no ties to take
@@ -1966,7 +2016,7 @@ __global__ __launch_bounds__(PLAN_T) void plan_kernel(Params p)
                 const uint32_t x = i / per_chunk, first = u0 + sh.own[x] * per;
                 if (full && phase == 1) {
                     const uint32_t v = __builtin_amdgcn_readfirstlane(first * SUB + (i - x * per_chunk));
-                    if (v < u1 * SUB) stream_subtile<SM_EXACT, RND, MAXCF>(p, v, lane, &sh.xb, (uint2*)&sh.lh[0][0] + wib * STAGE);
+                    if (v < u1 * SUB) stream_subtile<SM_EXACT, RND, false, MAXCF>(p, v, lane, &sh.xb, (uint2*)&sh.lh[0][0] + wib * STAGE);
                 } else {
                     const uint32_t u = first + (i - x * per_chunk);
                     if (u < u1) plan_recount(p, sh, u, hist, copies, lane);
@@ -2675,9 +2725,25 @@ __device__ __forceinline__ void gathered_load(const Params& p, int t, int j, int
 }
 
 // f(key - base, tile, value) for every gathered entry of this thread.
-template <typename F>
+template <bool D, typename F>
 __device__ __forceinline__ void gathered_each(const Params& p, int tid, const Gathered& g, F f)
 {
+    if (D && g.mode == MODE_WIDE) {
+        // the bin's entries are in the bracket lists, among those of other CFs' bins: a quarter of a sub-tile's slots per
+        // wavefront and round (those past the list's end hold whatever they do and are not used)
+        constexpr uint32_t K = TS / 64 / 4;
+#pragma unroll 1
+        for (uint32_t x = (uint32_t)tid >> 6; x < p.n_tiles * SUB * 4; x += EW) {
+            const uint32_t v = x / 4, at = (x & 3u) * (TS / 4) + (tid & 63), n = p.brk_cnt[v] & LISTED;
+            uint32_t k[K];
+#pragma unroll
+            for (uint32_t q = 0; q < K; ++q) k[q] = p.brk_key[(size_t)v * TS + at + q * 64];
+#pragma unroll
+            for (uint32_t q = 0; q < K; ++q)
+                if (at + q * 64 < n && k[q] >= g.base && k[q] - g.base <= g.span) f(k[q] - g.base, v / FINE, 0.0f);
+        }
+        return;
+    }
     if (g.spec) {
 #pragma unroll
         for (int q = 0; q < SPEC_Q; ++q)
@@ -2698,6 +2764,7 @@ __device__ __forceinline__ void gathered_each(const Params& p, int tid, const Ga
 }
 
 // g.tau / need / cnt_gt: the key of the k-th largest, how many equal to it are selected, how many lie above.
+template <bool D>
 __device__ __forceinline__ void gathered_resolve(const Params& p, int tid, Gathered& g, EmitShared& sh)
 {
     const int lane = tid & 63, wib = tid >> 6;
@@ -2706,7 +2773,8 @@ __device__ __forceinline__ void gathered_resolve(const Params& p, int tid, Gathe
 #pragma unroll
     for (int r = 0; r < REP; ++r) filled += g.fill[r];
     const uint32_t want = g.k - g.above;
-    if (g.mode != MODE_GATHER || filled != g.c || g.c > (uint32_t)LCAP || want == 0 || want > g.c) {
+    const bool wide = D && g.mode == MODE_WIDE;
+    if (!wide && (g.mode != MODE_GATHER || filled != g.c || g.c > (uint32_t)LCAP || want == 0 || want > g.c)) {
         if (tid == 0) p.status->error = 1;
         g.mode = MODE_FAIL;
         g.tau = g.base; g.need = 0; g.cnt_gt = g.above;
@@ -2722,7 +2790,7 @@ __device__ __forceinline__ void gathered_resolve(const Params& p, int tid, Gathe
     for (;;) {
         *(uint4*)&sh.hist[4 * tid] = make_uint4(0u, 0u, 0u, 0u);
         __syncthreads();
-        gathered_each(p, tid, g, [&](uint32_t d, uint32_t, float) {
+        gathered_each<D>(p, tid, g, [&](uint32_t d, uint32_t, float) {
             if ((d & pmask) == prefix) atomicAdd(&sh.hist[(d >> shift) & (NBIN - 1)], 1u);
         });
         __syncthreads();
@@ -2752,11 +2820,13 @@ __device__ __forceinline__ void gathered_resolve(const Params& p, int tid, Gathe
 }
 
 // Statistics of (segment t, CF j), by one workgroup.
-template <int U>
+template <int U, bool D>
 __device__ __forceinline__ void emit_stats(const Params& p, int t, int j, EmitShared& sh)
 {
     const int tid = threadIdx.x, lane = tid & 63, wib = tid >> 6;
-    const uint32_t u0 = seg_tile0(p, t) * (SUB / U), u1 = seg_tile1(p, t) * (SUB / U);
+    // (a direct call has no refine step to add up the sub-tiles' sums)
+    const uint32_t u0 = seg_tile0(p, t) * (D ? SUB : SUB / U), u1 = seg_tile1(p, t) * (D ? SUB : SUB / U);
+    const double *ssd = D ? p.ssd : p.ssd_t, *sss = D ? p.ovs : p.sss;
     Gathered g;
     gathered_load(p, t, j, tid, g);
     // the units' sums, eight units per thread and round, in a fixed order
@@ -2767,8 +2837,8 @@ __device__ __forceinline__ void emit_stats(const Params& p, int t, int j, EmitSh
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
             const uint32_t u = v0 + q * EWG;
-            xd[q] = (u < u1) ? p.ssd_t[u] : 0.0;
-            xj[q] = (u < u1) ? p.sss[(size_t)u * p.n_cf + j] : 0.0;
+            xd[q] = (u < u1) ? ssd[u] : 0.0;
+            xj[q] = (u < u1) ? sss[(size_t)u * p.n_cf + j] : 0.0;
         }
 #pragma unroll
         for (int q = 0; q < 8; ++q) { sd += xd[q]; sj += xj[q]; }
@@ -2778,14 +2848,25 @@ __device__ __forceinline__ void emit_stats(const Params& p, int t, int j, EmitSh
         kept = wave_sum(kept);
         if (lane == 0) sh.ws[0][wib] = kept;
     }
-    gathered_resolve(p, tid, g, sh);
+    gathered_resolve<D>(p, tid, g, sh);
     const uint32_t dtau = g.tau - g.base;  // the threshold inside the located bin
     // the entries of the located bin above the threshold (Random-k: and the one at it).  Their order in the gather
     // lists varies from run to run, so their energies are added as integers: every square, exact in binary64, is
     // scaled by a power of two that puts the largest of them below 2^50 and truncated, the sum of up to LCAP of them
     // fits 64 bits and does not depend on the order, and it is off by less than 2^-38 of itself.
     double ebin = 0.0;
-    if (g.mode == MODE_GATHER) {
+    if (D && g.mode == MODE_WIDE) {
+        // (too many for that, but their order is the lists', which does not vary)
+        double plain = 0.0;
+        gathered_each<D>(p, tid, g, [&](uint32_t d, uint32_t, float) {
+            const double v = (double)__uint_as_float(g.base + d);
+            plain += d > dtau ? v * v : 0.0;
+        });
+        plain = wave_sum(plain);
+        if (lane == 0) sh.dred[2][wib] = plain;
+        __syncthreads();
+        for (int w = 0; w < EW; ++w) ebin += sh.dred[2][w];
+    } else if (g.mode == MODE_GATHER) {
         const auto square = [&](uint32_t d, float val) {
             const bool in = d > dtau || (p.random && d == dtau);
             const double dv = p.random ? (double)val : (double)__uint_as_float(g.base + d);
@@ -2800,7 +2881,7 @@ __device__ __forceinline__ void emit_stats(const Params& p, int t, int j, EmitSh
                 const int ex = ilogb(m * m);                  // every square is below 2^(ex + 1)
                 const double sc = scalbn(1.0, 49 - ex);       // (a power of two: the product is exact)
                 uint64_t acc = 0;
-                gathered_each(p, tid, g, [&](uint32_t d, uint32_t, float val) { acc += (uint64_t)(square(d, val) * sc); });  // < 2^50 each
+                gathered_each<D>(p, tid, g, [&](uint32_t d, uint32_t, float val) { acc += (uint64_t)(square(d, val) * sc); });  // < 2^50 each
                 acc = wave_sum(acc);
                 if (lane == 0) sh.ured[wib] = acc;
                 __syncthreads();
@@ -2812,7 +2893,7 @@ __device__ __forceinline__ void emit_stats(const Params& p, int t, int j, EmitSh
         } else {
             double mx = 0.0, plain = 0.0;
             bool finite = true;
-            gathered_each(p, tid, g, [&](uint32_t d, uint32_t, float val) {
+            gathered_each<D>(p, tid, g, [&](uint32_t d, uint32_t, float val) {
                 const double x = square(d, val);
                 mx = fmax(mx, x);   // (a NaN square is skipped here and shows in the plain sum)
                 plain += x;
@@ -2834,7 +2915,7 @@ __device__ __forceinline__ void emit_stats(const Params& p, int t, int j, EmitSh
             } else if (mx > 0.0) {
                 const int ex = ilogb(mx);                      // 2^ex <= mx < 2^(ex + 1)
                 uint64_t acc = 0;
-                gathered_each(p, tid, g, [&](uint32_t d, uint32_t, float val) { acc += (uint64_t)scalbn(square(d, val), 49 - ex); });  // < 2^50 each
+                gathered_each<D>(p, tid, g, [&](uint32_t d, uint32_t, float val) { acc += (uint64_t)scalbn(square(d, val), 49 - ex); });  // < 2^50 each
                 acc = wave_sum(acc);
                 if (lane == 0) sh.ured[wib] = acc;
                 __syncthreads();
@@ -3246,8 +3327,8 @@ __global__ __launch_bounds__(LWG) void emit_kernel(Params p)
 }
 
 // Without a scan step.
-template <bool GEN, int U>
-__global__ __launch_bounds__(EWG) __attribute__((amdgpu_waves_per_eu(6, 8))) void resolve_emit_kernel(Params p)
+template <bool GEN, int U, bool D>
+__global__ __launch_bounds__(EWG) __attribute__((amdgpu_waves_per_eu(D ? 4 : 6, 8))) void resolve_emit_kernel(Params p)
 {
     constexpr bool HEADS = !GEN;
     constexpr int H = 64 / U;   // lanes per sub-tile's list
@@ -3258,7 +3339,7 @@ __global__ __launch_bounds__(EWG) __attribute__((amdgpu_waves_per_eu(6, 8))) voi
     const uint32_t n_stats = (uint32_t)p.n_seg * p.n_cf;
     if (blockIdx.x < n_stats) {
         const int t = (int)(blockIdx.x / (uint32_t)p.n_cf);
-        if (!seg_small(p, t)) emit_stats<U>(p, t, (int)(blockIdx.x - (uint32_t)t * p.n_cf), sh);
+        if (!seg_small(p, t)) emit_stats<U, D>(p, t, (int)(blockIdx.x - (uint32_t)t * p.n_cf), sh);
         return;
     }
     // ---- this workgroup's tiles [ub, ue) of segment t, a wavefront each
@@ -3283,14 +3364,29 @@ __global__ __launch_bounds__(EWG) __attribute__((amdgpu_waves_per_eu(6, 8))) voi
     }
     if (tid < EW) {
         const bool mine = ub + tid < ue;
-        sh.tg[tid] = mine ? p.tg0[ub + tid] : 0u;
-        sh.te[tid] = mine ? p.tin[ub + tid] : 0u;
+        uint32_t n_above = 0, n_in = 0;
+        if (mine && D) {
+#pragma unroll
+            for (int i = 0; i < U; ++i) {
+                const uint32_t v = (ub + tid) * U + i;
+                n_above += p.ovn[(size_t)v * p.n_cf + p.commit];
+                n_in += p.brk_cnt[v] >> ZERO_SHIFT;
+            }
+        } else if (mine) {
+            n_above = p.tg0[ub + tid];
+            n_in = p.tin[ub + tid];
+        }
+        sh.tg[tid] = n_above;
+        sh.te[tid] = n_in;
         sh.fg[tid] = 0;
         sh.fe[tid] = 0;
     }
     // what lies before the workgroup's tiles in the segment: whole groups of CTILES tiles, and single tiles at both ends
+    // (a direct call: single sub-tiles; what a bin that is resolved has in them are zeros)
     uint32_t pg = 0, pe = 0;
-    {
+    if constexpr (D) {
+        for (uint32_t v = tid; v < ub * U; v += EWG) { pg += p.ovn[(size_t)v * p.n_cf + p.commit]; pe += p.brk_cnt[v] >> ZERO_SHIFT; }
+    } else {
         const uint32_t g0 = (u0 + CTILES - 1u) / CTILES, g1 = ub / CTILES;   // whole groups, if g0 < g1
         const uint32_t head = g0 * CTILES < ub ? g0 * CTILES : ub, tail = g1 > g0 ? g1 * CTILES : head;
         for (uint32_t i = g0 + tid; i < g1; i += EWG) { const uint64_t v = p.csum[(size_t)i * 8]; pg += (uint32_t)(v >> 32); pe += (uint32_t)v; }
@@ -3321,14 +3417,14 @@ __global__ __launch_bounds__(EWG) __attribute__((amdgpu_waves_per_eu(6, 8))) voi
             return;
         }
     }
-    gathered_resolve(p, tid, g, sh);
+    gathered_resolve<D>(p, tid, g, sh);
     const uint32_t dtau = g.tau - g.base;  // the threshold inside the located bin
     // ---- the gathered entries above and at the threshold, by tile.  Entries equal to tau: those inside a located bin
     // that is one key wide, else the gathered ones
     const bool one_key = g.mode == MODE_RESOLVED;
     if (!one_key) pe = 0;
-    if (g.mode == MODE_GATHER) {
-        gathered_each(p, tid, g, [&](uint32_t d, uint32_t tile, float) {
+    if (g.mode == MODE_GATHER || (D && g.mode == MODE_WIDE)) {
+        gathered_each<D>(p, tid, g, [&](uint32_t d, uint32_t tile, float) {
             if (d < dtau) return;
             const bool gt = d > dtau;
             if (tile < ub) { if (gt) ++pg; else ++pe; }
@@ -4003,6 +4099,7 @@ constexpr uint64_t FINE_ANY = 512, FINE_MANY = 1536, MIDDLE_ANY = 1024, MIDDLE_M
 constexpr int64_t MANY_CF = 40;   // "many": at least every 40th entry is selected
 static_assert(FINE_MANY * (SUB / FINE) <= EMIT_RESIDENT && MIDDLE_MANY * (SUB / MIDDLE) <= EMIT_RESIDENT,
               "the wavefronts of such a call are resident at once");
+static_assert(DIRECT_MAX <= (int64_t)FINE_ANY * TW / 2, "a direct call's units are FINE sub-tiles");
 uint32_t units_per_tile(int64_t n, int n_seg, bool many)
 {
     const uint64_t tiles = max_tiles(n, n_seg);
@@ -4357,13 +4454,15 @@ static int compress_impl(const float* grad, float* residual, int64_t n, const do
     size_t table_bytes = 0;
     if (ns == 1) {
         for (int j = 0; j < n_cf; ++j) p.flat_k[j] = (uint32_t)gravac_topk_count(n, cf_list[j]);
-        p.flat_samples = sample_count((uint64_t)n, cf_min, cf_max, true);
+        p.direct = n <= DIRECT_MAX && p.bounds_from == BOUNDS_SAMPLED ? 1 : 0;
+        p.flat_samples = p.direct ? (uint32_t)n : sample_count((uint64_t)n, cf_min, cf_max, true);
+        static_assert(DIRECT_MAX <= SAMPLE_MAX_FLAT, "as many samples as the blocks can take");
         p.n_tiles = (uint32_t)((n + TW - 1) / TW);
         max_seg_tiles = p.n_tiles;
         // more than SAMPLE_MAX samples (never a tensor read whole): 2 or 4 times SAMPLE_BLOCK samples per block, the
         // fewest that leave at most DENSE_BLOCKS blocks (more blocks keep more loads in flight, fewer cost the
         // threshold kernel less)
-        if (p.flat_samples > (uint32_t)SAMPLE_MAX && (int64_t)p.flat_samples != n)
+        if (p.flat_samples > (uint32_t)SAMPLE_MAX && ((int64_t)p.flat_samples != n || p.direct))
             while (sample_rounds < DENSE_ROUNDS && p.flat_samples > (uint32_t)(DENSE_BLOCKS * SAMPLE_BLOCK * sample_rounds))
                 sample_rounds *= 2;
         const uint32_t per_block = SAMPLE_BLOCK * sample_rounds;
@@ -4488,14 +4587,18 @@ static int compress_impl(const float* grad, float* residual, int64_t n, const do
         hipLaunchKernelGGL((threshold_kernel<1, false>), dim3(ns, 1), dim3(1024), 0, stream, p);
     {
         // the pass exists in forms for 1, 2, 3, 4 and MAXCF CFs (its loops over the CFs are unrolled)
-        void (*const ef_forms[5])(Params) = {stream_kernel<SM_EF, false, 1>, stream_kernel<SM_EF, false, 2>,
-                                             stream_kernel<SM_EF, false, 3>, stream_kernel<SM_EF, false, 4>,
-                                             stream_kernel<SM_EF, false, MAXCF>};
-        void (*const rk_forms[5])(Params) = {stream_kernel<SM_EF, true, 1>, stream_kernel<SM_EF, true, 2>,
-                                             stream_kernel<SM_EF, true, 3>, stream_kernel<SM_EF, true, 4>,
-                                             stream_kernel<SM_EF, true, MAXCF>};
-        void (*kern)(Params) = single ? stream_kernel<SM_SINGLE, false, 1>   // (a second-level call has one CF)
-                                      : (random ? rk_forms[ncf_form] : ef_forms[ncf_form]);
+        void (*const ef_forms[5])(Params) = {stream_kernel<SM_EF, false, false, 1>, stream_kernel<SM_EF, false, false, 2>,
+                                             stream_kernel<SM_EF, false, false, 3>, stream_kernel<SM_EF, false, false, 4>,
+                                             stream_kernel<SM_EF, false, false, MAXCF>};
+        void (*const rk_forms[5])(Params) = {stream_kernel<SM_EF, true, false, 1>, stream_kernel<SM_EF, true, false, 2>,
+                                             stream_kernel<SM_EF, true, false, 3>, stream_kernel<SM_EF, true, false, 4>,
+                                             stream_kernel<SM_EF, true, false, MAXCF>};
+        void (*const direct_forms[5])(Params) = {stream_kernel<SM_EF, false, true, 1>, stream_kernel<SM_EF, false, true, 2>,
+                                                 stream_kernel<SM_EF, false, true, 3>, stream_kernel<SM_EF, false, true, 4>,
+                                                 stream_kernel<SM_EF, false, true, MAXCF>};
+        void (*kern)(Params) = single ? (p.direct ? stream_kernel<SM_SINGLE, false, true, 1>     // (a second-level call has one CF)
+                                                  : stream_kernel<SM_SINGLE, false, false, 1>)
+                                      : (random ? rk_forms : p.direct ? direct_forms : ef_forms)[ncf_form];
         if (!have_tiles) {
             if (ev) { (void)hipEventRecord((hipEvent_t)ev->pass_begin, stream); (void)hipEventRecord((hipEvent_t)ev->pass_end, stream); }
         } else if (ev)  // the kernel's own begin and end time stamps
@@ -4504,7 +4607,7 @@ static int compress_impl(const float* grad, float* residual, int64_t n, const do
         else
             hipLaunchKernelGGL(kern, dim3(sub_grid), dim3(WG), 0, stream, p);
     }
-    if (have_tiles && !fixed) {
+    if (have_tiles && !fixed && !p.direct) {
     // a flat call: as many workgroups as its tiles can keep busy should its bracket have failed; layerwise: one per tensor
     // and one more per PLAN_HELP tiles of a large one
     const uint32_t plan_flat = (p.n_tiles + PLAN_T / 64 - 1) / (PLAN_T / 64);
@@ -4522,17 +4625,18 @@ static int compress_impl(const float* grad, float* residual, int64_t n, const do
 #undef REFINE_FORMS
     const int fine = upt == 1 ? 0 : upt == SUB / MIDDLE ? 1 : 2;
     const int heads = (!random && p.n_tiles <= EMIT_RESIDENT) ? 1 : 0;
-    hipLaunchKernelGGL(refine_forms[fine][heads][ncf_form], dim3(light_grid), dim3(LWG), 0, stream, p);
+    if (!p.direct) hipLaunchKernelGGL(refine_forms[fine][heads][ncf_form], dim3(light_grid), dim3(LWG), 0, stream, p);
     const bool general = p.random || p.single;   // (the plain call has forms of its own)
     if (with_scan) {
         const uint32_t scan_slices = (max_seg_tiles + SCAN_SLICE - 1) / SCAN_SLICE;
         hipLaunchKernelGGL(scan_kernel, dim3(ns, scan_slices + n_cf), dim3(SCAN_T), 0, stream, p, scan_slices);
         hipLaunchKernelGGL(general ? emit_kernel<true> : emit_kernel<false>, dim3(light_grid), dim3(LWG), 0, stream, p);
     } else {
-        void (*const emit_forms[3][2])(Params) = {{resolve_emit_kernel<false, SUB>, resolve_emit_kernel<true, SUB>},
-                                                  {resolve_emit_kernel<false, MIDDLE>, resolve_emit_kernel<true, MIDDLE>},
-                                                  {resolve_emit_kernel<false, FINE>, resolve_emit_kernel<true, FINE>}};
-        hipLaunchKernelGGL(emit_forms[fine][general ? 1 : 0], dim3(emit_wgs + (uint32_t)(ns * n_cf)),
+        void (*const emit_forms[4][2])(Params) = {{resolve_emit_kernel<false, SUB, false>, resolve_emit_kernel<true, SUB, false>},
+                                                  {resolve_emit_kernel<false, MIDDLE, false>, resolve_emit_kernel<true, MIDDLE, false>},
+                                                  {resolve_emit_kernel<false, FINE, false>, resolve_emit_kernel<true, FINE, false>},
+                                                  {resolve_emit_kernel<false, FINE, true>, resolve_emit_kernel<true, FINE, true>}};
+        hipLaunchKernelGGL(emit_forms[fine + (p.direct ? 1 : 0)][general ? 1 : 0], dim3(emit_wgs + (uint32_t)(ns * n_cf)),
                            dim3(EWG), 0, stream, p);
     }
     }
