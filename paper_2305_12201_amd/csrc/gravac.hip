@@ -2953,12 +2953,25 @@ __device__ __forceinline__ void emit_stats(const Params& p, int t, int j, EmitSh
     }
 }
 
+constexpr uint32_t EMIT_STAGE = TS / 2;
+static_assert(EMIT_STAGE % 256 == 0, "a lane's four pairs are aligned and inside");
+// Streamed messages (the forms with S): pairs go through LDS and from there to memory four per lane with non-temporal hints.
+// What a kernel leaves in the L2 caches is written back when it ends, and nothing runs meanwhile; the hints have it written as
+// it comes, in pieces long enough to fill lines.  VGG16 shape at CF 10 (110 MB) 389 -> 360 us, ResNet101 shape with three CFs
+// (36 MB) 160.3 -> 153.3, 100 million elements at CF 10, 20 and 40 319 -> 296, 286 -> 277 and 250 -> 248, 30 million 111 -> 109
+// and, of 1.5 million pairs, 102.7 -> 101; with fewer pairs than that nothing or a loss (1 million of 100 million 236.9 ->
+// 238.1).  (As plain stores of 16 bytes it is as it was, and so are hints on stores of a pair per lane: 10 us slower.)
+constexpr int64_t STREAM_OUT = 1500000;   // pairs
+
 struct EmitCtx {
     uint32_t tau, take, pz;
     bool put_back;
     bool zero;   // selected entries are removed from the residual (not in a call without commit)
     int64_t pos, lim;
     uint32_t erun;
+    int32_t* sidx;     // selected pairs on their way to the message, in LDS: EMIT_STAGE of this wavefront's own ...
+    float* sval;
+    uint32_t staged;   // ... and their number
     // The first pass has left +0 in the residual of its listed sub-tiles for keys >= pz (not on the full exact route,
     // which has put acc back).  Those entries need no store here if they are selected, and get acc back if they are
     // not, which can only be when the threshold turned out to lie at or above pz.
@@ -2975,8 +2988,58 @@ struct EmitCtx {
     }
 };
 
-// One round of up to 64 listed candidates (idx, val), one per lane.
+// The staged pairs to their place in the message (which starts at any multiple of four bytes).
 template <bool GEN>
+__device__ __forceinline__ void emit_flush(const Params& p, EmitCtx& x)
+{
+    const bool single = GEN && p.single;
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");  // the wavefront's own LDS writes, read back by other lanes
+    const int64_t left = x.lim - x.pos;
+    if ((int64_t)x.staged > left) p.status->error = 1;   // cannot happen if the counts are consistent; never write out of range
+    const uint32_t n = (int64_t)x.staged > left ? (left > 0 ? (uint32_t)left : 0u) : x.staged;
+    // (values and indices one after the other: fewer registers)
+#pragma unroll 1
+    for (uint32_t i = 4u * (threadIdx.x & 63u); i < n; i += 256) {
+        float* to = p.out_val + x.pos + i;
+        const v4f b = *(const v4f*)(x.sval + i);
+        if (i + 4 <= n) {
+            st_stream(b, (v4fu*)to);
+        } else {
+#pragma unroll
+            for (uint32_t e = 0; e < 3; ++e)
+                if (i + e < n) to[e] = b[e];
+        }
+    }
+#pragma unroll 1
+    for (uint32_t i = 4u * (threadIdx.x & 63u); i < n; i += 256) {
+        int32_t* to = p.out_idx + x.pos + i;
+        v4i a = *(const v4i*)(x.sidx + i);
+        if (single) {
+            // positions in the message -> indices in the gradient (a place past the last pair takes the first one's)
+            const v4i at = a;
+#pragma unroll
+            for (uint32_t e = 0; e < 4; ++e) a[e] = p.map_idx[i + e < n ? at[e] : at[0]];
+            if (p.restore) {
+#pragma unroll
+                for (uint32_t e = 0; e < 4; ++e)
+                    if (i + e < n && (uint64_t)(int64_t)a[e] < (uint64_t)p.n_restore) p.restore[a[e]] = 0.0f;
+            }
+        }
+        if (i + 4 <= n) {
+            __builtin_nontemporal_store(a, (v4iu*)to);
+        } else {
+#pragma unroll
+            for (uint32_t e = 0; e < 3; ++e)
+                if (i + e < n) to[e] = a[e];
+        }
+    }
+    x.pos += x.staged;
+    x.staged = 0;
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");  // read before the next pairs overwrite them
+}
+
+// One round of up to 64 listed candidates (idx, val), one per lane.
+template <bool GEN, bool S>
 __device__ __forceinline__ void emit_listed(const Params& p, EmitCtx& x, int32_t idx, float val, bool live)
 {
     const bool rnd = GEN && p.random, single = GEN && p.single;
@@ -2986,6 +3049,20 @@ __device__ __forceinline__ void emit_listed(const Params& p, EmitCtx& x, int32_t
     bool sel = gt;
     if (me != 0ull) sel = gt || (eq && (x.erun + lanes_below(me)) < x.take);  // (few rounds hold a tie)
     const uint64_t ms = __ballot(sel);
+    if constexpr (S) {
+        if (x.staged > EMIT_STAGE - 64) emit_flush<GEN>(p, x);
+        if (sel) {
+            const uint32_t o = x.staged + lanes_below(ms);
+            x.sidx[o] = idx;
+            x.sval[o] = val;
+            if (!single && x.zero && key < x.pz) __builtin_nontemporal_store(0.0f, &p.res[idx]);
+        } else if (x.put_back && live && key >= x.pz) {
+            p.res[idx] = val;
+        }
+        x.staged += (uint32_t)__popcll(ms);
+        x.erun += (uint32_t)__popcll(me);
+        return;
+    }
     // the wavefront's pairs go to consecutive places from pos on: a uniform base and a small offset per lane
     const int64_t left = x.lim - x.pos;
     const uint32_t room = left >= 64 ? 64u : (left > 0 ? (uint32_t)left : 0u);
@@ -3021,7 +3098,7 @@ __device__ __forceinline__ void emit_listed(const Params& p, EmitCtx& x, int32_t
 //
 // One tile u of segment t, by one wavefront: x holds the threshold, the tile's tie quota and the place of its pairs; cc
 // are the tile's counts, hi4 / hv4 the heads of its lists.
-template <bool GEN, bool HEADS, int U>
+template <bool GEN, bool HEADS, int U, bool S>
 __device__ __forceinline__ void emit_unit(const Params& p, int t, uint32_t u, EmitCtx& x, const uint32_t (&cc)[U], const v4i& hi4,
                                           const v4f& hv4, int32_t* sidx, float* sval)
 {
@@ -3124,9 +3201,10 @@ __device__ __forceinline__ void emit_unit(const Params& p, int t, uint32_t u, Em
             for (uint32_t b = b0; b < b0 + 64 * 4 && b < cnt; b += 64) {
                 const int32_t idx = pop_front(iq);
                 const float val = pop_front(vq);
-                emit_listed<GEN>(p, x, idx, val, b + lane < cnt);
+                emit_listed<GEN, S>(p, x, idx, val, b + lane < cnt);
             }
         }
+        if constexpr (S) emit_flush<GEN>(p, x);
         return;
     }
     if (!any_dense) {
@@ -3136,15 +3214,18 @@ __device__ __forceinline__ void emit_unit(const Params& p, int t, uint32_t u, Em
         // about 7) have the round after the next one on its way while one is worked on (loaded when it is due: 85 instead
         // of 76 us for 2 million elements at CF 3; four rounds at once cost a wavefront per SIMD, 284 instead of 242 us for
         // 60 million at CF 5)
-        float va[2 * U];
-        int32_t ia[2 * U];
+        // (the streamed form, which needs registers for its stores, has the next AHEAD sub-tiles' rounds on their way)
+        constexpr int AHEAD = S && U > 4 ? 4 : U;
+        float va[2 * AHEAD];
+        int32_t ia[2 * AHEAD];
+        // (Random-k at CF 10: 151 -> 147 us with non-temporal loads; in the plain form they cost a 25 MB bucket 2 us)
+        const auto fetch = [&](int j, int q, float& v, int32_t& i) {
+            const size_t at = (size_t)j * TS + q * 64 + lane;
+            v = GEN ? __builtin_nontemporal_load(&cv[at]) : cv[at];
+            i = GEN ? __builtin_nontemporal_load(&ci[at]) : ci[at];
+        };
 #pragma unroll
-        for (int r = 0; r < 2 * U; ++r) {
-            // (Random-k at CF 10: 151 -> 147 us with non-temporal loads; in the plain form they cost a 25 MB bucket 2 us)
-            const size_t at = (r / 2) * TS + (r & 1) * 64 + lane;
-            va[r] = GEN ? __builtin_nontemporal_load(&cv[at]) : cv[at];
-            ia[r] = GEN ? __builtin_nontemporal_load(&ci[at]) : ci[at];
-        }
+        for (int r = 0; r < 2 * AHEAD; ++r) fetch(r / 2, r & 1, va[r], ia[r]);
 #pragma unroll 1
         for (int j = 0; j < U; ++j) {
             uint32_t c = 0;
@@ -3152,6 +3233,10 @@ __device__ __forceinline__ void emit_unit(const Params& p, int t, uint32_t u, Em
             for (int y = 0; y < U; ++y) c = y == j ? cc[y] : c;
             float v0 = pop_front(va), v1 = pop_front(va);
             int32_t i0 = pop_front(ia), i1 = pop_front(ia);
+            if (AHEAD < U && j + AHEAD < U) {
+                fetch(j + AHEAD, 0, va[2 * AHEAD - 2], ia[2 * AHEAD - 2]);
+                fetch(j + AHEAD, 1, va[2 * AHEAD - 1], ia[2 * AHEAD - 1]);
+            }
 #pragma unroll 1
             for (uint32_t b = 0; b < c; b += 64) {
                 const float val = v0;
@@ -3161,9 +3246,10 @@ __device__ __forceinline__ void emit_unit(const Params& p, int t, uint32_t u, Em
                     const uint32_t q = j * TS + ((b + 128 + lane) & (TS - 1));
                     v1 = cv[q]; i1 = ci[q];
                 }
-                emit_listed<GEN>(p, x, idx, val, b + lane < c);
+                emit_listed<GEN, S>(p, x, idx, val, b + lane < c);
             }
         }
+        if constexpr (S) emit_flush<GEN>(p, x);
         return;
     }
     // sub-tile by sub-tile: a tile with sub-tiles that keep no list
@@ -3202,7 +3288,7 @@ __device__ __forceinline__ void emit_unit(const Params& p, int t, uint32_t u, Em
                     const uint32_t q = j * TS + ((b + 128 + lane) & (TS - 1));
                     vq[1] = cv[q]; iq[1] = ci[q];
                 }
-                emit_listed<GEN>(p, x, idx, val, b + lane < c);
+                emit_listed<GEN, S>(p, x, idx, val, b + lane < c);
             }
             continue;
         }
@@ -3256,12 +3342,15 @@ __device__ __forceinline__ void emit_unit(const Params& p, int t, uint32_t u, Em
                 tot += (uint32_t)__popcll(m);
             }
             // the selected pairs go to their place in the sub-tile's part of the message, in LDS first
-            uint32_t o = staged + pre;
+            if constexpr (S) {
+                if (x.staged > EMIT_STAGE - ROW) emit_flush<GEN>(p, x);
+            }
+            uint32_t o = (S ? x.staged : staged) + pre;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 if (!sel[e]) continue;
                 int32_t gi = (int32_t)(g + e);
-                if (single) {
+                if (single && !S) {
                     gi = p.map_idx[g + e];
                     if (p.restore && (uint64_t)(int64_t)gi < (uint64_t)p.n_restore) p.restore[gi] = 0.0f;
                 }
@@ -3275,9 +3364,9 @@ __device__ __forceinline__ void emit_unit(const Params& p, int t, uint32_t u, Em
                 r.z = sel[2] ? 0.0f : a[2]; r.w = sel[3] ? 0.0f : a[3];
                 st_stream(r, (v4fu*)(p.res + g));   // (non-temporal, as the loads: VGG16 shape at CF 10 408 -> 398 us)
             }
-            staged += tot;
+            (S ? x.staged : staged) += tot;
             x.erun += ties_row;
-            if (q & 1) {
+            if (!S && (q & 1)) {
                 // ... and from there into the message, 64 consecutive pairs per store
                 __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");  // the wavefront's own LDS writes, read back by other lanes
                 if (x.pos + (int64_t)staged > x.lim) p.status->error = 1;  // cannot happen if the counts are consistent
@@ -3293,14 +3382,15 @@ __device__ __forceinline__ void emit_unit(const Params& p, int t, uint32_t u, Em
             }
         }
     }
+    if constexpr (S) emit_flush<GEN>(p, x);
 }
 
 // After the scan step.
-template <bool GEN>
+template <bool GEN, bool S>
 __global__ __launch_bounds__(LWG) void emit_kernel(Params p)
 {
-    __shared__ int32_t stage_idx[LWAVES][TS / 2];   // half a sub-tile's part of the message, per wavefront
-    __shared__ float stage_val[LWAVES][TS / 2];
+    __shared__ __attribute__((aligned(16))) int32_t stage_idx[LWAVES][EMIT_STAGE];   // half a sub-tile's part of the message, per wavefront
+    __shared__ __attribute__((aligned(16))) float stage_val[LWAVES][EMIT_STAGE];
     const int lane = threadIdx.x & 63, wib = threadIdx.x >> 6;
     const uint32_t u = __builtin_amdgcn_readfirstlane(blockIdx.x * LWAVES + wib);
     if (u >= p.n_tiles) return;
@@ -3323,11 +3413,12 @@ __global__ __launch_bounds__(LWG) void emit_kernel(Params p)
     x.lim = seg_out + (int64_t)seg_k(p, t, p.commit);  // end of this segment's message
     x.pos = seg_out + (int64_t)p.toff[u];
     x.erun = 0;
-    emit_unit<GEN, false, SUB>(p, t, u, x, cc, v4i{0, 0, 0, 0}, v4f{0.0f, 0.0f, 0.0f, 0.0f}, stage_idx[wib], stage_val[wib]);
+    x.sidx = stage_idx[wib]; x.sval = stage_val[wib]; x.staged = 0;
+    emit_unit<GEN, false, SUB, S>(p, t, u, x, cc, v4i{0, 0, 0, 0}, v4f{0.0f, 0.0f, 0.0f, 0.0f}, stage_idx[wib], stage_val[wib]);
 }
 
 // Without a scan step.
-template <bool GEN, int U, bool D>
+template <bool GEN, int U, bool D, bool S>
 __global__ __launch_bounds__(EWG) __attribute__((amdgpu_waves_per_eu(D ? 4 : 6, 8))) void resolve_emit_kernel(Params p)
 {
     constexpr bool HEADS = !GEN;
@@ -3455,11 +3546,12 @@ __global__ __launch_bounds__(EWG) __attribute__((amdgpu_waves_per_eu(D ? 4 : 6, 
     x.lim = seg_out + (int64_t)seg_k(p, t, p.commit);  // end of this segment's message
     x.pos = seg_out + (int64_t)(uint32_t)__builtin_amdgcn_readfirstlane(run_g + ties_before);
     x.erun = 0;
+    x.sidx = stage_idx[wib]; x.sval = stage_val[wib]; x.staged = 0;
     if constexpr (HEADS) {
         hi4 = *(const v4i*)&stage_idx[wib][4 * lane];
         hv4 = *(const v4f*)&stage_val[wib][4 * lane];
     }
-    emit_unit<GEN, HEADS, U>(p, t, ub + wib, x, cc, hi4, hv4, stage_idx[wib], stage_val[wib]);
+    emit_unit<GEN, HEADS, U, S>(p, t, ub + wib, x, cc, hi4, hv4, stage_idx[wib], stage_val[wib]);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -4627,16 +4719,19 @@ static int compress_impl(const float* grad, float* residual, int64_t n, const do
     const int heads = (!random && p.n_tiles <= EMIT_RESIDENT) ? 1 : 0;
     if (!p.direct) hipLaunchKernelGGL(refine_forms[fine][heads][ncf_form], dim3(light_grid), dim3(LWG), 0, stream, p);
     const bool general = p.random || p.single;   // (the plain call has forms of its own)
+    const int stream_out = !fixed && total_out >= STREAM_OUT ? 1 : 0;
+    void (*const scan_emit_forms[2][2])(Params) = {{emit_kernel<false, false>, emit_kernel<true, false>}, {emit_kernel<false, true>, emit_kernel<true, true>}};
     if (with_scan) {
         const uint32_t scan_slices = (max_seg_tiles + SCAN_SLICE - 1) / SCAN_SLICE;
         hipLaunchKernelGGL(scan_kernel, dim3(ns, scan_slices + n_cf), dim3(SCAN_T), 0, stream, p, scan_slices);
-        hipLaunchKernelGGL(general ? emit_kernel<true> : emit_kernel<false>, dim3(light_grid), dim3(LWG), 0, stream, p);
+        hipLaunchKernelGGL(scan_emit_forms[stream_out][general ? 1 : 0], dim3(light_grid), dim3(LWG), 0, stream, p);
     } else {
-        void (*const emit_forms[4][2])(Params) = {{resolve_emit_kernel<false, SUB, false>, resolve_emit_kernel<true, SUB, false>},
-                                                  {resolve_emit_kernel<false, MIDDLE, false>, resolve_emit_kernel<true, MIDDLE, false>},
-                                                  {resolve_emit_kernel<false, FINE, false>, resolve_emit_kernel<true, FINE, false>},
-                                                  {resolve_emit_kernel<false, FINE, true>, resolve_emit_kernel<true, FINE, true>}};
-        hipLaunchKernelGGL(emit_forms[fine + (p.direct ? 1 : 0)][general ? 1 : 0], dim3(emit_wgs + (uint32_t)(ns * n_cf)),
+        // (calls of smaller units have smaller messages)
+#define EMIT_FORMS(u, direct, streamed) {resolve_emit_kernel<false, u, direct, streamed>, resolve_emit_kernel<true, u, direct, streamed>}
+        void (*const emit_forms[5][2])(Params) = {EMIT_FORMS(SUB, false, false), EMIT_FORMS(MIDDLE, false, false), EMIT_FORMS(FINE, false, false),
+                                                  EMIT_FORMS(FINE, true, false), EMIT_FORMS(SUB, false, true)};
+#undef EMIT_FORMS
+        hipLaunchKernelGGL(emit_forms[p.direct ? 3 : fine == 0 && stream_out ? 4 : fine][general ? 1 : 0], dim3(emit_wgs + (uint32_t)(ns * n_cf)),
                            dim3(EWG), 0, stream, p);
     }
     }
