@@ -507,7 +507,7 @@ def main():
                    "n": n, "cf": cf, "k": k, "workers_decompressed": N_WORKERS},
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS, "traffic": traffic,
-                     "kernel": "stream_kernel<0, false, 1> (error feedback + candidate collection, Top-k keys, one CF)",
+                     "kernel": "stream_kernel<0, false, false, 1> (error feedback + candidate collection, Top-k keys, one CF)",
                      "kernel_ms": stream_ms, "algorithmic_bytes_per_launch": ALGO_BYTES_PER_ELEMENT * n,
                      "kernel_frac": achieved / HBM_PEAK_GBS,
                      "call_frac": call_achieved / HBM_PEAK_GBS, "call_ms": compress_ms,

@@ -102,8 +102,7 @@ int gravac_workspace_bytes(int64_t n, int n_cf, int n_seg, size_t* bytes_out);
  *   grad        device, float[n], read only.
  *   residual    device, float[n].  In: the leftover of earlier iterations.
  *               Out: acc with the committed selection's slots set to +0.0f (with GRAVAC_FLAG_NO_COMMIT: acc).
- *               (Both may start at any float boundary; the fast path, 16-byte accesses, is taken when both are
- *               16-byte aligned, as every allocator's buffers are.)
+ *               (Both may start at any float boundary.)
  *   n           1 <= n <= 2^31 - 1 (indices are int32).
  *   cf_list     host, double[n_cf], every entry finite and >= 1.  1 <= n_cf <= GRAVAC_MAX_CF.
  *   commit      position in cf_list of the CF whose selection is emitted into out_idx/out_val

@@ -10,21 +10,23 @@
 // [lo, top) of keys that holds the k-th largest key with a statistical safety margin.  ONE streaming
 // pass then reads grad and residual, writes acc back as the provisional residual, sums acc^2, and for
 // every CF counts (and sums the energy of) the entries above the bracket and histograms the entries
-// inside it.  The few entries inside some bracket go, in index order, into a per-sub-tile bracket list;
-// the entries that can belong to the committed selection go into a per-sub-tile candidate list, unless
-// the sub-tile is mostly candidates, in which case the emit step reads it again from the residual.
-// Everything after the pass works on those lists: locate the histogram bin that holds the k-th
-// largest, gather the few keys of that bin, resolve the exact key, scan the per-tile counts and emit
-// the message in ascending index order while zeroing the selected residual slots.  If a sampled
-// bracket turns out wrong the segment is redone by a route that cannot fail: a bin too coarse and too
-// full to resolve is binned again inside itself from the bracket lists; a k-th largest outside the
-// bracket is found from a 2048-bin histogram of the top key bits of all elements, after which the
-// lists are collected again.  Results are identical on every route; only the number of passes over
-// memory differs.
+// inside it.  The few entries inside some bracket go, in index order, into a per-sub-tile bracket list
+// (zeros are only counted); the entries that can belong to the committed selection go into a
+// per-sub-tile candidate list, unless the sub-tile is mostly candidates, in which case the emit step
+// reads it again from the residual.  Everything after the pass works on those lists: locate the
+// histogram bin that holds the k-th largest, gather the few keys of that bin, resolve the exact key,
+// scan the counts and emit the message in ascending index order while zeroing the selected residual
+// slots.  If a sampled bracket turns out wrong the segment is redone by a route that cannot fail: a bin
+// too coarse and too full to resolve is binned again inside itself from the bracket lists; a k-th
+// largest outside the bracket is found from a 2048-bin histogram of the top key bits of all elements,
+// after which the lists are collected again.  A flat tensor of at most DIRECT_MAX elements is sampled
+// whole, which gives the bin itself, and needs neither the bracket's histogram nor those routes.
+// Results are identical on every route; only the number of passes over memory differs.
 //
 // Units of work.  A tile is TW consecutive elements; the streaming pass gives each of its SUB
 // sub-tiles to one 64-lane wavefront, which owns that sub-tile's slots of the list arrays, so
-// ordered compaction needs no communication between wavefronts and no list can overflow.  Cross-tile
+// ordered compaction needs no communication between wavefronts and no list can overflow.  The list
+// kernels give a wavefront a unit: a tile, or in calls of few tiles half or a quarter of one.  Cross-tile
 // results (histograms, output offsets) are combined at kernel boundaries, and no workgroup waits for
 // another, except on the exact routes: they run inside the plan step, whose workgroups wait for each
 // other over counters in the workspace.  Such a workgroup works on one segment, waits only once every
@@ -243,7 +245,7 @@ struct Params {
     uint32_t* xq;        // [n_seg][XQ_LINE] the plan step's work queue of every segment (XQ_*)
     uint32_t* coarse;    // [n_seg][NBIN] histogram of key >> 20 (exact route)
     uint32_t* list_key;  // [copy blocks][LCAP] gather lists: key ... (before they are filled: the exact routes' histograms)
-    uint32_t* list_tile; //                          ... tile ...
+    uint32_t* list_tile; //                          ... unit ...
     float* list_val;     //                          ... and value (written for Random-k only) of the listed entries
     uint32_t* list_cnt;  // [copy blocks][32] fill counts of the gather lists, one cache line each
     uint32_t* samp_hist; // [n_sample_blocks][SBIN / 2] sample histograms, two 16-bit counts per word
@@ -252,19 +254,20 @@ struct Params {
     uint32_t* brk_cnt;   // [n_tiles][SUB] bracket-list entries of every sub-tile (| zeros counted instead of listed << ZERO_SHIFT)
     uint32_t* ovn;       // [n_tiles][SUB][n_cf] entries of the sub-tile above CF j's bracket
     double* ovs;         // [n_tiles][SUB][n_cf] ... and their sum of acc^2
-    uint32_t* tg0;       // [n_tiles] entries of the tile above the committed CF's located bin
-    uint32_t* tin;       // [n_tiles] entries of the tile inside that bin
+    // (units: tiles, or half or quarter tiles in calls of few; see units_per_tile)
+    uint32_t* tg0;       // [units] entries of the unit above the committed CF's located bin
+    uint32_t* tin;       // [units] entries of the unit inside that bin
     // a call with a scan step:
     uint32_t* toff;      // [n_tiles] offset of the tile's output inside its segment's message
     uint32_t* ttake;     // [n_tiles] how many of the tile's entries equal to tau(commit) are selected
     uint32_t* tsel;      // [n_tiles] pairs the tile emits
     // ... and one without (null otherwise):
-    uint64_t* csum;      // [n_tiles / CTILES, rounded up][8] sums of tg0 (high half) and tin over CTILES tiles: word 0 of a cache line
+    uint64_t* csum;      // [units / CTILES, rounded up][8] sums of tg0 (high half) and tin over CTILES units: word 0 of a cache line
     uint32_t n_csum;     // their number
     uint32_t* wseg;      // [workgroups of the emit step] the segment of each (layerwise; filled by threshold_kernel)
     double* ssd;         // [n_tiles][SUB] sum of acc^2 of every sub-tile
-    double* ssd_t;       // [n_tiles] sum of acc^2 of the tile
-    double* sss;         // [n_tiles][n_cf] sum of acc^2 over the tile's keys above CF j's located bin
+    double* ssd_t;       // [units] sum of acc^2 of the unit
+    double* sss;         // [units][n_cf] sum of acc^2 over the unit's keys above CF j's located bin
     int32_t* cand_idx;   // [n_tiles][SUB][TS] candidate list: sub-tile j of tile u owns the slots from (u*SUB + j)*TS
     float* cand_val;     // [n_tiles][SUB][TS]
     uint32_t* brk_key;   // [n_tiles][SUB][TS] bracket list: keys ...
@@ -2084,13 +2087,12 @@ __global__ __launch_bounds__(PLAN_T) void plan_kernel(Params p)
 }
 
 // ---------------------------------------------------------------------------------------------
-// R1: one wavefront per tile.  The tile's sums of the pass over the gradient (energy, entries above
-// every CF's bracket and their energy) are added up over its sub-tiles; then the tile's entries inside
+// R1: one wavefront per unit.  The unit's sums of the pass over the gradient (energy, entries above
+// every CF's bracket and their energy) are added up over its sub-tiles; then the unit's entries inside
 // the brackets are walked: per CF, those above the bin that holds the k-th largest are counted and
-// their energy summed, those inside that bin are gathered (key, tile, value).
+// their energy summed, those inside that bin are gathered (key, unit, value).
 // ---------------------------------------------------------------------------------------------
-// (the form for four CFs is held to 80 registers, a dozen values spilled: six wavefronts per SIMD instead of four
-// take the ResNet101 shape's tiles in one round instead of two)
+// (the forms for three and four CFs are held to six wavefronts per SIMD: the ResNet101 shape's tiles are one round then)
 // HEADS: the heads of the tile's lists are fetched before their lengths are known.  That pays where all tiles'
 // wavefronts are resident at once and the kernel's time is one wavefront's chain of round trips to memory (the
 // ResNet101 shape: 10.1 -> 7.9 us); with more tiles than that the chip is busy either way, and the extra loads and
@@ -2653,8 +2655,8 @@ __global__ __launch_bounds__(SCAN_T) void scan_kernel(Params p, uint32_t slices)
 // emit_kernel works from what the scan step has left.
 //
 // resolve_emit_kernel does the scan step's work itself: every workgroup resolves the committed CF of its segment to the
-// exact key tau of the k-th largest from the gathered entries, and adds up what lies before its eight tiles (totals of 64
-// tiles each, which the refine step has added up, and up to 126 single tiles at the ends).  The first n_seg n_cf workgroups
+// exact key tau of the k-th largest from the gathered entries, and adds up what lies before its eight units (totals of 64
+// units each, which the refine step has added up, and up to 126 single tiles at the ends).  The first n_seg n_cf workgroups
 // of its launch are the statistics of one (segment, CF) each.  The scan step is 6 to 8 us of round trips and barriers in
 // one or a few workgroups; repeated by all of them, part of it overlaps with the tiles' own first loads, and a launch is
 // spared: 1 MiB buckets 38.3 -> 33.8 us, 25 MB 74.7 -> 72.4, ResNet101 CF 100 129.9 -> 126.3, three CFs 197 -> 192, LSTM
@@ -3292,7 +3294,7 @@ __device__ __forceinline__ void emit_unit(const Params& p, int t, uint32_t u, Em
             }
             continue;
         }
-        // a whole, aligned sub-tile that kept acc in the residual (or is the message itself, single-source mode):
+        // a whole sub-tile that kept acc in the residual (or is the message itself, single-source mode):
         // four rows of 256 elements, a lane's four consecutive elements at a time.  Its rows were loaded while the
         // sub-tile before it was worked on; now the next such sub-tile's loads are issued.
         const int64_t s0 = tile0 + (int64_t)j * TS;
