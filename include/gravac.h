@@ -92,7 +92,8 @@ int64_t gravac_topk_count(int64_t n, double cf);
  * with a slot per element, so that no list can overflow), plus 56 KB per (segment, CF) and per 65,536 elements for
  * histograms and gather lists, plus 8 KB per sample block (the size allows 64 of them per tensor in layerwise mode,
  * 128 for a flat call).  Examples: 44,549,160 elements flat, one CF: 716 MB; the same as 314 tensors: 983 MB;
- * 138,357,544 elements flat: 2.22 GB.
+ * 138,357,544 elements flat: 2.22 GB.  The size does not fall as n or n_cf grows with the others kept: a workspace for
+ * the largest tensor does for a smaller one.
  */
 int gravac_workspace_bytes(int64_t n, int n_cf, int n_seg, size_t* bytes_out);
 

@@ -4200,6 +4200,13 @@ uint32_t units_per_tile(int64_t n, int n_seg, bool many)
     if (tiles <= (many ? FINE_MANY : FINE_ANY)) return SUB / FINE;
     return tiles <= (many ? MIDDLE_MANY : MIDDLE_ANY) ? SUB / MIDDLE : 1;
 }
+// Units of a call of up to `tiles` tiles, an upper bound that does not fall as they grow: units_per_tile does, and a workspace
+// for a larger tensor has to do for a smaller one.
+uint64_t max_units(uint64_t tiles)
+{
+    const uint64_t fine = tiles * (SUB / FINE);   // (what units_per_tile makes of up to MIDDLE_MANY tiles is at most EMIT_RESIDENT)
+    return tiles > EMIT_RESIDENT ? tiles : fine < EMIT_RESIDENT ? fine : EMIT_RESIDENT;
+}
 
 uint64_t max_sample_blocks(int64_t n, int n_seg)
 {
@@ -4233,7 +4240,7 @@ Layout make_layout(int64_t n, int n_cf, int n_seg)
     Layout L;
     size_t at = 0;
     auto take = [&](size_t bytes) { size_t o = at; at = align_up(at + bytes, 256); return o; };
-    const uint64_t nt = max_tiles(n, n_seg), nsb = max_sample_blocks(n, n_seg), nu = nt * units_per_tile(n, n_seg, true);   // (with fewer selected entries there are no more)
+    const uint64_t nt = max_tiles(n, n_seg), nsb = max_sample_blocks(n, n_seg), nu = max_units(nt);
     const size_t sc = (size_t)n_seg * n_cf;
     L.status = take(sizeof(Status));
     // host-built tables, one piece: SegInfo[n_seg], ktab[n_seg][n_cf], sblock_seg[sample blocks]

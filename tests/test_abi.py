@@ -57,6 +57,18 @@ def test_workspace_bytes():
         assert e.value.code == binding.ERR_INVALID_ARG
 
 
+@pytest.mark.parametrize("n_seg", [0, 2, 100, 1000])
+def test_workspace_bytes_do_not_fall(n_seg):
+    """A workspace for a larger tensor does for a smaller one: over all numbers of tiles of 8192 elements at which the list
+    kernels change the size of their units."""
+    before = np.zeros(8, np.int64)
+    for tiles in [1, 2, 16, 60, 64, 65, 100, *range(400, 3200), 4000, 6143, 6144, 6145, 6146, 20_000]:
+        n = max(tiles * 8192 - 3, n_seg)
+        size = np.array([binding.gravac_workspace_bytes(n, n_cf, n_seg) for n_cf in range(1, 9)])
+        assert (size >= before).all() and (np.diff(size) > 0).all(), (n, size, before)
+        before = size
+
+
 def _call(L, grad=0x1000, res=0x2000, n=100, cfs=(10.0,), commit=0, seg=None, out_idx=0x3000, out_val=0x4000,
           cap=100, out_stats=0x5000, ws=0x10000, ws_bytes=1 << 40):
     """Argument validation happens before any pointer is touched, so fake addresses are safe here."""
