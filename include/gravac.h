@@ -21,7 +21,8 @@
  *     stream).  Outputs are valid once the stream has been synchronised.
  *   - The library never allocates device memory: scratch space comes from the caller's
  *     `workspace`.  Calls that overlap in time must use different workspaces.  (Two that share one give
- *     unspecified results.  Workgroups of the exact route wait for each other over counters in the workspace;
+ *     unspecified results.  Workgroups of the exact route, and of the last step of a flat call of at most 524,288
+ *     elements whose threshold lies in a crowd of values, wait for each other over counters in the workspace;
  *     where another call has cleared them the wait ends after a minute or two, with the internal-error flag set.)
  *   - The library keeps no state between calls, with one exception: layerwise calls pass their segment tables
  *     through a ring of up to eight pinned host staging buffers that the library allocates on first use
@@ -307,7 +308,8 @@ int gravac_decompress_accumulate_static(const int32_t* idx, const float* val,
  *   [0] 1 if any segment took the exact-histogram fallback, [1] number of such segments,
  *   [2] internal-error flag (must be 0; else the call's outputs and residual are not to be used), [3] number of
  *   segments, [4] how many of [1] needed no second pass over the gradient (the located histogram bin was too coarse
- *   and too full and was binned again from the lists the pass had collected), [5..7] reserved.
+ *   and too full and was binned again from the lists the pass had collected), [5] 1 if that was in a flat Top-k call whose
+ *   sample is the whole tensor (at most 524,288 elements: its last step does it), [6..7] reserved.
  */
 int gravac_read_status(const void* workspace, void* stream, int32_t* out8);
 

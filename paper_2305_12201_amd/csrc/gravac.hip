@@ -28,10 +28,11 @@
 // ordered compaction needs no communication between wavefronts and no list can overflow.  The list
 // kernels give a wavefront a unit: a tile, or in calls of few tiles half or a quarter of one.  Cross-tile
 // results (histograms, output offsets) are combined at kernel boundaries, and no workgroup waits for
-// another, except on the exact routes: they run inside the plan step, whose workgroups wait for each
-// other over counters in the workspace.  Such a workgroup works on one segment, waits only once every
+// another, except on the exact routes, which run inside the plan step, and where a direct call's emit step
+// cuts a full bin again (wide_resolve): there the workgroups wait for each other over counters in the
+// workspace.  Such a workgroup works on one segment, waits only once every
 // chunk of it has been claimed, hence only for workgroups that are running and wait for nobody before
-// they have arrived, and gives up after a number of polls (plan_barrier).  Global atomics complete at a
+// they have arrived, and gives up after a number of polls (wait_for_all).  Global atomics complete at a
 // rate of roughly one per cache line per 10 ns on this part, so what takes many of them is spread: the
 // bracket histogram and the gather lists' fill counts exist in REP copies (picked from the sub-tile,
 // tile or workgroup number), the counts above the brackets lie on 64 lines.  The others are few: a
@@ -123,7 +124,7 @@ constexpr int FINE = 2, MIDDLE = 4; // sub-tiles per wavefront of the list kerne
 constexpr int XQ_WORDS = 8;         // a segment's work queue in the plan step: chunks claimed, then chunks done per phase
 constexpr int XQ_WIN = XQ_WORDS;    // ... and behind it the first key of its sample histogram's window
 constexpr int XQ_LINE = 32;         // words between two segments' queues: a cache line
-constexpr int BND_WORDS = 32;       // words of a segment's brackets, a cache line: lo, hi, mid and a spare one per CF
+constexpr int BND_WORDS = 32;       // words of a segment's brackets, a cache line: lo, hi, mid and (direct calls) mode per CF
 static_assert(4 * GRAVAC_MAX_CF <= BND_WORDS, "a bracket per CF");
 constexpr uint32_t WAIT_POLLS = 1u << 26;  // polls after which a workgroup of the plan step gives up on the others: at least
                                            // half a minute, where the longest wait of a call is milliseconds
@@ -132,7 +133,7 @@ constexpr uint32_t NONE = 0xFFFFFFFFu;
 constexpr uint32_t KEY_END = 0x80000000u;  // one past the largest key
 
 enum : uint32_t { MODE_RESOLVED = 0, MODE_GATHER = 1,
-                  MODE_WIDE = 2,   // a direct call's bin that is too full to gather or too wide: resolved from the bracket lists
+                  MODE_WIDE = 2,   // a direct call's bin that is too full to gather or too wide: cut again by the emit step
                   MODE_FAIL = 3 };
 // What the plan step found for a segment, the heaviest kind over its CFs:
 //   FAIL_TIES    the bin that holds the k-th largest is at most 2^11 keys wide and too full to gather (a mass of equal
@@ -176,7 +177,8 @@ struct Status {
     int n_seg;
     int n_narrow;             // segments of n_fail that were only binned again from their bracket lists
     int count;                // threshold sparsifier: entries at or above the threshold (written by the scan)
-    int pad[2];
+    int n_wide;               // 1: a direct call whose emit step has cut a full bin again (MODE_WIDE)
+    int pad;
 };
 
 typedef float v4f __attribute__((ext_vector_type(4)));
@@ -298,6 +300,15 @@ __device__ __forceinline__ uint32_t seg_rep(const Params& p, int t) { return is_
 __device__ __forceinline__ size_t seg_block(const Params& p, int t, int j)
 {
     return is_flat(p) ? (size_t)j * REP : (size_t)p.segs[t].pool0 + (size_t)j * p.segs[t].rep;
+}
+
+// A direct call's histograms of a bin that is cut again, one per round: in the values of CF j's gather lists, which Top-k does
+// not use.
+constexpr uint32_t WIDE_ROUNDS = 3;   // 11 bits each, of up to 31
+__device__ __forceinline__ uint32_t* wide_hist(const Params& p, int j, uint32_t round)
+{
+    static_assert(WIDE_ROUNDS * NBIN <= REP * LCAP && WIDE_ROUNDS * 11 >= 31, "the rounds' histograms fit, and resolve any key");
+    return (uint32_t*)p.list_val + (size_t)j * REP * LCAP + round * NBIN;
 }
 
 __device__ __forceinline__ uint32_t key_of(float a) { return __float_as_uint(a) & 0x7FFFFFFFu; }
@@ -759,7 +770,7 @@ __device__ __forceinline__ void reset_status(const Params& p, uint32_t tid)
 {
     if (tid != 0) return;
     p.status->any_fail = 0; p.status->n_fail = 0; p.status->error = 0; p.status->n_seg = p.n_seg;
-    p.status->n_narrow = 0; p.status->count = 0;
+    p.status->n_narrow = 0; p.status->count = 0; p.status->n_wide = 0;
     if (p.out_count && p.bounds_from != BOUNDS_FIXED) *p.out_count = p.total_out;  // (else the last step knows it)
 }
 
@@ -829,12 +840,12 @@ __global__ __launch_bounds__(256) void sample_kernel(Params p)
         for (uint32_t i = lb * 256 + tid; i < blocks; i += nbk * 256) p.list_cnt[(seg_block(p, t, 0) + i) * 32] = 0;
         if (is_flat(p) && b == 0) reset_status(p, tid);   // (a flat call has no threshold step)
         if (p.direct) return;
+        if (lb == 0 && tid < XQ_WORDS) p.xq[(size_t)t * XQ_LINE + tid] = 0;
         uint4* h1 = (uint4*)(p.hist1 + seg_block(p, t, 0) * NBIN);
         for (uint32_t i = lb * 256 + tid; i < blocks * NBIN / 4; i += nbk * 256) h1[i] = z;
         uint4* cs = (uint4*)(p.coarse + (size_t)t * NBIN);
         for (uint32_t i = lb * 256 + tid; i < NBIN / 4; i += nbk * 256) cs[i] = z;
         for (uint32_t i = lb * 256 + tid; i < (uint32_t)p.n_cf * 64; i += nbk * 256) p.ovfc[((size_t)t * p.n_cf * 64 + i) * 32] = 0;
-        if (lb == 0 && tid < XQ_WORDS) p.xq[(size_t)t * XQ_LINE + tid] = 0;
         if (is_flat(p) && b == 0 && p.bounds_from != BOUNDS_SAMPLED && tid < p.n_cf) known_bracket(p, 0, tid, p.bnd + 4 * tid);
         if (p.csum)
             for (uint32_t i = b * 256 + tid; i < p.n_csum; i += gridDim.x * 256) p.csum[(size_t)i * 8] = 0;
@@ -1127,18 +1138,27 @@ __global__ __launch_bounds__(64) void bracket_kernel(Params p)
             // all ranks are k, and all elements are counted: the bin of the k-th largest and what lies above it
             const uint32_t kj = (uint32_t)__builtin_amdgcn_readlane((int)rank_lo, j);
             const bool in1 = above1 < kj && above1 + h1 >= kj, in0 = above0 < kj && above0 + h0 >= kj;
-            if (!in1 && !in0) continue;
+            if (__ballot(in1 || in0) == 0ull) continue;
             const uint32_t bin = in1 ? bin0 + 1u : bin0, above = in1 ? above1 : above0, c = in1 ? h1 : h0;
+            // (the first and the last bin span many octaves, too many for sums scaled by the bin's bounds)
+            const uint32_t width = sample_bin_end(bin, w0) - sample_bin_first(bin, w0);
+            const bool wide = width != 1u && (c > (uint32_t)LCAP || width > (1u << SCSHIFT));
+            if (__ballot((in1 || in0) && wide) != 0ull) {
+                // where the emit step counts it again, and its queue
+                if (lane < XQ_WORDS) p.xq[lane] = 0;
+                uint4* h = (uint4*)wide_hist(p, j, 0);
+                for (uint32_t i = lane; i < WIDE_ROUNDS * NBIN / 4; i += 64) h[i] = make_uint4(0u, 0u, 0u, 0u);
+            }
+            if (!in1 && !in0) continue;
             const uint32_t lo = sample_bin_first(bin, w0), end = sample_bin_end(bin, w0), mid = key_inside(bin, w0, kj - above, c);
-            p.bnd[4 * j] = lo; p.bnd[4 * j + 1] = end; p.bnd[4 * j + 2] = mid;
             CfState st;
             st.k = kj; st.lo = lo; st.s = 0; st.base = lo; st.span = end - lo - 1u; st.above = above; st.c = c; st.top = end;
-            // (the first and the last bin span many octaves, too many for sums scaled by the bin's bounds)
-            st.mode = st.span == 0u ? MODE_RESOLVED : (c <= (uint32_t)LCAP && st.span < (1u << SCSHIFT) ? MODE_GATHER : MODE_WIDE);
+            st.mode = st.span == 0u ? MODE_RESOLVED : wide ? MODE_WIDE : MODE_GATHER;
             st.tau = lo; st.cnt_gt = above; st.need = kj - above;   // (if resolved)
             st.pad[0] = st.pad[1] = st.pad[2] = st.pad[3] = 0;
             p.st[j] = st;
-            if (st.mode == MODE_WIDE) { p.status->any_fail = 1; p.status->n_fail = 1; p.status->n_narrow = 1; }
+            p.bnd[4 * j] = lo; p.bnd[4 * j + 1] = end; p.bnd[4 * j + 2] = mid; p.bnd[4 * j + 3] = st.mode;
+            if (wide) { p.status->any_fail = 1; p.status->n_fail = 1; p.status->n_narrow = 1; p.status->n_wide = 1; }
             if (j == p.commit) {
                 SegState sg;
                 sg.fail = FAIL_NONE; sg.pz = zero_from(p, lo, end, mid);
@@ -1201,6 +1221,7 @@ struct SubCtx {
     uint32_t s0, s1;  // Random-k keys
     uint2* stage;     // this wavefront's entries in LDS: index and value ...
     uint32_t staged;  // ... and their number
+    uint32_t wide;    // a direct call: bit j: the entries of CF j's bin are not gathered (MODE_WIDE)
 };
 
 __device__ __forceinline__ v4f ld_stream(const v4fu* q)
@@ -1276,7 +1297,8 @@ __device__ __forceinline__ void stage_dense_row(SubCtx<1>& c, const float a[4], 
 // The staged entries, 64 at a time: per CF a count and the energy of those above its bracket and a histogram update for
 // those inside it; into the lists.  listed = whether the sub-tile keeps a candidate list; counted = whether the entries above
 // the bracket have been counted.
-// D (a direct call): those inside a bracket go to the gather lists; zeros are counted where they are found.
+// D (a direct call): those inside a bracket go to the gather lists, unless they are too many; zeros are counted where they are
+// found.
 template <bool RND, bool D, int NCF>
 __device__ __forceinline__ void flush_stage(const Params& p, uint32_t v, SubCtx<NCF>& c, bool listed, bool counted, int lane)
 {
@@ -1300,7 +1322,9 @@ __device__ __forceinline__ void flush_stage(const Params& p, uint32_t v, SubCtx<
                 const bool in = from && !above && !(D && key == 0u);
                 const uint64_t m = __ballot(in);
                 if (m == 0ull) continue;
-                if constexpr (D) {
+                if (D && ((c.wide >> j) & 1u)) {
+                    // (the bracket list has them)
+                } else if constexpr (D) {
                     const uint32_t lst = (uint32_t)j * REP + (blockIdx.x & (REP - 1u));
                     const int leader = __ffsll((unsigned long long)m) - 1;
                     uint32_t at = 0;
@@ -1436,7 +1460,7 @@ __device__ __forceinline__ void stream_subtile(const Params& p, uint32_t v, int 
     SubCtx<NCF> c;
     c.ncf = p.n_cf;
     c.s0 = p.rk_s0; c.s1 = p.rk_s1;
-    c.lo_min = NONE; c.lo_c = NONE; c.pz = NONE;
+    c.lo_min = NONE; c.lo_c = NONE; c.pz = NONE; c.wide = 0;
 #pragma unroll
     for (int j = 0; j < NCF; ++j) {
         c.ovn[j] = 0; c.ovs[j] = 0.0;
@@ -1449,7 +1473,10 @@ __device__ __forceinline__ void stream_subtile(const Params& p, uint32_t v, int 
                 c.lo[j] = (uint32_t)__builtin_amdgcn_readlane((int)word, 4 * j);
                 bracket_bins(c.lo[j], (uint32_t)__builtin_amdgcn_readlane((int)word, 4 * j + 1), c.sh[j], c.org[j], c.top[j]);
                 c.lo_min = c.lo[j] < c.lo_min ? c.lo[j] : c.lo_min;
-                if (D) c.top[j] = (uint32_t)__builtin_amdgcn_readlane((int)word, 4 * j + 1);   // (the bin, no more)
+                if (D) {
+                    c.top[j] = (uint32_t)__builtin_amdgcn_readlane((int)word, 4 * j + 1);   // (the bin, no more)
+                    c.wide |= (uint32_t)__builtin_amdgcn_readlane((int)word, 4 * j + 3) == MODE_WIDE ? 1u << j : 0u;
+                }
                 if (j == p.commit) {
                     c.lo_c = c.lo[j];
                     if (M == SM_EF) c.pz = zero_from(p, c.lo[j], c.top[j], (uint32_t)__builtin_amdgcn_readlane((int)word, 4 * j + 2));
@@ -1817,27 +1844,28 @@ __device__ __forceinline__ void plan_search(PlanShared& sh, int n_cf, int tid, S
 static_assert(4 * 8 * 257 <= CSUB * (NBIN + 1), "the teams' counts fit into the coarse counts' LDS");
 
 // Everything this workgroup has written is visible to the device; then all workgroups with chunks of the segment have
-// got here, and what they have written is visible to this one.  False (to every thread): they have not, after as many
+// got here (the counter has grown to `target` by what each of them adds, the number of its chunks), and what they have written
+// is visible to this one.  False (to every thread): they have not, after as many
 // polls as the call allows.  That takes a second call on the same workspace, which clears this one's counters or claims
 // its chunks; the wait must not hold the GPU for ever then.
-__device__ __forceinline__ bool plan_barrier(const Params& p, PlanShared& sh, uint32_t* done, uint32_t n_chunks, int tid)
+__device__ __forceinline__ bool wait_for_all(const Params& p, uint32_t n_own, uint32_t& arrived, uint32_t* done, uint32_t target, int tid)
 {
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");   // every wavefront's stores and atomics are done ...
     __syncthreads();
     if (tid == 0) {
         __threadfence();                                           // ... and leave this XCD's L2
-        atomicAdd(done, sh.n_own);
+        atomicAdd(done, n_own);
         uint32_t polls = 0;
         while (polls < p.wait_polls &&
-               __hip_atomic_load(done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < n_chunks + p.wait_extra) {
+               __hip_atomic_load(done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target + p.wait_extra) {
             __builtin_amdgcn_s_sleep(4);
             ++polls;
         }
-        sh.arrived = polls < p.wait_polls ? 1u : 0u;
+        arrived = polls < p.wait_polls ? 1u : 0u;
     }
     __syncthreads();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-    return sh.arrived != 0u;
+    return arrived != 0u;
 }
 
 // One tile's entries of the bracket lists into the histograms (first copy of CF 0 at hist) of the CFs that are cut again.
@@ -1991,7 +2019,7 @@ __global__ __launch_bounds__(PLAN_T) void plan_kernel(Params p)
                 if (v) atomicAdd(&gh[bin_word(i)], v);
             }
         }
-        bool arrived = plan_barrier(p, sh, &xq[1], n_chunks, tid);
+        bool arrived = wait_for_all(p, sh.n_own, sh.arrived, &xq[1], n_chunks, tid);
         if (full && arrived) {
             // the coarse (key >> 20) bin of every CF's k-th largest is the new bracket
             plan_search(sh, p.n_cf, tid, [&](int j, const uint32_t*& hist, uint32_t& nc, uint32_t& stride, const uint32_t*& extra, uint32_t& want) {
@@ -2025,7 +2053,7 @@ __global__ __launch_bounds__(PLAN_T) void plan_kernel(Params p)
                     if (u < u1) plan_recount(p, sh, u, hist, copies, lane);
                 }
             }
-            arrived = plan_barrier(p, sh, &xq[1 + phase], n_chunks, tid);
+            arrived = wait_for_all(p, sh.n_own, sh.arrived, &xq[1 + phase], n_chunks, tid);
             if (!arrived) break;
             // the part that holds the k-th largest
             plan_search(sh, p.n_cf, tid, [&](int j, const uint32_t*& h, uint32_t& nc, uint32_t& stride, const uint32_t*& extra, uint32_t& want) {
@@ -2667,6 +2695,8 @@ __global__ __launch_bounds__(SCAN_T) void scan_kernel(Params p, uint32_t slices)
 // ---------------------------------------------------------------------------------------------
 constexpr int EWG = 512;                    // threads
 constexpr int EW = EWG / 64;
+constexpr uint32_t WIDE_CHUNKS = (uint32_t)(DIRECT_MAX / (EW * FINE * TS));   // chunks of EW units of a direct call at most
+static_assert(DIRECT_MAX % (EW * FINE * TS) == 0 && DIRECT_MAX % TW == 0, "its units are whole chunks");
 constexpr uint32_t EMIT_RESIDENT = 6144;    // tiles (six wavefronts on each of 1024 SIMDs)
 constexpr int SPEC = EWG / REP;             // threads that fetch the head of one gather list before its length is known,
 constexpr int SPEC_Q = 2;                   // ... SPEC_Q entries each
@@ -2675,12 +2705,16 @@ static_assert(EWG % REP == 0 && SPEC * SPEC_Q <= LCAP && 4 * EWG == NBIN, "a thr
 struct EmitShared {
     uint32_t hist[NBIN];
     uint32_t wsum[EW];
-    uint32_t pick[2];
+    uint32_t pick[3];
     uint32_t fg[EW], fe[EW];                // gathered entries above / at the threshold, per tile of the workgroup
     uint32_t tg[EW], te[EW];                // the tiles' counts, as refine_kernel leaves them
     uint32_t ws[3][EW];
     double dred[3][EW];
     uint64_t ured[EW];
+    // a direct call's bins that are cut again, as they are then
+    uint32_t w_mode[MAXCF], w_base[MAXCF], w_span[MAXCF], w_above[MAXCF], w_c[MAXCF];
+    uint32_t got, n_own, arrived;
+    uint32_t own[WIDE_CHUNKS];              // the chunks of units this workgroup has claimed
 };
 
 // The located bin of one (segment, CF) and the entries gathered from it.
@@ -2727,25 +2761,9 @@ __device__ __forceinline__ void gathered_load(const Params& p, int t, int j, int
 }
 
 // f(key - base, tile, value) for every gathered entry of this thread.
-template <bool D, typename F>
+template <typename F>
 __device__ __forceinline__ void gathered_each(const Params& p, int tid, const Gathered& g, F f)
 {
-    if (D && g.mode == MODE_WIDE) {
-        // the bin's entries are in the bracket lists, among those of other CFs' bins: a quarter of a sub-tile's slots per
-        // wavefront and round (those past the list's end hold whatever they do and are not used)
-        constexpr uint32_t K = TS / 64 / 4;
-#pragma unroll 1
-        for (uint32_t x = (uint32_t)tid >> 6; x < p.n_tiles * SUB * 4; x += EW) {
-            const uint32_t v = x / 4, at = (x & 3u) * (TS / 4) + (tid & 63), n = p.brk_cnt[v] & LISTED;
-            uint32_t k[K];
-#pragma unroll
-            for (uint32_t q = 0; q < K; ++q) k[q] = p.brk_key[(size_t)v * TS + at + q * 64];
-#pragma unroll
-            for (uint32_t q = 0; q < K; ++q)
-                if (at + q * 64 < n && k[q] >= g.base && k[q] - g.base <= g.span) f(k[q] - g.base, v / FINE, 0.0f);
-        }
-        return;
-    }
     if (g.spec) {
 #pragma unroll
         for (int q = 0; q < SPEC_Q; ++q)
@@ -2765,18 +2783,35 @@ __device__ __forceinline__ void gathered_each(const Params& p, int tid, const Ga
     }
 }
 
-// g.tau / need / cnt_gt: the key of the k-th largest, how many equal to it are selected, how many lie above.
-template <bool D>
-__device__ __forceinline__ void gathered_resolve(const Params& p, int tid, Gathered& g, EmitShared& sh)
+// The bin of the left-th largest entry of a histogram of which thread tid holds bins 2044 - 4 tid .. 2047 - 4 tid: sh.pick is
+// the bin, what lies above it and what is in it.
+__device__ __forceinline__ void pick_bin(EmitShared& sh, const uint4& hv, uint32_t left, int tid)
 {
     const int lane = tid & 63, wib = tid >> 6;
+    const uint32_t hh[4] = {hv.w, hv.z, hv.y, hv.x}, mine = hv.x + hv.y + hv.z + hv.w;
+    const uint32_t incl = wave_scan(mine);
+    if (lane == 63) sh.wsum[wib] = incl;
+    __syncthreads();
+    uint32_t higher = incl - mine;   // entries in the bins above this thread's four
+#pragma unroll
+    for (int w = 0; w < EW; ++w) if (w < wib) higher += sh.wsum[w];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        if (higher < left && higher + hh[e] >= left) { sh.pick[0] = (uint32_t)(NBIN - 1 - 4 * tid - e); sh.pick[1] = higher; sh.pick[2] = hh[e]; }
+        higher += hh[e];
+    }
+    __syncthreads();
+}
+
+// g.tau / need / cnt_gt: the key of the k-th largest, how many equal to it are selected, how many lie above.
+__device__ __forceinline__ void gathered_resolve(const Params& p, int tid, Gathered& g, EmitShared& sh)
+{
     if (g.mode == MODE_RESOLVED) return;
     uint32_t filled = 0;
 #pragma unroll
     for (int r = 0; r < REP; ++r) filled += g.fill[r];
     const uint32_t want = g.k - g.above;
-    const bool wide = D && g.mode == MODE_WIDE;
-    if (!wide && (g.mode != MODE_GATHER || filled != g.c || g.c > (uint32_t)LCAP || want == 0 || want > g.c)) {
+    if (g.mode != MODE_GATHER || filled != g.c || g.c > (uint32_t)LCAP || want == 0 || want > g.c) {
         if (tid == 0) p.status->error = 1;
         g.mode = MODE_FAIL;
         g.tau = g.base; g.need = 0; g.cnt_gt = g.above;
@@ -2792,24 +2827,11 @@ __device__ __forceinline__ void gathered_resolve(const Params& p, int tid, Gathe
     for (;;) {
         *(uint4*)&sh.hist[4 * tid] = make_uint4(0u, 0u, 0u, 0u);
         __syncthreads();
-        gathered_each<D>(p, tid, g, [&](uint32_t d, uint32_t, float) {
+        gathered_each(p, tid, g, [&](uint32_t d, uint32_t, float) {
             if ((d & pmask) == prefix) atomicAdd(&sh.hist[(d >> shift) & (NBIN - 1)], 1u);
         });
         __syncthreads();
-        const uint4 hv = *(const uint4*)&sh.hist[NBIN - 4 - 4 * tid];
-        const uint32_t hh[4] = {hv.w, hv.z, hv.y, hv.x}, mine = hv.x + hv.y + hv.z + hv.w;
-        const uint32_t incl = wave_scan(mine);
-        if (lane == 63) sh.wsum[wib] = incl;
-        __syncthreads();
-        uint32_t higher = incl - mine;   // entries in the bins above this thread's four
-#pragma unroll
-        for (int w = 0; w < EW; ++w) if (w < wib) higher += sh.wsum[w];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            if (higher < left && higher + hh[e] >= left) { sh.pick[0] = (uint32_t)(NBIN - 1 - 4 * tid - e); sh.pick[1] = higher; }
-            higher += hh[e];
-        }
-        __syncthreads();
+        pick_bin(sh, *(const uint4*)&sh.hist[NBIN - 4 - 4 * tid], left, tid);
         prefix |= sh.pick[0] << shift;
         pmask |= (uint32_t)(NBIN - 1) << shift;
         gsum += sh.pick[1];
@@ -2821,6 +2843,179 @@ __device__ __forceinline__ void gathered_resolve(const Params& p, int tid, Gathe
     g.tau = g.base + prefix; g.cnt_gt = g.above + gsum; g.need = g.k - g.cnt_gt;
 }
 
+// A direct call whose pass has found bins too full to gather or too wide (a mass of equal values, magnitudes close together, a
+// second part of the tensor far from the finely binned octaves).  All workgroups of the emit step, the statistics' among them,
+// cut them together before they do anything else, as the plan step does on its exact routes and with the same kind of queue: the
+// units are claimed in chunks, a workgroup waits for chunks that running workgroups have claimed and for nothing else.  Per such
+// CF a histogram of 11 bits of the bin's keys from the bracket lists, until what holds the k-th largest is one key or little
+// enough to gather; then a walk that counts and sums up, per unit, what lies above that, and gathers what lies inside.
+// (524,288 elements, magnitudes within 10 % of each other, CF 100, and within 1 %; 255 values, CF 10; one value, CF 100: 39, 44, 41
+// and 73 us.  Resolved by every workgroup for itself from all lists: 253, 312, 184 and 924; by the plan and refine steps, two launches
+// more for every call: 37, 51, 78 and 820.)
+template <int U>
+__device__ __forceinline__ void wide_resolve(const Params& p, int tid, EmitShared& sh)
+{
+    const int lane = tid & 63, wib = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const uint32_t units = p.n_tiles * (SUB / U), n_chunks = (units + EW - 1u) / EW;
+    uint32_t waits = 0;
+    bool arrived = true;
+    if (tid == 0) sh.n_own = 0;
+    if (tid < p.n_cf) {
+        const CfState* st = &p.st[tid];
+        sh.w_mode[tid] = st->mode; sh.w_base[tid] = st->base; sh.w_span[tid] = st->span;
+        sh.w_above[tid] = st->above; sh.w_c[tid] = st->c;
+    }
+    // f(key, live) for the listed entries of unit u, by all lanes of a wavefront
+    const auto walk = [&](uint32_t u, auto f) {
+        const UnitLists<U> tl = bracket_lists<U>(p, u);
+        constexpr uint32_t K = 8;   // loads in flight
+#pragma unroll 1
+        for (int i = 0; i < U; ++i) {
+            uint32_t n = 0;
+#pragma unroll
+            for (int x = 0; x < U; ++x) n = x == i ? tl.start[x + 1] - tl.start[x] : n;
+            const uint32_t* src = p.brk_key + ((size_t)u * U + i) * TS + lane;
+#pragma unroll 1
+            for (uint32_t b = 0; b < n; b += 64 * K) {   // (a list's slots are a multiple of that; those past its end are not used)
+                static_assert(TS % (64 * K) == 0, "inside the sub-tile's slots");
+                uint32_t k[K];
+#pragma unroll
+                for (uint32_t q = 0; q < K; ++q) k[q] = src[b + 64 * q];
+#pragma unroll 1
+                for (uint32_t x = b; x < b + 64 * K && x < n; x += 64) {
+                    const uint32_t key = pop_front(k);
+                    f(key, x + lane < n);
+                }
+            }
+        }
+    };
+    bool first = true;
+    __syncthreads();
+#pragma unroll 1
+    for (int j = 0; j < p.n_cf && arrived; ++j) {
+        if (sh.w_mode[j] != MODE_WIDE) continue;
+        const uint32_t k = p.flat_k[j];
+        uint32_t base = sh.w_base[j], span = sh.w_span[j], above = sh.w_above[j], c = sh.w_c[j];
+#pragma unroll 1
+        for (uint32_t round = 0; round < WIDE_ROUNDS; ++round) {
+            // (keys of denormal numbers lie octaves apart: they are cut down to one)
+            if (span == 0u || (c <= (uint32_t)LCAP && span < (1u << SCSHIFT) && base >= 0x00800000u)) break;
+            const uint32_t nbits = 32u - (uint32_t)__clz((int)span), shift = nbits > 11u ? nbits - 11u : 0u;
+            *(uint4*)&sh.hist[4 * tid] = make_uint4(0u, 0u, 0u, 0u);
+            __syncthreads();
+            const auto count = [&](uint32_t u) {
+                walk(u, [&](uint32_t key, bool live) {
+                    const bool in = live && key >= base && key - base <= span;
+                    const uint32_t bin = (key - base) >> shift;
+                    // a mass of equal keys: the lanes that share the first one's bin add once
+                    const uint64_t m = __ballot(in);
+                    if (m == 0ull) return;
+                    const int leader = __ffsll((unsigned long long)m) - 1;
+                    const uint64_t same = __ballot(in && bin == (uint32_t)__shfl((int)bin, leader, 64));
+                    if (lane == leader) atomicAdd(&sh.hist[bin], (uint32_t)__popcll(same));
+                    else if (in && !((same >> lane) & 1ull)) atomicAdd(&sh.hist[bin], 1u);
+                });
+            };
+            if (first) {
+                // The chunks are claimed as they are worked on.  (The last thing of a round is a barrier for everybody.  With a
+                // statement of thread 0 there the compiler joins it with the one that the next round begins with, for which
+                // the other lanes of its wavefront then do not wait: they go round without it, for ever.)
+                first = false;
+                for (;;) {
+                    if (tid == 0) {
+                        sh.got = sh.n_own < WIDE_CHUNKS ? atomicAdd(&p.xq[0], 1u) : NONE;   // (there are no more than that)
+                        if (sh.got < n_chunks) sh.own[sh.n_own++] = sh.got;
+                    }
+                    __syncthreads();
+                    const uint32_t at = sh.got;
+                    if (at >= n_chunks) break;
+                    const uint32_t u = __builtin_amdgcn_readfirstlane(at * EW + wib);
+                    if (u < units) count(u);
+                    __syncthreads();
+                }
+            } else {
+                for (uint32_t x = 0; x < sh.n_own; ++x) {
+                    const uint32_t u = __builtin_amdgcn_readfirstlane(sh.own[x] * EW + wib);
+                    if (u < units) count(u);
+                }
+            }
+            __syncthreads();
+            uint32_t* all = wide_hist(p, j, round);
+#pragma unroll
+            for (uint32_t e = 0; e < 4; ++e) {
+                const uint32_t x = sh.hist[4 * tid + e];
+                if (x != 0u) atomicAdd(&all[4 * tid + e], x);
+            }
+            arrived = wait_for_all(p, sh.n_own, sh.arrived, &p.xq[1], ++waits * n_chunks, tid);
+            if (!arrived) break;
+            if (tid == 0) sh.pick[0] = NONE;
+            __syncthreads();
+            pick_bin(sh, *(const uint4*)&all[NBIN - 4 - 4 * tid], k - above, tid);
+            const uint32_t b = sh.pick[0];
+            if (b == NONE) { arrived = false; break; }   // cannot happen: the bin was counted from the same values
+            above += sh.pick[1];
+            c = sh.pick[2];
+            const uint32_t left = span - (b << shift);
+            base += b << shift;
+            span = (1u << shift) - 1u < left ? (1u << shift) - 1u : left;
+            __syncthreads();   // (pick is rewritten)
+        }
+        if (tid == 0) { sh.w_base[j] = base; sh.w_span[j] = span; sh.w_above[j] = above; sh.w_c[j] = c; }
+    }
+    __syncthreads();
+    if (arrived) {
+        // per unit: what lies above the bin as it is now, inside what it was; what lies inside it
+        for (uint32_t x = 0; x < sh.n_own; ++x) {
+            const uint32_t u = __builtin_amdgcn_readfirstlane(sh.own[x] * EW + wib);
+            if (u >= units) continue;
+#pragma unroll 1
+            for (int j = 0; j < p.n_cf; ++j) {
+                if (sh.w_mode[j] != MODE_WIDE) continue;
+                const uint32_t base = sh.w_base[j], span = sh.w_span[j], end = p.st[j].base + p.st[j].span;
+                const uint32_t lst = (uint32_t)j * REP + (u & (REP - 1u));
+                uint32_t n_above = 0, n_in = 0;
+                double sum = 0.0;
+                walk(u, [&](uint32_t key, bool live) {
+                    const bool from = live && key >= base && key <= end, gt = from && key - base > span, in = from && !gt;
+                    const double d = (double)__uint_as_float(key);
+                    sum += gt ? d * d : 0.0;
+                    n_above += (uint32_t)__popcll(__ballot(gt));
+                    const uint64_t m = __ballot(in);
+                    n_in += (uint32_t)__popcll(m);
+                    if (span == 0u || m == 0ull) return;
+                    const int leader = __ffsll((unsigned long long)m) - 1;
+                    uint32_t at = 0;
+                    if (lane == leader) at = atomicAdd(&p.list_cnt[lst * 32], (uint32_t)__popcll(m));
+                    const uint32_t pos = (uint32_t)__builtin_amdgcn_readlane((int)at, leader) + lanes_below(m);
+                    if (in && pos < LCAP) {
+                        p.list_key[lst * LCAP + pos] = key;
+                        p.list_tile[lst * LCAP + pos] = u;
+                    }
+                });
+                sum = wave_sum(sum);
+                if (lane == 0) {
+                    p.sss[(size_t)u * p.n_cf + j] = sum;
+                    if (j == p.commit) { p.tg0[u] = n_above; p.tin[u] = n_in; }
+                }
+            }
+        }
+        arrived = wait_for_all(p, sh.n_own, sh.arrived, &p.xq[1], ++waits * n_chunks, tid);
+    }
+    // (a wait that was given up: gathered_resolve flags the error)
+    if (tid < p.n_cf && sh.w_mode[tid] == MODE_WIDE) sh.w_mode[tid] = !arrived ? MODE_FAIL : (sh.w_span[tid] == 0u ? MODE_RESOLVED : MODE_GATHER);
+    __syncthreads();
+}
+
+// CF j's bin after that, if it was one of those.
+__device__ __forceinline__ bool wide_load(const Params& p, int j, int tid, Gathered& g, const EmitShared& sh)
+{
+    if (g.mode != MODE_WIDE) return false;
+    gathered_load(p, 0, j, tid, g);
+    g.mode = sh.w_mode[j]; g.base = sh.w_base[j]; g.span = sh.w_span[j]; g.above = sh.w_above[j]; g.c = sh.w_c[j];
+    g.tau = g.base; g.cnt_gt = g.above; g.need = g.k - g.above;   // (if it is one key)
+    return g.mode != MODE_FAIL;
+}
+
 // Statistics of (segment t, CF j), by one workgroup.
 template <int U, bool D>
 __device__ __forceinline__ void emit_stats(const Params& p, int t, int j, EmitShared& sh)
@@ -2829,6 +3024,7 @@ __device__ __forceinline__ void emit_stats(const Params& p, int t, int j, EmitSh
     // (a direct call has no refine step to add up the sub-tiles' sums)
     const uint32_t u0 = seg_tile0(p, t) * (D ? SUB : SUB / U), u1 = seg_tile1(p, t) * (D ? SUB : SUB / U);
     const double *ssd = D ? p.ssd : p.ssd_t, *sss = D ? p.ovs : p.sss;
+    const bool wide = D && p.status->n_wide != 0;
     Gathered g;
     gathered_load(p, t, j, tid, g);
     // the units' sums, eight units per thread and round, in a fixed order
@@ -2850,25 +3046,21 @@ __device__ __forceinline__ void emit_stats(const Params& p, int t, int j, EmitSh
         kept = wave_sum(kept);
         if (lane == 0) sh.ws[0][wib] = kept;
     }
-    gathered_resolve<D>(p, tid, g, sh);
+    if constexpr (D) {
+        if (wide) {
+            wide_resolve<U>(p, tid, sh);
+            if (wide_load(p, j, tid, g, sh))
+                for (uint32_t u = tid; u < p.n_tiles * (SUB / U); u += EWG) sj += p.sss[(size_t)u * p.n_cf + j];
+        }
+    }
+    gathered_resolve(p, tid, g, sh);
     const uint32_t dtau = g.tau - g.base;  // the threshold inside the located bin
     // the entries of the located bin above the threshold (Random-k: and the one at it).  Their order in the gather
     // lists varies from run to run, so their energies are added as integers: every square, exact in binary64, is
     // scaled by a power of two that puts the largest of them below 2^50 and truncated, the sum of up to LCAP of them
     // fits 64 bits and does not depend on the order, and it is off by less than 2^-38 of itself.
     double ebin = 0.0;
-    if (D && g.mode == MODE_WIDE) {
-        // (too many for that, but their order is the lists', which does not vary)
-        double plain = 0.0;
-        gathered_each<D>(p, tid, g, [&](uint32_t d, uint32_t, float) {
-            const double v = (double)__uint_as_float(g.base + d);
-            plain += d > dtau ? v * v : 0.0;
-        });
-        plain = wave_sum(plain);
-        if (lane == 0) sh.dred[2][wib] = plain;
-        __syncthreads();
-        for (int w = 0; w < EW; ++w) ebin += sh.dred[2][w];
-    } else if (g.mode == MODE_GATHER) {
+    if (g.mode == MODE_GATHER) {
         const auto square = [&](uint32_t d, float val) {
             const bool in = d > dtau || (p.random && d == dtau);
             const double dv = p.random ? (double)val : (double)__uint_as_float(g.base + d);
@@ -2883,7 +3075,7 @@ __device__ __forceinline__ void emit_stats(const Params& p, int t, int j, EmitSh
                 const int ex = ilogb(m * m);                  // every square is below 2^(ex + 1)
                 const double sc = scalbn(1.0, 49 - ex);       // (a power of two: the product is exact)
                 uint64_t acc = 0;
-                gathered_each<D>(p, tid, g, [&](uint32_t d, uint32_t, float val) { acc += (uint64_t)(square(d, val) * sc); });  // < 2^50 each
+                gathered_each(p, tid, g, [&](uint32_t d, uint32_t, float val) { acc += (uint64_t)(square(d, val) * sc); });  // < 2^50 each
                 acc = wave_sum(acc);
                 if (lane == 0) sh.ured[wib] = acc;
                 __syncthreads();
@@ -2895,7 +3087,7 @@ __device__ __forceinline__ void emit_stats(const Params& p, int t, int j, EmitSh
         } else {
             double mx = 0.0, plain = 0.0;
             bool finite = true;
-            gathered_each<D>(p, tid, g, [&](uint32_t d, uint32_t, float val) {
+            gathered_each(p, tid, g, [&](uint32_t d, uint32_t, float val) {
                 const double x = square(d, val);
                 mx = fmax(mx, x);   // (a NaN square is skipped here and shows in the plain sum)
                 plain += x;
@@ -2917,7 +3109,7 @@ __device__ __forceinline__ void emit_stats(const Params& p, int t, int j, EmitSh
             } else if (mx > 0.0) {
                 const int ex = ilogb(mx);                      // 2^ex <= mx < 2^(ex + 1)
                 uint64_t acc = 0;
-                gathered_each<D>(p, tid, g, [&](uint32_t d, uint32_t, float val) { acc += (uint64_t)scalbn(square(d, val), 49 - ex); });  // < 2^50 each
+                gathered_each(p, tid, g, [&](uint32_t d, uint32_t, float val) { acc += (uint64_t)scalbn(square(d, val), 49 - ex); });  // < 2^50 each
                 acc = wave_sum(acc);
                 if (lane == 0) sh.ured[wib] = acc;
                 __syncthreads();
@@ -3487,6 +3679,7 @@ __global__ __launch_bounds__(EWG) __attribute__((amdgpu_waves_per_eu(D ? 4 : 6, 
         if (tail + tid < ub) { pg += p.tg0[tail + tid]; pe += p.tin[tail + tid]; }
     }
     const SegState sg = p.seg[t];
+    const bool wide = D && p.status->n_wide != 0;
     Gathered g;
     gathered_load(p, t, p.commit, tid, g);
     if constexpr (HEADS) {   // (out of the registers while the threshold is resolved)
@@ -3510,14 +3703,25 @@ __global__ __launch_bounds__(EWG) __attribute__((amdgpu_waves_per_eu(D ? 4 : 6, 
             return;
         }
     }
-    gathered_resolve<D>(p, tid, g, sh);
+    if constexpr (D) {
+        if (wide) {
+            wide_resolve<U>(p, tid, sh);
+            if (wide_load(p, p.commit, tid, g, sh)) {
+                // what the units have above and inside the bin as it is now
+                if (tid < EW && ub + tid < ue) { sh.tg[tid] += p.tg0[ub + tid]; sh.te[tid] = p.tin[ub + tid]; }
+                pe = 0;
+                for (uint32_t u = tid; u < ub; u += EWG) { pg += p.tg0[u]; pe += p.tin[u]; }
+            }
+        }
+    }
+    gathered_resolve(p, tid, g, sh);
     const uint32_t dtau = g.tau - g.base;  // the threshold inside the located bin
     // ---- the gathered entries above and at the threshold, by tile.  Entries equal to tau: those inside a located bin
     // that is one key wide, else the gathered ones
     const bool one_key = g.mode == MODE_RESOLVED;
     if (!one_key) pe = 0;
-    if (g.mode == MODE_GATHER || (D && g.mode == MODE_WIDE)) {
-        gathered_each<D>(p, tid, g, [&](uint32_t d, uint32_t tile, float) {
+    if (g.mode == MODE_GATHER) {
+        gathered_each(p, tid, g, [&](uint32_t d, uint32_t tile, float) {
             if (d < dtau) return;
             const bool gt = d > dtau;
             if (tile < ub) { if (gt) ++pg; else ++pe; }
@@ -4926,7 +5130,8 @@ int gravac_read_status(const void* workspace, void* stream_v, int32_t* out8)
     Status s;
     if (hipMemcpy(&s, workspace, sizeof(Status), hipMemcpyDeviceToHost) != hipSuccess) return GRAVAC_ERR_HIP;
     out8[0] = s.any_fail; out8[1] = s.n_fail; out8[2] = s.error; out8[3] = s.n_seg; out8[4] = s.n_narrow;
-    out8[5] = out8[6] = out8[7] = 0;
+    out8[5] = s.n_wide;
+    out8[6] = out8[7] = 0;
     return GRAVAC_OK;
 }
 
