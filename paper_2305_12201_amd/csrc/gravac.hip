@@ -3151,10 +3151,17 @@ constexpr uint32_t EMIT_STAGE = TS / 2;
 static_assert(EMIT_STAGE % 256 == 0, "a lane's four pairs are aligned and inside");
 // Streamed messages (the forms with S): pairs go through LDS and from there to memory four per lane with non-temporal hints.
 // What a kernel leaves in the L2 caches is written back when it ends, and nothing runs meanwhile; the hints have it written as
-// it comes, in pieces long enough to fill lines.  VGG16 shape at CF 10 (110 MB) 389 -> 360 us, ResNet101 shape with three CFs
-// (36 MB) 160.3 -> 153.3, 100 million elements at CF 10, 20 and 40 319 -> 296, 286 -> 277 and 250 -> 248, 30 million 111 -> 109
-// and, of 1.5 million pairs, 102.7 -> 101; with fewer pairs than that nothing or a loss (1 million of 100 million 236.9 ->
-// 238.1).  (As plain stores of 16 bytes it is as it was, and so are hints on stores of a pair per lane: 10 us slower.)
+// it comes, in pieces long enough to fill lines.  Microseconds of a call without and with it, on the same buffers each time and (in
+// brackets) on three states in turn, Normal gradients:
+//    45 million, CF 10   145.3  143.2  (152.0  146.2)    CF 3    205.2  183.3  (240.4  215.9)    CF 2   223.0  239.4  (255.3  242.7)
+//    30 million, CF 10   112.0  110.8  (114.2  112.6)    CF 3    149.6  143.7  (180.4  160.2)    CF 2   162.6  174.1  (185.9  177.9)
+//   138 million, CF 10   373.4  358.1  (426.2  405.8)    CF 3    639.8  618.7  (640.4  619.2)    CF 2   700.3  661.6  (701.3  702.7)
+// (the VGG16 shape with its two parts, CF 10: 363.7 364.2 (388.5 373.2); a million pairs of 100 million elements 236.9 238.1, hence
+// the number below.  As plain stores of 16 bytes it is as it was, and so are hints on stores of a pair per lane: 10 us slower.)
+// Where two in five entries or more are selected a wavefront's 64 pairs fill lines by themselves, and a message of a call without a
+// scan step is left to the caches, which is slower only where the call before it has filled them with other buffers' results: 45
+// million at CF 2 after 512 MB have been read 238.6 260.7, after they have been written 266.9 271.6, Random-k 237.9 263.9 and 273.0
+// 278.6.  (66 million and more, with a scan step, are as fast or faster streamed except after a read, 334 363.)
 constexpr int64_t STREAM_OUT = 1500000;   // pairs
 
 struct EmitCtx {
@@ -4932,14 +4939,17 @@ static int compress_impl(const float* grad, float* residual, int64_t n, const do
     const int heads = (!random && p.n_tiles <= EMIT_RESIDENT) ? 1 : 0;
     if (!p.direct) hipLaunchKernelGGL(refine_forms[fine][heads][ncf_form], dim3(light_grid), dim3(LWG), 0, stream, p);
     const bool general = p.random || p.single;   // (the plain call has forms of its own)
-    const int stream_out = !fixed && total_out >= STREAM_OUT ? 1 : 0;
+    const int stream_out = !fixed && total_out >= STREAM_OUT && (with_scan || 5 * total_out < 2 * n) ? 1 : 0;   // (see STREAM_OUT)
     void (*const scan_emit_forms[2][2])(Params) = {{emit_kernel<false, false>, emit_kernel<true, false>}, {emit_kernel<false, true>, emit_kernel<true, true>}};
     if (with_scan) {
         const uint32_t scan_slices = (max_seg_tiles + SCAN_SLICE - 1) / SCAN_SLICE;
         hipLaunchKernelGGL(scan_kernel, dim3(ns, scan_slices + n_cf), dim3(SCAN_T), 0, stream, p, scan_slices);
         hipLaunchKernelGGL(scan_emit_forms[stream_out][general ? 1 : 0], dim3(light_grid), dim3(LWG), 0, stream, p);
     } else {
-        // (calls of smaller units have smaller messages)
+        // (There is a streamed form for units of a tile only.  Smaller units, of calls of up to 25 million elements, gain little by
+        // it: 16 and 24 million at CF 10 75.7 -> 75.3 and 94.6 -> 94.8 us, with a part a hundred times larger 83.7 -> 81.0 and
+        // 100.2 -> 98.7; 24 million at CF 4 110.3 -> 109.6, three states in turn 125.4 -> 114.6; at CF 2 138 -> 147.  Units of a tile,
+        // streamed, instead of them: 16 million at CF 10 79.5, at CF 4 98.7 instead of 92.7.)
 #define EMIT_FORMS(u, direct, streamed) {resolve_emit_kernel<false, u, direct, streamed>, resolve_emit_kernel<true, u, direct, streamed>}
         void (*const emit_forms[5][2])(Params) = {EMIT_FORMS(SUB, false, false), EMIT_FORMS(MIDDLE, false, false), EMIT_FORMS(FINE, false, false),
                                                   EMIT_FORMS(FINE, true, false), EMIT_FORMS(SUB, false, true)};

@@ -61,11 +61,12 @@ def test_second_level(rel):
 
 def test_streamed_messages():
     """1.5 million pairs and more in a call without a scan step, whose message goes through LDS: sub-tiles with and without
-    lists, a message that starts off a multiple of four pairs, Random-k, a second level with and without a residual."""
+    lists, a message that starts off a multiple of four pairs, Random-k, a second level with and without a residual; and a message
+    of every second entry, which does not."""
     n = 26_000_003
     g, r = gradient(n, 11), workloads.normal_gradient(n, 1e-5, seed=12)
     off = workloads.offsets_of([1_000_001, 25_000_000, 2])
-    for cfs, commit, seg in (([12.0], 0, None), ([3.0], 0, None), ([15.0, 200.0], 0, off)):
+    for cfs, commit, seg in (([12.0], 0, None), ([3.0], 0, None), ([15.0, 200.0], 0, off), ([2.0], 0, None), ([2.0, 100.0], 0, off)):
         check(g, r, cfs, commit, seg, what=f"CFs {cfs}")
     routes.check_randomk(g, r, [10.0], seed=3, what="Random-k")
     idx = (2 * np.arange(n, dtype=np.int64)).astype(np.int32)
