@@ -1,11 +1,21 @@
 """Helpers shared by the GPU parity tests: run the HIP library and the CPU oracle on the same inputs."""
+import ctypes
+
 import numpy as np
 import torch
 
 from oracle import oracle
 from paper_2305_12201_amd import binding
 
-STAT_RTOL = 1e-5   # tolerance on the statistics (fp64 sums in a different order); everything else is bit-exact
+
+def stat_rtol(n):
+    """Relative tolerance on the statistics of a call on n entries; everything else is compared bit for bit.
+
+    They are binary64 sums of squares, each exact.  A sum of n of them one after the other, as the oracle adds them up, is off
+    by at most n 2^-53 of itself, a quotient of two by twice that; the library's sums are a few hundred deep, and those of the
+    entries of the threshold's bin are truncated to 2^-38.  In a sum of up to 60 million squares of one size that is less than
+    one of them."""
+    return 2.0 ** -36 + n * 2.0 ** -52
 
 
 def gpu_compress(grad, residual, cfs, commit=0, seg=None, flags=0, comp=None):
@@ -24,6 +34,16 @@ def gpu_compress(grad, residual, cfs, commit=0, seg=None, flags=0, comp=None):
     return idx.cpu().numpy(), val.cpu().numpy(), stats.cpu().numpy(), r.cpu().numpy(), st
 
 
+def cut_again(workspace):
+    """Whether the last call on the workspace was direct and had to cut a full bin again (word 5 of its status)."""
+    out = (ctypes.c_int32 * 8)()
+    assert binding.lib().gravac_read_status(workspace.data_ptr(), torch.cuda.current_stream().cuda_stream, out) == 0
+    assert out[2] == 0
+    if out[5]:
+        assert list(out[:2]) == [1, 1] and out[4] == 1
+    return bool(out[5])
+
+
 def assert_same(gpu, ref, what=""):
     """gpu = (idx, val, stats, res[, status]); ref = (idx, val, stats, res) from the oracle."""
     gi, gv, gs, gr = gpu[:4]
@@ -36,7 +56,7 @@ def assert_same(gpu, ref, what=""):
     assert gs.shape == os_.shape
     # tau is exact; sums agree to rounding order
     assert np.array_equal(gs[..., 3], os_[..., 3], equal_nan=True), f"{what}: thresholds differ"
-    np.testing.assert_allclose(gs[..., :3], os_[..., :3], rtol=STAT_RTOL, atol=0, equal_nan=True, err_msg=what)
+    np.testing.assert_allclose(gs[..., :3], os_[..., :3], rtol=stat_rtol(gr.size), atol=0, equal_nan=True, err_msg=what)
 
 
 def oracle_compress(grad, residual, cfs, commit=0, seg=None):

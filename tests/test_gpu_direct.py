@@ -1,15 +1,13 @@
 """GPU parity of direct calls, the flat Top-k calls of at most 524,288 elements whose sampling kernel counts all of them, and
 of the calls just above that: bins with few entries, with more than a gather list holds, of one key, at either end of the
 keys.  Against the CPU oracle, bit for bit."""
-import ctypes
-
 import numpy as np
 import pytest
 import torch
 
 from paper_2305_12201_amd import binding, workloads
 from tests import test_gpu_multilevel as levels
-from tests.gpu_util import assert_same, check, gpu_compress, oracle_compress
+from tests.gpu_util import assert_same, check, cut_again, gpu_compress, oracle_compress
 
 pytestmark = pytest.mark.gpu
 
@@ -76,16 +74,6 @@ FULL = {
     "one value above others": lambda n, rng: np.where(rng.random(n) < 0.5, 1e-3, rng.standard_normal(n) * 1e-5),
     "denormal": lambda n, rng: rng.integers(-5000, 5000, n) * 2.0 ** -149,
 }
-
-
-def cut_again(workspace):
-    """Whether the last call on the workspace was direct and had to cut a full bin again (word 5 of its status)."""
-    out = (ctypes.c_int32 * 8)()
-    assert binding.lib().gravac_read_status(workspace.data_ptr(), torch.cuda.current_stream().cuda_stream, out) == 0
-    assert out[2] == 0
-    if out[5]:
-        assert list(out[:2]) == [1, 1] and out[4] == 1
-    return bool(out[5])
 
 
 @pytest.mark.parametrize("values", list(FULL))

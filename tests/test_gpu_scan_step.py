@@ -70,6 +70,6 @@ def test_second_level(inputs):
     ref_res = res.copy()
     ref = oracle.recompress(idx, val, 10.0, ref_res)
     for flags in (0, FB):
-        levels.assert_recompress_same(levels.gpu_recompress(idx, val, 10.0, res, flags=flags), ref, ref_res, f"flat, flags {flags}")
+        levels.assert_recompress_same(levels.gpu_recompress(idx, val, 10.0, res, flags=flags), ref, ref_res, val.size, f"flat, flags {flags}")
     counts = [36_000_001, 700, val.size - 36_000_701]
     levels.check_recompress(idx, val, 10.0, None, counts, what="tensors")
