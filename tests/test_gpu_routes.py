@@ -6,7 +6,7 @@ import torch
 
 from oracle import oracle
 from paper_2305_12201_amd import binding, workloads
-from tests.gpu_util import assert_same, check, gpu_compress, oracle_compress
+from tests.gpu_util import assert_same, check, cut_again, gpu_compress, oracle_compress
 from tests.test_gpu_randomk import check as check_randomk
 
 pytestmark = pytest.mark.gpu
@@ -35,31 +35,35 @@ def _mass(n, seed, share, value, rest):
 
 
 @pytest.mark.parametrize("flags", [0, FB])
-@pytest.mark.parametrize("n,share,cf", [(131_073, 0.5, 3.0), (300_007, 0.2, 10.0), (1_200_001, 0.9, 1.5), (700_001, 0.05, 25.0)])
+@pytest.mark.parametrize("n,share,cf", [(131_073, 0.5, 3.0), (300_007, 0.2, 10.0), (600_011, 0.5, 3.0), (900_007, 0.2, 10.0), (1_200_001, 0.9, 1.5),
+                                        (700_001, 0.05, 25.0)])
 def test_mass_of_equal_values(n, share, cf, flags):
     """The k-th largest is one of many equal values: its bin holds more entries than a gather list, on the exact route
-    after the lists have been collected again too."""
+    after the lists have been collected again too (at the two smallest sizes only there: without the flag the calls are direct)."""
     for value, rest in ((1e-3, 1e-3), (0.0, 1e-3), (np.float32(1.25), 1e-6)):
         g = _mass(n, n, share, value, rest)
         check(g, np.zeros(n, np.float32), [cf], flags=flags, what=f"mass of {value}")
         check(g, np.zeros(n, np.float32), [cf, 4 * cf, 40 * cf], 1, flags=flags, what=f"mass of {value}, three CFs")
 
 
-def test_wide_bracket_is_cut_twice():
+@pytest.mark.parametrize("n,direct", [(400_003, True), (700_003, False)])
+def test_wide_bracket_is_cut_twice(n, direct):
     """Magnitudes over hundreds of octaves and a mass of equal ones below: bins far wider than 2^11 keys, and still too
-    full when they are cut the first time."""
-    n = 400_003
+    full when they are cut the first time, by the plan step or, in a direct call, by the emit step."""
     rng = np.random.Generator(np.random.PCG64(5))
     g = np.exp(rng.uniform(-80.0, 0.0, n)).astype(np.float32)
     g[rng.random(n) < 0.5] = np.float32(1e-30)
     for cf in (2.0, 2.5, 3.0):
-        one, _ = check(g, np.zeros(n, np.float32), [cf], what=f"cf {cf}")
-        two, _ = check(g, np.zeros(n, np.float32), [cf, 10.0 * cf], 0, what=f"cf {cf} and {10 * cf}")
-        if cf == 2.0:
+        for cfs in ([cf], [cf, 10.0 * cf]):
+            comp = binding.Compressor(n, cfs, 0)
+            got = gpu_compress(g, np.zeros(n, np.float32), cfs, 0, comp=comp)
+            assert_same(got, oracle_compress(g, np.zeros(n, np.float32), cfs), f"cfs {cfs}")
+            if cf != 2.0:
+                continue
             # The k-th largest is one of the equal values.  They lie below 2^-48, where one bin of the sample takes in all
             # keys, so the bracket's bins are 2^18 keys wide, the first cut leaves 2^7, and those are as full as before.
-            for got in (one, two):
-                assert got[4]["fallback_segments"] == 1 and got[4]["narrow_fallback_segments"] == 1, got[4]
+            assert got[4]["fallback_segments"] == 1 and got[4]["narrow_fallback_segments"] == 1, got[4]
+            assert cut_again(comp.workspace) == direct
 
 
 @pytest.mark.parametrize("n_cf", [1, 2, 3, 5, 8])
@@ -130,8 +134,8 @@ def test_long_gather_lists(n, bits):
 @pytest.mark.parametrize("n", [3 * 8_192 + 5, 200_003])
 @pytest.mark.parametrize("cf", [1.2, 2.0, 2.8, 4.0, 6.0])
 def test_lists_of_many_rounds(n, cf):
-    """Sub-tiles with up to 383 listed candidates, and in buffers off a 16-byte boundary, where every sub-tile keeps its list,
-    with up to 1024."""
+    """Sub-tiles with up to 383 listed candidates (the last one, which is ragged, with as many as it has), in buffers on and off a
+    16-byte boundary."""
     g = workloads.normal_gradient(n, 1e-3, seed=n)
     r = workloads.normal_gradient(n, 1e-4, seed=n + 1)
     check(g, r, [cf], what="one CF")
@@ -144,6 +148,23 @@ def test_lists_of_many_rounds(n, cf):
     idx, val, stats = binding.Compressor(n, [cf], 0)(dg, dr)
     got = (idx.cpu().numpy(), val.cpu().numpy(), stats.cpu().numpy(), dr.cpu().numpy())
     assert_same(got, oracle_compress(g, r, [cf]), "off a 16-byte boundary")
+
+
+@pytest.mark.parametrize("cfs", [[1.2], [1.9], [2.6, 20.0]])
+def test_long_lists_of_ragged_sub_tiles(cfs):
+    """Tensors whose last, ragged sub-tile keeps a list whatever it holds: up to 1023 candidates, among sub-tiles without a list and
+    behind them, in tensors of one tile and of several."""
+    tails = [1023, 1022, 900, 640, 513, 512, 511, 449, 385, 384, 383, 129]
+    sizes = [tiles * 8_192 + rest * 1_024 + t for i, t in enumerate(tails) for tiles, rest in ((1, i % 8), (3 + i, (5 * i) % 8))]
+    off = workloads.offsets_of(sizes)
+    n = int(off[-1])
+    g = workloads.normal_gradient(n, 1e-3, seed=n)
+    r = workloads.normal_gradient(n, 1e-4, seed=1)
+    check(g, r, cfs, 0, off, what="tensors")
+    check(_coarse(g, 7), np.zeros(n, np.float32), cfs, len(cfs) - 1, off, what="tensors, ties")
+    check(g, r, cfs, 0, off, flags=FB, what="tensors, exact route")
+    for t in range(0, len(sizes), 5):
+        check(g[off[t]:off[t + 1]], r[off[t]:off[t + 1]], cfs, what=f"{sizes[t]} elements alone")
 
 
 @pytest.mark.parametrize("n", [1, 8_192, 8_193, 8 * 8_192, 8 * 8_192 + 1, 64 * 8_192, 64 * 8_192 + 1, 72 * 8_192 + 5])

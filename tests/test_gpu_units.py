@@ -23,12 +23,13 @@ def gradient(n, seed):
     return g
 
 
-@pytest.mark.parametrize("tiles", [511, 512, 1023, 1024, 1535, 1536])
-def test_limits(tiles):
-    # (the limits are on a bound that is a tile or two higher than a flat call's own number)
+@pytest.mark.parametrize("cf", [10.0, 20.0, 100.0])
+@pytest.mark.parametrize("tiles", [511, 512, 1023, 1024, 1535, 1536, 3071, 3072])
+def test_limits(tiles, cf):
+    """Quarter tiles with up to 511 tiles (up to 1535 at CF 10 and 20), half tiles with up to 1023 (3071), tiles above: the limits are
+    on a bound that is a tile higher than a flat call's own number."""
     n = tiles * TILE - 3
     g, r = gradient(n, tiles), workloads.normal_gradient(n, 1e-5, seed=1)
-    cf = 20.0 if tiles % 2 else 100.0
     ref = oracle_compress(g, r, [cf])
     without = ref[3].copy()
     without[ref[0]] = ref[1]
