@@ -1099,6 +1099,7 @@ __device__ __forceinline__ uint32_t zero_from(const Params& p, uint32_t lo, uint
 // (As a part of the pass, whose other wavefronts waited for it with their loads on their way, it was no faster: under the
 // pass's own traffic the round trips take two to three times as long.  25 MB buckets 64 -> 66 us, the ResNet101 shape 123.4
 // -> 121.7 at CF 100 and 164 -> 167 with three CFs.)
+template <bool D>  // a direct call
 __global__ __launch_bounds__(64) void bracket_kernel(Params p)
 {
     const uint32_t role = blockIdx.x, nb = p.n_sample_blocks, S = p.flat_samples;
@@ -1134,7 +1135,7 @@ __global__ __launch_bounds__(64) void bracket_kernel(Params p)
     const uint32_t above1 = g_above + last_lane(incl) - incl, above0 = above1 + h1;   // samples above each of this lane's bins
     const uint32_t bin0 = 2u * (role * 32u + (uint32_t)(lane & 31));
     for (int j = 0; j < p.n_cf; ++j) {
-        if (p.direct) {
+        if constexpr (D) {
             // all ranks are k, and all elements are counted: the bin of the k-th largest and what lies above it
             const uint32_t kj = (uint32_t)__builtin_amdgcn_readlane((int)rank_lo, j);
             const bool in1 = above1 < kj && above1 + h1 >= kj, in0 = above0 < kj && above0 + h0 >= kj;
@@ -1149,39 +1150,40 @@ __global__ __launch_bounds__(64) void bracket_kernel(Params p)
                 uint4* h = (uint4*)wide_hist(p, j, 0);
                 for (uint32_t i = lane; i < WIDE_ROUNDS * NBIN / 4; i += 64) h[i] = make_uint4(0u, 0u, 0u, 0u);
             }
-            if (!in1 && !in0) continue;
-            const uint32_t lo = sample_bin_first(bin, w0), end = sample_bin_end(bin, w0), mid = key_inside(bin, w0, kj - above, c);
-            CfState st;
-            st.k = kj; st.lo = lo; st.s = 0; st.base = lo; st.span = end - lo - 1u; st.above = above; st.c = c; st.top = end;
-            st.mode = st.span == 0u ? MODE_RESOLVED : wide ? MODE_WIDE : MODE_GATHER;
-            st.tau = lo; st.cnt_gt = above; st.need = kj - above;   // (if resolved)
-            st.pad[0] = st.pad[1] = st.pad[2] = st.pad[3] = 0;
-            p.st[j] = st;
-            p.bnd[4 * j] = lo; p.bnd[4 * j + 1] = end; p.bnd[4 * j + 2] = mid; p.bnd[4 * j + 3] = st.mode;
-            if (wide) { p.status->any_fail = 1; p.status->n_fail = 1; p.status->n_narrow = 1; p.status->n_wide = 1; }
-            if (j == p.commit) {
-                SegState sg;
-                sg.fail = FAIL_NONE; sg.pz = zero_from(p, lo, end, mid);
-                p.seg[0] = sg;
+            if (in1 || in0) {
+                const uint32_t lo = sample_bin_first(bin, w0), end = sample_bin_end(bin, w0), mid = key_inside(bin, w0, kj - above, c);
+                CfState st;
+                st.k = kj; st.lo = lo; st.s = 0; st.base = lo; st.span = end - lo - 1u; st.above = above; st.c = c; st.top = end;
+                st.mode = st.span == 0u ? MODE_RESOLVED : wide ? MODE_WIDE : MODE_GATHER;
+                st.tau = lo; st.cnt_gt = above; st.need = kj - above;   // (if resolved)
+                st.pad[0] = st.pad[1] = st.pad[2] = st.pad[3] = 0;
+                p.st[j] = st;
+                p.bnd[4 * j] = lo; p.bnd[4 * j + 1] = end; p.bnd[4 * j + 2] = mid; p.bnd[4 * j + 3] = st.mode;
+                if (wide) { p.status->any_fail = 1; p.status->n_fail = 1; p.status->n_narrow = 1; p.status->n_wide = 1; }
+                if (j == p.commit) {
+                    SegState sg;
+                    sg.fail = FAIL_NONE; sg.pz = zero_from(p, lo, end, mid);
+                    p.seg[0] = sg;
+                }
             }
-            continue;
+        } else {
+            const auto find = [&](uint32_t ranks, uint32_t word, uint32_t none, auto key) {
+                // the bin of the rank-th sample from the top, if it is one of this wavefront's
+                const uint32_t rank = (uint32_t)__builtin_amdgcn_readlane((int)ranks, j);
+                const bool in1 = above1 < rank && above1 + h1 >= rank, in0 = above0 < rank && above0 + h0 >= rank;
+                const uint64_t m = __ballot(in1 || in0);
+                if (m != 0ull) {
+                    const uint32_t value = key(in1 ? bin0 + 1u : bin0, rank - (in1 ? above1 : above0), in1 ? h1 : h0);
+                    if (in1 || in0) p.bnd[4 * j + word] = value;
+                } else if (role == 0u && S < rank) {
+                    if (lane == 0) p.bnd[4 * j + word] = none;   // fewer samples than a rank: the bracket is open on that side
+                }
+            };
+            // lower edge of the bin of the rank_lo-th sample from the top, upper edge of the bin of the rank_hi-th
+            find(rank_lo, 0u, 0u, [&](uint32_t bin, uint32_t, uint32_t) { return sample_bin_first(bin, w0); });
+            find(rank_hi, 1u, KEY_END, [&](uint32_t bin, uint32_t, uint32_t) { return sample_bin_end(bin, w0); });
+            find(rank_mid, 2u, NONE, [&](uint32_t bin, uint32_t down, uint32_t c) { return key_inside(bin, w0, down, c); });
         }
-        const auto find = [&](uint32_t ranks, uint32_t word, uint32_t none, auto key) {
-            // the bin of the rank-th sample from the top, if it is one of this wavefront's
-            const uint32_t rank = (uint32_t)__builtin_amdgcn_readlane((int)ranks, j);
-            const bool in1 = above1 < rank && above1 + h1 >= rank, in0 = above0 < rank && above0 + h0 >= rank;
-            const uint64_t m = __ballot(in1 || in0);
-            if (m != 0ull) {
-                const uint32_t value = key(in1 ? bin0 + 1u : bin0, rank - (in1 ? above1 : above0), in1 ? h1 : h0);
-                if (in1 || in0) p.bnd[4 * j + word] = value;
-            } else if (role == 0u && S < rank) {
-                if (lane == 0) p.bnd[4 * j + word] = none;   // fewer samples than a rank: the bracket is open on that side
-            }
-        };
-        // lower edge of the bin of the rank_lo-th sample from the top, upper edge of the bin of the rank_hi-th
-        find(rank_lo, 0u, 0u, [&](uint32_t bin, uint32_t, uint32_t) { return sample_bin_first(bin, w0); });
-        find(rank_hi, 1u, KEY_END, [&](uint32_t bin, uint32_t, uint32_t) { return sample_bin_end(bin, w0); });
-        find(rank_mid, 2u, NONE, [&](uint32_t bin, uint32_t down, uint32_t c) { return key_inside(bin, w0, down, c); });
     }
 }
 
@@ -2705,14 +2707,18 @@ static_assert(EWG % REP == 0 && SPEC * SPEC_Q <= LCAP && 4 * EWG == NBIN, "a thr
 struct EmitShared {
     uint32_t hist[NBIN];
     uint32_t wsum[EW];
-    uint32_t pick[3];
+    uint32_t pick[2];
     uint32_t fg[EW], fe[EW];                // gathered entries above / at the threshold, per tile of the workgroup
     uint32_t tg[EW], te[EW];                // the tiles' counts, as refine_kernel leaves them
     uint32_t ws[3][EW];
     double dred[3][EW];
     uint64_t ured[EW];
-    // a direct call's bins that are cut again, as they are then
-    uint32_t w_mode[MAXCF], w_base[MAXCF], w_span[MAXCF], w_above[MAXCF], w_c[MAXCF];
+};
+
+// A direct call's bins that are cut again, as they are then (wide_resolve).
+struct WideShared {
+    uint32_t mode[MAXCF], base[MAXCF], span[MAXCF], above[MAXCF], c[MAXCF];
+    uint32_t in;                            // entries in the bin that pick_bin has found
     uint32_t got, n_own, arrived;
     uint32_t own[WIDE_CHUNKS];              // the chunks of units this workgroup has claimed
 };
@@ -2784,8 +2790,8 @@ __device__ __forceinline__ void gathered_each(const Params& p, int tid, const Ga
 }
 
 // The bin of the left-th largest entry of a histogram of which thread tid holds bins 2044 - 4 tid .. 2047 - 4 tid: sh.pick is
-// the bin, what lies above it and what is in it.
-__device__ __forceinline__ void pick_bin(EmitShared& sh, const uint4& hv, uint32_t left, int tid)
+// the bin and what lies above it, *in what is in it.
+__device__ __forceinline__ void pick_bin(EmitShared& sh, const uint4& hv, uint32_t left, int tid, uint32_t* in = nullptr)
 {
     const int lane = tid & 63, wib = tid >> 6;
     const uint32_t hh[4] = {hv.w, hv.z, hv.y, hv.x}, mine = hv.x + hv.y + hv.z + hv.w;
@@ -2797,7 +2803,11 @@ __device__ __forceinline__ void pick_bin(EmitShared& sh, const uint4& hv, uint32
     for (int w = 0; w < EW; ++w) if (w < wib) higher += sh.wsum[w];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-        if (higher < left && higher + hh[e] >= left) { sh.pick[0] = (uint32_t)(NBIN - 1 - 4 * tid - e); sh.pick[1] = higher; sh.pick[2] = hh[e]; }
+        if (higher < left && higher + hh[e] >= left) {
+            sh.pick[0] = (uint32_t)(NBIN - 1 - 4 * tid - e);
+            sh.pick[1] = higher;
+            if (in) *in = hh[e];
+        }
         higher += hh[e];
     }
     __syncthreads();
@@ -2853,17 +2863,17 @@ __device__ __forceinline__ void gathered_resolve(const Params& p, int tid, Gathe
 // and 73 us.  Resolved by every workgroup for itself from all lists: 253, 312, 184 and 924; by the plan and refine steps, two launches
 // more for every call: 37, 51, 78 and 820.)
 template <int U>
-__device__ __forceinline__ void wide_resolve(const Params& p, int tid, EmitShared& sh)
+__device__ __forceinline__ void wide_resolve(const Params& p, int tid, EmitShared& sh, WideShared& ws)
 {
     const int lane = tid & 63, wib = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint32_t units = p.n_tiles * (SUB / U), n_chunks = (units + EW - 1u) / EW;
     uint32_t waits = 0;
     bool arrived = true;
-    if (tid == 0) sh.n_own = 0;
+    if (tid == 0) ws.n_own = 0;
     if (tid < p.n_cf) {
         const CfState* st = &p.st[tid];
-        sh.w_mode[tid] = st->mode; sh.w_base[tid] = st->base; sh.w_span[tid] = st->span;
-        sh.w_above[tid] = st->above; sh.w_c[tid] = st->c;
+        ws.mode[tid] = st->mode; ws.base[tid] = st->base; ws.span[tid] = st->span;
+        ws.above[tid] = st->above; ws.c[tid] = st->c;
     }
     // f(key, live) for the listed entries of unit u, by all lanes of a wavefront
     const auto walk = [&](uint32_t u, auto f) {
@@ -2893,9 +2903,9 @@ __device__ __forceinline__ void wide_resolve(const Params& p, int tid, EmitShare
     __syncthreads();
 #pragma unroll 1
     for (int j = 0; j < p.n_cf && arrived; ++j) {
-        if (sh.w_mode[j] != MODE_WIDE) continue;
+        if (ws.mode[j] != MODE_WIDE) continue;
         const uint32_t k = p.flat_k[j];
-        uint32_t base = sh.w_base[j], span = sh.w_span[j], above = sh.w_above[j], c = sh.w_c[j];
+        uint32_t base = ws.base[j], span = ws.span[j], above = ws.above[j], c = ws.c[j];
 #pragma unroll 1
         for (uint32_t round = 0; round < WIDE_ROUNDS; ++round) {
             // (keys of denormal numbers lie octaves apart: they are cut down to one)
@@ -2923,19 +2933,19 @@ __device__ __forceinline__ void wide_resolve(const Params& p, int tid, EmitShare
                 first = false;
                 for (;;) {
                     if (tid == 0) {
-                        sh.got = sh.n_own < WIDE_CHUNKS ? atomicAdd(&p.xq[0], 1u) : NONE;   // (there are no more than that)
-                        if (sh.got < n_chunks) sh.own[sh.n_own++] = sh.got;
+                        ws.got = ws.n_own < WIDE_CHUNKS ? atomicAdd(&p.xq[0], 1u) : NONE;   // (there are no more than that)
+                        if (ws.got < n_chunks) ws.own[ws.n_own++] = ws.got;
                     }
                     __syncthreads();
-                    const uint32_t at = sh.got;
+                    const uint32_t at = ws.got;
                     if (at >= n_chunks) break;
                     const uint32_t u = __builtin_amdgcn_readfirstlane(at * EW + wib);
                     if (u < units) count(u);
                     __syncthreads();
                 }
             } else {
-                for (uint32_t x = 0; x < sh.n_own; ++x) {
-                    const uint32_t u = __builtin_amdgcn_readfirstlane(sh.own[x] * EW + wib);
+                for (uint32_t x = 0; x < ws.n_own; ++x) {
+                    const uint32_t u = __builtin_amdgcn_readfirstlane(ws.own[x] * EW + wib);
                     if (u < units) count(u);
                 }
             }
@@ -2946,32 +2956,32 @@ __device__ __forceinline__ void wide_resolve(const Params& p, int tid, EmitShare
                 const uint32_t x = sh.hist[4 * tid + e];
                 if (x != 0u) atomicAdd(&all[4 * tid + e], x);
             }
-            arrived = wait_for_all(p, sh.n_own, sh.arrived, &p.xq[1], ++waits * n_chunks, tid);
+            arrived = wait_for_all(p, ws.n_own, ws.arrived, &p.xq[1], ++waits * n_chunks, tid);
             if (!arrived) break;
             if (tid == 0) sh.pick[0] = NONE;
             __syncthreads();
-            pick_bin(sh, *(const uint4*)&all[NBIN - 4 - 4 * tid], k - above, tid);
+            pick_bin(sh, *(const uint4*)&all[NBIN - 4 - 4 * tid], k - above, tid, &ws.in);
             const uint32_t b = sh.pick[0];
             if (b == NONE) { arrived = false; break; }   // cannot happen: the bin was counted from the same values
             above += sh.pick[1];
-            c = sh.pick[2];
+            c = ws.in;
             const uint32_t left = span - (b << shift);
             base += b << shift;
             span = (1u << shift) - 1u < left ? (1u << shift) - 1u : left;
             __syncthreads();   // (pick is rewritten)
         }
-        if (tid == 0) { sh.w_base[j] = base; sh.w_span[j] = span; sh.w_above[j] = above; sh.w_c[j] = c; }
+        if (tid == 0) { ws.base[j] = base; ws.span[j] = span; ws.above[j] = above; ws.c[j] = c; }
     }
     __syncthreads();
     if (arrived) {
         // per unit: what lies above the bin as it is now, inside what it was; what lies inside it
-        for (uint32_t x = 0; x < sh.n_own; ++x) {
-            const uint32_t u = __builtin_amdgcn_readfirstlane(sh.own[x] * EW + wib);
+        for (uint32_t x = 0; x < ws.n_own; ++x) {
+            const uint32_t u = __builtin_amdgcn_readfirstlane(ws.own[x] * EW + wib);
             if (u >= units) continue;
 #pragma unroll 1
             for (int j = 0; j < p.n_cf; ++j) {
-                if (sh.w_mode[j] != MODE_WIDE) continue;
-                const uint32_t base = sh.w_base[j], span = sh.w_span[j], end = p.st[j].base + p.st[j].span;
+                if (ws.mode[j] != MODE_WIDE) continue;
+                const uint32_t base = ws.base[j], span = ws.span[j], end = p.st[j].base + p.st[j].span;
                 const uint32_t lst = (uint32_t)j * REP + (u & (REP - 1u));
                 uint32_t n_above = 0, n_in = 0;
                 double sum = 0.0;
@@ -2999,26 +3009,26 @@ __device__ __forceinline__ void wide_resolve(const Params& p, int tid, EmitShare
                 }
             }
         }
-        arrived = wait_for_all(p, sh.n_own, sh.arrived, &p.xq[1], ++waits * n_chunks, tid);
+        arrived = wait_for_all(p, ws.n_own, ws.arrived, &p.xq[1], ++waits * n_chunks, tid);
     }
     // (a wait that was given up: gathered_resolve flags the error)
-    if (tid < p.n_cf && sh.w_mode[tid] == MODE_WIDE) sh.w_mode[tid] = !arrived ? MODE_FAIL : (sh.w_span[tid] == 0u ? MODE_RESOLVED : MODE_GATHER);
+    if (tid < p.n_cf && ws.mode[tid] == MODE_WIDE) ws.mode[tid] = !arrived ? MODE_FAIL : (ws.span[tid] == 0u ? MODE_RESOLVED : MODE_GATHER);
     __syncthreads();
 }
 
 // CF j's bin after that, if it was one of those.
-__device__ __forceinline__ bool wide_load(const Params& p, int j, int tid, Gathered& g, const EmitShared& sh)
+__device__ __forceinline__ bool wide_load(const Params& p, int j, int tid, Gathered& g, const WideShared& ws)
 {
     if (g.mode != MODE_WIDE) return false;
     gathered_load(p, 0, j, tid, g);
-    g.mode = sh.w_mode[j]; g.base = sh.w_base[j]; g.span = sh.w_span[j]; g.above = sh.w_above[j]; g.c = sh.w_c[j];
+    g.mode = ws.mode[j]; g.base = ws.base[j]; g.span = ws.span[j]; g.above = ws.above[j]; g.c = ws.c[j];
     g.tau = g.base; g.cnt_gt = g.above; g.need = g.k - g.above;   // (if it is one key)
     return g.mode != MODE_FAIL;
 }
 
 // Statistics of (segment t, CF j), by one workgroup.
 template <int U, bool D>
-__device__ __forceinline__ void emit_stats(const Params& p, int t, int j, EmitShared& sh)
+__device__ __forceinline__ void emit_stats(const Params& p, int t, int j, EmitShared& sh, WideShared& ws)
 {
     const int tid = threadIdx.x, lane = tid & 63, wib = tid >> 6;
     // (a direct call has no refine step to add up the sub-tiles' sums)
@@ -3048,8 +3058,8 @@ __device__ __forceinline__ void emit_stats(const Params& p, int t, int j, EmitSh
     }
     if constexpr (D) {
         if (wide) {
-            wide_resolve<U>(p, tid, sh);
-            if (wide_load(p, j, tid, g, sh))
+            wide_resolve<U>(p, tid, sh, ws);
+            if (wide_load(p, j, tid, g, ws))
                 for (uint32_t u = tid; u < p.n_tiles * (SUB / U); u += EWG) sj += p.sss[(size_t)u * p.n_cf + j];
         }
     }
@@ -3625,13 +3635,14 @@ __global__ __launch_bounds__(EWG) __attribute__((amdgpu_waves_per_eu(D ? 4 : 6, 
     constexpr bool HEADS = !GEN;
     constexpr int H = 64 / U;   // lanes per sub-tile's list
     __shared__ EmitShared sh;
+    __shared__ WideShared ws;   // (D)
     __shared__ __attribute__((aligned(16))) int32_t stage_idx[EW][TS / 2];   // half a sub-tile's part of the message, per wavefront
     __shared__ __attribute__((aligned(16))) float stage_val[EW][TS / 2];     // (before that: the heads of the tile's lists)
     const int tid = threadIdx.x, lane = tid & 63, wib = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint32_t n_stats = (uint32_t)p.n_seg * p.n_cf;
     if (blockIdx.x < n_stats) {
         const int t = (int)(blockIdx.x / (uint32_t)p.n_cf);
-        if (!seg_small(p, t)) emit_stats<U, D>(p, t, (int)(blockIdx.x - (uint32_t)t * p.n_cf), sh);
+        if (!seg_small(p, t)) emit_stats<U, D>(p, t, (int)(blockIdx.x - (uint32_t)t * p.n_cf), sh, ws);
         return;
     }
     // ---- this workgroup's tiles [ub, ue) of segment t, a wavefront each
@@ -3712,8 +3723,8 @@ __global__ __launch_bounds__(EWG) __attribute__((amdgpu_waves_per_eu(D ? 4 : 6, 
     }
     if constexpr (D) {
         if (wide) {
-            wide_resolve<U>(p, tid, sh);
-            if (wide_load(p, p.commit, tid, g, sh)) {
+            wide_resolve<U>(p, tid, sh, ws);
+            if (wide_load(p, p.commit, tid, g, ws)) {
                 // what the units have above and inside the bin as it is now
                 if (tid < EW && ub + tid < ue) { sh.tg[tid] += p.tg0[ub + tid]; sh.te[tid] = p.tin[ub + tid]; }
                 pe = 0;
@@ -4890,7 +4901,7 @@ static int compress_impl(const float* grad, float* residual, int64_t n, const do
     // a layerwise call's small tensors are done by their workgroups of this launch; few segments (none of them small):
     // their sample histograms are added up by SGRP workgroups each; many: by one each
     if (ns == 1 && p.bounds_from == BOUNDS_SAMPLED)
-        hipLaunchKernelGGL(bracket_kernel, dim3(RGRP), dim3(64), 0, stream, p);
+        hipLaunchKernelGGL(p.direct ? bracket_kernel<true> : bracket_kernel<false>, dim3(RGRP), dim3(64), 0, stream, p);
     else if (n_small)
         hipLaunchKernelGGL((threshold_kernel<1, true>), dim3(ns, 1), dim3(1024), 0, stream, p);
     else if (ns > 1 && ns <= 32 && p.bounds_from == BOUNDS_SAMPLED)
