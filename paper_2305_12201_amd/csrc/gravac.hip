@@ -108,8 +108,8 @@ constexpr uint32_t SKEY0 = SEXP0 << 23;
 constexpr uint32_t SCOARSE = SOCT << (23 - SCSHIFT), SFINE = SWIN << (23 - SFSHIFT), SLESS = SWIN << (23 - SCSHIFT);
 constexpr uint32_t SUSED = 1 + SCOARSE + SFINE - SLESS;   // bins in use: the first is the key 0 alone
 static_assert(SUSED <= (uint32_t)SBIN && (uint64_t)SKEY0 + ((uint64_t)SOCT << 23) <= 0x7F800000ull, "inside the finite keys");
-constexpr int SGRP = 8;             // the sample bins in SGRP groups: one workgroup of the threshold kernel each
-constexpr int RGRP = 64;            // ... and in RGRP groups, one wavefront of a flat call's pass each (bracket_role)
+constexpr int SGRP = 8;             // the sample bins in SGRP groups: a workgroup of the threshold kernel each (up to 32 tensors)
+constexpr int RGRP = 64;            // ... and in RGRP groups: a wavefront of the bracket kernel each (flat calls)
 constexpr int SAMPLE_BLOCK = 1024;  // samples per workgroup of the sampling kernel
 constexpr int SAMPLE_MAX = 65536;   // samples of a flat tensor at most (unless k n is large, see SAMPLE_MAX_FLAT)
 constexpr int SAMPLE_MAX_SEG = 32768;  // layerwise: samples per tensor at most (a tensor of up to twice that is read whole)
@@ -818,8 +818,8 @@ __device__ __forceinline__ uint32_t key_inside(uint32_t bin, uint32_t w0, uint32
 
 // ---------------------------------------------------------------------------------------------
 // K0a: sample acc = residual + grad at stratified positions; each workgroup histograms its samples in
-// LDS (SBIN bins, see sample_bin) and stores the counts as 16-bit numbers, and the
-// counts per group of SBIN / SGRP bins beside them.  The same launch clears what the later kernels
+// LDS (SBIN bins, see sample_bin) and stores the counts as 16-bit numbers, and beside them how many of its
+// samples lie above each of RGRP groups of bins.  The same launch clears what the later kernels
 // add to (every workgroup a share of its segment's histograms and counters); a call whose brackets
 // do not come from a sample launches it for that alone.
 // ---------------------------------------------------------------------------------------------
@@ -961,7 +961,7 @@ __global__ __launch_bounds__(256) void sample_kernel(Params p)
 
 // ---------------------------------------------------------------------------------------------
 // K0b: layerwise, per segment, add up the sample histograms and turn the sampled ranks into a bracket of keys per
-// CF.  (A flat call's pass over the gradient does that itself, bracket_role.)  G workgroups per segment; workgroup y adds up the bins [y, y + 1) * SBIN / G of all the
+// CF.  (Flat calls have bracket_kernel.)  G workgroups per segment; workgroup y adds up the bins [y, y + 1) * SBIN / G of all the
 // segment's sample blocks (what lies above them it knows from the blocks' group counts) and writes the
 // bracket ends that fall into its bins, so that no workgroup waits for another.  The kernels that
 // use the brackets derive the histogram shift and the rest from them (bracket_bins).
@@ -972,8 +972,9 @@ template <int G, bool SMALL, int P = 1>  // SMALL: the workgroups of tensors of 
 __global__ __launch_bounds__(P * 1024 / G) __attribute__((amdgpu_waves_per_eu(SMALL ? 8 : 1, 8))) void threshold_kernel(Params p)
 {
     constexpr int T = 1024 / G;          // thread i < T owns the bins 4 (y T + i) .. + 3: two words of every block's histogram
-    // P threads per such set of bins: thread i + x T adds up the blocks x, x + P, ... (the 64 to 128 blocks of a flat
-    // sample are then one round of loads per thread, not two to four; two threads are best up to 64 blocks, four beyond)
+    // P threads per such set of bins: thread i + x T adds up the blocks x, x + P, ..., of which a tensor has up to 64: one round
+    // of loads per thread with P = 2, two with P = 1 (tensors of 30 million, 20,000 and 1 million elements 109.4 us with one, 106.5
+    // with two, 105.5 with four threads; twenty of 2 million 129.3, 128.9 and 128.8; thirty of 65,537 45.1, 45.7 and 44.5)
     static_assert(P * 1024 / G <= 1024 && (G > 1 || P == 1), "threads of a workgroup");
     constexpr int NW = T / 64;
     static_assert(G == 1 || G == SGRP, "one workgroup per group of bins, or one for all");
@@ -1428,7 +1429,7 @@ struct ExactBounds {
 template <int M, bool RND, bool D, int NCF>
 __device__ __forceinline__ void stream_subtile(const Params& p, uint32_t v, int lane, const ExactBounds* xb, uint2* stage)
 {
-    constexpr bool EF = (M != SM_EXACT);  // a first pass: sums acc^2, takes the brackets from the threshold kernel
+    constexpr bool EF = (M != SM_EXACT);  // a first pass: sums acc^2, takes the brackets that were sampled
     const uint32_t u = v / SUB;  // tile
     if (u >= p.n_tiles) return;
     const int t = tile_seg(p, u);
@@ -3302,13 +3303,13 @@ __device__ __forceinline__ void emit_listed(const Params& p, EmitCtx& x, int32_t
 }
 
 // GEN false: compiled for the plain call (Top-k or threshold keys, gradient + residual).
-// HEADS (plain call only): the heads of the tile's eight lists, 32 candidates each, are fetched with the kernel's first
-// loads, before the lists' lengths are known; a tile whose lists are no longer than that is emitted from them, a
+// HEADS (plain call only): the heads of the unit's lists, 32 candidates each of a tile's eight lists, 64 of four, 128 of two, are fetched
+// with the kernel's first loads, before the lists' lengths are known; a unit whose lists are no longer than that is emitted from them, a
 // lane's four consecutive candidates at a time, one round trip to memory earlier.  As in the refine kernel this
 // pays where all tiles' wavefronts are resident at once, and the host picks the form by the number of tiles.
 //
-// One tile u of segment t, by one wavefront: x holds the threshold, the tile's tie quota and the place of its pairs; cc
-// are the tile's counts, hi4 / hv4 the heads of its lists.
+// One unit u of segment t, by one wavefront: x holds the threshold, the unit's tie quota and the place of its pairs; cc
+// are its sub-tiles' counts, hi4 / hv4 the heads of its lists.
 template <bool GEN, bool HEADS, int U, bool S>
 __device__ __forceinline__ void emit_unit(const Params& p, int t, uint32_t u, EmitCtx& x, const uint32_t (&cc)[U], const v4i& hi4,
                                           const v4f& hv4, int32_t* sidx, float* sval)
@@ -4784,7 +4785,7 @@ static int compress_impl(const float* grad, float* residual, int64_t n, const do
         max_seg_tiles = p.n_tiles;
         // more than SAMPLE_MAX samples (never a tensor read whole): 2 or 4 times SAMPLE_BLOCK samples per block, the
         // fewest that leave at most DENSE_BLOCKS blocks (more blocks keep more loads in flight, fewer cost the
-        // threshold kernel less)
+        // bracket kernel fewer round trips, one per 64 blocks)
         if (p.flat_samples > (uint32_t)SAMPLE_MAX && ((int64_t)p.flat_samples != n || p.direct))
             while (sample_rounds < DENSE_ROUNDS && p.flat_samples > (uint32_t)(DENSE_BLOCKS * SAMPLE_BLOCK * sample_rounds))
                 sample_rounds *= 2;
